@@ -63,6 +63,10 @@ struct OzCtx {
     int* fix = nullptr;                 // part buffer of the split tail of
     int fix_pieces = 0;                 // the purification products
     TailSplit tail{0, 1};
+    int nmod = 0;                       // moduli of the forward products (0: digit
+    uint8_t* res = nullptr;             // slices), their residues and tile list
+    const Tile* mtiles = nullptr;
+    int nmt = 0, mshape = 0;
 };
 
 void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
@@ -73,8 +77,12 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     const TileChoice tc = tile_choice_env(kind, S, n);
     x.rb = tc.rb;
     x.rb_stride = int64_t(x.KC) * S * kFragBytes;
-    x.pa = c.take<uint8_t>(plane_bytes(n, n, S, kind));
-    x.pb = c.take<uint8_t>(plane_bytes(n, n, S, kind));
+    const bool residues = mod_capacity(S) > 0;
+    const size_t planes = std::max(plane_bytes(n, n, S, kind),
+                                   residue_plane_bytes(n, n, kind) * mod_capacity(S));
+    x.pa = c.take<uint8_t>(planes);
+    x.pb = c.take<uint8_t>(planes);
+    if (residues) x.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
     x.ea = c.take<int>(round_up(n, kPad));
     x.eb = c.take<int>(round_up(n, kPad));
     x.ma = c.take<uint64_t>(round_up(n, kPad));
@@ -88,7 +96,7 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.scal = c.take<double>(8);
     x.pd = c.take<PurDesc>(1);
     x.st = c.take<DevState>(1);
-    x.fix_pieces = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && tc.split_tail
+    x.fix_pieces = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && tc.split_tail && !residues
                        ? tail_split_capacity(upper_tile_count(n, 32 * x.rb), x.KC, x.rb) : 0;
     x.fix = x.fix_pieces > 0 ? c.take<int>(size_t(x.fix_pieces) * piece_ints(S, x.rb)) : nullptr;
 }
@@ -101,6 +109,11 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
     DMP_CHECK(cached_tiles(tm, tn, false, &x.tiles_full, TM));
     x.nt_up = upper_tile_count(x.n, TM);
     x.nt_full = tm * tn;
+    x.nmod = mod_count(x.S, x.n, nocc);
+    if (x.nmod > 0) {
+        x.mshape = residue_shape(int64_t(residue_tile_count(x.n, kShapeWide, true)) * x.nmod);
+        DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
+    }
     x.tail = TailSplit{x.nt_up, 1};
     if (x.fix != nullptr && tail_split_enabled()) {
         int slots = 0;
@@ -158,6 +171,13 @@ MatDesc gemm_desc(const OzCtx& x, const uint8_t* pa, const int* ea, const uint8_
     return m;
 }
 
+// The plane layout of the forward products (residues where they use them).
+void forward_planes(const OzCtx& x, MatDesc& m) {
+    if (x.nmod == 0) return;
+    m.a_rb_stride = m.b_rb_stride = int64_t(x.KC / 2) * kFragBytes;
+    m.res = x.res;
+}
+
 // One forward iteration P_in -> (X2_out, P_out) with the purification
 // kernels; the coefficient is recomputed on the device from the traces.
 // The row maxima of X2 and of P_out come from the products' epilogues (into
@@ -168,15 +188,22 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
                       bool finalize, bool p_maxima, hipStream_t s) {
     SplitDesc sp = split_of(x, P_in, false, x.ma, x.ea, x.pa, 0);
     sp.clear = x.mb;
+    sp.lam = kLamIterate;
     if (p_maxima)
-        DMP_CHECK(launch_split_digits(sp, x.S, x.kind, x.st, s));
+        DMP_CHECK(launch_split_digits(sp, x.S, x.kind, x.st, s, x.nmod));
     else
-        DMP_CHECK(launch_split(sp, x.S, x.kind, x.st, s));
+        DMP_CHECK(launch_split(sp, x.S, x.kind, x.st, s, x.nmod));
+    auto product = [&](const GemmParams& p) -> int {
+        if (x.nmod > 0) return launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s, x.rb);
+        return launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb);
+    };
     GemmParams p{};
     p.tiles = x.tiles_up;
     p.one = gemm_desc(x, x.pa, x.ea, x.pa, x.ea, X2_out);
+    forward_planes(x, p.one);
     p.one.P = P_in;
     p.one.rowmax = x.mb;
+    p.mtiles = x.mtiles;
     p.partials = x.partials;
     p.states = x.st;
     p.mode = EPI_SQUARE;
@@ -185,18 +212,20 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         p.nfull = x.tail.nfull;
         p.nsplit = x.tail.nsplit;
     }
-    DMP_CHECK(launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb));
+    DMP_CHECK(product(p));
     DMP_CHECK(launch_finalize_coef(x.pd, x.st, 1, s));
     SplitDesc sx = split_of(x, X2_out, false, x.mb, x.eb, x.pb, 0);
     sx.clear = x.ma;
-    DMP_CHECK(launch_split_digits(sx, x.S, x.kind, x.st, s));
+    sx.lam = kLamIterate;
+    DMP_CHECK(launch_split_digits(sx, x.S, x.kind, x.st, s, x.nmod));
     p.one = gemm_desc(x, x.pb, x.eb, x.pa, x.ea, P_out);
+    forward_planes(x, p.one);
     p.one.P = P_in;
     p.one.X2 = X2_out;
     p.one.H = x.H;
     p.one.rowmax = x.ma;
     p.mode = EPI_UPDATE;
-    DMP_CHECK(launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb));
+    DMP_CHECK(product(p));
     if (finalize) DMP_CHECK(launch_finalize_iter(x.pd, x.st, 1, s));
     return DMP_OK;
 }

@@ -23,9 +23,10 @@ int blas_handle(hipStream_t stream, rocblas_handle* out);
 int native_dgemm(hipStream_t stream, bool ta, bool tb, int m, int n, int k, const double* A,
                  int lda, const double* B, int ldb, double* C, int ldc);
 
-int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st, hipStream_t s);
+// nmod > 0: the residues modulo kMods[0 .. nmod) instead of digits
+int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st, hipStream_t s, int nmod = 0);
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
-                        hipStream_t stream);
+                        hipStream_t stream, int nmod = 0);
 int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units,
                                 const DevState* st, hipStream_t stream);
 // coef.count > 0: the same launch also runs the coefficient step of the
@@ -34,7 +35,7 @@ int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units
 // none may.
 int launch_split_grouped_digits(const SplitDesc* descs_dev, int count, int units, int S,
                                 dmp_kind kind, const DevState* st, hipStream_t stream,
-                                const CoefArgs& coef = CoefArgs{}, bool combined = false);
+                                const CoefArgs& coef = CoefArgs{}, bool combined = false, int nmod = 0);
 
 struct GemmParams;
 // 32-row blocks per slice-GEMM tile (2: 64-row tiles, 4: 128-row tiles) of
@@ -47,6 +48,16 @@ int tile_blocks_for(dmp_kind kind, int S, int n);
 // variant: Ozaki kinds, S <= kMaxSlices64)
 int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStream_t stream,
                   int rb = 4);
+// A product through residues: the residue GEMM over the ``ntiles`` entries of
+// p.mtiles (tiles of shape ``shape``, modulus in the top byte of mat), then
+// the combination and the FP64 epilogue over the nout entries of p.tiles
+// (tile height 32 rb).
+int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
+                        hipStream_t stream, int rb);
+// its second half alone
+int launch_residue_epilogue(int nmod, const GemmParams& p, int nout, hipStream_t stream, int rb);
+// Device copy of the residue GEMM's tile list of one matrix, cached.
+int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count);
 // Workgroups of the purification-mode slice GEMM (kind, S, rb) resident on
 // the current device at once (CUs x workgroups per CU).
 int gemm_slots(int S, dmp_kind kind, int rb, int* slots);

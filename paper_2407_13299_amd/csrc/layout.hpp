@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "dmp.h"
+#include "modular.hpp"
 
 namespace dmp {
 
@@ -71,8 +72,19 @@ inline size_t plane_bytes(int64_t r, int64_t k, int s, dmp_kind kind) {
            (is_fp16_kind(kind) ? 2 : 1);
 }
 
+// Bytes of one residue plane of an R x K operand, and of the residues of an
+// M x N product (32 x 32 blocks of 1 KiB, row by row: lane l's 16 bytes at
+// 16 l, in the order of the MFMA accumulator).
+inline size_t residue_plane_bytes(int64_t r, int64_t k, dmp_kind kind) {
+    return size_t(round_up(r, kPad)) * size_t(round_up(k, kKPad)) * (is_fp16_kind(kind) ? 2 : 1);
+}
+inline size_t residue_out_bytes(int64_t m, int64_t n) {
+    return size_t(round_up(m, kPad)) * size_t(round_up(n, kPad));
+}
+
 // One output tile of a (possibly grouped) GEMM: rows [128 I, 128 I + 128),
-// columns [64 J, 64 J + 64) of matrix ``mat`` of a batch.
+// columns [64 J, 64 J + 64) of matrix ``mat`` of a batch.  In the tile lists
+// of the residue GEMM the top byte of ``mat`` is the modulus.
 struct Tile {
     uint16_t I, J;
     uint32_t mat;
@@ -100,6 +112,9 @@ struct MatDesc {
     int ldc;
     int state_index;       // index of the matrix's DevState
     int pad_;
+    uint8_t* res;          // residue products: the residues of the product,
+                           // [moduli][residue_out_bytes(M, N)]; pa, pb then
+                           // hold residue planes, each rows x a_rb_stride
 };
 
 // Device-side purification state of one matrix (host-readable copy).
@@ -143,6 +158,9 @@ struct SplitDesc {
     int sym;            // 1: A is symmetric and only its upper triangle (k >= r)
                         // holds it (trans == 0, A2 null): entry (r, k < r) is
                         // read as A[k, r]
+    int pad_;
+    double lam;         // residues: largest eigenvalue magnitude of the (positive
+                        // semidefinite) source, with some room; 0: none known
 };
 
 // Per-matrix arguments of the small purification kernels.
@@ -172,6 +190,12 @@ struct CoefArgs {
     int count;
     int method;
 };
+
+// Bounds on the spectrum of the purification operands (with room for the
+// rounding of their products): iterates and their squares have eigenvalues
+// in [0, 1]; TRS4's T = (4 - 2g) X + (g - 3) X2 + g I has t(x) in [0, 6] for
+// 0 <= g <= 6 and x in [0, 1].
+constexpr double kLamIterate = 1.0625, kLamTrs4 = 6.5;
 
 // Epilogue modes of the slice GEMM.
 enum EpiMode : int {
@@ -213,7 +237,13 @@ struct GemmParams {
     // purification modes: 1 stores only the upper triangle of the output
     // (no mirror; the next splits read it as symmetric, SplitDesc::sym)
     int upper_only;
+    const Tile* mtiles;     // residue products: the residue GEMM's tile list
 };
+
+// Tile shapes of the residue GEMM: 256 x 256, one workgroup per CU, and 128 x
+// 128, two per CU.
+constexpr int kShapeWide = 0, kShapeSmall = 1;
+constexpr int shape_edge(int shape) { return shape == kShapeWide ? 256 : 128; }
 
 // Tail split of a slice-GEMM launch: at most kMaxSplit parts per tile, at
 // least kMinSplitChunks reduction chunks per part, at most kMaxPieces parts

@@ -1,0 +1,320 @@
+// Residue products (see modular.hpp): for every modulus p_m the INT8 or FP16
+// matrix product of the operands' residue planes, reduced modulo p_m and
+// stored as bytes; the combination to FP64 and the epilogue are the
+// kResidue phase of the slice GEMM's kernel (ozgemm.hip).
+#include <type_traits>
+#include <vector>
+
+#include "host.hpp"
+#include "ldsload.hpp"
+
+namespace dmp {
+
+struct ModRow {
+    int p, c16;       // modulus, 2^16 mod p
+    float inv;        // 1 / p
+};
+struct ModRows {
+    ModRow r[kMaxMods];
+};
+constexpr ModRows make_rows() {
+    ModRows t{};
+    for (int m = 0; m < kMaxMods; ++m) t.r[m] = ModRow{kMods[m], 65536 % kMods[m], 1.0f / float(kMods[m])};
+    return t;
+}
+__constant__ const ModRows kModRows = make_rows();
+
+// One workgroup of WM x WN wavefronts owns a tile of 16 WM FM rows x 16 WN FN
+// columns of one modulus' product; each wavefront FM x FN blocks of 16 x 16,
+// so a chunk (64 INT8 or 32 FP16 reduction elements) takes FM FN matrix
+// instructions on FM + FN fragments of 1 KiB read from LDS.
+//
+// Bound: the chip's power limit under the matrix cores' load (residues are
+// dense random bytes; the clock falls to 1.7 GHz) and, behind it, the LDS,
+// which serves 128 bytes a cycle: unlike the slice GEMM, where S (S + 1) / 2
+// products share 2 S fragments, every product here reads its own.  Hence
+// 256 x 256 tiles of 8 wavefronts, 128 x 64 each (12 fragments read per 32
+// products, 128 accumulator registers, two wavefronts per SIMD, one
+// workgroup per CU).  16 x 16 x 64 products in boustrophedon order (one
+// operand changes from product to product) need less power than 32 x 32 x 32
+// ones: at n = 8192, 13 moduli on random residues, 2.64 against 2.86 ms
+// (2.71 and 2.50 POP/s at 1.72 and 1.50 GHz); row order 2.70 ms.  128 x 256
+// tiles, two workgroups per CU: 3.2 ms; all reads of a chunk ahead of its
+// products: 3.1 ms.
+//
+// Pipeline: fragments go from memory straight into LDS, NBUF stages of one
+// chunk, NBUF - 1 chunks ahead.  The fragments of chunk c + 1 are read from
+// LDS into registers between the products of chunk c, one read or load after
+// each product, so that neither the LDS latency, nor the barrier, nor a run
+// of other instructions stands between two products.  At the end of chunk c a
+// wavefront waits for its own loads of chunk c + 2 and the barrier publishes
+// that chunk; the stage reloaded during chunk c held chunk c - 1, whose
+// fragment reads had returned before the products of chunk c - 1 were
+// issued, ahead of that barrier.
+//
+// The accumulators start at a multiple of p above K 2^14 (INT8), so every
+// sum is positive: x mod p from its 16-bit halves, z = lo + hi (2^16 mod p)
+// < 2^22, q = rint(z / p) in FP32 (off by less than 2^-9.4, closer than any
+// z / p comes to a tie for odd p), r = z - q p.  FP16 sums are exact in FP32
+// up to 2^24, so they are reduced every 31 chunks.
+template <bool FP16, int WM, int WN, int FM, int FN, int NBUF, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p, int upper) {
+    constexpr int WAVES = WM * WN;
+    constexpr int AB = WM * FM, BB = WN * FN;       // 16-row blocks of the tile
+    constexpr int BLOCKS = AB + BB;                 // fragments of a stage
+    constexpr int STAGE = BLOCKS * kFragBytes;
+    constexpr int PER = BLOCKS / WAVES;             // loads per wavefront and stage
+    static_assert(BLOCKS % WAVES == 0 && NBUF >= 4 && FM % 2 == 0 && FN % 2 == 0,
+                  "equal loads per wavefront, whole 32 x 32 blocks");
+    __shared__ __align__(16) uint8_t lds[NBUF][STAGE];
+
+    const int b = blockIdx.x;
+    const int nb = gridDim.x;
+    const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
+    const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
+    const Tile tile = p.mtiles[t];
+    const int mod = int(tile.mat >> 24);
+    const MatDesc d = p.descs ? p.descs[tile.mat & 0xffffffu] : p.one;
+    const DevState* st = p.states ? p.states + d.state_index : nullptr;
+    if (st != nullptr && (st->done || (p.mode == EPI_UPDATE && st->gamma == 0.0))) return;
+    const bool clocked = p.clk != nullptr;
+    const uint64_t clk_c = clocked ? __builtin_amdgcn_s_memtime() : 0;
+    const uint64_t clk_r = clocked ? __builtin_amdgcn_s_memrealtime() : 0;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int rbs = int(round_up(d.M, kPad)) / 16, cbs = int(round_up(d.N, kPad)) / 16;
+    const int RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;   // chunks
+    const int64_t a_rb = d.a_rb_stride, b_rb = d.b_rb_stride;
+    const uint8_t* pa = d.pa + int64_t(mod) * rbs * a_rb;
+    const uint8_t* pb = d.pb + int64_t(mod) * cbs * b_rb;
+
+    // fragment f of a stage: 16-row block f of the left operand's part of the
+    // tile, then of the right's; blocks past the operand's last (a tile
+    // reaching beyond the padded matrix) load the last one and are not stored
+    v4i dsc[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int f = wave * PER + i;
+        const uint8_t* base;
+        int64_t bytes;
+        if (f < AB) {
+            base = pa + int64_t(min(int(tile.I) * AB + f, rbs - 1)) * a_rb;
+            bytes = a_rb;
+        } else {
+            base = pb + int64_t(min(int(tile.J) * BB + f - AB, cbs - 1)) * b_rb;
+            bytes = b_rb;
+        }
+        dsc[i] = sgpr_desc(base, int(bytes));
+    }
+    const uint32_t lbase = lds_offset(&lds[0][0]) + uint32_t(wave * PER * kFragBytes);
+    // load number i of chunk c into LDS stage ``slot``
+    auto load = [&](int i, int c, int slot) __attribute__((always_inline)) {
+        frag_to_lds(dsc[i], lbase + uint32_t(slot * STAGE + i * kFragBytes), lane * 16, c * kFragBytes);
+    };
+    auto issue = [&](int c, int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) load(i, c, slot);
+    };
+
+    using Acc = typename std::conditional<FP16, v4f, v4i>::type;
+    const ModRow mr = kModRows.r[mod];
+    const int pm = mr.p;
+    Acc acc[FM][FN];
+    {
+        using E = typename std::conditional<FP16, float, int>::type;
+        const E bias = FP16 ? E(0) : E((RC * (64 << 14) / pm + 1) * pm);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = Acc{bias, bias, bias, bias};
+    }
+
+    struct Frags {
+        v4i a[FM], b[FN];
+    };
+    // fragment number i (left operand's first) of the chunk in stage ``slot``
+    auto read = [&](int i, int slot, Frags& f) __attribute__((always_inline)) {
+        const uint8_t* s = &lds[0][0] + slot * STAGE + lane * 16;
+        if (i < FM)
+            f.a[i] = *reinterpret_cast<const v4i*>(s + (wm * FM + i) * kFragBytes);
+        else
+            f.b[i - FM] = *reinterpret_cast<const v4i*>(s + (AB + wn * FN + i - FM) * kFragBytes);
+    };
+    const float inv = mr.inv, pf = float(pm);
+    // FP32 integers |x| <= 2^24 to |x| <= p / 2: the first quotient may be
+    // off by one, the second, of a number below 2 p, is exact
+    auto fold = [&](float x) __attribute__((always_inline)) {
+        x = __builtin_fmaf(-rintf(x * inv), pf, x);
+        return __builtin_fmaf(-rintf(x * inv), pf, x);
+    };
+
+#pragma unroll
+    for (int s = 0; s < NBUF - 1; ++s)
+        if (s < RC) issue(s, s);
+    if (RC >= NBUF - 1) ops_wait<(NBUF - 3) * PER>(); else ops_wait<0>();
+    bare_barrier();
+    Frags fr[2];
+#pragma unroll
+    for (int i = 0; i < FM + FN; ++i) read(i, 0, fr[0]);
+    int slot = 0, flush = 0;
+    // one chunk: its products, with the fragment reads of the next chunk and
+    // the loads of chunk c + NBUF - 1 (MORE) spread between them.  After the
+    // last chunk the reads are of a stage whose contents are not used (no
+    // branch may stand between reads and products: the compiler would wait
+    // for every read at once).
+    auto step = [&](int c, const Frags& cur, Frags& nxt, auto more) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more)::value;
+        constexpr int R = FM + FN, OPS = R + (MORE ? PER : 0), Q = FM * FN;
+        const int prev = slot == 0 ? NBUF - 1 : slot - 1;
+        const int next = slot == NBUF - 1 ? 0 : slot + 1;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = q / FN, j = (i & 1) ? FN - 1 - q % FN : q % FN;
+            if constexpr (FP16)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(v8h, cur.a[i]), __builtin_bit_cast(v8h, cur.b[j]), acc[i][j], 0, 0, 0);
+            else
+                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.a[i], cur.b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int o = q * OPS / Q; o < (q + 1) * OPS / Q; ++o) {
+                if (o < R) read(o, next, nxt);
+                else load(o - R, c + NBUF - 1, prev);
+            }
+            if (q & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        vm_wait<MORE ? (NBUF - 3) * PER : 0>();
+        bare_barrier();
+        slot = next;
+        if constexpr (FP16) {
+            if (++flush == 31) {
+                flush = 0;
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[i][j][v] = fold(acc[i][j][v]);
+            }
+        }
+    };
+    int c = 0;
+    for (; c + NBUF < RC; c += 2) {
+        step(c, fr[0], fr[1], std::true_type{});
+        step(c + 1, fr[1], fr[0], std::true_type{});
+    }
+    for (; c < RC; c += 2) {
+        if (c + NBUF - 1 < RC) issue(c + NBUF - 1, slot == 0 ? NBUF - 1 : slot - 1);
+        step(c, fr[0], fr[1], std::false_type{});
+        if (c + 1 < RC) step(c + 1, fr[1], fr[0], std::false_type{});
+    }
+
+    // ---- residues of the sums, u + 128 as bytes --------------------------------
+    // in 32 x 32 blocks of 1 KiB: byte 16 L + v of a block is row (L / 32) 4 +
+    // 8 (v / 4) + v % 4, column L % 32 (the order in which the combination's
+    // wavefronts hold a quadrant).  Of a block's 2 x 2 matrix-instruction
+    // results lane l holds column l % 16 and rows 4 (l / 16) .. + 3; exchanging
+    // the right results of lanes 0 .. 31 with the left ones of lanes 32 .. 63
+    // leaves every lane 16 bytes of one column.
+    const int64_t plane = int64_t(rbs / 2) * (cbs / 2) * kFragBytes;
+    uint8_t* out = d.res + int64_t(mod) * plane +
+                   (((lane >> 4) & 1) * 32 + (lane >> 5) * 16 + (lane & 15)) * 16;
+    const uint32_t neg = uint32_t(256 - pm);
+    const uint32_t halves = 1u | (uint32_t(mr.c16) << 16);
+    auto residue = [&](auto x) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (FP16) {
+            return uint32_t(int(fold(x)));
+        } else {
+            typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+            const uint32_t z = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, uint32_t(x)),
+                                                      __builtin_bit_cast(us2, halves), 0u, false);
+            // q in the low bits of q + 1.5 2^23; only the low byte of z - q p
+            // is kept, so the bits above q do no harm
+            const float q = __builtin_fmaf(float(z), inv, 12582912.0f);
+            return z + __umul24(__float_as_uint(q), neg);
+        }
+    };
+    auto pack = [&](const Acc& a) __attribute__((always_inline)) {
+        uint32_t r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = residue(a[e]);
+        return (__builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu)) ^
+               0x80808080u;
+    };
+#pragma unroll
+    for (int i = 0; i < FM; i += 2)
+#pragma unroll
+        for (int j = 0; j < FN; j += 2) {
+            const int rb = (int(tile.I) * AB + wm * FM + i) / 2, cb = (int(tile.J) * BB + wn * FN + j) / 2;
+            if (rb >= rbs / 2 || cb >= cbs / 2 || (upper && rb > cb)) continue;   // wave-uniform
+            uint32_t w[4];
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(pack(acc[i + ti][j]), pack(acc[i + ti][j + 1]),
+                                                                 false, false);
+                w[2 * ti] = sw[0];
+                w[2 * ti + 1] = sw[1];
+            }
+            *reinterpret_cast<uint4*>(out + (int64_t(rb) * (cbs / 2) + cb) * kFragBytes) =
+                make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    if (clocked) {
+        const uint64_t dc = __builtin_amdgcn_s_memtime() - clk_c;
+        const uint64_t dr = __builtin_amdgcn_s_memrealtime() - clk_r;
+        if (threadIdx.x == 0) {
+            atomicAdd(p.clk + 0, static_cast<unsigned long long>(dc));
+            atomicAdd(p.clk + 1, static_cast<unsigned long long>(dr));
+        }
+    }
+}
+
+int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
+                        hipStream_t stream, int rb) {
+    if (ntiles <= 0 || nout <= 0) return DMP_OK;
+    if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || nmod < kModMin || nmod > kMaxMods ||
+        p.mtiles == nullptr || p.fix != nullptr) {
+        set_error("invalid residue product (%d moduli)", nmod);
+        return DMP_EINVAL;
+    }
+    const int upper = p.mode == EPI_STORE ? 0 : 1;
+    if (kind == DMP_OZ_FP16 && shape == kShapeWide)
+        k_residue_gemm<true, 2, 4, 8, 4, 4, 2><<<ntiles, 512, 0, stream>>>(p, upper);
+    else if (kind == DMP_OZ_FP16)
+        k_residue_gemm<true, 2, 4, 4, 2, 4, 4><<<ntiles, 512, 0, stream>>>(p, upper);
+    else if (shape == kShapeWide)
+        k_residue_gemm<false, 2, 4, 8, 4, 4, 2><<<ntiles, 512, 0, stream>>>(p, upper);
+    else
+        k_residue_gemm<false, 2, 4, 4, 2, 4, 4><<<ntiles, 512, 0, stream>>>(p, upper);
+    DMP_CHECK_HIP(hipGetLastError());
+    return launch_residue_epilogue(nmod, p, nout, stream, rb);
+}
+
+int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count) {
+    // device copies live until the process ends (as those of cached_tiles)
+    static KeyedCache<Tile> cache;
+    int dev = 0;
+    DMP_CHECK_HIP(hipGetDevice(&dev));
+    std::vector<Tile> host;
+    append_residue_tiles(host, n, nmod, shape, upper, 0);
+    *count = int(host.size());
+    int st = DMP_OK;
+    auto v = cache.get_or_create({dev, n, nmod, shape, upper ? 1 : 0}, [&]() -> std::shared_ptr<Tile> {
+        Tile* devp = nullptr;
+        hipError_t e = hipMalloc(&devp, host.size() * sizeof(Tile));
+        if (e == hipSuccess) e = hipMemcpy(devp, host.data(), host.size() * sizeof(Tile), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            set_error("tile list upload failed: %s", hipGetErrorString(e));
+            if (devp) (void)hipFree(devp);
+            st = DMP_EHIP;
+            return nullptr;
+        }
+        return std::shared_ptr<Tile>(devp, [](Tile*) {});   // kept for the process
+    });
+    if (!v) return st != DMP_OK ? st : DMP_EHIP;
+    *out = v.get();
+    return DMP_OK;
+}
+
+}  // namespace dmp

@@ -1,0 +1,119 @@
+// Products through residues (the multi-modulus form of the error-free
+// scheme): the operands of C = A B become integers X_i = rint(a_i 2^(s_i)),
+// one power of two per row of A and per column of B, small enough that
+// 2 |(X Y)_ij| < M = p_1 ... p_N for pairwise coprime p_m <= 256; the N
+// residue products X Y mod p_m are INT8 (or FP16) matrix products with exact
+// sums, and the Chinese remainder theorem gives the integer (X Y)_ij back.
+// Nothing is dropped: the only errors are the rounding to X, Y and the final
+// rounding to FP64.  Against S digit slices with S (S + 1) / 2 products per
+// element this takes N products; kModCount states N.
+//
+// Shared by host and device code (no HIP calls).
+#pragma once
+
+#include <cstdint>
+
+namespace dmp {
+
+constexpr int kMaxMods = 16;
+// The largest pairwise coprime integers up to 256, so that balanced residues
+// fit a signed byte.
+constexpr int kMods[kMaxMods] = {256, 255, 253, 251, 247, 241, 239, 233,
+                                 229, 227, 223, 217, 211, 199, 197, 193};
+
+// Slice counts whose purification products run through residues, and their
+// number.  S counts digit slices: its products keep 8S - 2 bits of every
+// operand row but drop the slice pairs i + j > S + 1, which leaves an error
+// of about 2^(e_i + f_j) 2^(-8S + 8) sqrt(k / 2048) 2^-0.8 (measured 5.7e-15
+// for S = 7 at k = 2048).  N is the smallest count whose rounding to X, Y
+// stays below that for operands with rows maxima >= 0.15 (density matrices
+// of at least 15 % filling): 11, 13 and 15 products against 21, 28 and 36.
+// Lower filling shrinks 2^(e_i) faster than the row norm, so one or two more
+// moduli are taken (mod_count).  S <= 5 and S >= 9 keep the digit slices:
+// below 6 the slices are few enough (15 products) and their truncation is
+// what is studied; beyond 8 the integers no longer fit FP64.
+constexpr int kModSlicesLo = 6, kModSlicesHi = 8;
+constexpr int kModCount[3] = {11, 13, 15};
+constexpr int kModMin = 11;
+
+// Capacity (moduli) a purification with S slices may use: 0 for digit slices.
+constexpr int mod_capacity(int S) {
+    if (S < kModSlicesLo || S > kModSlicesHi) return 0;
+    const int c = kModCount[S - kModSlicesLo] + 2;
+    return c < kMaxMods ? c : kMaxMods;
+}
+// Moduli of a purification with S slices, nocc of n levels occupied.
+constexpr int mod_count(int S, int n, int nocc) {
+    if (S < kModSlicesLo || S > kModSlicesHi) return 0;
+    const int64_t occ = nocc;
+    const int c = kModCount[S - kModSlicesLo] + (occ * 100 < int64_t(n) * 15 ? 1 : 0) +
+                  (occ * 1000 < int64_t(n) * 4 ? 1 : 0);
+    return c < mod_capacity(S) ? c : mod_capacity(S);
+}
+
+// Reconstruction constants of N moduli.  C' = X Y mod M satisfies C' / M =
+// frac(sum_m u_m y_m / p_m) for any representative u_m of its residue, y_m =
+// (M / p_m)^-1 mod p_m.  y_m / p_m is kept as w0 2^-40 + w1 2^-80 with
+// integers w0, w1 <= 2^40, so the sums over u_m in [0, 255] are exact in
+// FP64 (255 x 16 x 2^40 < 2^53) and the fraction is off by less than
+// 255 N 2^-81 < 2^-69.
+struct CrtTable {
+    double w0[kMaxMods], w1[kMaxMods];
+    double k0, k1;        // 128 sum w0, 128 sum w1 (bytes are stored as u + 128)
+    double mh, ml;        // M 2^-80 as a double and its remainder
+    double limit;         // largest admissible row norm of X: sqrt(M / 2), a little less
+};
+
+constexpr int inverse_mod(int a, int p) {
+    for (int x = 1; x < p; ++x)
+        if ((a * x) % p == 1) return x;
+    return 0;
+}
+
+constexpr double pow2(int e) {
+    double v = 1.0;
+    for (int i = 0; i < (e < 0 ? -e : e); ++i) v = e < 0 ? v * 0.5 : v * 2.0;
+    return v;
+}
+
+constexpr CrtTable make_crt(int N) {
+    CrtTable t{};
+    unsigned __int128 M = 1;
+    for (int m = 0; m < N; ++m) M *= unsigned(kMods[m]);
+    double s0 = 0.0, s1 = 0.0;
+    for (int m = 0; m < N; ++m) {
+        const int p = kMods[m];
+        int rest = 1;
+        for (int q = 0; q < N; ++q)
+            if (q != m) rest = int((int64_t(rest) * kMods[q]) % p);
+        const uint64_t y = uint64_t(inverse_mod(rest, p));
+        const uint64_t a = y << 40;
+        const uint64_t hi = a / uint64_t(p), rem = a % uint64_t(p);
+        const uint64_t lo = ((rem << 40) + uint64_t(p) / 2) / uint64_t(p);
+        t.w0[m] = double(hi);
+        t.w1[m] = double(lo);
+        s0 += t.w0[m];
+        s1 += t.w1[m];
+    }
+    t.k0 = 128.0 * s0;
+    t.k1 = 128.0 * s1;
+    const double md = double(M);                  // nearest double
+    const double rem = md >= double(M) && (unsigned __int128)(md) > M
+                           ? -double((unsigned __int128)(md) - M)
+                           : double(M - (unsigned __int128)(md));
+    t.mh = md * pow2(-80);
+    t.ml = rem * pow2(-80);
+    // sqrt(M / 2) by Newton's iteration, less 2^-13 of it
+    const double half = md * 0.5;
+    double r = pow2(60);
+    for (int i = 0; i < 60; ++i) r = 0.5 * (r + half / r);
+    t.limit = r * (1.0 - 0x1p-13);
+    return t;
+}
+
+template <int N>
+struct Crt {
+    static constexpr CrtTable table = make_crt(N);
+};
+
+}  // namespace dmp

@@ -40,80 +40,10 @@
 // In the purification modes only the upper triangle is computed and kept,
 // so every iterate is exactly symmetric and its row digits also serve as its
 // column digits.
-#include "common.hpp"
+#include "host.hpp"
+#include "ldsload.hpp"
 
 namespace dmp {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-// Workgroup barrier without the memory fence __syncthreads() implies (that
-// fence would also wait for the prefetch loads in flight); the signal fences
-// keep the compiler from moving memory accesses across it.  Before each
-// barrier the kernel waits for its own operand loads and LDS reads itself
-// (ops_wait).
-__device__ inline void bare_barrier() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// Fourth word of a raw buffer descriptor on gfx950 (32-bit data format,
-// no swizzle, no index stride).
-constexpr int kBufferWord3 = 0x00020000;
-
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-
-// Byte offset of a shared-memory address inside the workgroup's LDS.
-__device__ inline uint32_t lds_offset(const void* p) {
-    return static_cast<uint32_t>(reinterpret_cast<size_t>((const lds_u8*)(p)));
-}
-
-// A raw buffer descriptor (base, no stride, ``bytes`` records) as four
-// wave-uniform words, for the inline assembly below, which takes it in
-// scalar registers.
-__device__ inline v4i sgpr_desc(const void* base, int bytes) {
-    const uint64_t b = reinterpret_cast<uint64_t>(base);
-    v4i d;
-    d[0] = __builtin_amdgcn_readfirstlane(int(uint32_t(b)));
-    d[1] = __builtin_amdgcn_readfirstlane(int(uint32_t(b >> 32) & 0xffffu));
-    d[2] = __builtin_amdgcn_readfirstlane(bytes);
-    d[3] = kBufferWord3;
-    return d;
-}
-
-// One 1 KiB fragment block from global memory straight into LDS (a buffer
-// load with the LDS flag): lane l's 16 bytes at buffer offset voff + soff
-// land at LDS byte lds + 16 l, which is exactly the fragment layout, so no
-// register staging and no LDS store instruction is needed.  It is written
-// as inline assembly so that the compiler's wait counting, which would
-// otherwise wait for every such load before any LDS read, leaves it alone;
-// the kernel waits for these loads itself (ops_wait) before the barrier
-// that publishes them.  The load has no register destination; m0 holds the
-// LDS address and is set right before it.  m0 is a register the compiler
-// reserves; nothing else in these kernels reads it (gfx950 LDS instructions
-// do not use it), which tests/test_isa_m0.py checks on the compiled code.
-__device__ inline void frag_to_lds(v4i r, uint32_t lds, int voff, int soff) {
-    // the operands are wave-uniform; reading them from the first lane makes
-    // them scalar registers at this point even where register pressure has
-    // moved them to vector registers in between
-    v4i rs;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) rs[q] = __builtin_amdgcn_readfirstlane(r[q]);
-    const uint32_t ls = __builtin_amdgcn_readfirstlane(lds);
-    const int ss = __builtin_amdgcn_readfirstlane(soff);
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(ls), "v"(voff), "s"(rs), "s"(ss) : "memory", "m0");
-}
-
-// s_waitcnt vmcnt(N) lgkmcnt(0): at most N vector-memory operations of the
-// wavefront still in flight, and every LDS read returned.
-template <int N>
-__device__ inline void ops_wait() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory");
-}
 
 __device__ inline double wave_sum(double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -136,10 +66,13 @@ __device__ inline double wave_sum(double v) {
 // stored, no epilogue), then kFixup, one block per split tile (adds the
 // parts' group sums in place of the main loop, then runs the epilogue).
 // Separate instantiations keep the whole-tile kernel's registers as they are.
-constexpr int kWhole = 0, kPiece = 1, kFixup = 2;
+// kResidue: no main loop either; S counts the moduli of a residue product
+// (modular.hip), whose residues are combined into the FP64 sums instead.
+constexpr int kWhole = 0, kPiece = 1, kFixup = 2, kResidue = 3;
 template <int S, bool FP16, int TERMS = 0, bool PUR = false, int RB = 4, int PHASE = kWhole>
 __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams p) {
-    constexpr int BLOCKS = (RB + 2) * S;          // 1 KiB blocks per chunk
+    constexpr bool RESIDUE = PHASE == kResidue;
+    constexpr int BLOCKS = RESIDUE ? 2 * RB : (RB + 2) * S;   // 1 KiB blocks per chunk
     constexpr int STAGE = BLOCKS * kFragBytes;
     constexpr int WAVES = 2 * RB;
     constexpr int PER = (BLOCKS + WAVES - 1) / WAVES;  // loads per wavefront per chunk
@@ -154,7 +87,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // XCDs in turn; give every XCD one contiguous slice of the tile list.
     const int b = blockIdx.x;
     int t, part = 0;
-    if constexpr (PHASE == kWhole) {
+    if constexpr (PHASE == kWhole || RESIDUE) {
         const int nb = gridDim.x;
         const int xcd = b & 7, q = nb >> 3, rem = nb & 7, loc = b >> 3;
         t = p.spread ? b : (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
@@ -311,7 +244,34 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // Part u of the split tail keeps its group sums at piece u of p.fix:
     // [wavefront][group][4 x 4 values][lane], 16 bytes per lane and store.
     constexpr int64_t kPieceInts = int64_t(WAVES) * S * 16 * 64;
-    if constexpr (PHASE == kFixup) {
+    double hsum[16];
+    if constexpr (RESIDUE) {
+        // C' = X Y from its residues (modular.hpp): the fraction C' / M as
+        // S0 2^-40 + S1 2^-80 less its nearest integer, times M.  All
+        // loads are issued before the first is used.
+        if (!no_product) {
+            const int rbs = int(round_up(d.M, kPad)) / kFragRows, cbs = int(round_up(d.N, kPad)) / kFragRows;
+            const uint8_t* src = d.res + (int64_t(RB * I + wm) * cbs + 2 * J + wn) * kFragBytes + lane * 16;
+            const int64_t plane = int64_t(rbs) * cbs * kFragBytes;
+            v4i w[S];
+#pragma unroll
+            for (int m = 0; m < S; ++m) w[m] = *reinterpret_cast<const v4i*>(src + m * plane);
+            constexpr const CrtTable& T = Crt<S>::table;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                double f0 = -T.k0, f1 = -T.k1;
+#pragma unroll
+                for (int m = 0; m < S; ++m) {
+                    const double u = double((uint32_t(w[m][v >> 2]) >> (8 * (v & 3))) & 0xffu);
+                    f0 = __builtin_fma(u, T.w0[m], f0);
+                    f1 = __builtin_fma(u, T.w1[m], f1);
+                }
+                const double k = rint(__builtin_fma(f1, 0x1p-80, f0 * 0x1p-40));
+                const double x = __builtin_fma(__builtin_fma(k, -0x1p40, f0), 0x1p40, f1);
+                hsum[v] = __builtin_fma(x, T.mh, x * T.ml);
+            }
+        }
+    } else if constexpr (PHASE == kFixup) {
         if (!no_product) {
             const int* src = p.fix + int64_t(b) * p.nsplit * kPieceInts +
                              int64_t(wave) * (S * 16 * 64) + lane * 4;
@@ -418,10 +378,11 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // stored.  The compiler cannot tell that the output does not alias P,
     // X2, H or the exponents, so a load placed after a store would wait for
     // it and every element would pay a full memory latency.
-    double hsum[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        if constexpr (TERMS > 0) {
+        if constexpr (RESIDUE) {
+            if (no_product) hsum[v] = 0.0;
+        } else if constexpr (TERMS > 0) {
             hsum[v] = double(accf[v]);
         } else {
             double h = double(acc[S - 1][v]);
@@ -462,7 +423,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
         const int row = row0 + (v >> 2) * 8 + (v & 3);
         const double h = hsum[v];
         const int ei = eiv[v];
-        constexpr int shift = TERMS > 0 ? 0 : 2 * kTopBits;
+        constexpr int shift = TERMS > 0 || RESIDUE ? 0 : 2 * kTopBits;
         const double c = no_product ? 0.0
                          : (ei >= kNonFiniteExp || fj >= kNonFiniteExp)
                              ? __builtin_nan("")
@@ -674,6 +635,33 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
         kTerms[S](p, ntiles, stream);
     else
         kGemm[kWhole][S](kind == DMP_OZ_FP16, p, ntiles, rb, stream);
+    DMP_CHECK_HIP(hipGetLastError());
+    return DMP_OK;
+}
+
+// The combination of N residues and the FP64 epilogue of every mode.
+template <int N>
+static void launch_residue_n(const GemmParams& p, int ntiles, int rb, hipStream_t stream) {
+    const bool pur = purification_mode(p.mode);
+    if (rb == 2 && pur)
+        k_ozgemm<N, false, 0, true, 2, kResidue><<<ntiles, 256, 0, stream>>>(p);
+    else if (rb == 2)
+        k_ozgemm<N, false, 0, false, 2, kResidue><<<ntiles, 256, 0, stream>>>(p);
+    else if (pur)
+        k_ozgemm<N, false, 0, true, 4, kResidue><<<ntiles, kGemmThreads, 0, stream>>>(p);
+    else
+        k_ozgemm<N, false, 0, false, 4, kResidue><<<ntiles, kGemmThreads, 0, stream>>>(p);
+}
+
+int launch_residue_epilogue(int nmod, const GemmParams& p, int nout, hipStream_t stream, int rb) {
+    static void (*const table[kMaxMods - kModMin + 1])(const GemmParams&, int, int, hipStream_t) = {
+        launch_residue_n<11>, launch_residue_n<12>, launch_residue_n<13>,
+        launch_residue_n<14>, launch_residue_n<15>, launch_residue_n<16>};
+    if (nmod < kModMin || nmod > kMaxMods || (rb != 2 && rb != 4)) {
+        set_error("no residue combination for %d moduli", nmod);
+        return DMP_EINVAL;
+    }
+    table[nmod - kModMin](p, nout, rb, stream);
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }

@@ -102,6 +102,24 @@ void append_tiles(std::vector<Tile>& out, int tm, int tn, bool upper, uint32_t m
                 }
 }
 
+void append_residue_tiles(std::vector<Tile>& out, int n, int nmod, int shape, bool upper, uint32_t mat) {
+    const int edge = shape_edge(shape), t = (n + edge - 1) / edge, G = 1024 / edge;
+    for (int m = 0; m < nmod; ++m)
+        for (int si = 0; si < t; si += G)
+            for (int sj = 0; sj < t; sj += G)
+                for (int i = si; i < std::min(t, si + G); ++i)
+                    for (int j = sj; j < std::min(t, sj + G); ++j)
+                        if (!upper || i <= j)
+                            out.push_back(Tile{uint16_t(i), uint16_t(j), mat | (uint32_t(m) << 24)});
+}
+
+int residue_tile_count(int n, int shape, bool upper) {
+    const int edge = shape_edge(shape), t = (n + edge - 1) / edge;
+    return upper ? t * (t + 1) / 2 : t * t;
+}
+
+int residue_shape(int64_t wide) { return wide >= kWideTiles ? kShapeWide : kShapeSmall; }
+
 int tile_rows(int m, int TM) { return int(round_up(m, TM) / TM); }
 int tile_cols(int n) { return int(round_up(n, kTileN) / kTileN); }
 
@@ -212,16 +230,18 @@ int native_pairs(int n) {
 int oz_tiles(int n, int rb) { return upper_tile_count(n, 32 * rb); }
 
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
-                 int forced_rb, std::vector<GroupPlan>& groups) {
+                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc) {
     groups.clear();
     for (int b = 0; b < count; ++b) {
         const int S = kind == DMP_FP64_NATIVE ? 0 : slices[b];
+        const bool residues = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && mod_capacity(S) > 0;
+        const int nmod = residues ? mod_count(S, n[b], nocc ? nocc[b] : 0) : 0;
         const TileChoice tc = kind == DMP_FP64_NATIVE ? TileChoice{4, false}
                                                       : tile_choice(kind, S, n[b], forced_rb);
         GroupPlan* g = nullptr;
         for (auto& x : groups)
-            if (x.S == S && x.rb == tc.rb && x.split_tail == tc.split_tail &&
-                kind != DMP_FP64_NATIVE)
+            if (x.S == S && x.rb == tc.rb && x.split_tail == tc.split_tail && x.nmod == nmod &&
+                kind != DMP_FP64_NATIVE && !(residues && nocc == nullptr))
                 g = &x;
         if (!g) {
             groups.emplace_back();
@@ -231,13 +251,14 @@ void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int 
             g->method = method;
             g->rb = tc.rb;
             g->split_tail = tc.split_tail;
+            g->nmod = nmod;
         }
         g->idx.push_back(b);
         g->count++;
     }
 }
 
-static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind) {
+static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind, bool residues) {
     MatLayout m{};
     const size_t nn = size_t(n) * n;
     m.X2 = c.take<double>(nn);
@@ -246,8 +267,13 @@ static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind) {
         m.X3 = c.take<double>(nn);
         m.T = c.take<double>(nn);
     } else {
-        m.planesP = c.take<uint8_t>(plane_bytes(n, n, S, kind));
-        m.planesX = c.take<uint8_t>(plane_bytes(n, n, S, kind));
+        // residues: room for the capacity, so that the workspace does not
+        // depend on the occupation
+        const size_t planes = residues ? residue_plane_bytes(n, n, kind) * mod_capacity(S)
+                                       : plane_bytes(n, n, S, kind);
+        m.planesP = c.take<uint8_t>(planes);
+        m.planesX = c.take<uint8_t>(planes);
+        if (residues) m.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
         m.expP = c.take<int>(round_up(n, kPad));
         m.expX = c.take<int>(round_up(n, kPad));
         m.maxP = c.take<uint64_t>(round_up(n, kPad));
@@ -260,17 +286,19 @@ static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind) {
 }
 
 size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
-    size_t parts = 0;
+    size_t parts = 0, mtiles = 0;
+    const bool residues = g.nmod > 0;
     g.lay.resize(g.count);
     g.max_pairs = 1;
     g.min_kc = g.max_kc = 0;
     for (int b = 0; b < g.count; ++b) {
         const int nb = n[g.idx[b]];
-        g.lay[b] = carve_matrix(c, nb, g.S, g.kind);
+        g.lay[b] = carve_matrix(c, nb, g.S, g.kind, residues);
         if (g.kind == DMP_FP64_NATIVE) {
             parts = std::max<size_t>(parts, std::max(native_blocks(nb), native_pairs(nb)));
         } else {
             parts += size_t(oz_tiles(nb, g.rb));
+            if (residues) mtiles += size_t(residue_tile_count(nb, kShapeSmall, true)) * mod_capacity(g.S);
             const int kc = int(chunks_of(nb, g.kind));
             g.min_kc = b == 0 ? kc : std::min(g.min_kc, kc);
             g.max_kc = std::max(g.max_kc, kc);
@@ -279,7 +307,7 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
     }
     // part buffer of the tail split (Ozaki kinds), sized for the largest
     // matrix, so that a batch needs no less workspace than any of its members
-    g.fix_pieces = (g.kind == DMP_OZ_INT8 || g.kind == DMP_OZ_FP16) && g.split_tail
+    g.fix_pieces = (g.kind == DMP_OZ_INT8 || g.kind == DMP_OZ_FP16) && g.split_tail && !residues
                        ? tail_split_capacity(int(parts), g.max_kc, g.rb) : 0;
     g.fix = g.fix_pieces > 0 ? c.take<int>(size_t(g.fix_pieces) * piece_ints(g.S, g.rb)) : nullptr;
     // the refinement step reuses the partials of one matrix's tile pairs
@@ -296,6 +324,7 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
     g.up[0] = c.take<MatDesc>(g.count);
     g.up[1] = c.take<MatDesc>(g.count);
     g.tiles = c.take<Tile>(std::max<size_t>(1, g.kind == DMP_FP64_NATIVE ? 1 : parts));
+    g.mtiles = mtiles > 0 ? c.take<Tile>(mtiles) : nullptr;
     g.partials = c.take<double>(std::max<size_t>(1, parts) * kPartials);
     g.pairs = c.take<IPair>(g.max_pairs);
     return c.used();
@@ -334,6 +363,14 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
             append_tiles(out.tiles, tile_rows(nb, 32 * g.rb), tile_cols(nb), true, uint32_t(b),
                          32 * g.rb);
         }
+        if (g.nmod > 0) {
+            int64_t wide = 0;
+            for (int b : order) wide += int64_t(residue_tile_count(n[g.idx[b]], kShapeWide, true)) * g.nmod;
+            g.mshape = residue_shape(wide);
+            for (int b : order)
+                append_residue_tiles(out.mtiles, n[g.idx[b]], g.nmod, g.mshape, true, uint32_t(b));
+            g.nmt = int(out.mtiles.size());
+        }
     }
     for (int b = 0; b < cnt; ++b) {
         const int m = g.idx[b], nb = n[m];
@@ -363,8 +400,10 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         out.pd[b] = d;
         if (g.kind == DMP_FP64_NATIVE) continue;
         const int KC = int(chunks_of(nb, g.kind));
-        const int64_t rbs = int64_t(KC) * planes_of(g.S, g.kind) * kFragBytes;
+        const int64_t rbs = g.nmod > 0 ? int64_t(KC / 2) * kFragBytes
+                                       : int64_t(KC) * planes_of(g.S, g.kind) * kFragBytes;
         SplitDesc sd{};
+        sd.lam = kLamIterate;
         sd.lda = nb;
         sd.R = nb;
         sd.K = nb;
@@ -402,6 +441,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         out.st0[b] = sd;
         sd.A = L.Pw;
         out.st1[b] = sd;
+        out.st0[b].lam = out.st1[b].lam = kLamTrs4;
         sd.A2 = nullptr;
         sd.A = L.X2;
         sd.maxbits = L.maxX;
@@ -420,6 +460,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         md.state_index = b;
         md.H = H[m];
         md.X2 = L.X2;
+        md.res = L.res;
         // square: A = B = planes of P
         md.pa = L.planesP;
         md.pb = L.planesP;
@@ -460,7 +501,8 @@ std::vector<int64_t> launch_key(const std::vector<GroupPlan>& groups, int m, int
     for (const GroupPlan& g : groups) {
         k.insert(k.end(), {int64_t(g.count), int64_t(g.S), int64_t(g.kind), int64_t(g.method),
                            int64_t(g.rb), int64_t(g.ntiles), int64_t(g.units_rowmax),
-                           int64_t(g.units_digits), int64_t(g.tail.nfull), int64_t(g.tail.nsplit)});
+                           int64_t(g.units_digits), int64_t(g.tail.nfull), int64_t(g.tail.nsplit),
+                           int64_t(g.nmod), int64_t(g.nmt), int64_t(g.mshape)});
         p(g.pd);
         p(g.st);
         p(g.splitP[0]);
@@ -473,6 +515,7 @@ std::vector<int64_t> launch_key(const std::vector<GroupPlan>& groups, int m, int
         p(g.up[0]);
         p(g.up[1]);
         p(g.tiles);
+        p(g.mtiles);
         p(g.partials);
         p(g.fix);
     }

@@ -58,6 +58,15 @@ int tile_rows(int m, int TM = kTileM);
 int tile_cols(int n);
 int upper_tile_count(int n, int TM = kTileM);
 
+// Tile list of the residue GEMM of an n x n product: all ``nmod`` moduli, one
+// after the other (modulus in the top byte of ``mat``), tiles of shape
+// ``shape`` in 1024 x 1024 super-tiles.
+void append_residue_tiles(std::vector<Tile>& out, int n, int nmod, int shape, bool upper, uint32_t mat);
+int residue_tile_count(int n, int shape, bool upper);   // per modulus
+// Shape for a launch of ``wide`` tiles (all moduli) of the wide shape.
+constexpr int kWideTiles = 100;
+int residue_shape(int64_t wide);
+
 // Workgroups ("units") of the split kernels for an operand of R rows.
 int split_units_rowmax(int R);
 int split_units_colmax(int R, int K);
@@ -114,6 +123,7 @@ struct MatLayout {
     int* expX;
     uint64_t* maxP;
     uint64_t* maxX;
+    uint8_t* res;     // residue products: the residues of one product
     double* rows;
     int* rowbad;
     double* e0;
@@ -148,17 +158,23 @@ struct GroupPlan {
     int fix_pieces = 0;               // its capacity in parts
     int min_kc = 0, max_kc = 0;       // fewest / most reduction chunks of a matrix
     TailSplit tail{0, 1};             // tail split of the slice GEMMs
+    int nmod = 0;                     // moduli of its residue products (0: digit slices)
+    Tile* mtiles = nullptr;           // residue GEMM tile list, nmt entries of shape mshape
+    int nmt = 0, mshape = 0;
 };
 
 int native_blocks(int n);
 int native_pairs(int n);
 int oz_tiles(int n, int rb);
 
-// Partition a batch into groups of equal (S, tile choice); the choice
-// follows from each matrix's own (kind, S, n), so a matrix gets the same
-// tiles, hence bit-identical fixed-order sums, alone or in a batch.
+// Partition a batch into groups of equal (S, tile choice, moduli); the choice
+// follows from each matrix's own (kind, S, n, nocc), so a matrix gets the
+// same tiles and scales, hence bit-identical results, alone or in a batch.
+// nocc null (workspace queries, which do not know it): every matrix that may
+// use residues is a group of its own, which needs no less workspace than any
+// grouping the occupations can lead to.
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
-                 int forced_rb, std::vector<GroupPlan>& groups);
+                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc = nullptr);
 // Carve the workspace regions of a group (base == nullptr: measure only).
 size_t carve_group(Carver& c, GroupPlan& g, const int* n);
 
@@ -167,7 +183,7 @@ struct GroupHost {
     std::vector<PurDesc> pd;
     std::vector<SplitDesc> sp0, sp1, sx, st0, st1;
     std::vector<MatDesc> q0, q1, u0, u1;
-    std::vector<Tile> tiles;
+    std::vector<Tile> tiles, mtiles;
     std::vector<IPair> pairs;
 };
 // Fill the descriptors of a carved group for the caller's matrices; sets

@@ -555,6 +555,7 @@ int upload_group(GroupPlan& g, const double* const* H, double* const* P, const i
         DMP_CHECK(up(g.up[0], h.u0.data(), cnt * sizeof(MatDesc)));
         DMP_CHECK(up(g.up[1], h.u1.data(), cnt * sizeof(MatDesc)));
         DMP_CHECK(up(g.tiles, h.tiles.data(), h.tiles.size() * sizeof(Tile)));
+        DMP_CHECK(up(g.mtiles, h.mtiles.data(), h.mtiles.size() * sizeof(Tile)));
     }
     DMP_CHECK(up(g.pairs, h.pairs.data(), h.pairs.size() * sizeof(IPair)));
     return DMP_OK;
@@ -572,7 +573,8 @@ double gemm_ops(const GroupPlan& g, const int* n) {
     double t = 0.0;
     for (int b = 0; b < g.count; ++b) {
         const double m = n[g.idx[b]];
-        t += double(g.S) * (g.S + 1) * m * m * (m + 1) / 2.0;
+        const double products = g.nmod > 0 ? g.nmod : 0.5 * g.S * (g.S + 1);
+        t += products * m * m * (m + 1);
     }
     return t;
 }
@@ -597,7 +599,10 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
         DMP_CHECK_HIP(hipEventCreate(&t.stop));
         DMP_CHECK_HIP(hipEventRecord(t.start, s));
     }
-    DMP_CHECK(launch_ozgemm(g.S, g.kind, q, g.ntiles, s, g.rb));
+    if (g.nmod > 0)
+        DMP_CHECK(launch_residue_gemm(g.kind, g.nmod, g.mshape, q, g.nmt, g.ntiles, s, g.rb));
+    else
+        DMP_CHECK(launch_ozgemm(g.S, g.kind, q, g.ntiles, s, g.rb));
     if (timers) {
         DMP_CHECK_HIP(hipEventRecord(t.stop, s));
         t.which = which;
@@ -611,9 +616,11 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
 int launch_oz_iteration(GroupPlan& g, int par, hipStream_t s,
                         std::vector<PendingTimer>* timers = nullptr, double ops = 0.0) {
     // the row maxima of P come from the previous update's epilogue
-    DMP_CHECK(launch_split_grouped_digits(g.splitP[par], g.count, g.units_digits, g.S, g.kind, g.st, s));
+    DMP_CHECK(launch_split_grouped_digits(g.splitP[par], g.count, g.units_digits, g.S, g.kind, g.st, s,
+                                          CoefArgs{}, false, g.nmod));
     GemmParams p{};
     p.tiles = g.tiles;
+    p.mtiles = g.mtiles;
     p.descs = g.sq[par];
     p.partials = g.partials;
     p.states = g.st;
@@ -633,11 +640,11 @@ int launch_oz_iteration(GroupPlan& g, int par, hipStream_t s,
     // blocks of the same launch, the coefficient step (it reads only the
     // done flags of the states that step writes)
     DMP_CHECK(launch_split_grouped_digits(g.splitX, g.count, g.units_digits, g.S, g.kind, g.st, s,
-                                          CoefArgs{g.pd, g.st, g.count, g.method}));
+                                          CoefArgs{g.pd, g.st, g.count, g.method}, false, g.nmod));
     if (trs4) {
         DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
         DMP_CHECK(launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind,
-                                              g.st, s, CoefArgs{}, true));
+                                              g.st, s, CoefArgs{}, true, g.nmod));
     }
     p.descs = g.up[par];
     p.mode = EPI_UPDATE;
@@ -989,7 +996,7 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
     // same fixed-order trace sums and bit-identical results, alone or in a
     // batch)
     std::vector<GroupPlan> groups;
-    plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups);
+    plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr);
     Carver c(ws);
     for (auto& g : groups) carve_group(c, g, n);
     if (need_out) *need_out = c.used();

@@ -179,64 +179,17 @@ __device__ inline int exponent_of(uint64_t bits) {
     return e;
 }
 
-// Digits: a workgroup of 4 wavefronts owns one 32-row block of the operand
-// and 4 consecutive chunks of CK reduction elements (W = 4 CK); wave w turns
-// chunk 4 q + w into its fragment block, where lane l owns operand row l % 32
-// and NE = CK / 2 consecutive reduction elements (the MFMA operand layout).
-// Operand rows that are matrix rows (trans == 0, also the combined operand)
-// are first staged through LDS: the workgroup reads the 32 x W panel row by
-// row, each wave 64 consecutive doubles per load, so the HBM reads are
-// coalesced although every lane then needs a piece of its own row.  A
-// symmetric source kept as its upper triangle (d.sym) is read the same way
-// where the panel lies above the diagonal, as the transposed panel (32
-// contiguous doubles of each of W rows) where it lies below, and entry by
-// entry where it crosses the diagonal.  Columns (trans == 1) are read
-// directly: there consecutive lanes own consecutive rows, which are adjacent
-// in memory.
-// HALVES (Markidis kind, S = 2, FP16): instead of digits, the high and low
-// FP16 parts of x = a 2^-e (|x| < 1): X0 = FP16[x], X1 = FP16[x - X0].
-// COMB: the operand is the combination ta A + tb A2 + tc I (d.A2 set; the
-// TRS4 right operand); an instantiation of its own, so that the plain
-// split keeps the registers of its second staging array free.
-// coef.count > 0: the first coef.count blocks of the grid run the coefficient
-// step of the matrices instead (CoefArgs), beside the split's units.
-template <int S, bool FP16, bool HALVES = false, bool COMB = false>
-__global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int count,
-                                                SplitDesc one, const DevState* st, CoefArgs coef) {
-    constexpr int CK = FP16 ? 16 : 32;
+// The lane's NE operand elements (row r, reduction elements k0 .. k0 + NE - 1)
+// of the unit's 32 x 4 CK panel (row block rb, panel kq) into v, through LDS;
+// returns ``needed``, which is false for a wavefront past the last chunk.
+// Every wavefront of the workgroup must call it.
+template <int CK, bool COMB>
+__device__ __forceinline__ bool load_operand(const SplitDesc& d, const DevState* st, double* panel, int rb,
+                                             int kq, int r, int k0, bool needed, double (&v)[CK / 2]) {
     constexpr int NE = CK / 2;
     constexpr int W = 4 * CK;
     constexpr int LDW = W + 2;   // row stride in doubles: rows start 4 banks apart
     constexpr int PER = kFragRows * W / 256;
-    __shared__ double panel[kFragRows * LDW];
-    if (int(blockIdx.x) < coef.count) {
-        const int m = blockIdx.x;
-        if (coef.method == DMP_TRS4)
-            coef_trs4(coef.pd[m], coef.st[m], panel);
-        else
-            coef_canonical(coef.pd[m], coef.st[m], panel);
-        return;
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int local;
-    // a copy: held in scalar registers, so that the LDS stores below cannot
-    // alias it and force its fields to be reloaded
-    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x) - coef.count, &local);
-    if (skipped(d, st)) return;
-    const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
-    const int kq_count = (d.KC + 3) / 4;
-    if (local >= rb_count * kq_count) return;
-    const int rb = local / kq_count, kq = local % kq_count;
-    const int kc = kq * 4 + wave;
-    const int r = rb * kFragRows + (lane & 31);
-    const int k0 = kc * CK + (lane >> 5) * NE;
-    const int e = exponent_of(d.maxbits[r]);
-    if (kq == 0 && wave == 0 && lane < 32) {
-        d.expo[r] = e;
-        if (d.clear != nullptr) d.clear[r] = 0;
-    }
-
-    double v[NE];
     if (!d.trans) {
         // every wave takes part in the staging and the barrier
         // all loads are issued before the first LDS write, so PER of them
@@ -308,12 +261,12 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
             }
         }
         __syncthreads();
-        if (kc >= d.KC) return;
-        const double* src = panel + (lane & 31) * LDW + wave * CK + (lane >> 5) * NE;
+        if (!needed) return false;
+        const double* src = panel + (r - rb * kFragRows) * LDW + (k0 - kq * W);
 #pragma unroll
         for (int i = 0; i < NE; ++i) v[i] = src[i];
     } else {
-        if (kc >= d.KC) return;
+        if (!needed) return false;
         if (r < d.R) {
 #pragma unroll
             for (int i = 0; i < NE; ++i)
@@ -323,6 +276,67 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
             for (int i = 0; i < NE; ++i) v[i] = 0.0;
         }
     }
+    return true;
+}
+
+// Digits: a workgroup of 4 wavefronts owns one 32-row block of the operand
+// and 4 consecutive chunks of CK reduction elements (W = 4 CK); wave w turns
+// chunk 4 q + w into its fragment block, where lane l owns operand row l % 32
+// and NE = CK / 2 consecutive reduction elements (the MFMA operand layout).
+// Operand rows that are matrix rows (trans == 0, also the combined operand)
+// are first staged through LDS: the workgroup reads the 32 x W panel row by
+// row, each wave 64 consecutive doubles per load, so the HBM reads are
+// coalesced although every lane then needs a piece of its own row.  A
+// symmetric source kept as its upper triangle (d.sym) is read the same way
+// where the panel lies above the diagonal, as the transposed panel (32
+// contiguous doubles of each of W rows) where it lies below, and entry by
+// entry where it crosses the diagonal.  Columns (trans == 1) are read
+// directly: there consecutive lanes own consecutive rows, which are adjacent
+// in memory.
+// HALVES (Markidis kind, S = 2, FP16): instead of digits, the high and low
+// FP16 parts of x = a 2^-e (|x| < 1): X0 = FP16[x], X1 = FP16[x - X0].
+// COMB: the operand is the combination ta A + tb A2 + tc I (d.A2 set; the
+// TRS4 right operand); an instantiation of its own, so that the plain
+// split keeps the registers of its second staging array free.
+// coef.count > 0: the first coef.count blocks of the grid run the coefficient
+// step of the matrices instead (CoefArgs), beside the split's units.
+template <int S, bool FP16, bool HALVES = false, bool COMB = false>
+__global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int count,
+                                                SplitDesc one, const DevState* st, CoefArgs coef) {
+    constexpr int CK = FP16 ? 16 : 32;
+    constexpr int NE = CK / 2;
+    constexpr int W = 4 * CK;
+    constexpr int LDW = W + 2;
+    __shared__ double panel[kFragRows * LDW];
+    if (int(blockIdx.x) < coef.count) {
+        const int m = blockIdx.x;
+        if (coef.method == DMP_TRS4)
+            coef_trs4(coef.pd[m], coef.st[m], panel);
+        else
+            coef_canonical(coef.pd[m], coef.st[m], panel);
+        return;
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int local;
+    // a copy: held in scalar registers, so that the LDS stores below cannot
+    // alias it and force its fields to be reloaded
+    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x) - coef.count, &local);
+    if (skipped(d, st)) return;
+    const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
+    const int kq_count = (d.KC + 3) / 4;
+    if (local >= rb_count * kq_count) return;
+    const int rb = local / kq_count, kq = local % kq_count;
+    const int kc = kq * 4 + wave;
+    const int r = rb * kFragRows + (lane & 31);
+    const int k0 = kc * CK + (lane >> 5) * NE;
+    const int e = exponent_of(d.maxbits[r]);
+    if (kq == 0 && wave == 0 && lane < 32) {
+        d.expo[r] = e;
+        if (d.clear != nullptr) d.clear[r] = 0;
+    }
+
+    double v[NE];
+    if (!load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, kc < d.KC, v)) return;
 
     uint8_t* base = d.planes + (int64_t(rb) * d.KC + kc) * int64_t(S) * kFragBytes + lane * 16;
     if constexpr (HALVES) {
@@ -416,6 +430,119 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
             make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
+// Exponent t of an operand row of a residue product: X = rint(a 2^-t) with
+// 2^-t the largest power of two that keeps the row norm of X within
+// ``limit``.  The norm is bounded from the row maximum m: it is at most
+// sqrt(K) m, and at most sqrt(lam m) for a positive semidefinite source with
+// eigenvalues up to lam (|row i|^2 = (A^2)_ii <= lam A_ii <= lam m).
+__device__ inline int residue_exponent(uint64_t bits, int K, double lam, double limit) {
+    if (bits >= 0x7ff0000000000000ull) return kNonFiniteExp;
+    if (bits == 0) return 0;
+    const double m = __longlong_as_double(static_cast<long long>(bits));
+    double nu = sqrt(double(K)) * m;
+    if (lam > 0.0) nu = fmin(nu, sqrt(lam * m));
+    int en = 0, el = 0;
+    const double fn = frexp(nu, &en), fl = frexp(limit, &el);
+    return en - el + (fn > fl ? 1 : 0);
+}
+
+// Residues of an operand: the units and the staging of k_digits, with N
+// planes of one byte (FP16: one half) per element, plane m holding the
+// balanced residues modulo kMods[m].  A plane is laid out in fragments of 16
+// rows x 64 (FP16: 32) reduction elements, 1 KiB each in the order of a
+// 16 x 16 matrix instruction's operand (lane l: row l % 16, 16 bytes from
+// reduction element (l / 16) NE on); a 16-row block's fragments are
+// contiguous.  Each wavefront forms one of its unit's 2 x 2 fragments.  Per element X = Xh 2^27 + Xl exactly; per modulus
+// z = Xh (2^27 mod p) + Xl, q = rint(z / p) (|z| < 2^40, so the product with
+// 1 / p is off by less than 2^-13, closer than any z / p comes to a tie for
+// odd p), and z - q p modulo 256 is the residue's byte (p = 256: +-128 are
+// the same byte).  The integers z and q are read from the low words of z +
+// 1.5 2^52 and q + 1.5 2^52: four full-rate instructions per modulus.
+template <int N, bool FP16, bool COMB>
+__global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int count, SplitDesc one,
+                                                  const DevState* st, CoefArgs coef) {
+    constexpr int CK = FP16 ? 16 : 32;
+    constexpr int NE = CK / 2;
+    constexpr int W = 4 * CK;
+    __shared__ double panel[kFragRows * (W + 2)];
+    if (int(blockIdx.x) < coef.count) {
+        const int m = blockIdx.x;
+        if (coef.method == DMP_TRS4)
+            coef_trs4(coef.pd[m], coef.st[m], panel);
+        else
+            coef_canonical(coef.pd[m], coef.st[m], panel);
+        return;
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int local;
+    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x) - coef.count, &local);
+    if (skipped(d, st)) return;
+    const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
+    const int kq_count = (d.KC + 3) / 4;
+    if (local >= rb_count * kq_count) return;
+    const int rb = local / kq_count, kq = local % kq_count;
+    const int rows16 = rb * 2 + (wave & 1);          // 16-row block
+    const int rc = kq * 2 + (wave >> 1), RC = d.KC / 2;   // fragment along the reduction
+    const int r = rows16 * 16 + (lane & 15);
+    const int k0 = rc * 2 * CK + (lane >> 4) * NE;
+    const int e = residue_exponent(d.maxbits[r], d.K, d.lam, Crt<N>::table.limit);
+    if (rc == 0 && lane < 16) {
+        d.expo[r] = e;
+        if (d.clear != nullptr) d.clear[r] = 0;
+    }
+    double v[NE];
+    if (!load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v)) return;
+
+    constexpr double kMagic = 0x1.8p52;
+    auto low = [](double x) __attribute__((always_inline)) {
+        return uint32_t(static_cast<uint64_t>(__double_as_longlong(x)));
+    };
+    uint32_t w[N][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        constexpr int E = FP16 ? 2 : 4;   // elements per word
+        double xh[E], xl[E], xm[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const double x = e >= kNonFiniteExp ? 0.0 : rint(ldexp(v[g * E + i], -e));
+            xh[i] = rint(x * 0x1p-27);
+            xl[i] = __builtin_fma(xh[i], -0x1p27, x);
+            xm[i] = xl[i] + kMagic;
+        }
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const int p = kMods[m];
+            int c = (1 << 27) % p;
+            if (c > p / 2) c -= p;
+            uint32_t b[E];
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const uint32_t z = low(__builtin_fma(xh[i], double(c), xm[i]));
+                const uint32_t q = low(__builtin_fma(__builtin_fma(xh[i], double(c), xl[i]), 1.0 / p, kMagic));
+                // the low byte of z - q p (24-bit multiply-add: the bits
+                // above do not matter)
+                b[i] = z + __umul24(q, uint32_t(256 - p));
+            }
+            if constexpr (!FP16) {
+                w[m][g] = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) |
+                          __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+            } else {
+                // balanced residues are exact FP16 values (|r| <= 128)
+                uint32_t h = 0;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    h |= uint32_t(__half_as_ushort(__int2half_rn(int(int8_t(uint8_t(b[i])))))) << (16 * i);
+                w[m][g] = h;
+            }
+        }
+    }
+    const int64_t plane = int64_t(rb_count) * 2 * RC * kFragBytes;
+    uint8_t* base = d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16;
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+        *reinterpret_cast<uint4*>(base + m * plane) = make_uint4(w[m][0], w[m][1], w[m][2], w[m][3]);
+}
+
 // ---------------------------------------------------------------------------
 // Host launchers.
 
@@ -445,6 +572,22 @@ static void launch_halves(bool comb, const SplitDesc* descs, int count, const Sp
         k_digits<2, true, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
 }
 
+// Residue planes of N moduli.
+template <int N>
+static void launch_residues_n(bool fp16, bool comb, const SplitDesc* descs, int count,
+                              const SplitDesc& one, const DevState* st, int units,
+                              const CoefArgs& coef, hipStream_t stream) {
+    const unsigned grid = unsigned(units + coef.count);
+    if (fp16 && comb)
+        k_residues<N, true, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+    else if (fp16)
+        k_residues<N, true, false><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+    else if (comb)
+        k_residues<N, false, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+    else
+        k_residues<N, false, false><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+}
+
 using DigitsFn = void (*)(bool, bool, const SplitDesc*, int, const SplitDesc&, const DevState*,
                           int, const CoefArgs&, hipStream_t);
 static const DigitsFn kDigits[kMaxSlices + 1] = {
@@ -452,12 +595,33 @@ static const DigitsFn kDigits[kMaxSlices + 1] = {
     launch_digits_s<4>, launch_digits_s<5>,  launch_digits_s<6>,  launch_digits_s<7>,
     launch_digits_s<8>, launch_digits_s<9>,  launch_digits_s<10>, launch_digits_s<11>,
     launch_digits_s<12>};
+static const DigitsFn kResidues[kMaxMods - kModMin + 1] = {
+    launch_residues_n<11>, launch_residues_n<12>, launch_residues_n<13>,
+    launch_residues_n<14>, launch_residues_n<15>, launch_residues_n<16>};
 
+// The planes of ``units`` units: residues of nmod moduli, or (nmod 0) the
+// kind's digit or half planes.
+static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitDesc* descs, int count,
+                         const SplitDesc& one, const DevState* st, int units, const CoefArgs& coef,
+                         hipStream_t stream) {
+    if (nmod != 0 && (nmod < kModMin || nmod > kMaxMods)) {
+        set_error("no residue split for %d moduli", nmod);
+        return DMP_EINVAL;
+    }
+    if (nmod != 0)
+        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, coef, stream);
+    else if (kind == DMP_MARKIDIS_FP16)
+        launch_halves(comb, descs, count, one, st, units, coef, stream);
+    else
+        kDigits[S](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, coef, stream);
+    DMP_CHECK_HIP(hipGetLastError());
+    return DMP_OK;
+}
 
 // Split one operand.  ``d`` describes it; ``st`` (nullable) skips the work
 // once the state's done flag is set.
 int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
-                 hipStream_t stream) {
+                 hipStream_t stream, int nmod) {
     const int rp = int(round_up(d.R, kPad));
     if (rp == 0) return DMP_OK;
     if (!d.trans) {
@@ -466,29 +630,17 @@ int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
         k_fill_u64<<<(rp + 255) / 256, 256, 0, stream>>>(d.maxbits, rp, 0ull);
         if (d.K > 0) k_colmax<<<split_units_colmax(d.R, d.K), 256, 0, stream>>>(nullptr, 0, d, st);
     }
-    const bool comb = d.A2 != nullptr;
-    if (kind == DMP_MARKIDIS_FP16)
-        launch_halves(comb, nullptr, 0, d, st, split_units_digits(d.R, d.KC), CoefArgs{}, stream);
-    else
-        kDigits[S](kind == DMP_OZ_FP16, comb, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
-                   CoefArgs{}, stream);
-    DMP_CHECK_HIP(hipGetLastError());
-    return DMP_OK;
+    return launch_planes(S, kind, nmod, d.A2 != nullptr, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
+                         CoefArgs{}, stream);
 }
 
 // The digit kernel alone, for an operand whose maxima (d.maxbits: row maxima,
 // or column maxima when d.trans) an earlier product's epilogue accumulated.
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
-                        hipStream_t stream) {
+                        hipStream_t stream, int nmod) {
     if (round_up(d.R, kPad) == 0) return DMP_OK;
-    const bool comb = d.A2 != nullptr;
-    if (kind == DMP_MARKIDIS_FP16)
-        launch_halves(comb, nullptr, 0, d, st, split_units_digits(d.R, d.KC), CoefArgs{}, stream);
-    else
-        kDigits[S](kind == DMP_OZ_FP16, comb, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
-                   CoefArgs{}, stream);
-    DMP_CHECK_HIP(hipGetLastError());
-    return DMP_OK;
+    return launch_planes(S, kind, nmod, d.A2 != nullptr, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
+                         CoefArgs{}, stream);
 }
 
 // Grouped split of count operands (row splits only); descs in device memory
@@ -502,15 +654,9 @@ int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units
 
 int launch_split_grouped_digits(const SplitDesc* descs_dev, int count, int units, int S,
                                 dmp_kind kind, const DevState* st, hipStream_t stream,
-                                const CoefArgs& coef, bool combined) {
+                                const CoefArgs& coef, bool combined, int nmod) {
     if (units + coef.count <= 0) return DMP_OK;
-    if (kind == DMP_MARKIDIS_FP16)
-        launch_halves(combined, descs_dev, count, SplitDesc{}, st, units, coef, stream);
-    else
-        kDigits[S](kind == DMP_OZ_FP16, combined, descs_dev, count, SplitDesc{}, st, units, coef,
-                   stream);
-    DMP_CHECK_HIP(hipGetLastError());
-    return DMP_OK;
+    return launch_planes(S, kind, nmod, combined, descs_dev, count, SplitDesc{}, st, units, coef, stream);
 }
 
 }  // namespace dmp
