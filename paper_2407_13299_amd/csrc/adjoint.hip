@@ -74,10 +74,10 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.S = S;
     x.kind = kind;
     x.KC = int(chunks_of(n, kind));
-    const TileChoice tc = tile_choice_env(kind, S, n);
-    x.rb = tc.rb;
-    x.rb_stride = int64_t(x.KC) * S * kFragBytes;
     const bool residues = mod_capacity(S) > 0;
+    const TileChoice tc = tile_choice_env(kind, S, n);
+    x.rb = residues ? 2 : tc.rb;   // 64 x 64 output tiles, as dmp_purify's
+    x.rb_stride = int64_t(x.KC) * S * kFragBytes;
     const size_t planes = std::max(plane_bytes(n, n, S, kind),
                                    residue_plane_bytes(n, n, kind) * mod_capacity(S));
     x.pa = c.take<uint8_t>(planes);
@@ -194,7 +194,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
     else
         DMP_CHECK(launch_split(sp, x.S, x.kind, x.st, s, x.nmod));
     auto product = [&](const GemmParams& p) -> int {
-        if (x.nmod > 0) return launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s, x.rb);
+        if (x.nmod > 0) return launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s);
         return launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb);
     };
     GemmParams p{};

@@ -50,12 +50,9 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
                   int rb = 4);
 // A product through residues: the residue GEMM over the ``ntiles`` entries of
 // p.mtiles (tiles of shape ``shape``, modulus in the top byte of mat), then
-// the combination and the FP64 epilogue over the nout entries of p.tiles
-// (tile height 32 rb).
+// the combination and the FP64 epilogue over the nout 64 x 64 tiles of p.tiles.
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
-                        hipStream_t stream, int rb);
-// its second half alone
-int launch_residue_epilogue(int nmod, const GemmParams& p, int nout, hipStream_t stream, int rb);
+                        hipStream_t stream);
 // Device copy of the residue GEMM's tile list of one matrix, cached.
 int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count);
 // Workgroups of the purification-mode slice GEMM (kind, S, rb) resident on

@@ -1,7 +1,7 @@
 // Residue products (see modular.hpp): for every modulus p_m the INT8 or FP16
 // matrix product of the operands' residue planes, reduced modulo p_m and
-// stored as bytes; the combination to FP64 and the epilogue are the
-// kResidue phase of the slice GEMM's kernel (ozgemm.hip).
+// stored as bytes (k_residue_gemm); then the combination to FP64 and the
+// product's epilogue (k_combine).
 #include <type_traits>
 #include <vector>
 
@@ -270,8 +270,242 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
     }
 }
 
+// ---- combination ----------------------------------------------------------
+
+template <class T>
+using Global = __attribute__((address_space(1))) T;
+
+__device__ inline double sum64(double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Maxima over the 16 lanes of a row (data parallel primitives, no LDS).
+__device__ inline uint32_t max16(uint32_t v) {
+    auto ror = [](uint32_t x, auto n) __attribute__((always_inline)) {
+        return uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x120 + decltype(n)::value, 0xf, 0xf, false));
+    };
+    v = max(v, ror(v, std::integral_constant<int, 8>{}));
+    v = max(v, ror(v, std::integral_constant<int, 4>{}));
+    v = max(v, ror(v, std::integral_constant<int, 2>{}));
+    return max(v, ror(v, std::integral_constant<int, 1>{}));
+}
+
+// Rebuilds C' = X Y from its residues (modular.hpp) and runs the FP64 end of
+// the product, C = C' 2^(t_i + t_j), by mode as listed at the head of
+// ozgemm.hip.  One workgroup per 64 x 64 tile of p.tiles, a 32 x 32 quadrant
+// per wavefront: lane l holds column l % 32 and rows (l / 32) 4 + 8 (v / 4) +
+// v % 4, v < 16, the order in which the residues are stored, so every load is
+// a whole cache line.
+//
+// Bound: memory (N bytes of residues and 8 to 32 bytes of FP64 per element).
+// Every load is issued before the first result is formed; the four modes and
+// the quadrants that need no bounds or triangle checks are code of their own
+// (the shared epilogue of the slice GEMM, whose selects for modes, masks and
+// 64-bit maxima make half of its instructions, took 28 us at n = 2048 and
+// 335 us at n = 8192, N = 13).  Row maxima, which only choose the next
+// split's powers of two, are kept to the upper word, rounded up.
+template <int N, int MODE>
+__global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
+    constexpr bool PUR = MODE == EPI_SQUARE || MODE == EPI_UPDATE || MODE == EPI_SQUARE_TRS4;
+    constexpr bool UPPER = MODE != EPI_STORE;
+    __shared__ double red[4][kPartials];
+    const int b = blockIdx.x, nb = gridDim.x;
+    const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
+    const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
+    const Tile tile = p.tiles[t];
+    const MatDesc d = p.descs ? p.descs[tile.mat] : p.one;
+    const DevState* st = p.states ? p.states + d.state_index : nullptr;
+    if (st != nullptr && st->done) return;
+    double alpha = 0.0, beta = 0.0, gamma = 1.0;
+    if constexpr (MODE == EPI_UPDATE) {
+        alpha = st->alpha;
+        beta = st->beta;
+        gamma = st->gamma;
+    }
+    const bool has_product = MODE != EPI_UPDATE || gamma != 0.0;   // a TRS4 step without one
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int qr = 2 * int(tile.I) + (wave >> 1), qc = 2 * int(tile.J) + (wave & 1);
+    const int M = __builtin_amdgcn_readfirstlane(d.M), NC = __builtin_amdgcn_readfirstlane(d.N);
+    const int ldc = __builtin_amdgcn_readfirstlane(d.ldc);
+    const int lrow = (lane >> 5) * 4, lcol = lane & 31;
+    double s0 = 0.0, s1 = 0.0;
+
+    auto quadrant = [&](auto full) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full)::value;
+        const int cbs = int(round_up(NC, kPad)) / 32;
+        const int64_t plane = int64_t(round_up(M, kPad) * round_up(NC, kPad));
+        v4i w[N];
+        if (has_product) {
+            const Global<v4i>* src = reinterpret_cast<const Global<v4i>*>(
+                reinterpret_cast<uint64_t>(d.res) + (int64_t(qr) * cbs + qc) * kFragBytes);
+#pragma unroll
+            for (int m = 0; m < N; ++m) w[m] = src[m * (plane / 16) + lane];
+        }
+        // exponents: rows in groups of four
+        const Global<v4i>* ea = reinterpret_cast<const Global<v4i>*>(reinterpret_cast<uint64_t>(d.ea + qr * 32 + lrow));
+        v4i er[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) er[g] = ea[2 * g];
+        const int fj = reinterpret_cast<const Global<int>*>(reinterpret_cast<uint64_t>(d.eb))[qc * 32 + lcol];
+        // element v of the quadrant: in the matrix (and, for the modes on one
+        // triangle, on or above the diagonal)
+        const int row0 = qr * 32 + lrow, col = qc * 32 + lcol;
+        auto inside = [&](int v) __attribute__((always_inline)) {
+            const int row = row0 + 8 * (v >> 2) + (v & 3);
+            return FULL || (row < M && col < NC && (!UPPER || row <= col));
+        };
+        const int voff = lrow * ldc + lcol;
+        auto at = [&](const double* base, int v) __attribute__((always_inline)) {
+            // wave-uniform part of the address apart from the lane's
+            return reinterpret_cast<Global<double>*>(
+                reinterpret_cast<uint64_t>(base) +
+                8 * (int64_t(qr * 32 + 8 * (v >> 2) + (v & 3)) * ldc + qc * 32));
+        };
+        double pv[16], xv[16], hv[16];
+        if constexpr (PUR) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const bool in = inside(v);
+                pv[v] = in ? at(d.P, v)[voff] : 0.0;
+                if constexpr (MODE == EPI_UPDATE) {
+                    xv[v] = in ? at(d.X2, v)[voff] : 0.0;
+                    hv[v] = in ? at(d.H, v)[voff] : 0.0;
+                }
+            }
+        }
+        uint32_t hi[16], cmax = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            double out4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = 4 * g + e;
+                const int row = row0 + 8 * g + e;
+                double c = 0.0;
+                if (has_product) {
+                    // the fraction C' / M as f0 2^-40 + f1 2^-80 less its
+                    // nearest integer, times M
+                    constexpr const CrtTable& T = Crt<N>::table;
+                    double f0 = -T.k0, f1 = -T.k1;
+#pragma unroll
+                    for (int m = 0; m < N; ++m) {
+                        const double u = double((uint32_t(w[m][g]) >> (8 * e)) & 0xffu);
+                        f0 = __builtin_fma(u, T.w0[m], f0);
+                        f1 = __builtin_fma(u, T.w1[m], f1);
+                    }
+                    const double k = rint(__builtin_fma(f1, 0x1p-80, f0 * 0x1p-40));
+                    const double x = __builtin_fma(__builtin_fma(k, -0x1p40, f0), 0x1p40, f1);
+                    const int ei = er[g][e];
+                    c = ldexp(__builtin_fma(x, T.mh, x * T.ml), ei + fj);
+                    if (ei >= kNonFiniteExp || fj >= kNonFiniteExp) c = __builtin_nan("");
+                }
+                double o = c;
+                if constexpr (PUR) {
+                    const bool diag = !FULL && row == col;
+                    const double mult = diag ? 1.0 : 2.0;
+                    const double pij = pv[v];
+                    if (inside(v)) {
+                        if constexpr (MODE == EPI_SQUARE) {
+                            if (diag) s0 += pij - c;
+                            s1 += mult * c * ((diag ? 1.0 : 0.0) - pij);
+                        } else if constexpr (MODE == EPI_SQUARE_TRS4) {
+                            const double r = pij - c;
+                            s0 += mult * c * (4.0 * pij - 3.0 * c);
+                            s1 += mult * r * r;
+                        } else {
+                            o = alpha * pij + beta * xv[v] + gamma * c;
+                            s0 += mult * o * hv[v];
+                            if (diag) s1 += o;
+                        }
+                    }
+                }
+                out4[e] = o;
+                const uint32_t h = uint32_t(static_cast<uint64_t>(__double_as_longlong(o)) >> 32) & 0x7fffffffu;
+                hi[v] = inside(v) ? h : 0u;
+                cmax = max(cmax, hi[v]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (inside(4 * g + e)) at(d.out, 4 * g + e)[voff] = out4[e];
+            if (UPPER && !(PUR && p.upper_only)) {
+                // the mirror: four consecutive elements of row ``col``
+                Global<double>* mir = reinterpret_cast<Global<double>*>(
+                    reinterpret_cast<uint64_t>(d.out) + 8 * (int64_t(col) * ldc + row0 + 8 * g));
+                if constexpr (FULL) {
+                    typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+                    Global<d2>* m2 = reinterpret_cast<Global<d2>*>(mir);
+                    m2[0] = d2{out4[0], out4[1]};
+                    m2[1] = d2{out4[2], out4[3]};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (inside(4 * g + e) && row0 + 8 * g + e != col) mir[e] = out4[e];
+                }
+            }
+        }
+        // Row maxima (upper words).  Lanes 16 apart are combined two rows at
+        // a time by an exchange, after which the even 16-lane rows hold the
+        // first of the two rows and the odd ones the second; then over the
+        // 16 lanes; lane k < 8 of each 16-lane row holds pair k's maximum.
+        auto word = [](uint32_t h) { return (uint64_t(h) << 32) | (h != 0 ? 0xffffffffu : 0u); };
+        if (d.rowmax != nullptr) {
+            uint32_t mine = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const auto sw = __builtin_amdgcn_permlane16_swap(hi[2 * k], hi[2 * k + 1], false, false);
+                const uint32_t m = max16(max(uint32_t(sw[0]), uint32_t(sw[1])));
+                mine = (lane & 15) == k ? m : mine;
+            }
+            const int v = 2 * (lane & 7) + ((lane >> 4) & 1);
+            if ((lane & 15) < 8 && mine != 0)
+                atomicMax(reinterpret_cast<unsigned long long*>(d.rowmax) + row0 + 8 * (v >> 2) + (v & 3),
+                          static_cast<unsigned long long>(word(mine)));
+        }
+        uint64_t* const cdst = UPPER ? d.rowmax : d.colmax;
+        if (cdst != nullptr) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(cmax, cmax, false, false);
+            const uint32_t m = max(uint32_t(sw[0]), uint32_t(sw[1]));
+            if (lane < 32 && m != 0)
+                atomicMax(reinterpret_cast<unsigned long long*>(cdst) + col, static_cast<unsigned long long>(word(m)));
+        }
+    };
+    if (!UPPER || qr <= qc) {
+        if ((!UPPER || qr < qc) && (qr + 1) * 32 <= M && (qc + 1) * 32 <= NC)
+            quadrant(std::true_type{});
+        else
+            quadrant(std::false_type{});
+    }
+    if constexpr (PUR) {
+        s0 = sum64(s0);
+        s1 = sum64(s1);
+        if (lane == 0) {
+            red[wave][0] = s0;
+            red[wave][1] = s1;
+        }
+        __syncthreads();
+        if (threadIdx.x < kPartials)
+            p.partials[int64_t(t) * kPartials + threadIdx.x] =
+                ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+    }
+}
+
+template <int N>
+static int launch_combine(const GemmParams& p, int nout, hipStream_t stream) {
+    switch (p.mode) {
+        case EPI_STORE: k_combine<N, EPI_STORE><<<nout, 256, 0, stream>>>(p); break;
+        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM><<<nout, 256, 0, stream>>>(p); break;
+        case EPI_SQUARE: k_combine<N, EPI_SQUARE><<<nout, 256, 0, stream>>>(p); break;
+        case EPI_UPDATE: k_combine<N, EPI_UPDATE><<<nout, 256, 0, stream>>>(p); break;
+        default: k_combine<N, EPI_SQUARE_TRS4><<<nout, 256, 0, stream>>>(p);
+    }
+    DMP_CHECK_HIP(hipGetLastError());
+    return DMP_OK;
+}
+
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
-                        hipStream_t stream, int rb) {
+                        hipStream_t stream) {
     if (ntiles <= 0 || nout <= 0) return DMP_OK;
     if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || nmod < kModMin || nmod > kMaxMods ||
         p.mtiles == nullptr || p.fix != nullptr) {
@@ -288,7 +522,10 @@ int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p,
     else
         k_residue_gemm<false, 2, 4, 4, 2, 4, 4><<<ntiles, 512, 0, stream>>>(p, upper);
     DMP_CHECK_HIP(hipGetLastError());
-    return launch_residue_epilogue(nmod, p, nout, stream, rb);
+    static int (*const combine[kMaxMods - kModMin + 1])(const GemmParams&, int, hipStream_t) = {
+        launch_combine<11>, launch_combine<12>, launch_combine<13>,
+        launch_combine<14>, launch_combine<15>, launch_combine<16>};
+    return combine[nmod - kModMin](p, nout, stream);
 }
 
 int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count) {

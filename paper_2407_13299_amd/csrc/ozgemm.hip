@@ -40,7 +40,6 @@
 // In the purification modes only the upper triangle is computed and kept,
 // so every iterate is exactly symmetric and its row digits also serve as its
 // column digits.
-#include "host.hpp"
 #include "ldsload.hpp"
 
 namespace dmp {
@@ -66,13 +65,10 @@ __device__ inline double wave_sum(double v) {
 // stored, no epilogue), then kFixup, one block per split tile (adds the
 // parts' group sums in place of the main loop, then runs the epilogue).
 // Separate instantiations keep the whole-tile kernel's registers as they are.
-// kResidue: no main loop either; S counts the moduli of a residue product
-// (modular.hip), whose residues are combined into the FP64 sums instead.
-constexpr int kWhole = 0, kPiece = 1, kFixup = 2, kResidue = 3;
+constexpr int kWhole = 0, kPiece = 1, kFixup = 2;
 template <int S, bool FP16, int TERMS = 0, bool PUR = false, int RB = 4, int PHASE = kWhole>
 __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams p) {
-    constexpr bool RESIDUE = PHASE == kResidue;
-    constexpr int BLOCKS = RESIDUE ? 2 * RB : (RB + 2) * S;   // 1 KiB blocks per chunk
+    constexpr int BLOCKS = (RB + 2) * S;          // 1 KiB blocks per chunk
     constexpr int STAGE = BLOCKS * kFragBytes;
     constexpr int WAVES = 2 * RB;
     constexpr int PER = (BLOCKS + WAVES - 1) / WAVES;  // loads per wavefront per chunk
@@ -87,7 +83,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // XCDs in turn; give every XCD one contiguous slice of the tile list.
     const int b = blockIdx.x;
     int t, part = 0;
-    if constexpr (PHASE == kWhole || RESIDUE) {
+    if constexpr (PHASE == kWhole) {
         const int nb = gridDim.x;
         const int xcd = b & 7, q = nb >> 3, rem = nb & 7, loc = b >> 3;
         t = p.spread ? b : (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
@@ -244,34 +240,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // Part u of the split tail keeps its group sums at piece u of p.fix:
     // [wavefront][group][4 x 4 values][lane], 16 bytes per lane and store.
     constexpr int64_t kPieceInts = int64_t(WAVES) * S * 16 * 64;
-    double hsum[16];
-    if constexpr (RESIDUE) {
-        // C' = X Y from its residues (modular.hpp): the fraction C' / M as
-        // S0 2^-40 + S1 2^-80 less its nearest integer, times M.  All
-        // loads are issued before the first is used.
-        if (!no_product) {
-            const int rbs = int(round_up(d.M, kPad)) / kFragRows, cbs = int(round_up(d.N, kPad)) / kFragRows;
-            const uint8_t* src = d.res + (int64_t(RB * I + wm) * cbs + 2 * J + wn) * kFragBytes + lane * 16;
-            const int64_t plane = int64_t(rbs) * cbs * kFragBytes;
-            v4i w[S];
-#pragma unroll
-            for (int m = 0; m < S; ++m) w[m] = *reinterpret_cast<const v4i*>(src + m * plane);
-            constexpr const CrtTable& T = Crt<S>::table;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                double f0 = -T.k0, f1 = -T.k1;
-#pragma unroll
-                for (int m = 0; m < S; ++m) {
-                    const double u = double((uint32_t(w[m][v >> 2]) >> (8 * (v & 3))) & 0xffu);
-                    f0 = __builtin_fma(u, T.w0[m], f0);
-                    f1 = __builtin_fma(u, T.w1[m], f1);
-                }
-                const double k = rint(__builtin_fma(f1, 0x1p-80, f0 * 0x1p-40));
-                const double x = __builtin_fma(__builtin_fma(k, -0x1p40, f0), 0x1p40, f1);
-                hsum[v] = __builtin_fma(x, T.mh, x * T.ml);
-            }
-        }
-    } else if constexpr (PHASE == kFixup) {
+    if constexpr (PHASE == kFixup) {
         if (!no_product) {
             const int* src = p.fix + int64_t(b) * p.nsplit * kPieceInts +
                              int64_t(wave) * (S * 16 * 64) + lane * 4;
@@ -378,11 +347,10 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     // stored.  The compiler cannot tell that the output does not alias P,
     // X2, H or the exponents, so a load placed after a store would wait for
     // it and every element would pay a full memory latency.
+    double hsum[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        if constexpr (RESIDUE) {
-            if (no_product) hsum[v] = 0.0;
-        } else if constexpr (TERMS > 0) {
+        if constexpr (TERMS > 0) {
             hsum[v] = double(accf[v]);
         } else {
             double h = double(acc[S - 1][v]);
@@ -423,7 +391,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
         const int row = row0 + (v >> 2) * 8 + (v & 3);
         const double h = hsum[v];
         const int ei = eiv[v];
-        constexpr int shift = TERMS > 0 || RESIDUE ? 0 : 2 * kTopBits;
+        constexpr int shift = TERMS > 0 ? 0 : 2 * kTopBits;
         const double c = no_product ? 0.0
                          : (ei >= kNonFiniteExp || fj >= kNonFiniteExp)
                              ? __builtin_nan("")
@@ -635,33 +603,6 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
         kTerms[S](p, ntiles, stream);
     else
         kGemm[kWhole][S](kind == DMP_OZ_FP16, p, ntiles, rb, stream);
-    DMP_CHECK_HIP(hipGetLastError());
-    return DMP_OK;
-}
-
-// The combination of N residues and the FP64 epilogue of every mode.
-template <int N>
-static void launch_residue_n(const GemmParams& p, int ntiles, int rb, hipStream_t stream) {
-    const bool pur = purification_mode(p.mode);
-    if (rb == 2 && pur)
-        k_ozgemm<N, false, 0, true, 2, kResidue><<<ntiles, 256, 0, stream>>>(p);
-    else if (rb == 2)
-        k_ozgemm<N, false, 0, false, 2, kResidue><<<ntiles, 256, 0, stream>>>(p);
-    else if (pur)
-        k_ozgemm<N, false, 0, true, 4, kResidue><<<ntiles, kGemmThreads, 0, stream>>>(p);
-    else
-        k_ozgemm<N, false, 0, false, 4, kResidue><<<ntiles, kGemmThreads, 0, stream>>>(p);
-}
-
-int launch_residue_epilogue(int nmod, const GemmParams& p, int nout, hipStream_t stream, int rb) {
-    static void (*const table[kMaxMods - kModMin + 1])(const GemmParams&, int, int, hipStream_t) = {
-        launch_residue_n<11>, launch_residue_n<12>, launch_residue_n<13>,
-        launch_residue_n<14>, launch_residue_n<15>, launch_residue_n<16>};
-    if (nmod < kModMin || nmod > kMaxMods || (rb != 2 && rb != 4)) {
-        set_error("no residue combination for %d moduli", nmod);
-        return DMP_EINVAL;
-    }
-    table[nmod - kModMin](p, nout, rb, stream);
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }

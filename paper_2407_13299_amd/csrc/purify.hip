@@ -600,7 +600,7 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
         DMP_CHECK_HIP(hipEventRecord(t.start, s));
     }
     if (g.nmod > 0)
-        DMP_CHECK(launch_residue_gemm(g.kind, g.nmod, g.mshape, q, g.nmt, g.ntiles, s, g.rb));
+        DMP_CHECK(launch_residue_gemm(g.kind, g.nmod, g.mshape, q, g.nmt, g.ntiles, s));
     else
         DMP_CHECK(launch_ozgemm(g.S, g.kind, q, g.ntiles, s, g.rb));
     if (timers) {
