@@ -1,7 +1,7 @@
 // Device code shared by the purification kernels and the split kernel:
-// fixed-order block sums and the per-iteration coefficients computed from the
+// fixed-order block sums, the per-iteration coefficients computed from the
 // square's trace partials (the split of X2 runs them in extra blocks of its
-// own launch).
+// own launch) and the end of an iteration (run by the next split of P).
 #pragma once
 
 #include "common.hpp"
@@ -112,6 +112,47 @@ __device__ inline void coef_trs4(const PurDesc& d, DevState& s, double* sh) {
             s.tc = g;
         }
     }
+}
+
+constexpr double kStagnationWindow = 1e-2;
+
+// Energy of the new iterate from the update's trace partials and the stopping
+// rule of Sec. 3.  One block of 256 threads.
+__device__ inline void finalize_iteration(const PurDesc& d, DevState& s, double* sh) {
+    if (s.done) return;
+    double e, tr;
+    sum_partials(d, sh, &e, &tr);
+    if (threadIdx.x == 0) {
+        const double de = e - s.E;
+        s.dE_prev = s.dE;
+        s.dE = de;
+        s.E_prev = s.E;
+        s.E = e;
+        s.trace_p = tr;
+        s.iters += 1;
+        s.products += s.gamma != 0.0 ? 2 : 1;
+        int stop = -1;
+        if (!isfinite(e)) stop = DMP_STOP_NONFINITE;
+        else if (fabs(de) < s.tol) stop = DMP_STOP_CONVERGED;
+        else if (s.iters >= 2 && de > 0.0 && s.dE_prev > 0.0 && fabs(de) < kStagnationWindow)
+            stop = DMP_STOP_STAGNATED;
+        else if (s.iters >= s.max_iter) stop = DMP_STOP_MAX_ITER;
+        if (stop >= 0) {
+            s.done = 1;
+            s.stop_reason = stop;
+        }
+    }
+}
+
+// The step an extra block of a split launch runs for its matrix (CoefArgs).
+__device__ inline void coef_block(const CoefArgs& a, double* sh) {
+    const int m = blockIdx.x;
+    if (a.step == kStepFinalize)
+        finalize_iteration(a.pd[m], a.st[m], sh);
+    else if (a.method == DMP_TRS4)
+        coef_trs4(a.pd[m], a.st[m], sh);
+    else
+        coef_canonical(a.pd[m], a.st[m], sh);
 }
 
 }  // namespace dmp

@@ -180,15 +180,20 @@ struct PurDesc {
     int pad_;
 };
 
-// Coefficient step run by extra blocks of a split launch (count > 0): block
-// b < count computes the update weights of matrix b from the square's trace
-// partials (method: DMP_CANONICAL or DMP_TRS4), the split's units follow.  The split of X2 reads only
-// the done flags of the states these blocks write.
+// Step run by extra blocks of a split launch (count > 0): block b < count
+// works on matrix b, the split's units follow.  kStepCoef, in the split of
+// X2: the update weights from the square's trace partials (method:
+// DMP_CANONICAL or DMP_TRS4).  kStepFinalize, in the split of the next
+// iterate: energy and stopping rule of the iteration before.  The split reads
+// only the done flags of the states these blocks write; a split that misses a
+// flag set beside it only fills planes that no product will read.
+constexpr int kStepCoef = 0, kStepFinalize = 1;
 struct CoefArgs {
     const PurDesc* pd;
     DevState* st;
     int count;
     int method;
+    int step;
 };
 
 // Bounds on the spectrum of the purification operands (with room for the

@@ -6,6 +6,8 @@
 
 namespace dmp {
 
+typedef int v1i __attribute__((ext_vector_type(1)));
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));

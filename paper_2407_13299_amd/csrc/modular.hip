@@ -305,11 +305,12 @@ __device__ inline uint32_t max16(uint32_t v) {
 // 64-bit maxima make half of its instructions, took 28 us at n = 2048 and
 // 335 us at n = 8192, N = 13).  Row maxima, which only choose the next
 // split's powers of two, are kept to the upper word, rounded up.
-template <int N, int MODE>
-__global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
+template <int N, int MODE, int G>
+__global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams p) {
     constexpr bool PUR = MODE == EPI_SQUARE || MODE == EPI_UPDATE || MODE == EPI_SQUARE_TRS4;
     constexpr bool UPPER = MODE != EPI_STORE;
-    __shared__ double red[4][kPartials];
+    constexpr int WAVES = 16 / G;
+    __shared__ double red[WAVES][kPartials];
     const int b = blockIdx.x, nb = gridDim.x;
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
@@ -326,7 +327,9 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
     const bool has_product = MODE != EPI_UPDATE || gamma != 0.0;   // a TRS4 step without one
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int qr = 2 * int(tile.I) + (wave >> 1), qc = 2 * int(tile.J) + (wave & 1);
+    // quadrant (quad / 2, quad % 2) of the tile, row groups g0 .. g0 + G - 1 of it
+    const int quad = wave / (4 / G), g0 = wave % (4 / G) * G;
+    const int qr = 2 * int(tile.I) + (quad >> 1), qc = 2 * int(tile.J) + (quad & 1);
     const int M = __builtin_amdgcn_readfirstlane(d.M), NC = __builtin_amdgcn_readfirstlane(d.N);
     const int ldc = __builtin_amdgcn_readfirstlane(d.ldc);
     const int lrow = (lane >> 5) * 4, lcol = lane & 31;
@@ -336,22 +339,23 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
         constexpr bool FULL = decltype(full)::value;
         const int cbs = int(round_up(NC, kPad)) / 32;
         const int64_t plane = int64_t(round_up(M, kPad) * round_up(NC, kPad));
-        v4i w[N];
+        using Word = typename std::conditional<G == 4, v4i, typename std::conditional<G == 2, v2i, v1i>::type>::type;
+        Word w[N];
         if (has_product) {
-            const Global<v4i>* src = reinterpret_cast<const Global<v4i>*>(
-                reinterpret_cast<uint64_t>(d.res) + (int64_t(qr) * cbs + qc) * kFragBytes);
+            const Global<Word>* src = reinterpret_cast<const Global<Word>*>(
+                reinterpret_cast<uint64_t>(d.res) + (int64_t(qr) * cbs + qc) * kFragBytes + 4 * g0);
 #pragma unroll
-            for (int m = 0; m < N; ++m) w[m] = src[m * (plane / 16) + lane];
+            for (int m = 0; m < N; ++m) w[m] = src[(m * plane + lane * 16) / int(sizeof(Word))];
         }
         // exponents: rows in groups of four
-        const Global<v4i>* ea = reinterpret_cast<const Global<v4i>*>(reinterpret_cast<uint64_t>(d.ea + qr * 32 + lrow));
-        v4i er[4];
+        const Global<v4i>* ea = reinterpret_cast<const Global<v4i>*>(reinterpret_cast<uint64_t>(d.ea + qr * 32 + 8 * g0 + lrow));
+        v4i er[G];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) er[g] = ea[2 * g];
+        for (int g = 0; g < G; ++g) er[g] = ea[2 * g];
         const int fj = reinterpret_cast<const Global<int>*>(reinterpret_cast<uint64_t>(d.eb))[qc * 32 + lcol];
         // element v of the quadrant: in the matrix (and, for the modes on one
         // triangle, on or above the diagonal)
-        const int row0 = qr * 32 + lrow, col = qc * 32 + lcol;
+        const int row0 = qr * 32 + 8 * g0 + lrow, col = qc * 32 + lcol;
         auto inside = [&](int v) __attribute__((always_inline)) {
             const int row = row0 + 8 * (v >> 2) + (v & 3);
             return FULL || (row < M && col < NC && (!UPPER || row <= col));
@@ -361,12 +365,12 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
             // wave-uniform part of the address apart from the lane's
             return reinterpret_cast<Global<double>*>(
                 reinterpret_cast<uint64_t>(base) +
-                8 * (int64_t(qr * 32 + 8 * (v >> 2) + (v & 3)) * ldc + qc * 32));
+                8 * (int64_t(qr * 32 + 8 * (g0 + (v >> 2)) + (v & 3)) * ldc + qc * 32));
         };
-        double pv[16], xv[16], hv[16];
+        double pv[4 * G], xv[4 * G], hv[4 * G];
         if constexpr (PUR) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
+            for (int v = 0; v < 4 * G; ++v) {
                 const bool in = inside(v);
                 pv[v] = in ? at(d.P, v)[voff] : 0.0;
                 if constexpr (MODE == EPI_UPDATE) {
@@ -375,9 +379,9 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
                 }
             }
         }
-        uint32_t hi[16], cmax = 0;
+        uint32_t hi[4 * G], cmax = 0;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < G; ++g) {
             double out4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -448,18 +452,18 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
         // Row maxima (upper words).  Lanes 16 apart are combined two rows at
         // a time by an exchange, after which the even 16-lane rows hold the
         // first of the two rows and the odd ones the second; then over the
-        // 16 lanes; lane k < 8 of each 16-lane row holds pair k's maximum.
+        // 16 lanes; lane k < 2 G of each 16-lane row holds pair k's maximum.
         auto word = [](uint32_t h) { return (uint64_t(h) << 32) | (h != 0 ? 0xffffffffu : 0u); };
         if (d.rowmax != nullptr) {
             uint32_t mine = 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < 2 * G; ++k) {
                 const auto sw = __builtin_amdgcn_permlane16_swap(hi[2 * k], hi[2 * k + 1], false, false);
                 const uint32_t m = max16(max(uint32_t(sw[0]), uint32_t(sw[1])));
                 mine = (lane & 15) == k ? m : mine;
             }
-            const int v = 2 * (lane & 7) + ((lane >> 4) & 1);
-            if ((lane & 15) < 8 && mine != 0)
+            const int v = 2 * (lane & 15) + ((lane >> 4) & 1);
+            if ((lane & 15) < 2 * G && mine != 0)
                 atomicMax(reinterpret_cast<unsigned long long*>(d.rowmax) + row0 + 8 * (v >> 2) + (v & 3),
                           static_cast<unsigned long long>(word(mine)));
         }
@@ -485,20 +489,25 @@ __global__ __launch_bounds__(256, 2) void k_combine(GemmParams p) {
             red[wave][1] = s1;
         }
         __syncthreads();
-        if (threadIdx.x < kPartials)
-            p.partials[int64_t(t) * kPartials + threadIdx.x] =
-                ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+        if (threadIdx.x < kPartials) {
+            double r = 0.0;
+#pragma unroll
+            for (int i = 0; i < WAVES; ++i) r += red[i][threadIdx.x];
+            p.partials[int64_t(t) * kPartials + threadIdx.x] = r;
+        }
     }
 }
+
+constexpr int kCombineGroups = 2;
 
 template <int N>
 static int launch_combine(const GemmParams& p, int nout, hipStream_t stream) {
     switch (p.mode) {
-        case EPI_STORE: k_combine<N, EPI_STORE><<<nout, 256, 0, stream>>>(p); break;
-        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM><<<nout, 256, 0, stream>>>(p); break;
-        case EPI_SQUARE: k_combine<N, EPI_SQUARE><<<nout, 256, 0, stream>>>(p); break;
-        case EPI_UPDATE: k_combine<N, EPI_UPDATE><<<nout, 256, 0, stream>>>(p); break;
-        default: k_combine<N, EPI_SQUARE_TRS4><<<nout, 256, 0, stream>>>(p);
+        case EPI_STORE: k_combine<N, EPI_STORE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
+        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
+        case EPI_SQUARE: k_combine<N, EPI_SQUARE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
+        case EPI_UPDATE: k_combine<N, EPI_UPDATE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
+        default: k_combine<N, EPI_SQUARE_TRS4, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p);
     }
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;

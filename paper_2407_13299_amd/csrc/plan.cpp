@@ -314,8 +314,8 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
     g.fix = g.fix_pieces > 0 ? c.take<int>(size_t(g.fix_pieces) * piece_ints(g.S, g.rb)) : nullptr;
     // the refinement step reuses the partials of one matrix's tile pairs
     parts = std::max<size_t>(parts, size_t(g.max_pairs));
+    // what upload_group copies, in one run of the workspace
     g.pd = c.take<PurDesc>(g.count);
-    g.st = c.take<DevState>(g.count);
     g.splitP[0] = c.take<SplitDesc>(g.count);
     g.splitP[1] = c.take<SplitDesc>(g.count);
     g.splitX = c.take<SplitDesc>(g.count);
@@ -327,9 +327,48 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
     g.up[1] = c.take<MatDesc>(g.count);
     g.tiles = c.take<Tile>(std::max<size_t>(1, g.kind == DMP_FP64_NATIVE ? 1 : parts));
     g.mtiles = mtiles > 0 ? c.take<Tile>(mtiles) : nullptr;
-    g.partials = c.take<double>(std::max<size_t>(1, parts) * kPartials);
     g.pairs = c.take<IPair>(g.max_pairs);
+    g.st = c.take<DevState>(g.count);
+    g.partials = c.take<double>(std::max<size_t>(1, parts) * kPartials);
     return c.used();
+}
+
+// The residue tiles of a batch in plain block order, which the hardware deals
+// to the 8 XCDs in turn: the tiles of one matrix and modulus stay on one XCD,
+// whose L2 then holds their operand panels; these runs are dealt, the most
+// work first, to the XCD with the least.
+static void spread_residue_tiles(std::vector<Tile>& tiles, const int* n, const GroupPlan& g) {
+    constexpr int kXcds = 8;
+    struct Run {
+        size_t first, count;
+        double work;
+    };
+    std::vector<Run> runs;
+    for (size_t i = 0; i < tiles.size(); ++i) {
+        if (i == 0 || tiles[i].mat != tiles[i - 1].mat) runs.push_back(Run{i, 0, 0.0});
+        runs.back().count++;
+        runs.back().work += n[g.idx[tiles[i].mat & 0xffffffu]] + 64.0;
+    }
+    std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.work > b.work; });
+    std::vector<size_t> queue[kXcds];
+    double load[kXcds] = {};
+    for (const Run& r : runs) {
+        const int q = int(std::min_element(load, load + kXcds) - load);
+        for (size_t i = 0; i < r.count; ++i) queue[q].push_back(r.first + i);
+        load[q] += r.work;
+    }
+    std::vector<Tile> out;
+    out.reserve(tiles.size());
+    size_t next[kXcds] = {};
+    for (size_t pos = 0; pos < tiles.size(); ++pos) {
+        // the XCD's own queue, or the longest left once it is empty
+        int q = int(pos % kXcds);
+        if (next[q] == queue[q].size())
+            for (int x = 0; x < kXcds; ++x)
+                if (queue[x].size() - next[x] > queue[q].size() - next[q]) q = x;
+        out.push_back(tiles[queue[q][next[q]++]]);
+    }
+    tiles.swap(out);
 }
 
 void build_group(GroupPlan& g, const double* const* H, double* const* P, const int* n,
@@ -371,6 +410,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
             g.mshape = residue_shape(wide);
             for (int b : order)
                 append_residue_tiles(out.mtiles, n[g.idx[b]], g.nmod, g.mshape, true, uint32_t(b));
+            if (cnt > 1) spread_residue_tiles(out.mtiles, n, g);
             g.nmt = int(out.mtiles.size());
         }
     }

@@ -185,6 +185,7 @@ struct GroupHost {
     std::vector<MatDesc> q0, q1, u0, u1;
     std::vector<Tile> tiles, mtiles;
     std::vector<IPair> pairs;
+    std::vector<uint8_t> staged;   // the bytes of the one copy to the device
 };
 // Fill the descriptors of a carved group for the caller's matrices; sets
 // the group's tile count, unit counts, largest size and tail plan

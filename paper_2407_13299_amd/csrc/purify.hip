@@ -51,7 +51,6 @@ struct PendingTimer {
     int which;
     double ops;
 };
-constexpr double kStagnationWindow = 1e-2;
 
 
 __device__ inline double block_min(double v, double* sh) {
@@ -280,34 +279,9 @@ __global__ __launch_bounds__(256) void k_finalize_trs4(const PurDesc* pd, DevSta
     coef_trs4(pd[blockIdx.x], states[blockIdx.x], sh);
 }
 
-// Energy of the new iterate and the stopping rule of Sec. 3.
 __global__ __launch_bounds__(256) void k_finalize_iter(const PurDesc* pd, DevState* states) {
     __shared__ double sh[4];
-    const PurDesc& d = pd[blockIdx.x];
-    DevState& s = states[blockIdx.x];
-    if (s.done) return;
-    double e, tr;
-    sum_partials(d, sh, &e, &tr);
-    if (threadIdx.x == 0) {
-        const double de = e - s.E;
-        s.dE_prev = s.dE;
-        s.dE = de;
-        s.E_prev = s.E;
-        s.E = e;
-        s.trace_p = tr;
-        s.iters += 1;
-        s.products += s.gamma != 0.0 ? 2 : 1;
-        int stop = -1;
-        if (!isfinite(e)) stop = DMP_STOP_NONFINITE;
-        else if (fabs(de) < s.tol) stop = DMP_STOP_CONVERGED;
-        else if (s.iters >= 2 && de > 0.0 && s.dE_prev > 0.0 && fabs(de) < kStagnationWindow)
-            stop = DMP_STOP_STAGNATED;
-        else if (s.iters >= s.max_iter) stop = DMP_STOP_MAX_ITER;
-        if (stop >= 0) {
-            s.done = 1;
-            s.stop_reason = stop;
-        }
-    }
+    finalize_iteration(pd[blockIdx.x], states[blockIdx.x], sh);
 }
 
 // ---- native FP64 path: elementwise work around rocBLAS products -----------
@@ -528,36 +502,40 @@ const int2* as_int2(const IPair* p) { return reinterpret_cast<const int2*>(p); }
 
 // Fill a carved group's descriptors on the host and copy them to the
 // device; ``keep`` holds the host copies until the stream has passed the
-// copies.
-int upload_group(GroupPlan& g, const double* const* H, double* const* P, const int* n,
-                 const int* nocc, hipStream_t s, std::vector<std::unique_ptr<GroupHost>>& keep) {
+// copies.  ``pairs``: the 32 x 32 tile pairs are needed (FP64 steps).
+int upload_group(GroupPlan& g, const double* const* H, double* const* P, const int* n, const int* nocc,
+                 bool pairs, hipStream_t s, std::vector<std::unique_ptr<GroupHost>>& keep) {
     int slots = 0;
     if (g.fix != nullptr && tail_split_enabled())
         DMP_CHECK(resident_slots(g.S, g.kind, g.rb, &slots));
     keep.push_back(std::make_unique<GroupHost>());
     GroupHost& h = *keep.back();
     build_group(g, H, P, n, nocc, slots, h);
-    auto up = [&](void* dst, const void* src, size_t bytes) -> int {
-        if (bytes == 0) return DMP_OK;
-        DMP_CHECK_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
-        return DMP_OK;
+    // the descriptors are one region of the workspace: one copy
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(g.pd);
+    auto put = [&](const void* dst, const auto& v) {
+        if (dst == nullptr || v.empty()) return;
+        const size_t off = size_t(static_cast<const uint8_t*>(dst) - base);
+        const size_t bytes = v.size() * sizeof(v[0]);
+        if (h.staged.size() < off + bytes) h.staged.resize(off + bytes);
+        std::memcpy(h.staged.data() + off, v.data(), bytes);
     };
-    const size_t cnt = size_t(g.count);
-    DMP_CHECK(up(g.pd, h.pd.data(), cnt * sizeof(PurDesc)));
+    put(g.pd, h.pd);
     if (g.kind != DMP_FP64_NATIVE) {
-        DMP_CHECK(up(g.splitP[0], h.sp0.data(), cnt * sizeof(SplitDesc)));
-        DMP_CHECK(up(g.splitP[1], h.sp1.data(), cnt * sizeof(SplitDesc)));
-        DMP_CHECK(up(g.splitX, h.sx.data(), cnt * sizeof(SplitDesc)));
-        DMP_CHECK(up(g.splitT[0], h.st0.data(), cnt * sizeof(SplitDesc)));
-        DMP_CHECK(up(g.splitT[1], h.st1.data(), cnt * sizeof(SplitDesc)));
-        DMP_CHECK(up(g.sq[0], h.q0.data(), cnt * sizeof(MatDesc)));
-        DMP_CHECK(up(g.sq[1], h.q1.data(), cnt * sizeof(MatDesc)));
-        DMP_CHECK(up(g.up[0], h.u0.data(), cnt * sizeof(MatDesc)));
-        DMP_CHECK(up(g.up[1], h.u1.data(), cnt * sizeof(MatDesc)));
-        DMP_CHECK(up(g.tiles, h.tiles.data(), h.tiles.size() * sizeof(Tile)));
-        DMP_CHECK(up(g.mtiles, h.mtiles.data(), h.mtiles.size() * sizeof(Tile)));
+        put(g.splitP[0], h.sp0);
+        put(g.splitP[1], h.sp1);
+        put(g.splitX, h.sx);
+        put(g.splitT[0], h.st0);
+        put(g.splitT[1], h.st1);
+        put(g.sq[0], h.q0);
+        put(g.sq[1], h.q1);
+        put(g.up[0], h.u0);
+        put(g.up[1], h.u1);
+        put(g.tiles, h.tiles);
+        put(g.mtiles, h.mtiles);
     }
-    DMP_CHECK(up(g.pairs, h.pairs.data(), h.pairs.size() * sizeof(IPair)));
+    if (pairs) put(g.pairs, h.pairs);
+    DMP_CHECK_HIP(hipMemcpyAsync(g.pd, h.staged.data(), h.staged.size(), hipMemcpyHostToDevice, s));
     return DMP_OK;
 }
 
@@ -613,11 +591,15 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
 }
 
 // One Ozaki iteration of the whole group with iterate parity ``par``.
-int launch_oz_iteration(GroupPlan& g, int par, hipStream_t s,
+// ``follows``: an iteration queued before it still needs its end (energy,
+// stopping rule), which the split of P runs; this iteration's own end is left
+// to the next one or to launch_oz_end.
+int launch_oz_iteration(GroupPlan& g, int par, bool follows, hipStream_t s,
                         std::vector<PendingTimer>* timers = nullptr, double ops = 0.0) {
     // the row maxima of P come from the previous update's epilogue
     DMP_CHECK(launch_split_grouped_digits(g.splitP[par], g.count, g.units_digits, g.S, g.kind, g.st, s,
-                                          CoefArgs{}, false, g.nmod));
+                                          CoefArgs{g.pd, g.st, follows ? g.count : 0, g.method, kStepFinalize},
+                                          false, g.nmod));
     GemmParams p{};
     p.tiles = g.tiles;
     p.mtiles = g.mtiles;
@@ -640,7 +622,7 @@ int launch_oz_iteration(GroupPlan& g, int par, hipStream_t s,
     // blocks of the same launch, the coefficient step (it reads only the
     // done flags of the states that step writes)
     DMP_CHECK(launch_split_grouped_digits(g.splitX, g.count, g.units_digits, g.S, g.kind, g.st, s,
-                                          CoefArgs{g.pd, g.st, g.count, g.method}, false, g.nmod));
+                                          CoefArgs{g.pd, g.st, g.count, g.method, kStepCoef}, false, g.nmod));
     if (trs4) {
         DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
         DMP_CHECK(launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind,
@@ -648,9 +630,17 @@ int launch_oz_iteration(GroupPlan& g, int par, hipStream_t s,
     }
     p.descs = g.up[par];
     p.mode = EPI_UPDATE;
-    DMP_CHECK(timed_gemm(g, p, 1, ops, s, timers));
-    k_finalize_iter<<<g.count, 256, 0, s>>>(g.pd, g.st);
-    DMP_CHECK_HIP(hipGetLastError());
+    return timed_gemm(g, p, 1, ops, s, timers);
+}
+
+// m iterations of every group, starting from the even parity, and the end of
+// the last.
+int launch_oz_iterations(std::vector<GroupPlan>& groups, int m, hipStream_t s,
+                         std::vector<PendingTimer>* timers = nullptr, const int* n = nullptr) {
+    for (int it = 0; it < m; ++it)
+        for (auto& g : groups)
+            DMP_CHECK(launch_oz_iteration(g, it & 1, it > 0, s, timers, timers ? gemm_ops(g, n) : 0.0));
+    for (auto& g : groups) DMP_CHECK(launch_finalize_iter(g.pd, g.st, g.count, s));
     return DMP_OK;
 }
 
@@ -693,8 +683,7 @@ std::shared_ptr<CachedGraph> capture_iterations(std::vector<GroupPlan>& groups, 
         return nullptr;
     }
     bool ok = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) == hipSuccess;
-    for (int it = 0; ok && it < m; ++it)
-        for (auto& g : groups) ok = ok && launch_oz_iteration(g, it & 1, cap) == DMP_OK;
+    ok = ok && launch_oz_iterations(groups, m, cap) == DMP_OK;
     hipGraph_t gr = nullptr;
     const bool ended = hipStreamEndCapture(cap, &gr) == hipSuccess;
     hipGraphExec_t exec = nullptr;
@@ -740,8 +729,7 @@ int run_oz_timed(std::vector<GroupPlan>& groups, int max_iter, int m, hipStream_
     std::vector<PendingTimer> timers;
     const int rounds = (max_iter + m - 1) / m + 1;
     for (int r = 0; r < rounds; ++r) {
-        for (int it = 0; it < m; ++it)
-            for (auto& g : groups) DMP_CHECK(launch_oz_iteration(g, it & 1, s, &timers, gemm_ops(g, n)));
+        DMP_CHECK(launch_oz_iterations(groups, m, s, &timers, n));
         size_t off = 0;
         for (auto& g : groups) {
             DMP_CHECK_HIP(hipMemcpyAsync(host_st.data() + off, g.st, g.count * sizeof(DevState),
@@ -771,11 +759,13 @@ int run_oz_timed(std::vector<GroupPlan>& groups, int max_iter, int m, hipStream_
 // time (one cached graph, or eager launches with DMP_NO_GRAPH=1); matrices
 // that have stopped skip their work inside every launch.  Once a run of the
 // same launch sequence has finished, later runs start with one launch of a
-// second cached graph holding as many iterations as that run needed
-// (rounded up to a multiple of m), and the host reads the device states
-// once after it; a first run reads them after one replay.  A run that needs
-// more continues with replays of m, one always queued ahead of the state read
-// being checked, so the GPU does not wait for the host between replays.
+// second cached graph holding the whole multiples of m that run needed and
+// replays of two iterations for the rest (rounding up to m instead left up to
+// 7 empty iterations, 12 % of a run at n = 256), and the host reads the
+// device states once after them; a first run reads them after one replay.  A
+// run that needs more continues with replays of m, one always queued ahead of
+// the state read being checked, so the GPU does not wait for the host
+// between replays.
 int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
                   std::vector<DevState>& host_st, const int* n) {
     int max_n = 0;
@@ -791,14 +781,13 @@ int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
         cg = graph_cache().get_or_create(launch_key(groups, m, dev, env),
                                          [&]() { return capture_iterations(groups, m); });
     }
-    auto replay = [&]() -> int {
-        if (cg) {
-            DMP_CHECK_HIP(hipGraphLaunch(cg->exec, s));
+    // ``count`` iterations: the cached graph of that many, or eager launches
+    auto iterations = [&](int count, const std::shared_ptr<CachedGraph>& graph) -> int {
+        if (graph) {
+            DMP_CHECK_HIP(hipGraphLaunch(graph->exec, s));
             return DMP_OK;
         }
-        for (int it = 0; it < m; ++it)
-            for (auto& g : groups) DMP_CHECK(launch_oz_iteration(g, it & 1, s));
-        return DMP_OK;
+        return launch_oz_iterations(groups, count, s);
     };
     const size_t total = host_st.size();
     DevState* pin = pinned_states(2 * total);
@@ -830,35 +819,41 @@ int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
             if (!pin[slot * total + i].done) return false;
         return true;
     };
-    const int max_replays = (max_iter + m - 1) / m + 1;
-    const int first = cg && cg->last_iters > 0
-                          ? std::min(max_replays, std::max(1, (cg->last_iters + m - 1) / m))
-                          : 1;
+    const int budget = ((max_iter + m - 1) / m + 1) * m;   // iterations, even
+    const int predicted = std::min(budget, cg ? cg->last_iters : 0);
     int launched = 0;
-    // the predicted iterations as one graph (same parity at its end as after
-    // ``first`` replays of m, since m is even)
-    std::shared_ptr<CachedGraph> whole;
-    if (cg && first > 1) {
+    if (cg && predicted > 0) {
+        // every graph holds an even number of iterations, so each starts
+        // from the same iterate buffer
         int dev = 0;
         DMP_CHECK_HIP(hipGetDevice(&dev));
-        const int env = (tail_split_enabled() ? 1 : 0) | 2;
-        whole = graph_cache().get_or_create(launch_key(groups, first * m, dev, env), [&]() {
-            return capture_iterations(groups, first * m);
-        });
+        const int env = tail_split_enabled() ? 1 : 0;
+        auto graph_of = [&](int count, int tag) {
+            return graph_cache().get_or_create(launch_key(groups, count, dev, env | tag),
+                                               [&]() { return capture_iterations(groups, count); });
+        };
+        const int whole = predicted / m * m;
+        if (whole > 0) {
+            DMP_CHECK(iterations(whole, whole == m ? cg : graph_of(whole, 2)));
+            launched = whole;
+        }
+        if (launched < predicted) {
+            const auto two = m == 2 ? cg : graph_of(2, 4);
+            for (; launched < predicted; launched += 2) DMP_CHECK(iterations(2, two));
+        }
     }
-    if (whole) {
-        DMP_CHECK_HIP(hipGraphLaunch(whole->exec, s));
-        launched = first;
+    if (launched == 0) {
+        DMP_CHECK(iterations(m, cg));
+        launched = m;
     }
-    for (; launched < first; ++launched) DMP_CHECK(replay());
     DMP_CHECK(read(0));
     DMP_CHECK_HIP(hipEventSynchronize(ev[0]));
     int last = 0;                 // slot of the newest read checked
     bool done = finished(0);
     int pending = -1, slot = 1;   // read in flight, and the slot of the next one
-    while (!done && launched < max_replays) {
-        DMP_CHECK(replay());
-        ++launched;
+    while (!done && launched < budget) {
+        DMP_CHECK(iterations(m, cg));
+        launched += m;
         DMP_CHECK(read(slot));
         if (pending >= 0) {
             DMP_CHECK_HIP(hipEventSynchronize(ev[pending]));
@@ -1011,33 +1006,30 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
     std::vector<std::unique_ptr<GroupHost>> keep;
     StreamDrain drain{s};   // declared after ``keep``: the stream drains first
     for (auto& g : groups) {
-        DMP_CHECK(upload_group(g, H, P, n, nocc, s, keep));
+        DMP_CHECK(upload_group(g, H, P, n, nocc, kind == DMP_FP64_NATIVE || (flags & DMP_REFINE_MCWEENY), s, keep));
         DMP_CHECK(launch_init(g, tol, max_iter, s));
     }
     std::vector<DevState> host_st(count);
-    {
-        size_t off = 0;
-        for (auto& g : groups) {
-            DMP_CHECK_HIP(hipMemcpyAsync(host_st.data() + off, g.st, g.count * sizeof(DevState),
-                                         hipMemcpyDeviceToHost, s));
-            off += g.count;
-        }
-        DMP_CHECK_HIP(hipStreamSynchronize(s));
-        keep.clear();
+    // a non-finite H sets its state's done flag: nothing iterates on it, and
+    // the state read that ends the run reports it
+    auto reject_nonfinite = [&]() -> int {
         for (auto& h : host_st)
             if (h.nonfinite) {
                 set_error("H holds a non-finite entry");
                 return DMP_ENONFINITE;
             }
-    }
+        return DMP_OK;
+    };
     if (kind == DMP_FP64_NATIVE) {
         size_t off = 0;
         for (auto& g : groups) {
             DMP_CHECK(run_native(g, max_iter, s, host_st[off], (flags & DMP_NATIVE_TRIANGLE) != 0));
             off += g.count;
         }
+        DMP_CHECK(reject_nonfinite());
     } else {
         DMP_CHECK(run_oz_groups(groups, max_iter, s, host_st, n));
+        DMP_CHECK(reject_nonfinite());
         for (auto& g : groups)
             if (g.method == DMP_CANONICAL) {
                 k_mirror_iterate<<<dim3(kE0Blocks, g.count), 256, 0, s>>>(g.pd, g.st);

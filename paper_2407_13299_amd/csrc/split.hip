@@ -309,11 +309,7 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
     constexpr int LDW = W + 2;
     __shared__ double panel[kFragRows * LDW];
     if (int(blockIdx.x) < coef.count) {
-        const int m = blockIdx.x;
-        if (coef.method == DMP_TRS4)
-            coef_trs4(coef.pd[m], coef.st[m], panel);
-        else
-            coef_canonical(coef.pd[m], coef.st[m], panel);
+        coef_block(coef, panel);
         return;
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -466,11 +462,7 @@ __global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int co
     constexpr int W = 4 * CK;
     __shared__ double panel[kFragRows * (W + 2)];
     if (int(blockIdx.x) < coef.count) {
-        const int m = blockIdx.x;
-        if (coef.method == DMP_TRS4)
-            coef_trs4(coef.pd[m], coef.st[m], panel);
-        else
-            coef_canonical(coef.pd[m], coef.st[m], panel);
+        coef_block(coef, panel);
         return;
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -485,13 +477,16 @@ __global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int co
     const int rc = kq * 2 + (wave >> 1), RC = d.KC / 2;   // fragment along the reduction
     const int r = rows16 * 16 + (lane & 15);
     const int k0 = rc * 2 * CK + (lane >> 4) * NE;
-    const int e = residue_exponent(d.maxbits[r], d.K, d.lam, Crt<N>::table.limit);
+    // the operand's loads are issued before the exponents are worked out
+    const uint64_t bits = d.maxbits[r];
+    double v[NE];
+    const bool needed = load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v);
+    const int e = residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit);
     if (rc == 0 && lane < 16) {
         d.expo[r] = e;
         if (d.clear != nullptr) d.clear[r] = 0;
     }
-    double v[NE];
-    if (!load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v)) return;
+    if (!needed) return;
 
     constexpr double kMagic = 0x1.8p52;
     auto low = [](double x) __attribute__((always_inline)) {
