@@ -83,7 +83,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    // wavefronts w and w + 4 share a SIMD: the lower half of the tile's
+    // wavefronts is rotated against the upper one, so that a tile of which
+    // only the left or only the upper half is in the matrix keeps every SIMD
+    // busy with one wavefront
+    const int wm = wave / WN, wn = (wave % WN + wm * (WN / 2)) % WN;
     const int rbs = int(round_up(d.M, kPad)) / 16, cbs = int(round_up(d.N, kPad)) / 16;
     const int RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;   // chunks
     const int64_t a_rb = d.a_rb_stride, b_rb = d.b_rb_stride;
@@ -200,6 +204,20 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
             }
         }
     };
+    // a wavefront whose blocks all lie outside the matrix (or below the
+    // diagonal) only loads
+    const int first_row = int(tile.I) * AB * 16 + wm * FM * 16, first_col = int(tile.J) * BB * 16 + wn * FN * 16;
+    const bool idle = first_row >= d.M || first_col >= d.N || (upper && first_row >= first_col + FN * 16);
+    if (__builtin_amdgcn_readfirstlane(int(idle))) {
+        for (int c = 0; c < RC; ++c) {
+            const bool more = c + NBUF - 1 < RC;
+            if (more) issue(c + NBUF - 1, slot == 0 ? NBUF - 1 : slot - 1);
+            if (more) vm_wait<(NBUF - 3) * PER>(); else vm_wait<0>();
+            bare_barrier();
+            slot = slot == NBUF - 1 ? 0 : slot + 1;
+        }
+        return;
+    }
     int c = 0;
     for (; c + NBUF < RC; c += 2) {
         step(c, fr[0], fr[1], std::true_type{});
@@ -368,16 +386,21 @@ __global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams
                 8 * (int64_t(qr * 32 + 8 * (g0 + (v >> 2)) + (v & 3)) * ldc + qc * 32));
         };
         double pv[4 * G], xv[4 * G], hv[4 * G];
-        if constexpr (PUR) {
+        // a matrix with weight zero is not read (the canonical branch c >= 1/2
+        // has alpha = 0, a TRS4 step with a product alpha = beta = 0)
+        auto fetch = [&](const double* src, bool wanted, double (&to)[4 * G]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int v = 0; v < 4 * G; ++v) {
-                const bool in = inside(v);
-                pv[v] = in ? at(d.P, v)[voff] : 0.0;
-                if constexpr (MODE == EPI_UPDATE) {
-                    xv[v] = in ? at(d.X2, v)[voff] : 0.0;
-                    hv[v] = in ? at(d.H, v)[voff] : 0.0;
-                }
+            for (int v = 0; v < 4 * G; ++v) to[v] = 0.0;
+            if (wanted) {
+#pragma unroll
+                for (int v = 0; v < 4 * G; ++v)
+                    if (inside(v)) to[v] = at(src, v)[voff];
             }
+        };
+        if constexpr (PUR) fetch(d.P, MODE != EPI_UPDATE || alpha != 0.0, pv);
+        if constexpr (MODE == EPI_UPDATE) {
+            fetch(d.X2, beta != 0.0, xv);
+            fetch(d.H, true, hv);
         }
         uint32_t hi[4 * G], cmax = 0;
 #pragma unroll
