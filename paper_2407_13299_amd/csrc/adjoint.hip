@@ -60,6 +60,8 @@ struct OzCtx {
     int nt_up = 0;                      // products and the symmetric store)
     const Tile* tiles_full = nullptr;
     int nt_full = 0;
+    int* expo[2] = {nullptr, nullptr};       // residue products: exponents and row
+    uint64_t* maxi[2] = {nullptr, nullptr};  // maxima of the iterates, by parity
     int* fix = nullptr;                 // part buffer of the split tail of
     int fix_pieces = 0;                 // the purification products
     TailSplit tail{0, 1};
@@ -82,7 +84,13 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
                                    residue_plane_bytes(n, n, kind) * mod_capacity(S));
     x.pa = c.take<uint8_t>(planes);
     x.pb = c.take<uint8_t>(planes);
-    if (residues) x.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+    if (residues) {
+        x.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+        for (int i = 0; i < 2; ++i) {
+            x.expo[i] = c.take<int>(round_up(n, kPad));
+            x.maxi[i] = c.take<uint64_t>(round_up(n, kPad));
+        }
+    }
     x.ea = c.take<int>(round_up(n, kPad));
     x.eb = c.take<int>(round_up(n, kPad));
     x.ma = c.take<uint64_t>(round_up(n, kPad));
@@ -171,61 +179,91 @@ MatDesc gemm_desc(const OzCtx& x, const uint8_t* pa, const int* ea, const uint8_
     return m;
 }
 
-// The plane layout of the forward products (residues where they use them).
-void forward_planes(const OzCtx& x, MatDesc& m) {
-    if (x.nmod == 0) return;
-    m.a_rb_stride = m.b_rb_stride = int64_t(x.KC / 2) * kFragBytes;
-    m.res = x.res;
+// The iterate P of parity ``par`` as the operand of residue products: its row
+// maxima and its planes, with the exponents they imply or (expo non-null) given
+// ones.
+int start_residues(const OzCtx& x, const double* P, int par, const int* expo, hipStream_t s) {
+    SplitDesc d = split_of(x, P, false, x.maxi[par], x.expo[par], x.pa, 0);
+    d.lam = kLamIterate;
+    if (expo == nullptr) return launch_split(d, x.S, x.kind, x.st, s, x.nmod);
+    DMP_CHECK_HIP(hipMemcpyAsync(x.expo[par], expo, size_t(round_up(x.n, kPad)) * sizeof(int),
+                                 hipMemcpyDeviceToDevice, s));
+    DMP_CHECK(launch_rowmax(d, x.st, s));
+    d.maxbits = nullptr;
+    return launch_split_digits(d, x.S, x.kind, x.st, s, x.nmod);
 }
 
 // One forward iteration P_in -> (X2_out, P_out) with the purification
 // kernels; the coefficient is recomputed on the device from the traces.
-// The row maxima of X2 and of P_out come from the products' epilogues (into
-// x.mb and x.ma, each zeroed by the split before its product); p_maxima:
-// x.ma already holds those of P_in (the previous iteration's update), so
-// its split runs only the digit kernel.
+// Digit slices: the row maxima of X2 and of P_out come from the products'
+// epilogues (into x.mb and x.ma, each zeroed by the split before its
+// product); p_maxima: x.ma already holds those of P_in (the previous
+// iteration's update), so its split runs only the digit kernel.  Residues:
+// the products write the planes of X2 and P_out; those of P_in (parity
+// ``par``) are in place.
 int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double* P_out,
-                      bool finalize, bool p_maxima, hipStream_t s) {
-    SplitDesc sp = split_of(x, P_in, false, x.ma, x.ea, x.pa, 0);
-    sp.clear = x.mb;
-    sp.lam = kLamIterate;
-    if (p_maxima)
-        DMP_CHECK(launch_split_digits(sp, x.S, x.kind, x.st, s, x.nmod));
-    else
-        DMP_CHECK(launch_split(sp, x.S, x.kind, x.st, s, x.nmod));
-    auto product = [&](const GemmParams& p) -> int {
-        if (x.nmod > 0) return launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s);
-        return launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb);
-    };
+                      bool finalize, bool p_maxima, int par, hipStream_t s) {
     GemmParams p{};
     p.tiles = x.tiles_up;
-    p.one = gemm_desc(x, x.pa, x.ea, x.pa, x.ea, X2_out);
-    forward_planes(x, p.one);
-    p.one.P = P_in;
-    p.one.rowmax = x.mb;
     p.mtiles = x.mtiles;
     p.partials = x.partials;
     p.states = x.st;
     p.mode = EPI_SQUARE;
+    if (x.nmod > 0) {
+        const int64_t stride = int64_t(x.KC / 2) * kFragBytes;
+        MatDesc q = gemm_desc(x, x.pa, x.expo[par], x.pa, x.expo[par], X2_out);
+        q.a_rb_stride = q.b_rb_stride = stride;
+        q.res = x.res;
+        q.P = P_in;
+        q.planes_out = x.pb;
+        q.expo_out = x.eb;
+        q.maxin = x.maxi[par];
+        q.clear = x.maxi[par ^ 1];
+        q.growth = kGrowthSquare;
+        p.one = q;
+        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s));
+        q.pa = x.pb;
+        q.ea = x.eb;
+        q.out = P_out;
+        q.X2 = X2_out;
+        q.H = x.H;
+        q.rowmax = x.maxi[par ^ 1];
+        q.planes_out = x.pa;
+        q.expo_out = x.expo[par ^ 1];
+        q.clear = nullptr;
+        q.growth = kGrowthCanonical;
+        p.one = q;
+        p.mode = EPI_UPDATE;
+        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s,
+                                      CoefArgs{x.pd, x.st, 1, DMP_CANONICAL, kStepCoef}));
+        return finalize ? launch_finalize_iter(x.pd, x.st, 1, s) : DMP_OK;
+    }
+    SplitDesc sp = split_of(x, P_in, false, x.ma, x.ea, x.pa, 0);
+    sp.clear = x.mb;
+    if (p_maxima)
+        DMP_CHECK(launch_split_digits(sp, x.S, x.kind, x.st, s));
+    else
+        DMP_CHECK(launch_split(sp, x.S, x.kind, x.st, s));
+    p.one = gemm_desc(x, x.pa, x.ea, x.pa, x.ea, X2_out);
+    p.one.P = P_in;
+    p.one.rowmax = x.mb;
     if (x.tail.nsplit > 1) {   // the split tail of the purification products
         p.fix = x.fix;
         p.nfull = x.tail.nfull;
         p.nsplit = x.tail.nsplit;
     }
-    DMP_CHECK(product(p));
+    DMP_CHECK(launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb));
     DMP_CHECK(launch_finalize_coef(x.pd, x.st, 1, s));
     SplitDesc sx = split_of(x, X2_out, false, x.mb, x.eb, x.pb, 0);
     sx.clear = x.ma;
-    sx.lam = kLamIterate;
-    DMP_CHECK(launch_split_digits(sx, x.S, x.kind, x.st, s, x.nmod));
+    DMP_CHECK(launch_split_digits(sx, x.S, x.kind, x.st, s));
     p.one = gemm_desc(x, x.pb, x.eb, x.pa, x.ea, P_out);
-    forward_planes(x, p.one);
     p.one.P = P_in;
     p.one.X2 = X2_out;
     p.one.H = x.H;
     p.one.rowmax = x.ma;
     p.mode = EPI_UPDATE;
-    DMP_CHECK(product(p));
+    DMP_CHECK(launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb));
     if (finalize) DMP_CHECK(launch_finalize_iter(x.pd, x.st, 1, s));
     return DMP_OK;
 }
@@ -473,6 +511,8 @@ struct dmp_tape {
     std::vector<double> c, t1, t2;
     std::vector<int> branch, clamped;
     std::vector<double*> ckpt;   // device copies of P_0, P_stride, ...
+    std::vector<int*> ckpt_expo; // residue products, stride > 1: the exponents of
+                                 // their planes (which recomputed steps start from)
     std::vector<double*> x2;     // stride 1: X2_0, X2_1, ... as well (no recomputation)
     std::vector<void*> owned;    // the device allocations holding them
     void* fwd_ws = nullptr;      // forward workspace (owned)
@@ -628,7 +668,23 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
         pool.pop_back();
         return DMP_OK;
     };
-    auto checkpoint = [&](const double* src, std::vector<double*>& into) -> int {
+    auto checkpoint = [&](const double* src, int par, std::vector<double*>& into) -> int {
+        if (x.nmod > 0 && stride > 1) {
+            const size_t bytes = size_t(round_up(n, kPad)) * sizeof(int);
+            int* e = nullptr;
+            if (hipMalloc(&e, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                set_error("hipMalloc of a checkpoint's exponents failed");
+                return DMP_ENOMEM;
+            }
+            t->owned.push_back(e);
+            t->ckpt_expo.push_back(e);
+            const hipError_t err = hipMemcpyAsync(e, x.expo[par], bytes, hipMemcpyDeviceToDevice, s);
+            if (err != hipSuccess) {
+                set_error("checkpoint copy failed: %s", hipGetErrorString(err));
+                return DMP_EHIP;
+            }
+        }
         double* d = nullptr;
         DMP_CHECK(slot(&d));
         into.push_back(d);
@@ -653,8 +709,9 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
     constexpr int kStepsPerRead = 4;
     double* cur = P;
     double* nxt = Pw;
-    if (!h.done) st = checkpoint(P, t->ckpt);
-    if (stride == 1 && !h.done) cur = t->ckpt[0];
+    if (!h.done && x.nmod > 0) st = start_residues(x, P, 0, nullptr, s);
+    if (st == DMP_OK && !h.done) st = checkpoint(P, 0, t->ckpt);
+    if (st == DMP_OK && stride == 1 && !h.done) cur = t->ckpt[0];
     int launched = 0;
     bool done = h.done != 0;
     while (st == DMP_OK && !done && launched < max_iter) {
@@ -667,7 +724,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
                 if (st != DMP_OK) break;
                 t->x2.push_back(x2k);
             }
-            st = forward_iteration(x, cur, x2k, nxt, true, launched > 0, s);
+            st = forward_iteration(x, cur, x2k, nxt, true, launched > 0, launched & 1, s);
             if (st != DMP_OK) break;
             k_record_step<<<1, 64, 0, s>>>(x.st, hist);
             if (hipGetLastError() != hipSuccess) {
@@ -680,7 +737,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
                 t->ckpt.push_back(cur);
             } else {
                 std::swap(cur, nxt);
-                if ((launched + 1) % stride == 0) st = checkpoint(cur, t->ckpt);
+                if ((launched + 1) % stride == 0) st = checkpoint(cur, (launched + 1) & 1, t->ckpt);
             }
         }
         if (st != DMP_OK) break;
@@ -817,9 +874,10 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
             DMP_CHECK_HIP(hipMemcpyAsync(segP[0], t->ckpt[seg], size_t(n) * n * sizeof(double),
                                          hipMemcpyDeviceToDevice, s));
             DMP_CHECK_HIP(hipMemcpyAsync(x.st, &fresh, sizeof(fresh), hipMemcpyHostToDevice, s));
+            if (x.nmod > 0) DMP_CHECK(start_residues(x, segP[0], start & 1, t->ckpt_expo[seg], s));
             for (int j = start; j < end; ++j)
                 DMP_CHECK(forward_iteration(x, segP[j - start], segX[j - start], segP[j - start + 1],
-                                            false, j > start, s));
+                                            false, j > start, j & 1, s));
         }
         for (int j = end - 1; j >= start; --j) {
             const double* P = stored ? t->ckpt[j] : segP[j - start];

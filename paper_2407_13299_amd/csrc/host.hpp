@@ -27,6 +27,8 @@ int native_dgemm(hipStream_t stream, bool ta, bool tb, int m, int n, int k, cons
 int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st, hipStream_t s, int nmod = 0);
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
                         hipStream_t stream, int nmod = 0);
+// the row maxima of one operand alone (trans == 0)
+int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t s);
 int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units,
                                 const DevState* st, hipStream_t stream);
 // coef.count > 0: the same launch also runs the coefficient step of the
@@ -51,8 +53,9 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
 // A product through residues: the residue GEMM over the ``ntiles`` entries of
 // p.mtiles (tiles of shape ``shape``, modulus in the top byte of mat), then
 // the combination and the FP64 epilogue over the nout 64 x 64 tiles of p.tiles.
+// ``step`` (count > 0) runs in extra blocks of the residue GEMM.
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
-                        hipStream_t stream);
+                        hipStream_t stream, const CoefArgs& step = CoefArgs{});
 // Device copy of the residue GEMM's tile list of one matrix, cached.
 int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count);
 // Workgroups of the purification-mode slice GEMM (kind, S, rb) resident on

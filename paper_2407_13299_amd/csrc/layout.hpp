@@ -112,9 +112,18 @@ struct MatDesc {
     int ldc;
     int state_index;       // index of the matrix's DevState
     int pad_;
-    uint8_t* res;          // residue products: the residues of the product,
-                           // [moduli][residue_out_bytes(M, N)]; pa, pb then
-                           // hold residue planes, each rows x a_rb_stride
+    // residue products (pa, pb hold residue planes, each rows x a_rb_stride):
+    uint8_t* res;          // the residues of the product, [moduli][residue_out_bytes(M, N)]
+    // The purification modes also write the residue planes of the output, as
+    // the next product's operand.  Their row exponents follow from the row
+    // maxima of the iterate P before the product: |row i of the output| <=
+    // growth |row i of P| (the output is a polynomial of P whose quotient by x
+    // stays below ``growth`` on the spectrum).
+    uint8_t* planes_out;
+    int* expo_out;
+    const uint64_t* maxin; // row maxima of P
+    uint64_t* clear;       // nullable: row maxima to zero, for a later launch
+    double growth;
 };
 
 // Device-side purification state of one matrix (host-readable copy).
@@ -180,13 +189,15 @@ struct PurDesc {
     int pad_;
 };
 
-// Step run by extra blocks of a split launch (count > 0): block b < count
-// works on matrix b, the split's units follow.  kStepCoef, in the split of
-// X2: the update weights from the square's trace partials (method:
-// DMP_CANONICAL or DMP_TRS4).  kStepFinalize, in the split of the next
-// iterate: energy and stopping rule of the iteration before.  The split reads
-// only the done flags of the states these blocks write; a split that misses a
-// flag set beside it only fills planes that no product will read.
+// Step run by extra blocks of a launch (count > 0): block b < count works on
+// matrix b, the launch's own blocks follow.  kStepCoef, in the split of X2
+// (digit slices) or in the residue GEMM of the update: the update weights from
+// the square's trace partials (method: DMP_CANONICAL or DMP_TRS4).
+// kStepFinalize, in the split of the next iterate or in the residue GEMM of
+// its square: energy and stopping rule of the iteration before.  The launch's
+// own blocks read only the done flags of the states these blocks write; one
+// that misses a flag set beside it only writes planes or residues that nothing
+// will read.
 constexpr int kStepCoef = 0, kStepFinalize = 1;
 struct CoefArgs {
     const PurDesc* pd;
@@ -201,6 +212,11 @@ struct CoefArgs {
 // in [0, 1]; TRS4's T = (4 - 2g) X + (g - 3) X2 + g I has t(x) in [0, 6] for
 // 0 <= g <= 6 and x in [0, 1].
 constexpr double kLamIterate = 1.0625, kLamTrs4 = 6.5;
+// MatDesc::growth, with the same room: x^2 / x <= 1; the canonical maps have
+// f(x) / x <= 5 / 4 (c < 1/2: ((1 - 2c) + (1 + c) x - x^2) / (1 - c) at x = (1
+// + c) / 2; c >= 1/2: (1 + c)^2 / (4 c) <= 9 / 8); of TRS4's, 2 - x <= 2 is the
+// largest (x t(x) <= 1.4).
+constexpr double kGrowthSquare = 1.0625, kGrowthCanonical = 1.375, kGrowthTrs4 = 2.125;
 
 // Epilogue modes of the slice GEMM.
 enum EpiMode : int {
@@ -243,6 +259,9 @@ struct GemmParams {
     // (no mirror; the next splits read it as symmetric, SplitDesc::sym)
     int upper_only;
     const Tile* mtiles;     // residue products: the residue GEMM's tile list
+    // residue products: the update has no product while the state's gamma is 0
+    // (TRS4; the state's gamma must be final before the launch)
+    int skip_zero;
 };
 
 // Tile shapes of the residue GEMM: 256 x 256, one workgroup per CU, and 128 x

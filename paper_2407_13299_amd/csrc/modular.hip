@@ -5,8 +5,10 @@
 #include <type_traits>
 #include <vector>
 
+#include "coef.hpp"
 #include "host.hpp"
 #include "ldsload.hpp"
+#include "residues.hpp"
 
 namespace dmp {
 
@@ -58,7 +60,7 @@ __constant__ const ModRows kModRows = make_rows();
 // z / p comes to a tie for odd p), r = z - q p.  FP16 sums are exact in FP32
 // up to 2^24, so they are reduced every 31 chunks.
 template <bool FP16, int WM, int WN, int FM, int FN, int NBUF, int OCC>
-__global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p, int upper) {
+__global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p, int upper, CoefArgs extra) {
     constexpr int WAVES = WM * WN;
     constexpr int AB = WM * FM, BB = WN * FN;       // 16-row blocks of the tile
     constexpr int BLOCKS = AB + BB;                 // fragments of a stage
@@ -68,15 +70,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
                   "equal loads per wavefront, whole 32 x 32 blocks");
     __shared__ __align__(16) uint8_t lds[NBUF][STAGE];
 
-    const int b = blockIdx.x;
-    const int nb = gridDim.x;
+    if (int(blockIdx.x) < extra.count) {
+        if (threadIdx.x < 256) coef_block(extra, reinterpret_cast<double*>(&lds[0][0]));
+        return;
+    }
+    const int b = int(blockIdx.x) - extra.count;
+    const int nb = int(gridDim.x) - extra.count;
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
     const Tile tile = p.mtiles[t];
     const int mod = int(tile.mat >> 24);
     const MatDesc d = p.descs ? p.descs[tile.mat & 0xffffffu] : p.one;
     const DevState* st = p.states ? p.states + d.state_index : nullptr;
-    if (st != nullptr && (st->done || (p.mode == EPI_UPDATE && st->gamma == 0.0))) return;
+    if (st != nullptr && (st->done || (p.skip_zero && st->gamma == 0.0))) return;
     const bool clocked = p.clk != nullptr;
     const uint64_t clk_c = clocked ? __builtin_amdgcn_s_memtime() : 0;
     const uint64_t clk_r = clocked ? __builtin_amdgcn_s_memrealtime() : 0;
@@ -311,24 +317,31 @@ __device__ inline uint32_t max16(uint32_t v) {
 
 // Rebuilds C' = X Y from its residues (modular.hpp) and runs the FP64 end of
 // the product, C = C' 2^(t_i + t_j), by mode as listed at the head of
-// ozgemm.hip.  One workgroup per 64 x 64 tile of p.tiles, a 32 x 32 quadrant
-// per wavefront: lane l holds column l % 32 and rows (l / 32) 4 + 8 (v / 4) +
-// v % 4, v < 16, the order in which the residues are stored, so every load is
-// a whole cache line.
+// ozgemm.hip.  One workgroup per 64 x 64 tile of p.tiles, half a 32 x 32
+// quadrant per wavefront: lane l holds column l % 32 and rows (l / 32) 4 + 8 g
+// + e, e < 4, of two row groups g, the order in which the residues are stored,
+// so every load is a whole cache line.
 //
-// Bound: memory (N bytes of residues and 8 to 32 bytes of FP64 per element).
-// Every load is issued before the first result is formed; the four modes and
-// the quadrants that need no bounds or triangle checks are code of their own
-// (the shared epilogue of the slice GEMM, whose selects for modes, masks and
-// 64-bit maxima make half of its instructions, took 28 us at n = 2048 and
-// 335 us at n = 8192, N = 13).  Row maxima, which only choose the next
-// split's powers of two, are kept to the upper word, rounded up.
-template <int N, int MODE, int G>
-__global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams p) {
+// The purification modes then form the residues of the output from the tile
+// in LDS: its four 16-row blocks' fragments (chunk J) and, transposed, those of
+// its 64 columns (chunk I), one fragment (FP16: two) per wavefront.  So an
+// iterate or a square is split without being read again, and without the
+// launch that did (k_residues: 23 us at n = 2048, 290 us at n = 8192).  The
+// exponents come from the row maxima of the iterate before the product
+// (MatDesc::growth), as the output's own are known only when every tile is done.
+//
+// Bound: memory (N to 2 N bytes of residues and 12 to 28 bytes of FP64 per
+// element).  Every load is issued before the first result is formed; modes,
+// and quadrants that need no bounds or triangle checks, are code of their own.
+// Row maxima, which only choose powers of two, are kept to the upper word,
+// rounded up.
+template <int N, int MODE, bool FP16>
+__global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
     constexpr bool PUR = MODE == EPI_SQUARE || MODE == EPI_UPDATE || MODE == EPI_SQUARE_TRS4;
     constexpr bool UPPER = MODE != EPI_STORE;
-    constexpr int WAVES = 16 / G;
+    constexpr int G = 2, WAVES = 8, LDT = 66;
     __shared__ double red[WAVES][kPartials];
+    __shared__ double out_tile[PUR ? 64 * LDT : 1];
     const int b = blockIdx.x, nb = gridDim.x;
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
@@ -342,7 +355,7 @@ __global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams
         beta = st->beta;
         gamma = st->gamma;
     }
-    const bool has_product = MODE != EPI_UPDATE || gamma != 0.0;   // a TRS4 step without one
+    const bool has_product = MODE != EPI_UPDATE || !p.skip_zero || gamma != 0.0;   // a TRS4 step without one
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     // quadrant (quad / 2, quad % 2) of the tile, row groups g0 .. g0 + G - 1 of it
@@ -449,6 +462,9 @@ __global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams
                     }
                 }
                 out4[e] = o;
+                if constexpr (PUR)
+                    out_tile[((quad >> 1) * 32 + 8 * (g0 + g) + lrow + e) * LDT + (quad & 1) * 32 + lcol] =
+                        inside(v) ? o : 0.0;
                 const uint32_t h = uint32_t(static_cast<uint64_t>(__double_as_longlong(o)) >> 32) & 0x7fffffffu;
                 hi[v] = inside(v) ? h : 0u;
                 cmax = max(cmax, hi[v]);
@@ -518,26 +534,66 @@ __global__ __launch_bounds__(1024 / G, G == 4 ? 2 : 4) void k_combine(GemmParams
             for (int i = 0; i < WAVES; ++i) r += red[i][threadIdx.x];
             p.partials[int64_t(t) * kPartials + threadIdx.x] = r;
         }
+
+        // ---- residue planes of the output ------------------------------------
+        const bool diag = tile.I == tile.J;
+        const int side = wave >> 2, blk = wave & 3;   // rows of the tile or, transposed, its columns
+        if (side == 1 && diag) return;
+        const int K64 = FP16 ? 2 : 1;                 // fragments per 64 reduction elements
+        constexpr int NE = FP16 ? 8 : 16;
+        const int rbs = int(round_up(M, kPad)) / 16, RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;
+        const int lr = blk * 16 + (lane & 15);        // the lane's row (column) of the tile
+        const int row = 64 * int(side == 0 ? tile.I : tile.J) + lr, chunk = int(side == 0 ? tile.J : tile.I);
+        const int tx = residue_exponent(d.maxin[row], d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
+        if (diag && lane < 16) {
+            d.expo_out[row] = tx;
+            if (d.clear != nullptr) d.clear[row] = 0;
+        }
+        const int64_t plane = int64_t(rbs) * RC * kFragBytes;
+#pragma unroll
+        for (int f = 0; f < K64; ++f) {
+            const int k0 = f * 32 + (lane >> 4) * NE;
+            double x[NE];
+            if (side == 0) {
+#pragma unroll
+                for (int i = 0; i < NE; ++i) {
+                    // below the diagonal of a diagonal tile: the mirror's element
+                    const bool low = diag && lr > k0 + i;
+                    x[i] = out_tile[low ? (k0 + i) * LDT + lr : lr * LDT + k0 + i];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < NE; ++i) x[i] = out_tile[(k0 + i) * LDT + lr];
+            }
+            store_residues<N, FP16>(
+                x, tx, d.planes_out + (int64_t(row / 16) * RC + chunk * K64 + f) * kFragBytes + lane * 16, plane);
+        }
     }
 }
 
-constexpr int kCombineGroups = 2;
-
 template <int N>
-static int launch_combine(const GemmParams& p, int nout, hipStream_t stream) {
+static int launch_combine(bool fp16, const GemmParams& p, int nout, hipStream_t stream) {
     switch (p.mode) {
-        case EPI_STORE: k_combine<N, EPI_STORE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
-        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
-        case EPI_SQUARE: k_combine<N, EPI_SQUARE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
-        case EPI_UPDATE: k_combine<N, EPI_UPDATE, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p); break;
-        default: k_combine<N, EPI_SQUARE_TRS4, kCombineGroups><<<nout, 1024 / kCombineGroups, 0, stream>>>(p);
+        case EPI_STORE: k_combine<N, EPI_STORE, false><<<nout, 512, 0, stream>>>(p); break;
+        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, false><<<nout, 512, 0, stream>>>(p); break;
+        case EPI_SQUARE:
+            if (fp16) k_combine<N, EPI_SQUARE, true><<<nout, 512, 0, stream>>>(p);
+            else k_combine<N, EPI_SQUARE, false><<<nout, 512, 0, stream>>>(p);
+            break;
+        case EPI_UPDATE:
+            if (fp16) k_combine<N, EPI_UPDATE, true><<<nout, 512, 0, stream>>>(p);
+            else k_combine<N, EPI_UPDATE, false><<<nout, 512, 0, stream>>>(p);
+            break;
+        default:
+            if (fp16) k_combine<N, EPI_SQUARE_TRS4, true><<<nout, 512, 0, stream>>>(p);
+            else k_combine<N, EPI_SQUARE_TRS4, false><<<nout, 512, 0, stream>>>(p);
     }
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }
 
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
-                        hipStream_t stream) {
+                        hipStream_t stream, const CoefArgs& step) {
     if (ntiles <= 0 || nout <= 0) return DMP_OK;
     if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || nmod < kModMin || nmod > kMaxMods ||
         p.mtiles == nullptr || p.fix != nullptr) {
@@ -545,19 +601,20 @@ int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p,
         return DMP_EINVAL;
     }
     const int upper = p.mode == EPI_STORE ? 0 : 1;
+    const int grid = ntiles + step.count;
     if (kind == DMP_OZ_FP16 && shape == kShapeWide)
-        k_residue_gemm<true, 2, 4, 8, 4, 4, 2><<<ntiles, 512, 0, stream>>>(p, upper);
+        k_residue_gemm<true, 2, 4, 8, 4, 4, 2><<<grid, 512, 0, stream>>>(p, upper, step);
     else if (kind == DMP_OZ_FP16)
-        k_residue_gemm<true, 2, 4, 4, 2, 4, 4><<<ntiles, 512, 0, stream>>>(p, upper);
+        k_residue_gemm<true, 2, 4, 4, 2, 4, 4><<<grid, 512, 0, stream>>>(p, upper, step);
     else if (shape == kShapeWide)
-        k_residue_gemm<false, 2, 4, 8, 4, 4, 2><<<ntiles, 512, 0, stream>>>(p, upper);
+        k_residue_gemm<false, 2, 4, 8, 4, 4, 2><<<grid, 512, 0, stream>>>(p, upper, step);
     else
-        k_residue_gemm<false, 2, 4, 4, 2, 4, 4><<<ntiles, 512, 0, stream>>>(p, upper);
+        k_residue_gemm<false, 2, 4, 4, 2, 4, 4><<<grid, 512, 0, stream>>>(p, upper, step);
     DMP_CHECK_HIP(hipGetLastError());
-    static int (*const combine[kMaxMods - kModMin + 1])(const GemmParams&, int, hipStream_t) = {
+    static int (*const combine[kMaxMods - kModMin + 1])(bool, const GemmParams&, int, hipStream_t) = {
         launch_combine<11>, launch_combine<12>, launch_combine<13>,
         launch_combine<14>, launch_combine<15>, launch_combine<16>};
-    return combine[nmod - kModMin](p, nout, stream);
+    return combine[nmod - kModMin](kind == DMP_OZ_FP16, p, nout, stream);
 }
 
 int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count) {

@@ -275,7 +275,11 @@ static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind, bool resid
                                        : plane_bytes(n, n, S, kind);
         m.planesP = c.take<uint8_t>(planes);
         m.planesX = c.take<uint8_t>(planes);
-        if (residues) m.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+        if (residues) {
+            m.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+            m.expP1 = c.take<int>(round_up(n, kPad));
+            m.maxP1 = c.take<uint64_t>(round_up(n, kPad));
+        }
         m.expP = c.take<int>(round_up(n, kPad));
         m.expX = c.take<int>(round_up(n, kPad));
         m.maxP = c.take<uint64_t>(round_up(n, kPad));
@@ -524,6 +528,33 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         md.P = L.Pw;
         md.out = P[m];
         out.u1[b] = md;
+        if (g.nmod > 0) {
+            // the products write the planes of their outputs themselves; the
+            // exponents and row maxima of the iterates alternate, as one
+            // iterate's are read while the next one's are written
+            int* const expo[2] = {L.expP, L.expP1};
+            uint64_t* const maxi[2] = {L.maxP, L.maxP1};
+            for (int par = 0; par < 2; ++par) {
+                MatDesc& q = par == 0 ? out.q0[b] : out.q1[b];
+                MatDesc& u = par == 0 ? out.u0[b] : out.u1[b];
+                q.ea = q.eb = expo[par];
+                q.rowmax = nullptr;
+                q.planes_out = L.planesX;
+                q.expo_out = L.expX;
+                q.maxin = maxi[par];
+                q.clear = maxi[par ^ 1];
+                q.growth = kGrowthSquare;
+                u.eb = expo[par];
+                u.rowmax = maxi[par ^ 1];
+                u.planes_out = L.planesP;
+                u.expo_out = expo[par ^ 1];
+                u.maxin = maxi[par];
+                u.growth = g.method == DMP_TRS4 ? kGrowthTrs4 : kGrowthCanonical;
+                // T replaces the iterate as the right operand, in its planes
+                // and exponents
+                (par == 0 ? out.st0[b] : out.st1[b]).expo = expo[par];
+            }
+        }
     }
     g.ntiles = int(out.tiles.size());
     g.tail = TailSplit{g.ntiles, 1};

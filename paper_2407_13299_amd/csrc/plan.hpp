@@ -123,7 +123,9 @@ struct MatLayout {
     int* expX;
     uint64_t* maxP;
     uint64_t* maxX;
-    uint8_t* res;     // residue products: the residues of one product
+    uint8_t* res;     // residue products: the residues of one product, and a second
+    int* expP1;       // set of exponents and row maxima of the iterates
+    uint64_t* maxP1;
     double* rows;
     int* rowbad;
     double* e0;

@@ -544,6 +544,10 @@ int launch_init(GroupPlan& g, double tol, int max_iter, hipStream_t s) {
     // row maxima of P0 (later iterates get theirs from the update's epilogue)
     if (g.kind != DMP_FP64_NATIVE)
         DMP_CHECK(launch_split_grouped_rowmax(g.splitP[0], g.count, g.units_rowmax, g.st, s));
+    // residue products split the later iterates and squares themselves
+    if (g.nmod > 0)
+        DMP_CHECK(launch_split_grouped_digits(g.splitP[0], g.count, g.units_digits, g.S, g.kind, g.st, s,
+                                              CoefArgs{}, false, g.nmod));
     return DMP_OK;
 }
 
@@ -557,8 +561,9 @@ double gemm_ops(const GroupPlan& g, const int* n) {
     return t;
 }
 
+// ``step``: for the residue GEMM's extra blocks.
 int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStream_t s,
-               std::vector<PendingTimer>* timers) {
+               std::vector<PendingTimer>* timers, const CoefArgs& step = CoefArgs{}) {
     PendingTimer t{};
     GemmParams q = p;
     if (timers) {
@@ -578,7 +583,7 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
         DMP_CHECK_HIP(hipEventRecord(t.start, s));
     }
     if (g.nmod > 0)
-        DMP_CHECK(launch_residue_gemm(g.kind, g.nmod, g.mshape, q, g.nmt, g.ntiles, s));
+        DMP_CHECK(launch_residue_gemm(g.kind, g.nmod, g.mshape, q, g.nmt, g.ntiles, s, step));
     else
         DMP_CHECK(launch_ozgemm(g.S, g.kind, q, g.ntiles, s, g.rb));
     if (timers) {
@@ -592,42 +597,54 @@ int timed_gemm(GroupPlan& g, const GemmParams& p, int which, double ops, hipStre
 
 // One Ozaki iteration of the whole group with iterate parity ``par``.
 // ``follows``: an iteration queued before it still needs its end (energy,
-// stopping rule), which the split of P runs; this iteration's own end is left
-// to the next one or to launch_oz_end.
+// stopping rule), which runs in extra blocks of this one's first launch; this
+// iteration's own end is left to the next one or to launch_finalize_iter.
 int launch_oz_iteration(GroupPlan& g, int par, bool follows, hipStream_t s,
                         std::vector<PendingTimer>* timers = nullptr, double ops = 0.0) {
-    // the row maxima of P come from the previous update's epilogue
-    DMP_CHECK(launch_split_grouped_digits(g.splitP[par], g.count, g.units_digits, g.S, g.kind, g.st, s,
-                                          CoefArgs{g.pd, g.st, follows ? g.count : 0, g.method, kStepFinalize},
-                                          false, g.nmod));
+    const bool trs4 = g.method == DMP_TRS4;
+    const CoefArgs end{g.pd, g.st, follows ? g.count : 0, g.method, kStepFinalize};
+    const CoefArgs coef{g.pd, g.st, g.count, g.method, kStepCoef};
     GemmParams p{};
     p.tiles = g.tiles;
     p.mtiles = g.mtiles;
     p.descs = g.sq[par];
     p.partials = g.partials;
     p.states = g.st;
-    const bool trs4 = g.method == DMP_TRS4;
     p.mode = trs4 ? EPI_SQUARE_TRS4 : EPI_SQUARE;
     // canonical iterates and X2 stay upper triangles (their splits read them
     // as symmetric); TRS4's combined operand needs full rows
     p.upper_only = trs4 ? 0 : 1;
     p.spread = g.count > 1 ? 1 : 0;
+    auto split_t = [&]() -> int {
+        DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
+        return launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind, g.st, s,
+                                           CoefArgs{}, true, g.nmod);
+    };
+    if (g.nmod > 0) {
+        DMP_CHECK(timed_gemm(g, p, 0, ops, s, timers, end));
+        if (trs4) {   // T needs the coefficients
+            k_finalize_trs4<<<g.count, 256, 0, s>>>(g.pd, g.st);
+            DMP_CHECK_HIP(hipGetLastError());
+            DMP_CHECK(split_t());
+            p.skip_zero = 1;
+        }
+        p.descs = g.up[par];
+        p.mode = EPI_UPDATE;
+        return timed_gemm(g, p, 1, ops, s, timers, trs4 ? CoefArgs{} : coef);
+    }
     if (g.tail.nsplit > 1) {
         p.fix = g.fix;
         p.nfull = g.tail.nfull;
         p.nsplit = g.tail.nsplit;
     }
+    // the row maxima of P come from the previous update's epilogue
+    DMP_CHECK(launch_split_grouped_digits(g.splitP[par], g.count, g.units_digits, g.S, g.kind, g.st, s, end));
     DMP_CHECK(timed_gemm(g, p, 0, ops, s, timers));
     // the split of X2 (row maxima from the square's epilogue) and, in extra
     // blocks of the same launch, the coefficient step (it reads only the
     // done flags of the states that step writes)
-    DMP_CHECK(launch_split_grouped_digits(g.splitX, g.count, g.units_digits, g.S, g.kind, g.st, s,
-                                          CoefArgs{g.pd, g.st, g.count, g.method, kStepCoef}, false, g.nmod));
-    if (trs4) {
-        DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
-        DMP_CHECK(launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind,
-                                              g.st, s, CoefArgs{}, true, g.nmod));
-    }
+    DMP_CHECK(launch_split_grouped_digits(g.splitX, g.count, g.units_digits, g.S, g.kind, g.st, s, coef));
+    if (trs4) DMP_CHECK(split_t());
     p.descs = g.up[par];
     p.mode = EPI_UPDATE;
     return timed_gemm(g, p, 1, ops, s, timers);

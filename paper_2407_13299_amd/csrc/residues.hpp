@@ -1,0 +1,88 @@
+// Device code shared by the residue split and the residue combination: the
+// power of two of an operand row and the residues of its elements.
+#pragma once
+
+#include <hip/hip_fp16.h>
+
+#include "common.hpp"
+
+namespace dmp {
+
+// Exponent t of an operand row of a residue product: X = rint(a 2^-t) with
+// 2^-t the largest power of two that keeps the row norm of X within
+// ``limit``.  The norm is bounded from the row maximum m (its bit pattern; only
+// the upper word counts, rounded up): it is at most sqrt(K) m, and at most
+// sqrt(lam m) for a positive semidefinite source with eigenvalues up to lam
+// (|row i|^2 = (A^2)_ii <= lam A_ii <= lam m).
+__device__ inline int residue_exponent(uint64_t bits, int K, double lam, double limit) {
+    if (bits >= 0x7ff0000000000000ull) return kNonFiniteExp;
+    if (bits == 0) return 0;
+    const double m = __longlong_as_double(static_cast<long long>(bits | 0xffffffffull));
+    double nu = sqrt(double(K)) * m;
+    if (lam > 0.0) nu = fmin(nu, sqrt(lam * m));
+    int en = 0, el = 0;
+    const double fn = frexp(nu, &en), fl = frexp(limit, &el);
+    return en - el + (fn > fl ? 1 : 0);
+}
+
+// One lane's 16 bytes of a fragment in each of N planes: the balanced
+// residues of X = rint(v 2^-t) for NE = 16 elements (FP16: 8, as halves);
+// plane m starts at m ``plane`` bytes from ``base``.  Per element X = Xh 2^27
+// + Xl exactly; per modulus z = Xh (2^27 mod p) + Xl, q = rint(z / p) (|z| <
+// 2^40, so the product with 1 / p is off by less than 2^-13, closer than any
+// z / p comes to a tie for odd p), and z - q p modulo 256 is the residue's
+// byte (p = 256: +-128 are the same byte).  The integers z and q are read from
+// the low words of z + 1.5 2^52 and q + 1.5 2^52: four full-rate instructions
+// per modulus.
+template <int N, bool FP16>
+__device__ __forceinline__ void store_residues(const double (&v)[FP16 ? 8 : 16], int t, uint8_t* base,
+                                               int64_t plane) {
+    constexpr double kMagic = 0x1.8p52;
+    auto low = [](double x) __attribute__((always_inline)) {
+        return uint32_t(static_cast<uint64_t>(__double_as_longlong(x)));
+    };
+    uint32_t w[N][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        constexpr int E = FP16 ? 2 : 4;   // elements per word
+        double xh[E], xl[E], xm[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const double x = t >= kNonFiniteExp ? 0.0 : rint(ldexp(v[g * E + i], -t));
+            xh[i] = rint(x * 0x1p-27);
+            xl[i] = __builtin_fma(xh[i], -0x1p27, x);
+            xm[i] = xl[i] + kMagic;
+        }
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const int p = kMods[m];
+            int c = (1 << 27) % p;
+            if (c > p / 2) c -= p;
+            uint32_t b[E];
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const uint32_t z = low(__builtin_fma(xh[i], double(c), xm[i]));
+                const uint32_t q = low(__builtin_fma(__builtin_fma(xh[i], double(c), xl[i]), 1.0 / p, kMagic));
+                // the low byte of z - q p (24-bit multiply-add: the bits
+                // above do not matter)
+                b[i] = z + __umul24(q, uint32_t(256 - p));
+            }
+            if constexpr (!FP16) {
+                w[m][g] = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) |
+                          __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+            } else {
+                // balanced residues are exact FP16 values (|r| <= 128)
+                uint32_t h = 0;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    h |= uint32_t(__half_as_ushort(__int2half_rn(int(int8_t(uint8_t(b[i])))))) << (16 * i);
+                w[m][g] = h;
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+        *reinterpret_cast<uint4*>(base + m * plane) = make_uint4(w[m][0], w[m][1], w[m][2], w[m][3]);
+}
+
+}  // namespace dmp

@@ -17,6 +17,7 @@
 #include "coef.hpp"
 #include "common.hpp"
 #include "plan.hpp"
+#include "residues.hpp"
 
 #include <hip/hip_fp16.h>
 
@@ -426,48 +427,29 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
             make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
-// Exponent t of an operand row of a residue product: X = rint(a 2^-t) with
-// 2^-t the largest power of two that keeps the row norm of X within
-// ``limit``.  The norm is bounded from the row maximum m: it is at most
-// sqrt(K) m, and at most sqrt(lam m) for a positive semidefinite source with
-// eigenvalues up to lam (|row i|^2 = (A^2)_ii <= lam A_ii <= lam m).
-__device__ inline int residue_exponent(uint64_t bits, int K, double lam, double limit) {
-    if (bits >= 0x7ff0000000000000ull) return kNonFiniteExp;
-    if (bits == 0) return 0;
-    const double m = __longlong_as_double(static_cast<long long>(bits));
-    double nu = sqrt(double(K)) * m;
-    if (lam > 0.0) nu = fmin(nu, sqrt(lam * m));
-    int en = 0, el = 0;
-    const double fn = frexp(nu, &en), fl = frexp(limit, &el);
-    return en - el + (fn > fl ? 1 : 0);
-}
-
 // Residues of an operand: the units and the staging of k_digits, with N
 // planes of one byte (FP16: one half) per element, plane m holding the
-// balanced residues modulo kMods[m].  A plane is laid out in fragments of 16
-// rows x 64 (FP16: 32) reduction elements, 1 KiB each in the order of a
-// 16 x 16 matrix instruction's operand (lane l: row l % 16, 16 bytes from
-// reduction element (l / 16) NE on); a 16-row block's fragments are
-// contiguous.  Each wavefront forms one of its unit's 2 x 2 fragments.  Per element X = Xh 2^27 + Xl exactly; per modulus
-// z = Xh (2^27 mod p) + Xl, q = rint(z / p) (|z| < 2^40, so the product with
-// 1 / p is off by less than 2^-13, closer than any z / p comes to a tie for
-// odd p), and z - q p modulo 256 is the residue's byte (p = 256: +-128 are
-// the same byte).  The integers z and q are read from the low words of z +
-// 1.5 2^52 and q + 1.5 2^52: four full-rate instructions per modulus.
+// balanced residues modulo kMods[m] (residues.hpp).  A plane is laid out in
+// fragments of 16 rows x 64 (FP16: 32) reduction elements, 1 KiB each in the
+// order of a 16 x 16 matrix instruction's operand (lane l: row l % 16, 16
+// bytes from reduction element (l / 16) NE on); a 16-row block's fragments are
+// contiguous.  Each wavefront forms one of its unit's 2 x 2 fragments.  The
+// iterates of a purification and their squares get their planes from the
+// combination that forms them; this kernel serves the first iterate, TRS4's T
+// and the restart from a checkpoint, whose exponents are given (maxbits
+// null).  Bound by memory: 8 + N bytes per element, 4.8 TB/s at n = 8192,
+// N = 13 (292 us); half of the moduli per wavefront, twice the wavefronts, took
+// 400 us.
 template <int N, bool FP16, bool COMB>
 __global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int count, SplitDesc one,
-                                                  const DevState* st, CoefArgs coef) {
+                                                  const DevState* st) {
     constexpr int CK = FP16 ? 16 : 32;
     constexpr int NE = CK / 2;
     constexpr int W = 4 * CK;
     __shared__ double panel[kFragRows * (W + 2)];
-    if (int(blockIdx.x) < coef.count) {
-        coef_block(coef, panel);
-        return;
-    }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int local;
-    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x) - coef.count, &local);
+    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x), &local);
     if (skipped(d, st)) return;
     const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
     const int kq_count = (d.KC + 3) / 4;
@@ -478,64 +460,15 @@ __global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int co
     const int r = rows16 * 16 + (lane & 15);
     const int k0 = rc * 2 * CK + (lane >> 4) * NE;
     // the operand's loads are issued before the exponents are worked out
-    const uint64_t bits = d.maxbits[r];
+    const uint64_t bits = d.maxbits != nullptr ? d.maxbits[r] : 0;
     double v[NE];
     const bool needed = load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v);
-    const int e = residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit);
-    if (rc == 0 && lane < 16) {
-        d.expo[r] = e;
-        if (d.clear != nullptr) d.clear[r] = 0;
-    }
+    const int e = d.maxbits != nullptr ? residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit) : d.expo[r];
+    if (rc == 0 && lane < 16 && d.maxbits != nullptr) d.expo[r] = e;
     if (!needed) return;
 
-    constexpr double kMagic = 0x1.8p52;
-    auto low = [](double x) __attribute__((always_inline)) {
-        return uint32_t(static_cast<uint64_t>(__double_as_longlong(x)));
-    };
-    uint32_t w[N][4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        constexpr int E = FP16 ? 2 : 4;   // elements per word
-        double xh[E], xl[E], xm[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-            const double x = e >= kNonFiniteExp ? 0.0 : rint(ldexp(v[g * E + i], -e));
-            xh[i] = rint(x * 0x1p-27);
-            xl[i] = __builtin_fma(xh[i], -0x1p27, x);
-            xm[i] = xl[i] + kMagic;
-        }
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            const int p = kMods[m];
-            int c = (1 << 27) % p;
-            if (c > p / 2) c -= p;
-            uint32_t b[E];
-#pragma unroll
-            for (int i = 0; i < E; ++i) {
-                const uint32_t z = low(__builtin_fma(xh[i], double(c), xm[i]));
-                const uint32_t q = low(__builtin_fma(__builtin_fma(xh[i], double(c), xl[i]), 1.0 / p, kMagic));
-                // the low byte of z - q p (24-bit multiply-add: the bits
-                // above do not matter)
-                b[i] = z + __umul24(q, uint32_t(256 - p));
-            }
-            if constexpr (!FP16) {
-                w[m][g] = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) |
-                          __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
-            } else {
-                // balanced residues are exact FP16 values (|r| <= 128)
-                uint32_t h = 0;
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    h |= uint32_t(__half_as_ushort(__int2half_rn(int(int8_t(uint8_t(b[i])))))) << (16 * i);
-                w[m][g] = h;
-            }
-        }
-    }
-    const int64_t plane = int64_t(rb_count) * 2 * RC * kFragBytes;
-    uint8_t* base = d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16;
-#pragma unroll
-    for (int m = 0; m < N; ++m)
-        *reinterpret_cast<uint4*>(base + m * plane) = make_uint4(w[m][0], w[m][1], w[m][2], w[m][3]);
+    store_residues<N, FP16>(v, e, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
+                            int64_t(rb_count) * 2 * RC * kFragBytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -570,17 +503,15 @@ static void launch_halves(bool comb, const SplitDesc* descs, int count, const Sp
 // Residue planes of N moduli.
 template <int N>
 static void launch_residues_n(bool fp16, bool comb, const SplitDesc* descs, int count,
-                              const SplitDesc& one, const DevState* st, int units,
-                              const CoefArgs& coef, hipStream_t stream) {
-    const unsigned grid = unsigned(units + coef.count);
+                              const SplitDesc& one, const DevState* st, int units, hipStream_t stream) {
     if (fp16 && comb)
-        k_residues<N, true, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_residues<N, true, true><<<units, 256, 0, stream>>>(descs, count, one, st);
     else if (fp16)
-        k_residues<N, true, false><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_residues<N, true, false><<<units, 256, 0, stream>>>(descs, count, one, st);
     else if (comb)
-        k_residues<N, false, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_residues<N, false, true><<<units, 256, 0, stream>>>(descs, count, one, st);
     else
-        k_residues<N, false, false><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_residues<N, false, false><<<units, 256, 0, stream>>>(descs, count, one, st);
 }
 
 using DigitsFn = void (*)(bool, bool, const SplitDesc*, int, const SplitDesc&, const DevState*,
@@ -590,7 +521,9 @@ static const DigitsFn kDigits[kMaxSlices + 1] = {
     launch_digits_s<4>, launch_digits_s<5>,  launch_digits_s<6>,  launch_digits_s<7>,
     launch_digits_s<8>, launch_digits_s<9>,  launch_digits_s<10>, launch_digits_s<11>,
     launch_digits_s<12>};
-static const DigitsFn kResidues[kMaxMods - kModMin + 1] = {
+using ResiduesFn = void (*)(bool, bool, const SplitDesc*, int, const SplitDesc&, const DevState*, int,
+                            hipStream_t);
+static const ResiduesFn kResidues[kMaxMods - kModMin + 1] = {
     launch_residues_n<11>, launch_residues_n<12>, launch_residues_n<13>,
     launch_residues_n<14>, launch_residues_n<15>, launch_residues_n<16>};
 
@@ -599,12 +532,12 @@ static const DigitsFn kResidues[kMaxMods - kModMin + 1] = {
 static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitDesc* descs, int count,
                          const SplitDesc& one, const DevState* st, int units, const CoefArgs& coef,
                          hipStream_t stream) {
-    if (nmod != 0 && (nmod < kModMin || nmod > kMaxMods)) {
+    if (nmod != 0 && (nmod < kModMin || nmod > kMaxMods || coef.count != 0)) {
         set_error("no residue split for %d moduli", nmod);
         return DMP_EINVAL;
     }
     if (nmod != 0)
-        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, coef, stream);
+        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, stream);
     else if (kind == DMP_MARKIDIS_FP16)
         launch_halves(comb, descs, count, one, st, units, coef, stream);
     else
@@ -627,6 +560,12 @@ int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
     }
     return launch_planes(S, kind, nmod, d.A2 != nullptr, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
                          CoefArgs{}, stream);
+}
+
+int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t stream) {
+    k_rowmax<<<split_units_rowmax(d.R), 256, 0, stream>>>(nullptr, 0, d, st);
+    DMP_CHECK_HIP(hipGetLastError());
+    return DMP_OK;
 }
 
 // The digit kernel alone, for an operand whose maxima (d.maxbits: row maxima,
