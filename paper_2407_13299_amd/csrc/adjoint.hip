@@ -69,6 +69,8 @@ struct OzCtx {
     uint8_t* res = nullptr;             // slices), their residues and tile list
     const Tile* mtiles = nullptr;
     int nmt = 0, mshape = 0;
+    const Tile* tiles_out = nullptr;    // and the tiles of their combination
+    int nt_out = 0;
 };
 
 void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
@@ -78,7 +80,7 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.KC = int(chunks_of(n, kind));
     const bool residues = mod_capacity(S) > 0;
     const TileChoice tc = tile_choice_env(kind, S, n);
-    x.rb = residues ? 2 : tc.rb;   // 64 x 64 output tiles, as dmp_purify's
+    x.rb = tc.rb;
     x.rb_stride = int64_t(x.KC) * S * kFragBytes;
     const size_t planes = std::max(plane_bytes(n, n, S, kind),
                                    residue_plane_bytes(n, n, kind) * mod_capacity(S));
@@ -96,7 +98,7 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.ma = c.take<uint64_t>(round_up(n, kPad));
     x.mb = c.take<uint64_t>(round_up(n, kPad));
     x.mc = c.take<uint64_t>(round_up(n, kPad));
-    x.partials = c.take<double>(size_t(std::max(upper_tile_count(n, 32 * x.rb), 1)) * kPartials);
+    x.partials = c.take<double>(size_t(std::max(upper_tile_count(n, residues ? 32 : 32 * x.rb), 1)) * kPartials);
     x.rows = c.take<double>(3 * size_t(n));
     x.rowbad = c.take<int>(n);
     x.e0 = c.take<double>(e0_blocks());
@@ -121,6 +123,8 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
     if (x.nmod > 0) {
         x.mshape = residue_shape(int64_t(residue_tile_count(x.n, kShapeWide, true)) * x.nmod);
         DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
+        DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, true, &x.tiles_out, 32));
+        x.nt_out = upper_tile_count(x.n, 32);
     }
     x.tail = TailSplit{x.nt_up, 1};
     if (x.fix != nullptr && tail_split_enabled()) {
@@ -139,7 +143,7 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
     d.n = x.n;
     d.nocc = nocc;
     d.part_begin = 0;
-    d.part_end = x.nt_up;
+    d.part_end = x.nmod > 0 ? x.nt_out : x.nt_up;
     DMP_CHECK_HIP(hipMemcpyAsync(x.pd, &d, sizeof(d), hipMemcpyHostToDevice, s));
     DMP_CHECK_HIP(hipStreamSynchronize(s));
     return DMP_OK;
@@ -204,7 +208,7 @@ int start_residues(const OzCtx& x, const double* P, int par, const int* expo, hi
 int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double* P_out,
                       bool finalize, bool p_maxima, int par, hipStream_t s) {
     GemmParams p{};
-    p.tiles = x.tiles_up;
+    p.tiles = x.nmod > 0 ? x.tiles_out : x.tiles_up;
     p.mtiles = x.mtiles;
     p.partials = x.partials;
     p.states = x.st;
@@ -221,7 +225,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         q.clear = x.maxi[par ^ 1];
         q.growth = kGrowthSquare;
         p.one = q;
-        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s));
+        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_out, s));
         q.pa = x.pb;
         q.ea = x.eb;
         q.out = P_out;
@@ -234,7 +238,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         q.growth = kGrowthCanonical;
         p.one = q;
         p.mode = EPI_UPDATE;
-        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_up, s,
+        DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_out, s,
                                       CoefArgs{x.pd, x.st, 1, DMP_CANONICAL, kStepCoef}));
         return finalize ? launch_finalize_iter(x.pd, x.st, 1, s) : DMP_OK;
     }

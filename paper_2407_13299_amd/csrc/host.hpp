@@ -52,7 +52,7 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
                   int rb = 4);
 // A product through residues: the residue GEMM over the ``ntiles`` entries of
 // p.mtiles (tiles of shape ``shape``, modulus in the top byte of mat), then
-// the combination and the FP64 epilogue over the nout 64 x 64 tiles of p.tiles.
+// the combination and the FP64 epilogue over the nout 32 x 64 tiles of p.tiles.
 // ``step`` (count > 0) runs in extra blocks of the residue GEMM.
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
                         hipStream_t stream, const CoefArgs& step = CoefArgs{});

@@ -317,14 +317,16 @@ __device__ inline uint32_t max16(uint32_t v) {
 
 // Rebuilds C' = X Y from its residues (modular.hpp) and runs the FP64 end of
 // the product, C = C' 2^(t_i + t_j), by mode as listed at the head of
-// ozgemm.hip.  One workgroup per 64 x 64 tile of p.tiles, half a 32 x 32
-// quadrant per wavefront: lane l holds column l % 32 and rows (l / 32) 4 + 8 g
-// + e, e < 4, of two row groups g, the order in which the residues are stored,
-// so every load is a whole cache line.
+// ozgemm.hip.  One workgroup per 32 x 64 tile of p.tiles, half of one of its
+// two 32 x 32 quadrants per wavefront: lane l holds column l % 32 and rows (l /
+// 32) 4 + 8 g + e, e < 4, of two row groups g, the order in which the residues
+// are stored, so every load is a whole cache line.  (64 x 64 tiles of 8
+// wavefronts leave 528 workgroups for 512 places at n = 2048.)
 //
 // The purification modes then form the residues of the output from the tile
-// in LDS: its four 16-row blocks' fragments (chunk J) and, transposed, those of
-// its 64 columns (chunk I), one fragment (FP16: two) per wavefront.  So an
+// in LDS: the fragments of its two 16-row blocks (wavefronts 0 and 1) and,
+// transposed, half of the fragments of its four 16-column blocks (wavefronts
+// 2 and 3, two blocks each).  So an
 // iterate or a square is split without being read again, and without the
 // launch that did (k_residues: 23 us at n = 2048, 290 us at n = 8192).  The
 // exponents come from the row maxima of the iterate before the product
@@ -336,12 +338,12 @@ __device__ inline uint32_t max16(uint32_t v) {
 // Row maxima, which only choose powers of two, are kept to the upper word,
 // rounded up.
 template <int N, int MODE, bool FP16>
-__global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
+__global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
     constexpr bool PUR = MODE == EPI_SQUARE || MODE == EPI_UPDATE || MODE == EPI_SQUARE_TRS4;
     constexpr bool UPPER = MODE != EPI_STORE;
-    constexpr int G = 2, WAVES = 8, LDT = 66;
+    constexpr int G = 2, WAVES = 4, LDT = 66;
     __shared__ double red[WAVES][kPartials];
-    __shared__ double out_tile[PUR ? 64 * LDT : 1];
+    __shared__ double out_tile[PUR ? 32 * LDT : 1];
     const int b = blockIdx.x, nb = gridDim.x;
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
@@ -358,9 +360,9 @@ __global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
     const bool has_product = MODE != EPI_UPDATE || !p.skip_zero || gamma != 0.0;   // a TRS4 step without one
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    // quadrant (quad / 2, quad % 2) of the tile, row groups g0 .. g0 + G - 1 of it
+    // quadrant ``quad`` of the tile, row groups g0 .. g0 + G - 1 of it
     const int quad = wave / (4 / G), g0 = wave % (4 / G) * G;
-    const int qr = 2 * int(tile.I) + (quad >> 1), qc = 2 * int(tile.J) + (quad & 1);
+    const int qr = int(tile.I), qc = 2 * int(tile.J) + quad;
     const int M = __builtin_amdgcn_readfirstlane(d.M), NC = __builtin_amdgcn_readfirstlane(d.N);
     const int ldc = __builtin_amdgcn_readfirstlane(d.ldc);
     const int lrow = (lane >> 5) * 4, lcol = lane & 31;
@@ -463,8 +465,7 @@ __global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
                 }
                 out4[e] = o;
                 if constexpr (PUR)
-                    out_tile[((quad >> 1) * 32 + 8 * (g0 + g) + lrow + e) * LDT + (quad & 1) * 32 + lcol] =
-                        inside(v) ? o : 0.0;
+                    out_tile[(8 * (g0 + g) + lrow + e) * LDT + quad * 32 + lcol] = inside(v) ? o : 0.0;
                 const uint32_t h = uint32_t(static_cast<uint64_t>(__double_as_longlong(o)) >> 32) & 0x7fffffffu;
                 hi[v] = inside(v) ? h : 0u;
                 cmax = max(cmax, hi[v]);
@@ -536,37 +537,64 @@ __global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
         }
 
         // ---- residue planes of the output ------------------------------------
-        const bool diag = tile.I == tile.J;
-        const int side = wave >> 2, blk = wave & 3;   // rows of the tile or, transposed, its columns
-        if (side == 1 && diag) return;
-        const int K64 = FP16 ? 2 : 1;                 // fragments per 64 reduction elements
+        // Rows (wave 0, 1): 16-row block ``wave`` of the tile over all 64
+        // columns.  Columns (wave 2, 3): the mirror's rows, 16-column blocks 2
+        // (wave - 2) and the next, lanes 0 .. 31 and 32 .. 63, over the tile's 32
+        // rows.  On the diagonal the upper tile (I even) writes its rows
+        // whole and the mirror of its right half, the lower one (I odd, whose
+        // left half lies below the diagonal) the right half of its rows.
+        const int half = int(tile.I) & 1;
+        const bool diag = int(tile.I) >> 1 == int(tile.J);
+        const bool rows = wave < 2;
+        if (diag && !rows && (half == 1 || wave == 2)) return;
+        constexpr int K64 = FP16 ? 2 : 1;             // fragments per 64 reduction elements
         constexpr int NE = FP16 ? 8 : 16;
         const int rbs = int(round_up(M, kPad)) / 16, RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;
-        const int lr = blk * 16 + (lane & 15);        // the lane's row (column) of the tile
-        const int row = 64 * int(side == 0 ? tile.I : tile.J) + lr, chunk = int(side == 0 ? tile.J : tile.I);
-        const int tx = residue_exponent(d.maxin[row], d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
-        if (diag && lane < 16) {
+        // the lane's row of the output planes, and what it has of the chunk
+        const int lr = rows ? wave * 16 + (lane & 15) : (wave - 2) * 32 + (lane >> 5) * 16 + (lane & 15);
+        const int row = rows ? 32 * int(tile.I) + lr : 64 * int(tile.J) + lr;
+        const int chunk = rows ? int(tile.J) : int(tile.I) >> 1;
+        const int tx =
+            residue_exponent(d.maxin[row], d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
+        if (diag && rows && lane < 16) {
             d.expo_out[row] = tx;
             if (d.clear != nullptr) d.clear[row] = 0;
         }
         const int64_t plane = int64_t(rbs) * RC * kFragBytes;
+        uint8_t* const rowbase = d.planes_out + (int64_t(row / 16) * RC + chunk * K64) * kFragBytes;
+        // FP16: a fragment holds 32 reduction elements, so the columns' half of a
+        // chunk is one of its two fragments, formed in two passes of 16
+        constexpr int PASSES = K64;
 #pragma unroll
-        for (int f = 0; f < K64; ++f) {
-            const int k0 = f * 32 + (lane >> 4) * NE;
+        for (int f = 0; f < PASSES; ++f) {
             double x[NE];
-            if (side == 0) {
+            if (rows) {
+                const int k0 = f * 32 + (lane >> 4) * NE;
+                const bool left = diag && k0 < 32;    // the diagonal quadrant of an upper tile
 #pragma unroll
                 for (int i = 0; i < NE; ++i) {
-                    // below the diagonal of a diagonal tile: the mirror's element
-                    const bool low = diag && lr > k0 + i;
+                    const bool low = left && lr > k0 + i;
                     x[i] = out_tile[low ? (k0 + i) * LDT + lr : lr * LDT + k0 + i];
                 }
+                // lower tile on the diagonal: its diagonal quadrant is the right one
+                if (diag && half == 1) {
+#pragma unroll
+                    for (int i = 0; i < NE; ++i)
+                        if (k0 >= 32 && lr > k0 - 32 + i) x[i] = out_tile[(k0 - 32 + i) * LDT + 32 + lr];
+                }
+                store_residues<N, FP16>(x, tx, rowbase + f * kFragBytes + lane * 16, plane,
+                                        !(diag && half == 1) || k0 >= 32);
             } else {
+                // elements k of the tile's rows: 16 per lane group (FP16: two
+                // groups of 8, one per pass)
+                const int k0 = FP16 ? f * 16 + ((lane >> 4) & 1) * 8 : ((lane >> 4) & 1) * 16;
 #pragma unroll
                 for (int i = 0; i < NE; ++i) x[i] = out_tile[(k0 + i) * LDT + lr];
+                const int pos = half * 32 + k0;       // reduction element within the chunk
+                uint8_t* const at16 = FP16 ? rowbase + (pos / 32) * kFragBytes + ((pos % 32) / 8 * 16 + (lane & 15)) * 16
+                                           : rowbase + (pos / 16 * 16 + (lane & 15)) * 16;
+                store_residues<N, FP16>(x, tx, at16, plane);
             }
-            store_residues<N, FP16>(
-                x, tx, d.planes_out + (int64_t(row / 16) * RC + chunk * K64 + f) * kFragBytes + lane * 16, plane);
         }
     }
 }
@@ -574,19 +602,19 @@ __global__ __launch_bounds__(512, 4) void k_combine(GemmParams p) {
 template <int N>
 static int launch_combine(bool fp16, const GemmParams& p, int nout, hipStream_t stream) {
     switch (p.mode) {
-        case EPI_STORE: k_combine<N, EPI_STORE, false><<<nout, 512, 0, stream>>>(p); break;
-        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, false><<<nout, 512, 0, stream>>>(p); break;
+        case EPI_STORE: k_combine<N, EPI_STORE, false><<<nout, 256, 0, stream>>>(p); break;
+        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, false><<<nout, 256, 0, stream>>>(p); break;
         case EPI_SQUARE:
-            if (fp16) k_combine<N, EPI_SQUARE, true><<<nout, 512, 0, stream>>>(p);
-            else k_combine<N, EPI_SQUARE, false><<<nout, 512, 0, stream>>>(p);
+            if (fp16) k_combine<N, EPI_SQUARE, true><<<nout, 256, 0, stream>>>(p);
+            else k_combine<N, EPI_SQUARE, false><<<nout, 256, 0, stream>>>(p);
             break;
         case EPI_UPDATE:
-            if (fp16) k_combine<N, EPI_UPDATE, true><<<nout, 512, 0, stream>>>(p);
-            else k_combine<N, EPI_UPDATE, false><<<nout, 512, 0, stream>>>(p);
+            if (fp16) k_combine<N, EPI_UPDATE, true><<<nout, 256, 0, stream>>>(p);
+            else k_combine<N, EPI_UPDATE, false><<<nout, 256, 0, stream>>>(p);
             break;
         default:
-            if (fp16) k_combine<N, EPI_SQUARE_TRS4, true><<<nout, 512, 0, stream>>>(p);
-            else k_combine<N, EPI_SQUARE_TRS4, false><<<nout, 512, 0, stream>>>(p);
+            if (fp16) k_combine<N, EPI_SQUARE_TRS4, true><<<nout, 256, 0, stream>>>(p);
+            else k_combine<N, EPI_SQUARE_TRS4, false><<<nout, 256, 0, stream>>>(p);
     }
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;

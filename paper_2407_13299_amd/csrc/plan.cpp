@@ -236,9 +236,9 @@ void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int 
         const int S = kind == DMP_FP64_NATIVE ? 0 : slices[b];
         const bool residues = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && mod_capacity(S) > 0;
         const int nmod = residues ? mod_count(S, n[b], nocc ? nocc[b] : 0) : 0;
-        // residues: the combination runs on 64 x 64 tiles
+        // residues: the combination runs on 32 x 64 tiles
         const TileChoice tc = kind == DMP_FP64_NATIVE ? TileChoice{4, false}
-                              : residues              ? TileChoice{2, false}
+                              : residues              ? TileChoice{1, false}
                                                       : tile_choice(kind, S, n[b], forced_rb);
         GroupPlan* g = nullptr;
         for (auto& x : groups)

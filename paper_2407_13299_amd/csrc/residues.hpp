@@ -27,7 +27,8 @@ __device__ inline int residue_exponent(uint64_t bits, int K, double lam, double 
 
 // One lane's 16 bytes of a fragment in each of N planes: the balanced
 // residues of X = rint(v 2^-t) for NE = 16 elements (FP16: 8, as halves);
-// plane m starts at m ``plane`` bytes from ``base``.  Per element X = Xh 2^27
+// plane m starts at m ``plane`` bytes from ``base`` (a lane that is not
+// ``wanted`` stores nothing).  Per element X = Xh 2^27
 // + Xl exactly; per modulus z = Xh (2^27 mod p) + Xl, q = rint(z / p) (|z| <
 // 2^40, so the product with 1 / p is off by less than 2^-13, closer than any
 // z / p comes to a tie for odd p), and z - q p modulo 256 is the residue's
@@ -36,7 +37,7 @@ __device__ inline int residue_exponent(uint64_t bits, int K, double lam, double 
 // per modulus.
 template <int N, bool FP16>
 __device__ __forceinline__ void store_residues(const double (&v)[FP16 ? 8 : 16], int t, uint8_t* base,
-                                               int64_t plane) {
+                                               int64_t plane, bool wanted = true) {
     constexpr double kMagic = 0x1.8p52;
     auto low = [](double x) __attribute__((always_inline)) {
         return uint32_t(static_cast<uint64_t>(__double_as_longlong(x)));
@@ -80,6 +81,7 @@ __device__ __forceinline__ void store_residues(const double (&v)[FP16 ? 8 : 16],
             }
         }
     }
+    if (!wanted) return;
 #pragma unroll
     for (int m = 0; m < N; ++m)
         *reinterpret_cast<uint4*>(base + m * plane) = make_uint4(w[m][0], w[m][1], w[m][2], w[m][3]);
