@@ -1,5 +1,6 @@
 // C-ABI entry points of the Ozaki-scheme GEMM (Sec. 2.4).
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "host.hpp"
@@ -19,23 +20,24 @@ struct GemmLayout {
     TailSplit tail;
 };
 
-// Split tail of the m x n product's 128 x 64 tiles on the current device; the
+// Split tail of the m x n product's tiles on the current device; the
 // workspace query and the launch take the same plan, so the part buffer is
 // only as large as the launch needs (none when the tiles fill whole rounds).
 TailSplit gemm_tail(int m, int n, int k, int s, dmp_kind kind) {
-    const int tiles = m > 0 && n > 0 ? tile_rows(m) * tile_cols(n) : 0;
+    const int rb = gemm_tile_blocks(m, n, s, kind);
+    const int tiles = m > 0 && n > 0 ? tile_rows(m, 32 * rb) * tile_cols(n) : 0;
     TailSplit t{tiles, 1};
     if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || k <= 0 || tiles == 0 ||
         !tail_split_enabled())
         return t;
     const int kc = int(chunks_of(k, kind));
-    const int cap = tail_split_capacity(tiles, kc, 4);
+    const int cap = tail_split_capacity(tiles, kc, rb);
     int slots = 0;
-    if (cap <= 0 || resident_slots(s, kind, 4, &slots) != DMP_OK) {
+    if (cap <= 0 || resident_slots(s, kind, rb, &slots) != DMP_OK) {
         clear_error();
         return t;
     }
-    return plan_tail_split(tiles, slots, kc, cap);
+    return plan_gemm_split(tiles, slots, kc, cap);
 }
 
 // ``split``: plan a split tail (single products; the grouped launch keeps
@@ -49,9 +51,10 @@ GemmLayout carve_gemm(Carver& c, int m, int n, int k, int s, dmp_kind kind, bool
     g.eb = c.take<int>(round_up(n, kPad));
     g.ma = c.take<uint64_t>(round_up(m, kPad));
     g.mb = c.take<uint64_t>(round_up(n, kPad));
-    const int tiles = m > 0 && n > 0 ? tile_rows(m) * tile_cols(n) : 0;
+    const int rb = gemm_tile_blocks(m, n, s, kind);
+    const int tiles = m > 0 && n > 0 ? tile_rows(m, 32 * rb) * tile_cols(n) : 0;
     const size_t parts = g.tail.nsplit > 1 ? size_t(tiles - g.tail.nfull) * g.tail.nsplit : 0;
-    g.fix = parts > 0 ? c.take<int>(parts * piece_ints(s, 4)) : nullptr;
+    g.fix = parts > 0 ? c.take<int>(parts * piece_ints(s, rb)) : nullptr;
     return g;
 }
 
@@ -151,14 +154,14 @@ int dmp_ozaki_gemm(char transA, char transB, int m, int n, int k, const double* 
     db.maxbits = g.mb;
     db.expo = g.eb;
     db.planes = g.pb;
-    DMP_CHECK(launch_split(da, slices, kind, nullptr, s));
-    DMP_CHECK(launch_split(db, slices, kind, nullptr, s));
+    DMP_CHECK(launch_split_pair(da, db, slices, kind, s));
 
-    const int tm = tile_rows(m), tn = tile_cols(n);
-    const Tile* tiles = nullptr;
-    DMP_CHECK(cached_tiles(tm, tn, false, &tiles));
+    // the tile of a block follows from its number: no tile list
+    const int rb = gemm_tile_blocks(m, n, slices, kind);
+    const int tm = tile_rows(m, 32 * rb), tn = tile_cols(n);
     GemmParams p{};
-    p.tiles = tiles;
+    p.tm = tm;
+    p.tn = tn;
     p.descs = nullptr;
     p.one.pa = g.pa;
     p.one.pb = g.pb;
@@ -178,7 +181,7 @@ int dmp_ozaki_gemm(char transA, char transB, int m, int n, int k, const double* 
         p.nfull = g.tail.nfull;
         p.nsplit = g.tail.nsplit;
     }
-    return launch_ozgemm(slices, kind, p, tm * tn, s);
+    return launch_ozgemm(slices, kind, p, tm * tn, s, rb);
 }
 
 // ---------------------------------------------------------------------------
@@ -195,7 +198,7 @@ size_t dmp_gemm_batched_workspace_bytes(int count, const int* m, const int* n, c
     size_t tiles = 0;
     for (int b = 0; b < count; ++b) {
         if (kind != DMP_FP64_NATIVE) carve_gemm(c, m[b], n[b], k[b], slices, kind);
-        tiles += size_t(tile_rows(m[b])) * size_t(tile_cols(n[b]));
+        tiles += size_t(tile_rows(m[b], 64)) * size_t(tile_cols(n[b]));   // the lower tile height
     }
     c.take<SplitDesc>(2 * size_t(count));
     c.take<MatDesc>(count);
@@ -238,12 +241,10 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
     Carver c(ws);
     std::vector<GemmLayout> lay(count);
     for (int b = 0; b < count; ++b) lay[b] = carve_gemm(c, m[b], n[b], k[b], slices, kind);
-    SplitDesc* sd_dev = c.take<SplitDesc>(2 * size_t(count));
-    MatDesc* md_dev = c.take<MatDesc>(count);
-    std::vector<SplitDesc> sa(count), sb(count);
+    // operands: all left ones, then all right ones
+    std::vector<SplitDesc> sd(2 * size_t(count));
     std::vector<MatDesc> md(count);
     std::vector<Tile> tiles;
-    int ur_a = 0, ud_a = 0, ur_b = 0, ud_b = 0;
     for (int b = 0; b < count; ++b) {
         const int KC = int(chunks_of(k[b], kind));
         SplitDesc d{};
@@ -257,26 +258,17 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
         d.expo = lay[b].ea;
         d.planes = lay[b].pa;
         d.state_index = -1;
-        d.ub_rowmax = ur_a;
-        d.ub_digits = ud_a;
-        ur_a += split_units_rowmax(m[b]);
-        ud_a += split_units_digits(m[b], KC);
-        sa[b] = d;
+        sd[b] = d;
         // B's operand rows are its columns: transpose the digit read by
         // splitting B^T, i.e. columns of the row-major k x n matrix.
-        SplitDesc e = d;
-        e.A = B[b];
-        e.lda = n[b];
-        e.R = n[b];
-        e.trans = 1;
-        e.maxbits = lay[b].mb;
-        e.expo = lay[b].eb;
-        e.planes = lay[b].pb;
-        e.ub_rowmax = ur_b;
-        e.ub_digits = ud_b;
-        ur_b += 0;
-        ud_b += split_units_digits(n[b], KC);
-        sb[b] = e;
+        d.A = B[b];
+        d.lda = n[b];
+        d.R = n[b];
+        d.trans = 1;
+        d.maxbits = lay[b].mb;
+        d.expo = lay[b].eb;
+        d.planes = lay[b].pb;
+        sd[count + b] = d;
         MatDesc q{};
         q.pa = lay[b].pa;
         q.pb = lay[b].pb;
@@ -292,35 +284,41 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
         q.state_index = -1;
         md[b] = q;
     }
+    SplitUnits units;
+    count_split_units(sd.data(), int(sd.size()), units);
+    const bool self = split_takes_maxima(sd.data(), int(sd.size()));
+    if (self)
+        for (SplitDesc& d : sd) d.maxbits = nullptr;
     // tiles of the longest reductions first (dispatched in that order)
+    const int rb = batch_tile_blocks(count, m, n, slices, kind);
     std::vector<int> order(count);
     for (int b = 0; b < count; ++b) order[b] = b;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return k[x] > k[y]; });
-    for (int b : order) append_tiles(tiles, tile_rows(m[b]), tile_cols(n[b]), false, uint32_t(b));
+    for (int b : order)
+        append_tiles(tiles, tile_rows(m[b], 32 * rb), tile_cols(n[b]), false, uint32_t(b), 32 * rb);
+    // descriptors and tiles in one copy
+    SplitDesc* sd_dev = c.take<SplitDesc>(2 * size_t(count));
+    MatDesc* md_dev = c.take<MatDesc>(count);
     Tile* t_dev = c.take<Tile>(tiles.size());
-    // the host vectors must outlive the asynchronous copies (the stream is
-    // drained before any error return); the launches below stay asynchronous
-    hipError_t e = hipMemcpyAsync(sd_dev, sa.data(), count * sizeof(SplitDesc), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(md_dev, md.data(), count * sizeof(MatDesc), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(t_dev, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, s);
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(sd_dev);
+    std::vector<uint8_t> staged(size_t(reinterpret_cast<const uint8_t*>(t_dev) - base) + tiles.size() * sizeof(Tile));
+    std::memcpy(staged.data(), sd.data(), sd.size() * sizeof(SplitDesc));
+    std::memcpy(staged.data() + (reinterpret_cast<const uint8_t*>(md_dev) - base), md.data(), md.size() * sizeof(MatDesc));
+    std::memcpy(staged.data() + (reinterpret_cast<const uint8_t*>(t_dev) - base), tiles.data(),
+                tiles.size() * sizeof(Tile));
+    // the host copy must outlive the asynchronous one (the stream is drained
+    // before any error return); the launches below stay asynchronous
+    const hipError_t e = hipMemcpyAsync(sd_dev, staged.data(), staged.size(), hipMemcpyHostToDevice, s);
     const hipError_t e_sync = hipStreamSynchronize(s);
     DMP_CHECK_HIP(e);
     DMP_CHECK_HIP(e_sync);
-    // A: one grouped row split; B: column splits (per product, small count)
-    DMP_CHECK(launch_split_grouped_rowmax(sd_dev, count, ur_a, nullptr, s));
-    DMP_CHECK(launch_split_grouped_digits(sd_dev, count, ud_a, slices, kind, nullptr, s));
-    for (int b = 0; b < count; ++b) {
-        SplitDesc e = sb[b];
-        DMP_CHECK(launch_split(e, slices, kind, nullptr, s));
-    }
+    DMP_CHECK(launch_split_set(sd_dev, 2 * count, units, !self, slices, kind, s));
     GemmParams p{};
     p.tiles = t_dev;
     p.descs = md_dev;
     p.mode = EPI_STORE;
     p.spread = count > 1 ? 1 : 0;
-    DMP_CHECK(launch_ozgemm(slices, kind, p, int(tiles.size()), s));
+    DMP_CHECK(launch_ozgemm(slices, kind, p, int(tiles.size()), s, rb));
     return DMP_OK;
 }
 

@@ -27,6 +27,12 @@ int native_dgemm(hipStream_t stream, bool ta, bool tb, int m, int n, int k, cons
 int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st, hipStream_t s, int nmod = 0);
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
                         hipStream_t stream, int nmod = 0);
+// both operands of a product
+int launch_split_pair(const SplitDesc& a, const SplitDesc& b, int S, dmp_kind kind, hipStream_t s);
+// the operands of many products (descriptors in device memory); maxima: run
+// the maxima's launches too
+int launch_split_set(const SplitDesc* descs_dev, int count, const SplitUnits& u, bool maxima, int S,
+                     dmp_kind kind, hipStream_t stream);
 // the row maxima of one operand alone (trans == 0)
 int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t s);
 int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units,

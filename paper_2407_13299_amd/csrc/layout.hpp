@@ -156,21 +156,34 @@ struct SplitDesc {
     int R, K;           // rows / reduction length of the operand
     int trans;          // 0: operand row r is A[r, :]; 1: operand row r is A[:, r]
     int KC;             // chunks along the reduction (padded K / CK)
-    uint64_t* maxbits;  // [Rp] bit pattern of max |row|
+    uint64_t* maxbits;  // [Rp] bit pattern of max |row|; null: the digit split
+                        // takes the maxima itself (residues: expo is given)
     int* expo;          // [Rp] exponents
     uint8_t* planes;    // digit planes
     uint64_t* clear;    // nullable: rows [0, R padded) of this array are zeroed
                         // (the row maxima the next product accumulates)
-    int ub_rowmax;      // first k_rowmax unit of this matrix (grouped)
-    int ub_digits;      // first k_digits unit of this matrix (grouped)
+    int ub_rowmax;      // first k_rowmax unit of this operand in its set
+    int ub_digits;      // first k_digits unit
+    int ub_colmax;      // first k_colmax unit (none unless trans)
     int state_index;    // -1: no state
     int sym;            // 1: A is symmetric and only its upper triangle (k >= r)
                         // holds it (trans == 0, A2 null): entry (r, k < r) is
                         // read as A[k, r]
-    int pad_;
     double lam;         // residues: largest eigenvalue magnitude of the (positive
                         // semidefinite) source, with some room; 0: none known
 };
+
+// The operands of a split launch: an array in device memory, or one or two by
+// value (descs null).
+struct SplitSet {
+    const SplitDesc* descs;
+    int count;
+    SplitDesc two[2];
+};
+// Stages of a split: k_rowmax (zeroing, for operands read by columns),
+// k_colmax, k_digits / k_residues; rows of A per k_colmax unit.
+constexpr int kStageMax = 0, kStageColmax = 1, kStageDigits = 2;
+constexpr int kColmaxRows = 128;
 
 // Per-matrix arguments of the small purification kernels.
 struct PurDesc {
@@ -233,7 +246,9 @@ constexpr int kPartials = 2;   // partial sums written per tile
 
 // Arguments of one slice-GEMM launch.
 struct GemmParams {
-    const Tile* tiles;
+    const Tile* tiles;      // null (whole tiles of one full product): the order of
+                            // append_tiles over a tm x tn grid, worked out per block
+    int tm, tn;
     const MatDesc* descs;   // grouped launch (device); nullptr: use ``one``
     MatDesc one;
     double* partials;       // [tiles][kPartials] (purification modes)

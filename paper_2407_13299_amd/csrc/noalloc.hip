@@ -1,10 +1,10 @@
 // Allocation-free variant of the Ozaki-scheme GEMM (Sec. 2.4) for callers
 // that cannot allocate device memory (code under HIP graph capture, tight
 // serving loops, harnesses that forbid it).  Its scratch memory (the digit
-// planes, exponents and maxima of both operands and the tile list) is one
-// file-scope device array, held by every GPU the library runs on until the
-// process ends; the tile list is written by a kernel, so nothing is staged
-// from host memory either.  Every call on a GPU shares that GPU's array:
+// planes, exponents and maxima of both operands) is one file-scope device
+// array, held by every GPU the library runs on until the process ends; the
+// tiles follow from the block numbers, so nothing is staged from host memory
+// either.  Every call on a GPU shares that GPU's array:
 // calls that overlap on one GPU (several streams or threads) race.
 #include <algorithm>
 #include <mutex>
@@ -49,23 +49,6 @@ int scratch_address(void** out) {
     return DMP_OK;
 }
 
-// Tiles of a tm x tn grid of 128 x 64 output tiles in the order of
-// append_tiles(..., upper = false): 512 x 512 super-tiles row-major, and
-// row-major inside each.  Super-row si holds rows [GI si, GI si + ri) of
-// all tn columns; its super-tile sj holds columns [GJ sj, GJ sj + cj).
-__global__ void k_fill_tiles(Tile* out, int tm, int tn) {
-    constexpr int GI = 512 / kTileM, GJ = 512 / kTileN;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= tm * tn) return;
-    const int si = t / (GI * tn);
-    const int ri = min(GI, tm - si * GI);
-    const int r = t - si * GI * tn;
-    const int sj = r / (GJ * ri);
-    const int cj = min(GJ, tn - sj * GJ);
-    const int r2 = r - sj * GJ * ri;
-    out[t] = Tile{uint16_t(si * GI + r2 / cj), uint16_t(sj * GJ + r2 % cj), 0u};
-}
-
 __global__ void k_zero_matrix(double* c, int m, int n, int ldc) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < int64_t(m) * n) c[(i / n) * ldc + i % n] = 0.0;
@@ -78,7 +61,6 @@ struct NoAllocLayout {
     int* eb;
     uint64_t* ma;
     uint64_t* mb;
-    Tile* tiles;
 };
 
 NoAllocLayout carve_noalloc(Carver& c, int m, int n, int k, int s, dmp_kind kind) {
@@ -89,7 +71,8 @@ NoAllocLayout carve_noalloc(Carver& c, int m, int n, int k, int s, dmp_kind kind
     g.eb = c.take<int>(round_up(n, kPad));
     g.ma = c.take<uint64_t>(round_up(m, kPad));
     g.mb = c.take<uint64_t>(round_up(n, kPad));
-    g.tiles = c.take<Tile>(size_t(tile_rows(m)) * size_t(tile_cols(n)));
+    // part of the documented size limit, unused
+    c.take<Tile>(size_t(tile_rows(m)) * size_t(tile_cols(n)));
     return g;
 }
 
@@ -185,14 +168,14 @@ int dmp_ozaki_gemm_noalloc(char transA, char transB, int m, int n, int k, const 
     db.maxbits = g.mb;
     db.expo = g.eb;
     db.planes = g.pb;
-    DMP_CHECK(launch_split(da, slices, kind, nullptr, s));
-    DMP_CHECK(launch_split(db, slices, kind, nullptr, s));
+    DMP_CHECK(launch_split_pair(da, db, slices, kind, s));
 
-    const int tm = tile_rows(m), tn = tile_cols(n);
-    k_fill_tiles<<<unsigned((tm * tn + 255) / 256), 256, 0, s>>>(g.tiles, tm, tn);
-    DMP_CHECK_HIP(hipGetLastError());
+    // the tile of a block follows from its number: no tile list
+    const int rb = gemm_tile_blocks(m, n, slices, kind);
+    const int tm = tile_rows(m, 32 * rb), tn = tile_cols(n);
     GemmParams p{};
-    p.tiles = g.tiles;
+    p.tm = tm;
+    p.tn = tn;
     p.descs = nullptr;
     p.one.pa = g.pa;
     p.one.pb = g.pb;
@@ -209,7 +192,7 @@ int dmp_ozaki_gemm_noalloc(char transA, char transB, int m, int n, int k, const 
     p.mode = EPI_STORE;
     // whole tiles only (a split tail would need its part buffer sized from
     // an occupancy query)
-    return launch_ozgemm(slices, kind, p, tm * tn, s);
+    return launch_ozgemm(slices, kind, p, tm * tn, s, rb);
 }
 
 }  // extern "C"

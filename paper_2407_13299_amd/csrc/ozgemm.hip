@@ -49,6 +49,22 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
+// Tile number t of a tm x tn grid of TM x 64 tiles in the order of
+// append_tiles(..., upper = false): 512 x 512 super-tiles row-major, and
+// row-major inside each.  Super-row si holds rows [GI si, GI si + ri) of all tn
+// columns; its super-tile sj holds columns [GJ sj, GJ sj + cj).
+template <int TM>
+__device__ inline Tile tile_of(int t, int tm, int tn) {
+    constexpr int GI = 512 / TM, GJ = 512 / kTileN;
+    const int si = t / (GI * tn);
+    const int ri = min(GI, tm - si * GI);
+    const int r = t - si * GI * tn;
+    const int sj = r / (GJ * ri);
+    const int cj = min(GJ, tn - sj * GJ);
+    const int r2 = r - sj * GJ * ri;
+    return Tile{uint16_t(si * GI + r2 / cj), uint16_t(sj * GJ + r2 % cj), 0u};
+}
+
 // TERMS > 0: the Markidis product (Sec. 4.5) on the same tiles: S = 2 FP16
 // planes (high, low parts), the first TERMS of A0 B0, A0 B1, A1 B0, A1 B1
 // accumulated in one FP32 accumulator, and C = acc 2^(e_i + f_j).
@@ -93,7 +109,7 @@ __global__ __launch_bounds__(128 * RB, RB == 4 ? 1 : 2) void k_ozgemm(GemmParams
     } else {
         t = p.nfull + b;
     }
-    const Tile tile = p.tiles[t];
+    const Tile tile = p.tiles != nullptr ? p.tiles[t] : tile_of<32 * RB>(t, p.tm, p.tn);
     const MatDesc d = p.descs ? p.descs[tile.mat] : p.one;
     const DevState* st = p.states ? p.states + d.state_index : nullptr;
     if (st != nullptr && st->done) return;

@@ -132,10 +132,31 @@ int upper_tile_count(int n, int TM) {
 }
 
 int split_units_rowmax(int R) { return int(round_up(R, kPad)) / 4; }
-int split_units_colmax(int R, int K) { return ((R + 63) / 64) * ((K + 255) / 256); }
+int split_units_colmax(int R, int K) { return ((R + 63) / 64) * ((K + kColmaxRows - 1) / kColmaxRows); }
 int split_units_digits(int R, int KC) { return int(round_up(R, kPad)) / kFragRows * ((KC + 3) / 4); }
 
 int64_t chunks_of(int k, dmp_kind kind) { return round_up(k, kKPad) / chunk_k(kind); }
+
+void count_split_units(SplitDesc* d, int count, SplitUnits& u) {
+    u = SplitUnits{};
+    for (int i = 0; i < count; ++i) {
+        d[i].ub_rowmax = u.rowmax;
+        d[i].ub_colmax = u.colmax;
+        d[i].ub_digits = u.digits;
+        u.rowmax += split_units_rowmax(d[i].R);
+        u.colmax += d[i].trans ? split_units_colmax(d[i].R, d[i].K) : 0;
+        u.digits += split_units_digits(d[i].R, d[i].KC);
+    }
+}
+
+bool split_takes_maxima(const SplitDesc* d, int count) {
+    double bytes = 0.0;
+    for (int i = 0; i < count; ++i) {
+        if (d[i].K > kSelfMaxK) return false;
+        bytes += double((d[i].K + 127) / 128) * d[i].R * d[i].K * 8.0;
+    }
+    return bytes <= kSelfMaxBytes;
+}
 
 // ---- split tail -------------------------------------------------------------------
 
@@ -152,6 +173,25 @@ TailSplit plan_tail_split(int ntiles, int slots, int min_kc, int max_pieces) {
     t.nfull = ntiles - r;
     t.nsplit = parts;
     return t;
+}
+
+TailSplit plan_gemm_split(int ntiles, int slots, int min_kc, int max_pieces) {
+    if (ntiles <= 0 || 2 * ntiles > slots) return plan_tail_split(ntiles, slots, min_kc, max_pieces);
+    const int parts = std::min({split_parts_max(min_kc), slots / ntiles, max_pieces / ntiles});
+    if (parts < 2 || min_kc - min_kc / parts < kMinSavedChunks) return TailSplit{ntiles, 1};
+    return TailSplit{0, parts};
+}
+
+int gemm_tile_blocks(int m, int n, int S, dmp_kind kind) {
+    if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || S > kMaxSlices64) return 4;
+    return int64_t(tile_rows(m)) * tile_cols(n) < kLowTileCount ? 2 : 4;
+}
+
+int batch_tile_blocks(int count, const int* m, const int* n, int S, dmp_kind kind) {
+    if ((kind != DMP_OZ_INT8 && kind != DMP_OZ_FP16) || S > kMaxSlices64) return 4;
+    int64_t tiles = 0;
+    for (int b = 0; b < count; ++b) tiles += int64_t(tile_rows(m[b])) * tile_cols(n[b]);
+    return tiles < kLowTileCount ? 2 : 4;
 }
 
 int tail_split_capacity(int ntiles, int min_kc, int rb) {

@@ -72,6 +72,17 @@ int split_units_rowmax(int R);
 int split_units_colmax(int R, int K);
 int split_units_digits(int R, int KC);
 int64_t chunks_of(int k, dmp_kind kind);
+// Units of each stage of a set of operands; fills their first-unit fields.
+struct SplitUnits {
+    int rowmax = 0, colmax = 0, digits = 0;
+};
+void count_split_units(SplitDesc* d, int count, SplitUnits& u);
+// Whether the digit split of a set takes the row maxima itself: every
+// workgroup then reads its 32 rows over the whole reduction, K / 128 times in
+// all, instead of one or two launches before it.
+constexpr int kSelfMaxK = 512;
+constexpr double kSelfMaxBytes = 1e9;
+bool split_takes_maxima(const SplitDesc* d, int count);
 
 // ---- split tail -----------------------------------------------------------
 // Tail split of ``ntiles`` tiles of equal cost: tiles [0, nfull) whole, the
@@ -85,6 +96,16 @@ struct TailSplit {
 // as many parts as fill it (at most kMaxSplit, at least kMinSplitChunks of
 // the ``min_kc`` chunks each, at most ``max_pieces`` parts in all).
 TailSplit plan_tail_split(int ntiles, int slots, int min_kc, int max_pieces);
+// The same for the tiles of one general product, which may also be too few to
+// fill half of the slots: then every tile is split, if that shortens the
+// reduction by at least kMinSavedChunks chunks.
+constexpr int kMinSavedChunks = 24;
+TailSplit plan_gemm_split(int ntiles, int slots, int min_kc, int max_pieces);
+// Tile height (32-row blocks) of a general m x n product, and of a batch of
+// them: 64 rows, two workgroups per CU, below kLowTileCount tiles of 128 rows.
+constexpr int kLowTileCount = 256;
+int gemm_tile_blocks(int m, int n, int S, dmp_kind kind);
+int batch_tile_blocks(int count, const int* m, const int* n, int S, dmp_kind kind);
 // Parts of a tail split a group of ``ntiles`` tiles of height 32 rb may need
 // (the size of its part buffer in pieces, 0 when no split can arise).
 int tail_split_capacity(int ntiles, int min_kc, int rb);

@@ -25,21 +25,26 @@ namespace dmp {
 
 
 
-template <bool ROWMAX>
-__device__ inline const SplitDesc& pick(const SplitDesc* descs, int count,
-                                        const SplitDesc& one, int unit, int* local) {
-    if (descs == nullptr) {
-        *local = unit;
-        return one;
+// First unit of an operand in a stage of the split.
+template <int STAGE>
+__device__ inline int first_unit(const SplitDesc& d) {
+    return STAGE == kStageMax ? d.ub_rowmax : STAGE == kStageColmax ? d.ub_colmax : d.ub_digits;
+}
+
+template <int STAGE>
+__device__ inline const SplitDesc& pick(const SplitSet& set, int unit, int* local) {
+    if (set.descs == nullptr) {
+        const SplitDesc& d = set.two[set.count == 2 && unit >= first_unit<STAGE>(set.two[1]) ? 1 : 0];
+        *local = unit - first_unit<STAGE>(d);
+        return d;
     }
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {   // last matrix whose first unit <= unit
+    int lo = 0, hi = set.count - 1;
+    while (lo < hi) {   // last operand whose first unit <= unit
         int mid = (lo + hi + 1) >> 1;
-        int b = ROWMAX ? descs[mid].ub_rowmax : descs[mid].ub_digits;
-        if (b <= unit) lo = mid; else hi = mid - 1;
+        if (first_unit<STAGE>(set.descs[mid]) <= unit) lo = mid; else hi = mid - 1;
     }
-    *local = unit - (ROWMAX ? descs[lo].ub_rowmax : descs[lo].ub_digits);
-    return descs[lo];
+    *local = unit - first_unit<STAGE>(set.descs[lo]);
+    return set.descs[lo];
 }
 
 __device__ inline bool finished(const DevState* st, int idx) {
@@ -80,18 +85,19 @@ __device__ inline uint64_t wave_max(uint64_t v) {
 }
 
 // Max |.| of every operand row (trans == 0): one wavefront per row, units are
-// groups of 4 rows (one workgroup of 256 threads).
-__global__ __launch_bounds__(256) void k_rowmax(const SplitDesc* descs, int count,
-                                                SplitDesc one, const DevState* st) {
+// groups of 4 rows (one workgroup of 256 threads).  An operand whose rows are
+// columns of A (trans == 1) has its maxima zeroed here, 4 a unit, for k_colmax.
+__global__ __launch_bounds__(256) void k_rowmax(SplitSet set, const DevState* st) {
     int local;
-    const SplitDesc& d = pick<true>(descs, count, one, blockIdx.x, &local);
+    const SplitDesc& d = pick<kStageMax>(set, blockIdx.x, &local);
     if (skipped(d, st)) return;
     const int lane = threadIdx.x & 63;
     const int r = local * 4 + (threadIdx.x >> 6);
     const int rp = int(round_up(d.R, kPad));
     if (r >= rp) return;
     uint64_t m = 0;
-    if (r < d.R && d.A2 == nullptr) {
+    if (d.trans) {
+    } else if (r < d.R && d.A2 == nullptr) {
         const double* row = d.A + int64_t(r) * d.lda;
         for (int k = lane; k < d.K; k += 64) {
             const uint64_t b = abs_bits(row[k]);
@@ -109,23 +115,33 @@ __global__ __launch_bounds__(256) void k_rowmax(const SplitDesc* descs, int coun
 }
 
 // Max |.| of every operand row when the operand row is a column of A
-// (trans == 1).  Unit = (64 columns, 256 rows of A); partial maxima are
+// (trans == 1).  Unit = (64 columns, kColmaxRows rows of A); partial maxima are
 // combined with an integer atomicMax on the bit patterns (non-negative
-// doubles order like their bits), so the result is order independent.
-__global__ __launch_bounds__(256) void k_colmax(const SplitDesc* descs, int count,
-                                                SplitDesc one, const DevState* st) {
+// doubles order like their bits), so the result is order independent.  Latency
+// bound while the units are few, so a thread's loads are issued eight at a
+// time (one at a time over 256 rows: 30 us for a 4096 x 96 operand).
+__global__ __launch_bounds__(256) void k_colmax(SplitSet set, const DevState* st) {
     int local;
-    const SplitDesc& d = pick<true>(descs, count, one, blockIdx.x, &local);
+    const SplitDesc& d = pick<kStageColmax>(set, blockIdx.x, &local);
     if (finished(st, d.state_index)) return;
     const int cb = (d.R + 63) / 64;
     const int col = (local % cb) * 64 + (threadIdx.x & 63);
-    const int k0 = (local / cb) * 256 + (threadIdx.x >> 6);
+    const int k0 = (local / cb) * kColmaxRows + (threadIdx.x >> 6);
     __shared__ uint64_t red[4][64];
     uint64_t m = 0;
     if (col < d.R) {
-        for (int k = k0, e = min(d.K, (local / cb) * 256 + 256); k < e; k += 4) {
-            const uint64_t b = abs_bits(d.A[int64_t(k) * d.lda + col]);
-            m = b > m ? b : m;
+        const int e = min(d.K, (local / cb + 1) * kColmaxRows);
+#pragma unroll
+        for (int h = 0; h < kColmaxRows / 4; h += 8) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)   // past the end: the last row again
+                v[u] = d.A[int64_t(min(k0 + 4 * (h + u), e - 1)) * d.lda + col];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint64_t b = abs_bits(v[u]);
+                m = b > m ? b : m;
+            }
         }
     }
     red[threadIdx.x >> 6][threadIdx.x & 63] = m;
@@ -138,9 +154,52 @@ __global__ __launch_bounds__(256) void k_colmax(const SplitDesc* descs, int coun
     }
 }
 
-__global__ void k_fill_u64(uint64_t* p, int64_t n, uint64_t v) {
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+// Maxima of the 32 operand rows of block rb from the whole operand, into
+// ``out`` (LDS, 32 words; ``scratch`` 256 words).  256 threads; ends with a
+// barrier.
+__device__ inline void block_maxima(const SplitDesc& d, int rb, uint64_t* scratch, uint64_t* out) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (!d.trans) {
+        // a wavefront takes 8 rows, one load of each in flight
+        const int r0 = rb * kFragRows + (tid >> 6) * 8;
+        uint64_t m[8] = {};
+#pragma unroll 2
+        for (int k = lane; k < d.K; k += 64) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = d.A[int64_t(min(r0 + u, d.R - 1)) * d.lda + k];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m[u] = abs_bits(v[u]) > m[u] ? abs_bits(v[u]) : m[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint64_t w = wave_max(m[u]);
+            if (lane == 0) out[(tid >> 6) * 8 + u] = r0 + u < d.R ? w : 0;
+        }
+        __syncthreads();
+        return;
+    }
+    // 8 threads per row, eight loads of each in flight
+    const int r = rb * kFragRows + (tid & 31);
+    uint64_t m = 0;
+    if (r < d.R) {
+#pragma unroll 2
+        for (int k = tid >> 5; k < d.K; k += 64) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = d.A[int64_t(min(k + 8 * u, d.K - 1)) * d.lda + r];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m = abs_bits(v[u]) > m ? abs_bits(v[u]) : m;
+        }
+    }
+    scratch[tid] = m;
+    __syncthreads();
+    if (tid < 32) {
+#pragma unroll
+        for (int u = 1; u < 8; ++u) m = scratch[32 * u + tid] > m ? scratch[32 * u + tid] : m;
+        out[tid] = m;
+    }
+    __syncthreads();
 }
 
 template <int S>
@@ -302,8 +361,7 @@ __device__ __forceinline__ bool load_operand(const SplitDesc& d, const DevState*
 // coef.count > 0: the first coef.count blocks of the grid run the coefficient
 // step of the matrices instead (CoefArgs), beside the split's units.
 template <int S, bool FP16, bool HALVES = false, bool COMB = false>
-__global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int count,
-                                                SplitDesc one, const DevState* st, CoefArgs coef) {
+__global__ __launch_bounds__(256) void k_digits(SplitSet set, const DevState* st, CoefArgs coef) {
     constexpr int CK = FP16 ? 16 : 32;
     constexpr int NE = CK / 2;
     constexpr int W = 4 * CK;
@@ -317,7 +375,7 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
     int local;
     // a copy: held in scalar registers, so that the LDS stores below cannot
     // alias it and force its fields to be reloaded
-    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x) - coef.count, &local);
+    const SplitDesc d = pick<kStageDigits>(set, int(blockIdx.x) - coef.count, &local);
     if (skipped(d, st)) return;
     const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
     const int kq_count = (d.KC + 3) / 4;
@@ -326,7 +384,16 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
     const int kc = kq * 4 + wave;
     const int r = rb * kFragRows + (lane & 31);
     const int k0 = kc * CK + (lane >> 5) * NE;
-    const int e = exponent_of(d.maxbits[r]);
+    uint64_t bits;
+    if (d.maxbits != nullptr) {
+        bits = d.maxbits[r];
+    } else {
+        // no maxima given: taken here, by every workgroup of the row block
+        __shared__ uint64_t maxima[kFragRows];
+        block_maxima(d, rb, reinterpret_cast<uint64_t*>(panel), maxima);
+        bits = maxima[lane & 31];
+    }
+    const int e = exponent_of(bits);
     if (kq == 0 && wave == 0 && lane < 32) {
         d.expo[r] = e;
         if (d.clear != nullptr) d.clear[r] = 0;
@@ -441,15 +508,14 @@ __global__ __launch_bounds__(256) void k_digits(const SplitDesc* descs, int coun
 // N = 13 (292 us); half of the moduli per wavefront, twice the wavefronts, took
 // 400 us.
 template <int N, bool FP16, bool COMB>
-__global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int count, SplitDesc one,
-                                                  const DevState* st) {
+__global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* st) {
     constexpr int CK = FP16 ? 16 : 32;
     constexpr int NE = CK / 2;
     constexpr int W = 4 * CK;
     __shared__ double panel[kFragRows * (W + 2)];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int local;
-    const SplitDesc d = pick<false>(descs, count, one, int(blockIdx.x), &local);
+    const SplitDesc d = pick<kStageDigits>(set, int(blockIdx.x), &local);
     if (skipped(d, st)) return;
     const int rb_count = int(round_up(d.R, kPad)) / kFragRows;
     const int kq_count = (d.KC + 3) / 4;
@@ -475,95 +541,86 @@ __global__ __launch_bounds__(256) void k_residues(const SplitDesc* descs, int co
 // Host launchers.
 
 template <int S>
-static void launch_digits_s(bool fp16, bool comb, const SplitDesc* descs, int count,
-                            const SplitDesc& one, const DevState* st, int units,
+static void launch_digits_s(bool fp16, bool comb, const SplitSet& set, const DevState* st, int units,
                             const CoefArgs& coef, hipStream_t stream) {
     const unsigned grid = unsigned(units + coef.count);
     if (fp16 && comb)
-        k_digits<S, true, false, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<S, true, false, true><<<grid, 256, 0, stream>>>(set, st, coef);
     else if (fp16)
-        k_digits<S, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<S, true><<<grid, 256, 0, stream>>>(set, st, coef);
     else if (comb)
-        k_digits<S, false, false, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<S, false, false, true><<<grid, 256, 0, stream>>>(set, st, coef);
     else
-        k_digits<S, false><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<S, false><<<grid, 256, 0, stream>>>(set, st, coef);
 }
 
 // The Markidis kind's two FP16 parts (S = 2).
-static void launch_halves(bool comb, const SplitDesc* descs, int count, const SplitDesc& one,
-                          const DevState* st, int units, const CoefArgs& coef,
-                          hipStream_t stream) {
+static void launch_halves(bool comb, const SplitSet& set, const DevState* st, int units,
+                          const CoefArgs& coef, hipStream_t stream) {
     const unsigned grid = unsigned(units + coef.count);
     if (comb)
-        k_digits<2, true, true, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<2, true, true, true><<<grid, 256, 0, stream>>>(set, st, coef);
     else
-        k_digits<2, true, true><<<grid, 256, 0, stream>>>(descs, count, one, st, coef);
+        k_digits<2, true, true><<<grid, 256, 0, stream>>>(set, st, coef);
 }
 
 // Residue planes of N moduli.
 template <int N>
-static void launch_residues_n(bool fp16, bool comb, const SplitDesc* descs, int count,
-                              const SplitDesc& one, const DevState* st, int units, hipStream_t stream) {
+static void launch_residues_n(bool fp16, bool comb, const SplitSet& set, const DevState* st, int units,
+                              hipStream_t stream) {
     if (fp16 && comb)
-        k_residues<N, true, true><<<units, 256, 0, stream>>>(descs, count, one, st);
+        k_residues<N, true, true><<<units, 256, 0, stream>>>(set, st);
     else if (fp16)
-        k_residues<N, true, false><<<units, 256, 0, stream>>>(descs, count, one, st);
+        k_residues<N, true, false><<<units, 256, 0, stream>>>(set, st);
     else if (comb)
-        k_residues<N, false, true><<<units, 256, 0, stream>>>(descs, count, one, st);
+        k_residues<N, false, true><<<units, 256, 0, stream>>>(set, st);
     else
-        k_residues<N, false, false><<<units, 256, 0, stream>>>(descs, count, one, st);
+        k_residues<N, false, false><<<units, 256, 0, stream>>>(set, st);
 }
 
-using DigitsFn = void (*)(bool, bool, const SplitDesc*, int, const SplitDesc&, const DevState*,
-                          int, const CoefArgs&, hipStream_t);
+using DigitsFn = void (*)(bool, bool, const SplitSet&, const DevState*, int, const CoefArgs&, hipStream_t);
 static const DigitsFn kDigits[kMaxSlices + 1] = {
     nullptr,           launch_digits_s<1>,  launch_digits_s<2>,  launch_digits_s<3>,
     launch_digits_s<4>, launch_digits_s<5>,  launch_digits_s<6>,  launch_digits_s<7>,
     launch_digits_s<8>, launch_digits_s<9>,  launch_digits_s<10>, launch_digits_s<11>,
     launch_digits_s<12>};
-using ResiduesFn = void (*)(bool, bool, const SplitDesc*, int, const SplitDesc&, const DevState*, int,
-                            hipStream_t);
+using ResiduesFn = void (*)(bool, bool, const SplitSet&, const DevState*, int, hipStream_t);
 static const ResiduesFn kResidues[kMaxMods - kModMin + 1] = {
     launch_residues_n<11>, launch_residues_n<12>, launch_residues_n<13>,
     launch_residues_n<14>, launch_residues_n<15>, launch_residues_n<16>};
 
 // The planes of ``units`` units: residues of nmod moduli, or (nmod 0) the
 // kind's digit or half planes.
-static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitDesc* descs, int count,
-                         const SplitDesc& one, const DevState* st, int units, const CoefArgs& coef,
-                         hipStream_t stream) {
+static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitSet& set, const DevState* st,
+                         int units, const CoefArgs& coef, hipStream_t stream) {
     if (nmod != 0 && (nmod < kModMin || nmod > kMaxMods || coef.count != 0)) {
         set_error("no residue split for %d moduli", nmod);
         return DMP_EINVAL;
     }
     if (nmod != 0)
-        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, stream);
+        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, set, st, units, stream);
     else if (kind == DMP_MARKIDIS_FP16)
-        launch_halves(comb, descs, count, one, st, units, coef, stream);
+        launch_halves(comb, set, st, units, coef, stream);
     else
-        kDigits[S](kind == DMP_OZ_FP16, comb, descs, count, one, st, units, coef, stream);
+        kDigits[S](kind == DMP_OZ_FP16, comb, set, st, units, coef, stream);
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }
 
-// Split one operand.  ``d`` describes it; ``st`` (nullable) skips the work
-// once the state's done flag is set.
-int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
-                 hipStream_t stream, int nmod) {
-    const int rp = int(round_up(d.R, kPad));
-    if (rp == 0) return DMP_OK;
-    if (!d.trans) {
-        k_rowmax<<<split_units_rowmax(d.R), 256, 0, stream>>>(nullptr, 0, d, st);
-    } else {
-        k_fill_u64<<<(rp + 255) / 256, 256, 0, stream>>>(d.maxbits, rp, 0ull);
-        if (d.K > 0) k_colmax<<<split_units_colmax(d.R, d.K), 256, 0, stream>>>(nullptr, 0, d, st);
-    }
-    return launch_planes(S, kind, nmod, d.A2 != nullptr, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
-                         CoefArgs{}, stream);
+static SplitSet single(const SplitDesc& d) {
+    SplitSet s{};
+    s.two[0] = d;
+    s.two[0].ub_rowmax = s.two[0].ub_colmax = s.two[0].ub_digits = 0;
+    s.count = 1;
+    return s;
 }
 
-int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t stream) {
-    k_rowmax<<<split_units_rowmax(d.R), 256, 0, stream>>>(nullptr, 0, d, st);
+// Maxima of the operands of a set: rowmax_units of k_rowmax, colmax_units of
+// k_colmax.
+static int launch_maxima(const SplitSet& set, int rowmax_units, int colmax_units, const DevState* st,
+                         hipStream_t stream) {
+    if (rowmax_units > 0) k_rowmax<<<rowmax_units, 256, 0, stream>>>(set, st);
+    if (colmax_units > 0) k_colmax<<<colmax_units, 256, 0, stream>>>(set, st);
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }
@@ -573,24 +630,66 @@ int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t stream) {
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
                         hipStream_t stream, int nmod) {
     if (round_up(d.R, kPad) == 0) return DMP_OK;
-    return launch_planes(S, kind, nmod, d.A2 != nullptr, nullptr, 0, d, st, split_units_digits(d.R, d.KC),
+    return launch_planes(S, kind, nmod, d.A2 != nullptr, single(d), st, split_units_digits(d.R, d.KC),
                          CoefArgs{}, stream);
+}
+
+// Split one operand.  ``d`` describes it; ``st`` (nullable) skips the work
+// once the state's done flag is set.
+int launch_split(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
+                 hipStream_t stream, int nmod) {
+    if (round_up(d.R, kPad) == 0) return DMP_OK;
+    DMP_CHECK(launch_maxima(single(d), split_units_rowmax(d.R), d.trans ? split_units_colmax(d.R, d.K) : 0,
+                            st, stream));
+    return launch_split_digits(d, S, kind, st, stream, nmod);
+}
+
+int launch_rowmax(const SplitDesc& d, const DevState* st, hipStream_t stream) {
+    return launch_maxima(single(d), split_units_rowmax(d.R), 0, st, stream);
+}
+
+int launch_split_pair(const SplitDesc& a, const SplitDesc& b, int S, dmp_kind kind, hipStream_t stream) {
+    SplitSet set{};
+    set.count = 2;
+    set.two[0] = a;
+    set.two[1] = b;
+    SplitUnits u;
+    count_split_units(set.two, 2, u);
+    if (split_takes_maxima(set.two, 2)) {
+        set.two[0].maxbits = set.two[1].maxbits = nullptr;
+    } else {
+        DMP_CHECK(launch_maxima(set, u.rowmax, u.colmax, nullptr, stream));
+    }
+    return launch_planes(S, kind, 0, false, set, nullptr, u.digits, CoefArgs{}, stream);
+}
+
+int launch_split_set(const SplitDesc* descs_dev, int count, const SplitUnits& u, bool maxima, int S,
+                     dmp_kind kind, hipStream_t stream) {
+    SplitSet set{};
+    set.descs = descs_dev;
+    set.count = count;
+    if (maxima) DMP_CHECK(launch_maxima(set, u.rowmax, u.colmax, nullptr, stream));
+    return launch_planes(S, kind, 0, false, set, nullptr, u.digits, CoefArgs{}, stream);
 }
 
 // Grouped split of count operands (row splits only); descs in device memory
 // with ub_rowmax / ub_digits the first unit of every matrix in each kernel.
 int launch_split_grouped_rowmax(const SplitDesc* descs_dev, int count, int units,
                                 const DevState* st, hipStream_t stream) {
-    if (units > 0) k_rowmax<<<units, 256, 0, stream>>>(descs_dev, count, SplitDesc{}, st);
-    DMP_CHECK_HIP(hipGetLastError());
-    return DMP_OK;
+    SplitSet set{};
+    set.descs = descs_dev;
+    set.count = count;
+    return launch_maxima(set, units, 0, st, stream);
 }
 
 int launch_split_grouped_digits(const SplitDesc* descs_dev, int count, int units, int S,
                                 dmp_kind kind, const DevState* st, hipStream_t stream,
                                 const CoefArgs& coef, bool combined, int nmod) {
     if (units + coef.count <= 0) return DMP_OK;
-    return launch_planes(S, kind, nmod, combined, descs_dev, count, SplitDesc{}, st, units, coef, stream);
+    SplitSet set{};
+    set.descs = descs_dev;
+    set.count = count;
+    return launch_planes(S, kind, nmod, combined, set, st, units, coef, stream);
 }
 
 }  // namespace dmp
