@@ -31,7 +31,7 @@
 namespace dmp {
 namespace {
 
-constexpr int kDotBlocks = 256;
+constexpr int kDotBlocks = 1024;
 
 // Single-matrix Ozaki context: device buffers for one split pair and the
 // purification state of one matrix.
@@ -71,6 +71,11 @@ struct OzCtx {
     int nmt = 0, mshape = 0;
     const Tile* tiles_out = nullptr;    // and the tiles of their combination
     int nt_out = 0;
+    // backward products: moduli, the tile lists of the symmetric and of the
+    // full products and of the latter's combination
+    int bmod = 0, nt_bsym = 0, nt_bfull = 0, nt_outfull = 0;
+    int shape_bsym = 0, shape_bfull = 0;
+    const Tile *bsym = nullptr, *bfull = nullptr, *tiles_outfull = nullptr;
 };
 
 void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
@@ -125,6 +130,19 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
         DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
         DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, true, &x.tiles_out, 32));
         x.nt_out = upper_tile_count(x.n, 32);
+        // The backward operands Y and M = Y P have no bound on their row norms
+        // but sqrt(n) times the row maximum, so their products take the
+        // capacity (15 moduli for S = 7): the rounding to X then stays below
+        // the truncation of the digit slices for any row.
+        x.bmod = mod_capacity(x.S);
+        auto list = [&](bool upper, const Tile** out, int* count, int* shape) -> int {
+            *shape = residue_shape(int64_t(residue_tile_count(x.n, kShapeWide, upper)) * x.bmod);
+            return cached_residue_tiles(x.n, x.bmod, *shape, upper, out, count);
+        };
+        DMP_CHECK(list(true, &x.bsym, &x.nt_bsym, &x.shape_bsym));
+        DMP_CHECK(list(false, &x.bfull, &x.nt_bfull, &x.shape_bfull));
+        DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, false, &x.tiles_outfull, 32));
+        x.nt_outfull = tile_rows(x.n, 32) * tn;
     }
     x.tail = TailSplit{x.nt_up, 1};
     if (x.fix != nullptr && tail_split_enabled()) {
@@ -301,6 +319,14 @@ int gemm_store(const OzCtx& x, const uint8_t* pa, const int* ea, const uint8_t* 
     p.one.rowmax = rowmax;
     p.one.colmax = colmax;
     p.mode = sym ? EPI_STORE_SYM : EPI_STORE;
+    if (x.bmod > 0) {
+        p.one.a_rb_stride = p.one.b_rb_stride = int64_t(x.KC / 2) * kFragBytes;
+        p.one.res = x.res;
+        p.tiles = sym ? x.tiles_out : x.tiles_outfull;
+        p.mtiles = sym ? x.bsym : x.bfull;
+        return launch_residue_gemm(x.kind, x.bmod, sym ? x.shape_bsym : x.shape_bfull, p,
+                                   sym ? x.nt_bsym : x.nt_bfull, sym ? x.nt_out : x.nt_outfull, s);
+    }
     return launch_ozgemm(x.S, x.kind, p, sym ? x.nt_up : x.nt_full, s, x.rb);
 }
 
@@ -338,18 +364,34 @@ __global__ __launch_bounds__(256) void k_sym(const double* A, double* Y, int n, 
     }
 }
 
-// Block partials of sum Y o P, sum Y o X2, sum MP o P (fixed grid).
+// Block partials of sum Y o P, sum Y o X2, sum MP o P (fixed grid).  Bound by
+// memory (32 bytes per element): four elements' loads are in flight per thread
+// (one at a time on 256 blocks: 42 us at n = 2048).
 __global__ __launch_bounds__(256) void k_adj_dots(const double* Y, const double* P,
                                                   const double* X2, const double* MP, int n,
                                                   double* out) {
     __shared__ double sh[4];
-    const int64_t tot = int64_t(n) * n;
+    const int64_t tot = int64_t(n) * n, step = int64_t(kDotBlocks) * 256;
     double a = 0.0, b = 0.0, c = 0.0;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < tot; i += int64_t(kDotBlocks) * 256) {
-        const double y = Y[i], p = P[i];
-        a += y * p;
-        b += y * X2[i];
-        c += MP[i] * p;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < tot; i += 4 * step) {
+        double y[4], p[4], x[4], m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t k = i + u * step;
+            const bool in = k < tot;
+            const int64_t kk = in ? k : i;
+            y[u] = Y[kk];
+            p[u] = P[kk];
+            x[u] = X2[kk];
+            m[u] = MP[kk];
+            if (!in) y[u] = m[u] = 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a += y[u] * p[u];
+            b += y[u] * x[u];
+            c += m[u] * p[u];
+        }
     }
     a = bsum(a, sh);
     b = bsum(b, sh);
@@ -893,16 +935,17 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
             // digit kernels.  PM = P Y P is symmetric: upper tiles, mirrored.
             SplitDesc sy = split_of(x, Y, false, x.ma, x.ea, x.pa, -1);
             sy.clear = x.mc;
-            DMP_CHECK(launch_split(sy, x.S, x.kind, nullptr, s));
+            DMP_CHECK(launch_split(sy, x.S, x.kind, nullptr, s, x.bmod));
             SplitDesc sp = split_of(x, P, false, x.mb, x.eb, x.pb, -1);
             sp.clear = x.ma;
-            DMP_CHECK(launch_split(sp, x.S, x.kind, nullptr, s));
+            sp.lam = kLamIterate;
+            DMP_CHECK(launch_split(sp, x.S, x.kind, nullptr, s, x.bmod));
             DMP_CHECK(gemm_store(x, x.pa, x.ea, x.pb, x.eb, M, x.ma, x.mc, false, s));
             DMP_CHECK(launch_split_digits(split_of(x, M, false, x.ma, x.ea, x.pa, -1), x.S, x.kind,
-                                          nullptr, s));
+                                          nullptr, s, x.bmod));
             DMP_CHECK(gemm_store(x, x.pa, x.ea, x.pb, x.eb, MP, nullptr, nullptr, false, s));
             DMP_CHECK(launch_split_digits(split_of(x, M, true, x.mc, x.ea, x.pa, -1), x.S, x.kind,
-                                          nullptr, s));
+                                          nullptr, s, x.bmod));
             DMP_CHECK(gemm_store(x, x.pb, x.eb, x.pa, x.ea, PM, nullptr, nullptr, true, s));
             const double cc = t->c[j];
             const int br = t->branch[j];

@@ -150,12 +150,9 @@ void count_split_units(SplitDesc* d, int count, SplitUnits& u) {
 }
 
 bool split_takes_maxima(const SplitDesc* d, int count) {
-    double bytes = 0.0;
-    for (int i = 0; i < count; ++i) {
+    for (int i = 0; i < count; ++i)
         if (d[i].K > kSelfMaxK) return false;
-        bytes += double((d[i].K + 127) / 128) * d[i].R * d[i].K * 8.0;
-    }
-    return bytes <= kSelfMaxBytes;
+    return true;
 }
 
 // ---- split tail -------------------------------------------------------------------
@@ -176,7 +173,7 @@ TailSplit plan_tail_split(int ntiles, int slots, int min_kc, int max_pieces) {
 }
 
 TailSplit plan_gemm_split(int ntiles, int slots, int min_kc, int max_pieces) {
-    if (ntiles <= 0 || 2 * ntiles > slots) return plan_tail_split(ntiles, slots, min_kc, max_pieces);
+    if (ntiles <= 0 || 4 * ntiles > slots) return plan_tail_split(ntiles, slots, min_kc, max_pieces);
     const int parts = std::min({split_parts_max(min_kc), slots / ntiles, max_pieces / ntiles});
     if (parts < 2 || min_kc - min_kc / parts < kMinSavedChunks) return TailSplit{ntiles, 1};
     return TailSplit{0, parts};

@@ -78,10 +78,11 @@ struct SplitUnits {
 };
 void count_split_units(SplitDesc* d, int count, SplitUnits& u);
 // Whether the digit split of a set takes the row maxima itself: every
-// workgroup then reads its 32 rows over the whole reduction, K / 128 times in
-// all, instead of one or two launches before it.
+// workgroup then reads its 32 rows over the whole reduction, instead of one or
+// two launches before it.  That read is a chain of K / 64 loads: at K = 64 ..
+// 512 the split takes 9 .. 11 us beside 5 us and two launches of 4 us, at K =
+// 1301 60 us beside 12 + 11 us.
 constexpr int kSelfMaxK = 512;
-constexpr double kSelfMaxBytes = 1e9;
 bool split_takes_maxima(const SplitDesc* d, int count);
 
 // ---- split tail -----------------------------------------------------------
@@ -97,12 +98,15 @@ struct TailSplit {
 // the ``min_kc`` chunks each, at most ``max_pieces`` parts in all).
 TailSplit plan_tail_split(int ntiles, int slots, int min_kc, int max_pieces);
 // The same for the tiles of one general product, which may also be too few to
-// fill half of the slots: then every tile is split, if that shortens the
-// reduction by at least kMinSavedChunks chunks.
+// fill a quarter of the slots (half of the CUs): then every tile is split, if
+// that shortens the reduction by at least kMinSavedChunks chunks (the fixup
+// launch costs about 20 us: 4096 x 96 x 4096 at S = 8 298 -> 188 us, but 208
+// tiles of 41 chunks in two parts 54 -> 77 us).
 constexpr int kMinSavedChunks = 24;
 TailSplit plan_gemm_split(int ntiles, int slots, int min_kc, int max_pieces);
 // Tile height (32-row blocks) of a general m x n product, and of a batch of
-// them: 64 rows, two workgroups per CU, below kLowTileCount tiles of 128 rows.
+// them: 64 rows, two workgroups per CU, below kLowTileCount tiles of 128 rows
+// (one round of the chip; 1000 x 777 x 1301, 104 tiles: 60 -> 38 us).
 constexpr int kLowTileCount = 256;
 int gemm_tile_blocks(int m, int n, int S, dmp_kind kind);
 int batch_tile_blocks(int count, const int* m, const int* n, int S, dmp_kind kind);

@@ -530,7 +530,10 @@ __global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* 
     double v[NE];
     const bool needed = load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v);
     const int e = d.maxbits != nullptr ? residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit) : d.expo[r];
-    if (rc == 0 && lane < 16 && d.maxbits != nullptr) d.expo[r] = e;
+    if (rc == 0 && lane < 16) {
+        if (d.maxbits != nullptr) d.expo[r] = e;
+        if (d.clear != nullptr) d.clear[r] = 0;
+    }
     if (!needed) return;
 
     store_residues<N, FP16>(v, e, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
