@@ -273,6 +273,10 @@ struct GemmParams {
     // purification modes: 1 stores only the upper triangle of the output
     // (no mirror; the next splits read it as symmetric, SplitDesc::sym)
     int upper_only;
+    // residue products: 1 for a launch of one matrix (number 0; its descriptor
+    // and state are then read beside the tile, not after it).  The state of
+    // matrix ``mat`` is states[mat].
+    int lone;
     const Tile* mtiles;     // residue products: the residue GEMM's tile list
     // residue products: the update has no product while the state's gamma is 0
     // (TRS4; the state's gamma must be final before the launch)

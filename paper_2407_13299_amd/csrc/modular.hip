@@ -79,9 +79,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
     const Tile tile = p.mtiles[t];
-    const int mod = int(tile.mat >> 24);
-    const MatDesc d = p.descs ? p.descs[tile.mat & 0xffffffu] : p.one;
-    const DevState* st = p.states ? p.states + d.state_index : nullptr;
+    const int mod = int(tile.mat >> 24), mat = p.lone ? 0 : int(tile.mat & 0xffffffu);
+    const MatDesc d = p.descs ? p.descs[mat] : p.one;
+    const DevState* st = p.states ? p.states + mat : nullptr;
     if (st != nullptr && (st->done || (p.skip_zero && st->gamma == 0.0))) return;
     const bool clocked = p.clk != nullptr;
     const uint64_t clk_c = clocked ? __builtin_amdgcn_s_memtime() : 0;
@@ -299,9 +299,26 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
 template <class T>
 using Global = __attribute__((address_space(1))) T;
 
+// Sum over a wavefront: within rows of 16 lanes by data parallel primitives
+// (no LDS), then the four rows.
 __device__ inline double sum64(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    auto ror = [](double x, auto n) __attribute__((always_inline)) {
+        const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
+        const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b)), 0x120 + decltype(n)::value, 0xf, 0xf, false));
+        const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(b >> 32), 0x120 + decltype(n)::value, 0xf, 0xf, false));
+        return __longlong_as_double(static_cast<long long>((uint64_t(hi) << 32) | lo));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
+    auto row = [&](int r) __attribute__((always_inline)) {
+        const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), 16 * r));
+        const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(b >> 32), 16 * r));
+        return __longlong_as_double(static_cast<long long>((uint64_t(hi) << 32) | lo));
+    };
+    return (row(0) + row(1)) + (row(2) + row(3));
 }
 
 // Maxima over the 16 lanes of a row (data parallel primitives, no LDS).
@@ -315,41 +332,50 @@ __device__ inline uint32_t max16(uint32_t v) {
     return max(v, ror(v, std::integral_constant<int, 1>{}));
 }
 
+constexpr bool pur_mode(int mode) {
+    return mode == EPI_SQUARE || mode == EPI_UPDATE || mode == EPI_SQUARE_TRS4;
+}
+
 // Rebuilds C' = X Y from its residues (modular.hpp) and runs the FP64 end of
 // the product, C = C' 2^(t_i + t_j), by mode as listed at the head of
-// ozgemm.hip.  One workgroup per 32 x 64 tile of p.tiles, half of one of its
-// two 32 x 32 quadrants per wavefront: lane l holds column l % 32 and rows (l /
-// 32) 4 + 8 g + e, e < 4, of two row groups g, the order in which the residues
-// are stored, so every load is a whole cache line.  (64 x 64 tiles of 8
-// wavefronts leave 528 workgroups for 512 places at n = 2048.)
+// ozgemm.hip.  One workgroup per 32 x 64 tile of p.tiles, a quarter (WAVES = 8)
+// or half (4) of one of its two 32 x 32 quadrants per wavefront: lane l holds
+// column l % 32 and rows (l / 32) 4 + 8 g + e, e < 4, of one or two row groups
+// g, the order in which the residues are stored.
 //
 // The purification modes then form the residues of the output from the tile
-// in LDS: the fragments of its two 16-row blocks (wavefronts 0 and 1) and,
-// transposed, half of the fragments of its four 16-column blocks (wavefronts
-// 2 and 3, two blocks each).  So an
-// iterate or a square is split without being read again, and without the
-// launch that did (k_residues: 23 us at n = 2048, 290 us at n = 8192).  The
-// exponents come from the row maxima of the iterate before the product
-// (MatDesc::growth), as the output's own are known only when every tile is done.
+// in LDS: half of the wavefronts the fragments of its two 16-row blocks, half,
+// transposed, those of its four 16-column blocks.  So an iterate or a square
+// is split without being read again, and without the launch that did
+// (k_residues: 23 us at n = 2048, 290 us at n = 8192).  The exponents come from
+// the row maxima of the iterate before the product (MatDesc::growth), as the
+// output's own are known only when every tile is done.
 //
-// Bound: memory (N to 2 N bytes of residues and 12 to 28 bytes of FP64 per
-// element).  Every load is issued before the first result is formed; modes,
-// and quadrants that need no bounds or triangle checks, are code of their own.
-// Row maxima, which only choose powers of two, are kept to the upper word,
-// rounded up.
-template <int N, int MODE, bool FP16>
-__global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
-    constexpr bool PUR = MODE == EPI_SQUARE || MODE == EPI_UPDATE || MODE == EPI_SQUARE_TRS4;
+// Bound: memory for many tiles (N to 2 N bytes of residues and 12 to 28 bytes
+// of FP64 per element; n = 2048: 30 and 36 us); for few tiles the chain of
+// latencies, with one wavefront per SIMD (n = 256: 7.9 and 9.0 us, 4.5 of them
+// the two rounds of loads and the launch).  Hence 8 wavefronts rather than 4
+// (9.6 and 11 us) where the tiles do not fill the chip; loops and constants
+// that need few instruction and scalar-cache lines (store_residues; n = 256
+// as a whole 680 to 541 us); wavefront sums without LDS; every load issued before
+// the first result is formed.  The partial sums are formed per row group and
+// added in one order, so that both widths give the same bits.  Row maxima,
+// which only choose powers of two, are kept to the upper word, rounded up.
+template <int N, int MODE, bool FP16, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 4) void k_combine(GemmParams p) {
+    constexpr bool PUR = pur_mode(MODE);
     constexpr bool UPPER = MODE != EPI_STORE;
-    constexpr int G = 2, WAVES = 4, LDT = 66;
-    __shared__ double red[WAVES][kPartials];
+    static_assert(WAVES == 8 || (WAVES == 4 && !FP16), "a lane's part of the planes: 8 or 16 bytes");
+    constexpr int G = 8 / WAVES, LDT = 65;
+    __shared__ double red[8][kPartials];
     __shared__ double out_tile[PUR ? 32 * LDT : 1];
     const int b = blockIdx.x, nb = gridDim.x;
     const int xcd = b & 7, qq = nb >> 3, rem = nb & 7, loc = b >> 3;
     const int t = p.spread ? b : (xcd < rem) ? xcd * (qq + 1) + loc : rem * (qq + 1) + (xcd - rem) * qq + loc;
     const Tile tile = p.tiles[t];
-    const MatDesc d = p.descs ? p.descs[tile.mat] : p.one;
-    const DevState* st = p.states ? p.states + d.state_index : nullptr;
+    const int mat = p.lone ? 0 : int(tile.mat);
+    const MatDesc d = p.descs ? p.descs[mat] : p.one;
+    const DevState* st = p.states ? p.states + mat : nullptr;
     if (st != nullptr && st->done) return;
     double alpha = 0.0, beta = 0.0, gamma = 1.0;
     if constexpr (MODE == EPI_UPDATE) {
@@ -366,7 +392,26 @@ __global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
     const int M = __builtin_amdgcn_readfirstlane(d.M), NC = __builtin_amdgcn_readfirstlane(d.N);
     const int ldc = __builtin_amdgcn_readfirstlane(d.ldc);
     const int lrow = (lane >> 5) * 4, lcol = lane & 31;
-    double s0 = 0.0, s1 = 0.0;
+    double s0[G] = {}, s1[G] = {};
+    // the planes of the output (below): what this wavefront writes, and the
+    // exponent of the lane's row
+    constexpr int K64 = FP16 ? 2 : 1;             // fragments per 64 reduction elements
+    const int half = int(tile.I) & 1;
+    const bool diag = int(tile.I) >> 1 == int(tile.J), rows = wave < WAVES / 2;
+    constexpr int NE = WAVES == 8 ? 8 : 16;       // elements per lane
+    const int lr = WAVES == 8 ? (rows ? wave >> 1 : wave - 4) * 16 + (lane & 15)
+                              : (rows ? wave * 16 : (wave - 2) * 32 + (lane >> 5) * 16) + (lane & 15);
+    const int k0 = WAVES == 8 ? (rows ? (wave & 1) * 32 : 0) + (lane >> 4) * 8
+                              : (rows ? lane >> 4 : (lane >> 4) & 1) * 16;
+    const int row = rows ? 32 * int(tile.I) + lr : 64 * int(tile.J) + lr;
+    const uint64_t rmax = PUR ? d.maxin[row] : 0;
+    ModSplit split{};
+    if constexpr (PUR) split = lane_split();
+    int tx = 0;
+    auto exponent = [&]() __attribute__((always_inline)) {
+        if constexpr (PUR)
+            tx = residue_exponent(rmax, d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
+    };
 
     auto quadrant = [&](auto full) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full)::value;
@@ -417,6 +462,7 @@ __global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
             fetch(d.X2, beta != 0.0, xv);
             fetch(d.H, true, hv);
         }
+        exponent();   // between the loads and their first use
         uint32_t hi[4 * G], cmax = 0;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -450,16 +496,16 @@ __global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
                     const double pij = pv[v];
                     if (inside(v)) {
                         if constexpr (MODE == EPI_SQUARE) {
-                            if (diag) s0 += pij - c;
-                            s1 += mult * c * ((diag ? 1.0 : 0.0) - pij);
+                            if (diag) s0[g] += pij - c;
+                            s1[g] += mult * c * ((diag ? 1.0 : 0.0) - pij);
                         } else if constexpr (MODE == EPI_SQUARE_TRS4) {
                             const double r = pij - c;
-                            s0 += mult * c * (4.0 * pij - 3.0 * c);
-                            s1 += mult * r * r;
+                            s0[g] += mult * c * (4.0 * pij - 3.0 * c);
+                            s1[g] += mult * r * r;
                         } else {
                             o = alpha * pij + beta * xv[v] + gamma * c;
-                            s0 += mult * o * hv[v];
-                            if (diag) s1 += o;
+                            s0[g] += mult * o * hv[v];
+                            if (diag) s1[g] += o;
                         }
                     }
                 }
@@ -520,19 +566,23 @@ __global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
             quadrant(std::true_type{});
         else
             quadrant(std::false_type{});
+    } else {
+        exponent();
     }
     if constexpr (PUR) {
-        s0 = sum64(s0);
-        s1 = sum64(s1);
-        if (lane == 0) {
-            red[wave][0] = s0;
-            red[wave][1] = s1;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const double t0 = sum64(s0[g]), t1 = sum64(s1[g]);
+            if (lane == 0) {
+                red[wave * G + g][0] = t0;
+                red[wave * G + g][1] = t1;
+            }
         }
         __syncthreads();
         if (threadIdx.x < kPartials) {
             double r = 0.0;
 #pragma unroll
-            for (int i = 0; i < WAVES; ++i) r += red[i][threadIdx.x];
+            for (int i = 0; i < 8; ++i) r += red[i][threadIdx.x];
             p.partials[int64_t(t) * kPartials + threadIdx.x] = r;
         }
 
@@ -543,78 +593,69 @@ __global__ __launch_bounds__(256, 4) void k_combine(GemmParams p) {
         // rows.  On the diagonal the upper tile (I even) writes its rows
         // whole and the mirror of its right half, the lower one (I odd, whose
         // left half lies below the diagonal) the right half of its rows.
-        const int half = int(tile.I) & 1;
-        const bool diag = int(tile.I) >> 1 == int(tile.J);
-        const bool rows = wave < 2;
-        if (diag && !rows && (half == 1 || wave == 2)) return;
-        constexpr int K64 = FP16 ? 2 : 1;             // fragments per 64 reduction elements
-        constexpr int NE = FP16 ? 8 : 16;
-        const int rbs = int(round_up(M, kPad)) / 16, RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;
-        // the lane's row of the output planes, and what it has of the chunk
-        const int lr = rows ? wave * 16 + (lane & 15) : (wave - 2) * 32 + (lane >> 5) * 16 + (lane & 15);
-        const int row = rows ? 32 * int(tile.I) + lr : 64 * int(tile.J) + lr;
-        const int chunk = rows ? int(tile.J) : int(tile.I) >> 1;
-        const int tx =
-            residue_exponent(d.maxin[row], d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
-        if (diag && rows && lane < 16) {
+        if (diag && rows && (WAVES == 4 || (wave & 1)) && lane < 16) {
             d.expo_out[row] = tx;
             if (d.clear != nullptr) d.clear[row] = 0;
         }
+        if (diag && !rows && (half == 1 || wave < WAVES * 3 / 4)) return;
+        const bool wanted = !diag || !rows || half == 0 || k0 >= 32;
+        if (WAVES == 8 && !wanted) return;
+        const int rbs = int(round_up(M, kPad)) / 16, RC = __builtin_amdgcn_readfirstlane(d.KC) / 2;
         const int64_t plane = int64_t(rbs) * RC * kFragBytes;
-        uint8_t* const rowbase = d.planes_out + (int64_t(row / 16) * RC + chunk * K64) * kFragBytes;
-        // FP16: a fragment holds 32 reduction elements, so the columns' half of a
-        // chunk is one of its two fragments, formed in two passes of 16
-        constexpr int PASSES = K64;
+        // the lane's first element: reduction element ``pos`` of the chunk
+        const int pos = rows ? k0 : half * 32 + k0;
+        const int chunk = rows ? int(tile.J) : int(tile.I) >> 1;
+        uint8_t* const at = d.planes_out + (int64_t(row / 16) * RC + chunk * K64) * kFragBytes +
+                            (FP16 ? pos / 32 * kFragBytes + (pos % 32 / 8 * 16 + (lane & 15)) * 16
+                                  : (pos / 16 * 16 + (lane & 15)) * 16 + pos % 16);
+        double x[NE];
+        if (rows) {
+            // below the diagonal of a quadrant on it (the left one of an
+            // upper tile, the right one of a lower one): the mirror's element
+            const int c0 = half * 32;
+            const bool on = diag && (k0 & 32) == c0;
 #pragma unroll
-        for (int f = 0; f < PASSES; ++f) {
-            double x[NE];
-            if (rows) {
-                const int k0 = f * 32 + (lane >> 4) * NE;
-                const bool left = diag && k0 < 32;    // the diagonal quadrant of an upper tile
+            for (int i = 0; i < NE; ++i)
+                x[i] = out_tile[on && lr > k0 - c0 + i ? (k0 - c0 + i) * LDT + c0 + lr : lr * LDT + k0 + i];
+        } else {
 #pragma unroll
-                for (int i = 0; i < NE; ++i) {
-                    const bool low = left && lr > k0 + i;
-                    x[i] = out_tile[low ? (k0 + i) * LDT + lr : lr * LDT + k0 + i];
-                }
-                // lower tile on the diagonal: its diagonal quadrant is the right one
-                if (diag && half == 1) {
-#pragma unroll
-                    for (int i = 0; i < NE; ++i)
-                        if (k0 >= 32 && lr > k0 - 32 + i) x[i] = out_tile[(k0 - 32 + i) * LDT + 32 + lr];
-                }
-                store_residues<N, FP16>(x, tx, rowbase + f * kFragBytes + lane * 16, plane,
-                                        !(diag && half == 1) || k0 >= 32);
-            } else {
-                // elements k of the tile's rows: 16 per lane group (FP16: two
-                // groups of 8, one per pass)
-                const int k0 = FP16 ? f * 16 + ((lane >> 4) & 1) * 8 : ((lane >> 4) & 1) * 16;
-#pragma unroll
-                for (int i = 0; i < NE; ++i) x[i] = out_tile[(k0 + i) * LDT + lr];
-                const int pos = half * 32 + k0;       // reduction element within the chunk
-                uint8_t* const at16 = FP16 ? rowbase + (pos / 32) * kFragBytes + ((pos % 32) / 8 * 16 + (lane & 15)) * 16
-                                           : rowbase + (pos / 16 * 16 + (lane & 15)) * 16;
-                store_residues<N, FP16>(x, tx, at16, plane);
-            }
+            for (int i = 0; i < NE; ++i) x[i] = out_tile[(k0 + i) * LDT + lr];
+        }
+        store_residues<N, FP16>(x, tx, split, at, plane, wanted);
+    }
+}
+
+// Tiles from which the wavefronts of a tile are 4 instead of 8 (but for the
+// update, whose operands then do not fit the registers): square of n = 2048,
+// 1056 tiles, 28.8 against 30.4 us; n = 1400, 506 tiles, 17.6 against 16.5 us;
+// n = 256, 20 tiles, 9.6 against 7.9 us.
+constexpr int kFourWaveTiles = 1024;
+
+template <int N, int MODE>
+static void combine(bool fp16, const GemmParams& p, int nout, hipStream_t stream) {
+    if constexpr (pur_mode(MODE)) {
+        if (fp16) {
+            k_combine<N, MODE, true, 8><<<nout, 512, 0, stream>>>(p);
+            return;
         }
     }
+    if constexpr (MODE != EPI_UPDATE) {
+        if (nout >= kFourWaveTiles) {
+            k_combine<N, MODE, false, 4><<<nout, 256, 0, stream>>>(p);
+            return;
+        }
+    }
+    k_combine<N, MODE, false, 8><<<nout, 512, 0, stream>>>(p);
 }
 
 template <int N>
 static int launch_combine(bool fp16, const GemmParams& p, int nout, hipStream_t stream) {
     switch (p.mode) {
-        case EPI_STORE: k_combine<N, EPI_STORE, false><<<nout, 256, 0, stream>>>(p); break;
-        case EPI_STORE_SYM: k_combine<N, EPI_STORE_SYM, false><<<nout, 256, 0, stream>>>(p); break;
-        case EPI_SQUARE:
-            if (fp16) k_combine<N, EPI_SQUARE, true><<<nout, 256, 0, stream>>>(p);
-            else k_combine<N, EPI_SQUARE, false><<<nout, 256, 0, stream>>>(p);
-            break;
-        case EPI_UPDATE:
-            if (fp16) k_combine<N, EPI_UPDATE, true><<<nout, 256, 0, stream>>>(p);
-            else k_combine<N, EPI_UPDATE, false><<<nout, 256, 0, stream>>>(p);
-            break;
-        default:
-            if (fp16) k_combine<N, EPI_SQUARE_TRS4, true><<<nout, 256, 0, stream>>>(p);
-            else k_combine<N, EPI_SQUARE_TRS4, false><<<nout, 256, 0, stream>>>(p);
+        case EPI_STORE: combine<N, EPI_STORE>(fp16, p, nout, stream); break;
+        case EPI_STORE_SYM: combine<N, EPI_STORE_SYM>(fp16, p, nout, stream); break;
+        case EPI_SQUARE: combine<N, EPI_SQUARE>(fp16, p, nout, stream); break;
+        case EPI_UPDATE: combine<N, EPI_UPDATE>(fp16, p, nout, stream); break;
+        default: combine<N, EPI_SQUARE_TRS4>(fp16, p, nout, stream);
     }
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;

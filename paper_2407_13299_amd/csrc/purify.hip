@@ -615,6 +615,7 @@ int launch_oz_iteration(GroupPlan& g, int par, bool follows, hipStream_t s,
     // as symmetric); TRS4's combined operand needs full rows
     p.upper_only = trs4 ? 0 : 1;
     p.spread = g.count > 1 ? 1 : 0;
+    p.lone = g.count == 1 ? 1 : 0;
     auto split_t = [&]() -> int {
         DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
         return launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind, g.st, s,

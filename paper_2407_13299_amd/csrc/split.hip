@@ -527,6 +527,7 @@ __global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* 
     const int k0 = rc * 2 * CK + (lane >> 4) * NE;
     // the operand's loads are issued before the exponents are worked out
     const uint64_t bits = d.maxbits != nullptr ? d.maxbits[r] : 0;
+    const ModSplit split = lane_split();
     double v[NE];
     const bool needed = load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v);
     const int e = d.maxbits != nullptr ? residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit) : d.expo[r];
@@ -536,7 +537,7 @@ __global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* 
     }
     if (!needed) return;
 
-    store_residues<N, FP16>(v, e, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
+    store_residues<N, FP16>(v, e, split, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
                             int64_t(rb_count) * 2 * RC * kFragBytes);
 }
 
