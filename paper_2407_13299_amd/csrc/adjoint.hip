@@ -26,12 +26,18 @@
 #include <mutex>
 #include <vector>
 
+#include "coef.hpp"
 #include "host.hpp"
 
 namespace dmp {
 namespace {
 
 constexpr int kDotBlocks = 1024;
+// Smallest n whose backward products run through residues: below, an operand's
+// split and the combination are launches more than the digit slices need.  A
+// whole gradient with digit slices and with residues: n = 240 2.28 and 2.43
+// ms, n = 840 5.14 and 5.32, n = 1176 7.65 and 7.88, n = 1568 12.6 and 12.0.
+constexpr int kResidueBackward = 1400;
 
 // Single-matrix Ozaki context: device buffers for one split pair and the
 // purification state of one matrix.
@@ -126,17 +132,19 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
     x.nt_full = tm * tn;
     x.nmod = mod_count(x.S, x.n, nocc);
     if (x.nmod > 0) {
-        x.mshape = residue_shape(int64_t(residue_tile_count(x.n, kShapeWide, true)) * x.nmod);
+        x.mshape = residue_shape(1, &x.n, x.nmod, true);
         DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
         DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, true, &x.tiles_out, 32));
         x.nt_out = upper_tile_count(x.n, 32);
+    }
+    if (x.nmod > 0 && x.n >= kResidueBackward) {
         // The backward operands Y and M = Y P have no bound on their row norms
         // but sqrt(n) times the row maximum, so their products take the
         // capacity (15 moduli for S = 7): the rounding to X then stays below
         // the truncation of the digit slices for any row.
         x.bmod = mod_capacity(x.S);
         auto list = [&](bool upper, const Tile** out, int* count, int* shape) -> int {
-            *shape = residue_shape(int64_t(residue_tile_count(x.n, kShapeWide, upper)) * x.bmod);
+            *shape = residue_shape(1, &x.n, x.bmod, upper);
             return cached_residue_tiles(x.n, x.bmod, *shape, upper, out, count);
         };
         DMP_CHECK(list(true, &x.bsym, &x.nt_bsym, &x.shape_bsym));
@@ -215,6 +223,22 @@ int start_residues(const OzCtx& x, const double* P, int par, const int* expo, hi
     return launch_split_digits(d, x.S, x.kind, x.st, s, x.nmod);
 }
 
+// Coefficient data of one recorded step.
+struct StepRecord {
+    double c, t1, t2;
+    int branch, clamped;
+};
+
+// The end of an iteration and its record (index iters - 1); once the run has
+// stopped, every later launch rewrites that entry with the same values.
+__global__ __launch_bounds__(256) void k_finish_step(const PurDesc* pd, DevState* st, StepRecord* hist) {
+    __shared__ double sh[4];
+    finalize_iteration(*pd, *st, sh);
+    const DevState& s = *st;
+    if (threadIdx.x == 0 && s.iters > 0)
+        hist[s.iters - 1] = StepRecord{s.c, s.t1, s.t2, s.branch, s.clamped};
+}
+
 // One forward iteration P_in -> (X2_out, P_out) with the purification
 // kernels; the coefficient is recomputed on the device from the traces.
 // Digit slices: the row maxima of X2 and of P_out come from the products'
@@ -222,9 +246,16 @@ int start_residues(const OzCtx& x, const double* P, int par, const int* expo, hi
 // product); p_maxima: x.ma already holds those of P_in (the previous
 // iteration's update), so its split runs only the digit kernel.  Residues:
 // the products write the planes of X2 and P_out; those of P_in (parity
-// ``par``) are in place.
+// ``par``) are in place.  ``hist`` (null when an iteration is recomputed): the
+// iteration's end and record.
 int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double* P_out,
-                      bool finalize, bool p_maxima, int par, hipStream_t s) {
+                      StepRecord* hist, bool p_maxima, int par, hipStream_t s) {
+    auto finish = [&]() -> int {
+        if (hist == nullptr) return DMP_OK;
+        k_finish_step<<<1, 256, 0, s>>>(x.pd, x.st, hist);
+        DMP_CHECK_HIP(hipGetLastError());
+        return DMP_OK;
+    };
     GemmParams p{};
     p.tiles = x.nmod > 0 ? x.tiles_out : x.tiles_up;
     p.mtiles = x.mtiles;
@@ -258,7 +289,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         p.mode = EPI_UPDATE;
         DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_out, s,
                                       CoefArgs{x.pd, x.st, 1, DMP_CANONICAL, kStepCoef}));
-        return finalize ? launch_finalize_iter(x.pd, x.st, 1, s) : DMP_OK;
+        return finish();
     }
     SplitDesc sp = split_of(x, P_in, false, x.ma, x.ea, x.pa, 0);
     sp.clear = x.mb;
@@ -286,23 +317,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
     p.one.rowmax = x.ma;
     p.mode = EPI_UPDATE;
     DMP_CHECK(launch_ozgemm(x.S, x.kind, p, x.nt_up, s, x.rb));
-    if (finalize) DMP_CHECK(launch_finalize_iter(x.pd, x.st, 1, s));
-    return DMP_OK;
-}
-
-// Coefficient data of one recorded step.
-struct StepRecord {
-    double c, t1, t2;
-    int branch, clamped;
-};
-
-// Records the step the state has just finished (index iters - 1); once the
-// run has stopped, every later launch rewrites that entry with the same
-// values.
-__global__ void k_record_step(const DevState* st, StepRecord* hist) {
-    const DevState& s = *st;
-    if (threadIdx.x == 0 && s.iters > 0)
-        hist[s.iters - 1] = StepRecord{s.c, s.t1, s.t2, s.branch, s.clamped};
+    return finish();
 }
 
 // C = A B for n x n operands already split: (pa, ea) rows of A, (pb, eb)
@@ -328,20 +343,6 @@ int gemm_store(const OzCtx& x, const uint8_t* pa, const int* ea, const uint8_t* 
                                    sym ? x.nt_bsym : x.nt_bfull, sym ? x.nt_out : x.nt_outfull, s);
     }
     return launch_ozgemm(x.S, x.kind, p, sym ? x.nt_up : x.nt_full, s, x.rb);
-}
-
-__device__ inline double wsum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-__device__ inline double bsum(double v, double* sh) {
-    v = wsum(v);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const double r = ((sh[0] + sh[1]) + sh[2]) + sh[3];
-    __syncthreads();
-    return r;
 }
 
 // Y = (A + A^T) / 2 on 32 x 32 tile pairs (I <= J), through LDS.
@@ -393,9 +394,9 @@ __global__ __launch_bounds__(256) void k_adj_dots(const double* Y, const double*
             c += m[u] * p[u];
         }
     }
-    a = bsum(a, sh);
-    b = bsum(b, sh);
-    c = bsum(c, sh);
+    a = block_sum(a, sh);
+    b = block_sum(b, sh);
+    c = block_sum(c, sh);
     if (threadIdx.x == 0) {
         out[blockIdx.x * 4 + 0] = a;
         out[blockIdx.x * 4 + 1] = b;
@@ -413,9 +414,9 @@ __global__ __launch_bounds__(256) void k_adj_cbar(const double* dots, double c, 
         b += dots[i * 4 + 1];
         g += dots[i * 4 + 2];
     }
-    a = bsum(a, sh);
-    b = bsum(b, sh);
-    g = bsum(g, sh);
+    a = block_sum(a, sh);
+    b = block_sum(b, sh);
+    g = block_sum(g, sh);
     if (threadIdx.x == 0) {
         double cbar = 0.0;
         if (!clamped) {
@@ -483,8 +484,8 @@ __global__ __launch_bounds__(256) void k_adj_dots0(const double* Y, const double
         yh += Y[i] * H[i];
         if (i / n == i % n) tr += Y[i];
     }
-    tr = bsum(tr, sh);
-    yh = bsum(yh, sh);
+    tr = block_sum(tr, sh);
+    yh = block_sum(yh, sh);
     if (threadIdx.x == 0) {
         out[blockIdx.x * 4 + 0] = tr;
         out[blockIdx.x * 4 + 1] = yh;
@@ -498,8 +499,8 @@ __global__ __launch_bounds__(256) void k_adj_scal0(const double* dots, double* s
         tr += dots[i * 4 + 0];
         yh += dots[i * 4 + 1];
     }
-    tr = bsum(tr, sh);
-    yh = bsum(yh, sh);
+    tr = block_sum(tr, sh);
+    yh = block_sum(yh, sh);
     if (threadIdx.x == 0) {
         scal[1] = tr;
         scal[2] = yh;
@@ -770,14 +771,8 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
                 if (st != DMP_OK) break;
                 t->x2.push_back(x2k);
             }
-            st = forward_iteration(x, cur, x2k, nxt, true, launched > 0, launched & 1, s);
+            st = forward_iteration(x, cur, x2k, nxt, hist, launched > 0, launched & 1, s);
             if (st != DMP_OK) break;
-            k_record_step<<<1, 64, 0, s>>>(x.st, hist);
-            if (hipGetLastError() != hipSuccess) {
-                set_error("launch of the step record failed");
-                st = DMP_EHIP;
-                break;
-            }
             if (stride == 1) {
                 cur = nxt;
                 t->ckpt.push_back(cur);
@@ -923,7 +918,7 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
             if (x.nmod > 0) DMP_CHECK(start_residues(x, segP[0], start & 1, t->ckpt_expo[seg], s));
             for (int j = start; j < end; ++j)
                 DMP_CHECK(forward_iteration(x, segP[j - start], segX[j - start], segP[j - start + 1],
-                                            false, j > start, j & 1, s));
+                                            nullptr, j > start, j & 1, s));
         }
         for (int j = end - 1; j >= start; --j) {
             const double* P = stored ? t->ckpt[j] : segP[j - start];

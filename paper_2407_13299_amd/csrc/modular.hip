@@ -361,8 +361,9 @@ constexpr bool pur_mode(int mode) {
 // the first result is formed.  The partial sums are formed per row group and
 // added in one order, so that both widths give the same bits.  Row maxima,
 // which only choose powers of two, are kept to the upper word, rounded up.
+// (The update at 4 wavefronts needs 145 registers: three wavefronts per SIMD.)
 template <int N, int MODE, bool FP16, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 4) void k_combine(GemmParams p) {
+__global__ __launch_bounds__(64 * WAVES, MODE == EPI_UPDATE && WAVES == 4 ? 3 : 4) void k_combine(GemmParams p) {
     constexpr bool PUR = pur_mode(MODE);
     constexpr bool UPPER = MODE != EPI_STORE;
     static_assert(WAVES == 8 || (WAVES == 4 && !FP16), "a lane's part of the planes: 8 or 16 bytes");
@@ -625,10 +626,11 @@ __global__ __launch_bounds__(64 * WAVES, 4) void k_combine(GemmParams p) {
     }
 }
 
-// Tiles from which the wavefronts of a tile are 4 instead of 8 (but for the
-// update, whose operands then do not fit the registers): square of n = 2048,
-// 1056 tiles, 28.8 against 30.4 us; n = 1400, 506 tiles, 17.6 against 16.5 us;
-// n = 256, 20 tiles, 9.6 against 7.9 us.
+// Tiles from which a tile has 4 wavefronts instead of 8 (half the exponents,
+// row maxima and requests per element).  Square and update, 4 and 8: 24
+// matrices of n = 256 .. 1024, 2700 tiles, 61 and 76 against 72 and 83 us; n =
+// 2048, 1056 tiles, 28.8 and 35.5 against 30.4 and 36.1 us; n = 1400, 506 tiles,
+// square 17.6 against 16.5 us; n = 256, 20 tiles, 9.6 against 7.9 us.
 constexpr int kFourWaveTiles = 1024;
 
 template <int N, int MODE>
@@ -639,13 +641,10 @@ static void combine(bool fp16, const GemmParams& p, int nout, hipStream_t stream
             return;
         }
     }
-    if constexpr (MODE != EPI_UPDATE) {
-        if (nout >= kFourWaveTiles) {
-            k_combine<N, MODE, false, 4><<<nout, 256, 0, stream>>>(p);
-            return;
-        }
-    }
-    k_combine<N, MODE, false, 8><<<nout, 512, 0, stream>>>(p);
+    if (nout >= kFourWaveTiles)
+        k_combine<N, MODE, false, 4><<<nout, 256, 0, stream>>>(p);
+    else
+        k_combine<N, MODE, false, 8><<<nout, 512, 0, stream>>>(p);
 }
 
 template <int N>

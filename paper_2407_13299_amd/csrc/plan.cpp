@@ -118,7 +118,16 @@ int residue_tile_count(int n, int shape, bool upper) {
     return upper ? t * (t + 1) / 2 : t * t;
 }
 
-int residue_shape(int64_t wide) { return wide >= kWideTiles ? kShapeWide : kShapeSmall; }
+int residue_shape(int count, const int* n, int nmod, bool upper) {
+    int64_t tiles = 0, wide = 0, small = 0;
+    for (int b = 0; b < count; ++b) {
+        const int t = residue_tile_count(n[b], kShapeWide, upper), chunks = (n[b] + 63) / 64 + kTileStartChunks;
+        tiles += int64_t(t) * nmod;
+        wide += int64_t(t) * chunks;
+        small += int64_t(residue_tile_count(n[b], kShapeSmall, upper)) * chunks;
+    }
+    return tiles < kWideTiles || 10 * small < kSmallPerWide10 * wide ? kShapeSmall : kShapeWide;
+}
 
 int tile_rows(int m, int TM) { return int(round_up(m, TM) / TM); }
 int tile_cols(int n) { return int(round_up(n, kTileN) / kTileN); }
@@ -446,9 +455,9 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
                          32 * g.rb);
         }
         if (g.nmod > 0) {
-            int64_t wide = 0;
-            for (int b : order) wide += int64_t(residue_tile_count(n[g.idx[b]], kShapeWide, true)) * g.nmod;
-            g.mshape = residue_shape(wide);
+            std::vector<int> sizes;
+            for (int b : order) sizes.push_back(n[g.idx[b]]);
+            g.mshape = residue_shape(cnt, sizes.data(), g.nmod, true);
             for (int b : order)
                 append_residue_tiles(out.mtiles, n[g.idx[b]], g.nmod, g.mshape, true, uint32_t(b));
             if (cnt > 1) spread_residue_tiles(out.mtiles, n, g);

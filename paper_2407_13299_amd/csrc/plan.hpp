@@ -63,9 +63,17 @@ int upper_tile_count(int n, int TM = kTileM);
 // ``shape`` in 1024 x 1024 super-tiles.
 void append_residue_tiles(std::vector<Tile>& out, int n, int nmod, int shape, bool upper, uint32_t mat);
 int residue_tile_count(int n, int shape, bool upper);   // per modulus
-// Shape for a launch of ``wide`` tiles (all moduli) of the wide shape.
-constexpr int kWideTiles = 100;
-int residue_shape(int64_t wide);
+// Shape for a launch of the products of ``count`` matrices: 256 x 256 tiles
+// where there are kWideTiles of them (all moduli) and they are not mostly
+// empty.  A tile of a matrix costs its 64-element chunks and kTileStartChunks
+// more; the chip does 2.8 small tiles in the time of a wide one.  One GEMM, wide
+// and small: n = 700, 78 wide tiles, 12.2 and 11.6 us; n = 1024, 130 tiles, 16.1
+// and 19.4 us; n = 1400 33.0 and 33.5 us; n = 2048 57 and 65 us; batches of 40 of
+// n = 64 .. 256 (work in small tiles 2.2 times that in wide ones) 15.3 and
+// 11.2 us, 48 of 128 .. 512 (2.6) 39.0 and 33.4 us, 30 of 100 .. 800 (2.8) 73.4
+// and 73.9 us, 24 of 256 .. 1024 (2.9) 94.6 and 98.9 us.
+constexpr int kWideTiles = 100, kTileStartChunks = 4, kSmallPerWide10 = 28;
+int residue_shape(int count, const int* n, int nmod, bool upper);
 
 // Workgroups ("units") of the split kernels for an operand of R rows.
 int split_units_rowmax(int R);
