@@ -6,7 +6,7 @@ with H resident in HBM before the timed region starts.  Prints one JSON line:
 value = FP64-equivalent TFLOP/s = iterations * 2 products * 2 n^3 / time.
 
 Beside it: native FP64 purification (rocBLAS DGEMM, same driver) on the same
-GPU, the roofline of the dominant kernel (the INT8 slice-pair GEMM, timed with
+GPU, the roofline of the dominant product (its INT8 matrix products, timed with
 HIP events inside the library on the launch stream), the accuracy against the
 stored oracle samples, and the oracle itself timed on the host on a bounded
 sample (two FP64 iterations with numpy).
@@ -67,12 +67,19 @@ def kernel_code_digest(path):
     return hashlib.sha256(re.sub(r"\s+", "", text).encode()).hexdigest()
 
 
+def by_residues(slices):
+    """Whether the library runs purification products of this slice count
+    through residues (one matrix product per modulus) instead of slice pairs."""
+    return 6 <= slices <= 8
+
+
 def profiled_traffic(kind, slices, which="update"):
-    """HBM bytes per product of the slice GEMM (summed over its launches) from
+    """HBM bytes per product (summed over its launches) from
     the committed rocprofv3 counter summary, or None when that summary was
     taken on another version of the kernel code (or for another configuration)."""
-    path = os.path.join(ROOT, "profiles", f"k_ozgemm_{kind}_s{slices}_tb8192_traffic.md")
-    src = os.path.join(ROOT, "paper_2407_13299_amd", "csrc", "ozgemm.hip")
+    kernel, source = ("residue", "modular.hip") if by_residues(slices) else ("k_ozgemm", "ozgemm.hip")
+    path = os.path.join(ROOT, "profiles", f"{kernel}_{kind}_s{slices}_tb8192_traffic.md")
+    src = os.path.join(ROOT, "paper_2407_13299_amd", "csrc", source)
     if not os.path.exists(path):
         return None
     vals = {}
@@ -511,6 +518,7 @@ def main():
             avg_ms = ms_k[i].value / nl[i].value
             per_launch = ops[i].value / nl[i].value
             kernels[name] = dict(avg_ms=avg_ms, launches=nl[i].value,
+                                 matrix_products=round(per_launch / (float(n) * n * (n + 1))),
                                  tops=per_launch / (avg_ms / 1e3) / 1e12,
                                  clock_ghz=clk[i].value)
     dom = kernels.get("update") or kernels.get("square") or {}
@@ -604,10 +612,11 @@ def main():
         "data": "synthetic",
         "config": {"workload": a.workload, "n": n, "nocc": nocc, "tol": tol,
                    "kind": a.kind, "slices": a.slices, "iterations": it,
-                   "products": 2 * it, "slice_products_per_product": a.slices * (a.slices + 1) // 2,
+                   "products": 2 * it, "slice_products_per_product": dom.get("matrix_products"),
                    "gemm_time_share": gemm_share,
                    "instrumented_ms": instrumented_ms, **acc},
-        "roofline": {"bound": "mfma", "kernel": "k_ozgemm (update: X2 P, upper triangle)",
+        "roofline": {"bound": "mfma", "kernel": ("k_residue_gemm + k_combine" if by_residues(a.slices) else "k_ozgemm") +
+                     " (update: X2 P, upper triangle)",
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "ops": "int8 multiply-adds counted as 2 ops" if a.kind == "int8" else "fp16",
                      "frac": achieved / peak if peak else None,

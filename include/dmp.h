@@ -14,6 +14,12 @@
  *     entry.  The slice products run on INT8 MFMA with exact INT32
  *     accumulation (DMP_OZ_INT8) or FP16 MFMA with FP32 accumulation flushed
  *     into INT32 before it can round (DMP_OZ_FP16).
+ *     With S = 6, 7 or 8 the products of a purification (and of the adjoint
+ *     from n = 1400 on) take the multi-modulus form of the scheme instead: the
+ *     scaled rows become integers, 11, 13 or 15 (up to 16) exact products of
+ *     their residues modulo p <= 256 run on the same matrix cores, and the
+ *     Chinese remainder theorem gives the integer product back, with a smaller
+ *     error than the S slices'.
  *   - Density-matrix purification (Sec. 2.3; canonical, trace-conserving
  *     form of Palser and Manolopoulos cited in Sec. 1): from
  *     P0 = lam (mu I - H) + (nocc/n) I the iteration
@@ -316,21 +322,22 @@ void dmp_tape_free(dmp_tape* tape);
  * Kernel timing (instrumentation; process-wide state, not for concurrent
  * use from several host threads).  dmp_timing_enable(1) or (2): the
  * purification entry points record a HIP event pair on the caller's stream
- * around every slice-GEMM launch (and launch without graph capture), and
+ * around every matrix product (and launch without graph capture), and
  * accumulate the durations once each batch of iterations has completed;
  * (2) also turns on the clock counters read by dmp_timing_clock (a few
  * instructions and two atomic adds per workgroup); 0 turns timing off.
  *   which = 0: the squaring GEMM (P P), 1: the update GEMM (X2 P).
  *   *total_ms: summed kernel time; *launches: number of launches timed;
  *   *ops: summed algorithmic integer (or FP16) operations of those
- *   launches, 2 * S(S+1)/2 * n * n(n+1)/2 per launch (the upper triangle of
- *   an n x n product; padding excluded).
+ *   launches, 2 * N * n * n(n+1)/2 per launch (the upper triangle of an n x
+ *   n product; padding excluded), N = S(S+1)/2 slice pairs or the number of
+ *   moduli.
  * ------------------------------------------------------------------- */
 void dmp_timing_enable(int on);
 void dmp_timing_reset(void);
 int dmp_timing_read(int which, double* total_ms, long long* launches, double* ops);
 
-/* Mean shader clock (GHz) inside the slice-GEMM launches of kind ``which``
+/* Mean shader clock (GHz) inside the matrix-product launches of kind ``which``
  * timed in mode 2 since the last dmp_timing_reset: every workgroup adds its
  * span in shader-clock cycles (s_memtime) and in 100 MHz
  * real-time ticks (s_memrealtime) to two device counters, and the clock is

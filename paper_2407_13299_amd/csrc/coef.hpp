@@ -1,7 +1,7 @@
 // Device code shared by the purification kernels and the split kernel:
 // fixed-order block sums, the per-iteration coefficients computed from the
-// square's trace partials (the split of X2 runs them in extra blocks of its
-// own launch) and the end of an iteration (run by the next split of P).
+// square's trace partials and the end of an iteration, both run in extra
+// blocks of the launch that follows (CoefArgs).
 #pragma once
 
 #include "common.hpp"

@@ -82,8 +82,9 @@ inline size_t residue_out_bytes(int64_t m, int64_t n) {
     return size_t(round_up(m, kPad)) * size_t(round_up(n, kPad));
 }
 
-// One output tile of a (possibly grouped) GEMM: rows [128 I, 128 I + 128),
-// columns [64 J, 64 J + 64) of matrix ``mat`` of a batch.  In the tile lists
+// One output tile of a (possibly grouped) GEMM: of matrix ``mat`` of a batch
+// columns [64 J, 64 J + 64) and rows [128 I, 128 I + 128) (64 rows in the lists
+// of 64-row tiles, 32 in those of the residue combination).  In the tile lists
 // of the residue GEMM the top byte of ``mat`` is the modulus.
 struct Tile {
     uint16_t I, J;

@@ -2,7 +2,14 @@
 // (Sec. 2.3 and 2.4; canonical trace-conserving form cited in Sec. 1).
 //
 // Per iteration and per matrix (every phase is one launch over all matrices
-// of a group; matrices that have stopped skip their blocks):
+// of a group; matrices that have stopped skip their blocks).  S = 6, 7, 8 by
+// residues (modular.hip), every product a residue GEMM and a combination that
+// also writes the planes of its output:
+//   SQUARE              X2 = P P, partial traces, planes of X2; extra blocks of
+//                       the GEMM: the end of the iteration before
+//   UPDATE              P' and its planes, partial tr(P'H); extra blocks of the
+//                       GEMM: t1, t2, c, branch, (alpha, beta, gamma)
+// Otherwise by digit slices:
 //   split(P)            row exponents + digit planes of P (serve as both
 //                       operands: P is exactly symmetric)
 //   gemm SQUARE         X2 = P P, partial traces
@@ -14,9 +21,10 @@
 // TRS4 (Sec. 3) runs the same phases: the square's epilogue gives tr F and
 // tr G, finalize_trs4 picks gamma and the branch, and the second product is
 // X2 T with T = (4 - 2 gamma) X + (gamma - 3) X2 + gamma I formed inside the
-// split (or no product at all on the X2 and 2X - X2 branches).
+// split (or no product at all on the X2 and 2X - X2 branches); with residues
+// T has a finalize, a row-maxima and a split launch of its own.
 // All reductions are fixed-order (no floating-point atomics), so runs are
-// bitwise reproducible.  FP64 everywhere except the slice products (Sec. 4).
+// bitwise reproducible.  FP64 everywhere except the slice (residue) products (Sec. 4).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
