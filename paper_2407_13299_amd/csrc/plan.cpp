@@ -93,24 +93,33 @@ void append_tiles(std::vector<Tile>& out, int tm, int tn, bool upper, uint32_t m
     // super-tiles of GI x GJ tiles = 512 x 512 elements
     const int GI = 512 / TM, GJ = 512 / kTileN;
     const int sm = (tm + GI - 1) / GI, sn = (tn + GJ - 1) / GJ;
+    const size_t need = out.size() + size_t(tm) * tn;
+    if (out.capacity() < need) out.reserve(std::max(need, 2 * out.capacity()));
     for (int si = 0; si < sm; ++si)
         for (int sj = 0; sj < sn; ++sj)
-            for (int i = si * GI; i < std::min(tm, si * GI + GI); ++i)
-                for (int j = sj * GJ; j < std::min(tn, sj * GJ + GJ); ++j) {
-                    if (upper && !tile_in_upper(i, j, TM)) continue;
-                    out.push_back(Tile{uint16_t(i), uint16_t(j), mat});
-                }
+            for (int i = si * GI; i < std::min(tm, si * GI + GI); ++i) {
+                // the first column of an upper triangle's row (tile_in_upper)
+                const int lo = std::max(sj * GJ, upper ? std::max(0, (TM * i - kTileN + 1 + kTileN - 1) / kTileN) : 0);
+                for (int j = lo; j < std::min(tn, sj * GJ + GJ); ++j) out.push_back(Tile{uint16_t(i), uint16_t(j), mat});
+            }
 }
 
 void append_residue_tiles(std::vector<Tile>& out, int n, int nmod, int shape, bool upper, uint32_t mat) {
     const int edge = shape_edge(shape), t = (n + edge - 1) / edge, G = 1024 / edge;
-    for (int m = 0; m < nmod; ++m)
-        for (int si = 0; si < t; si += G)
-            for (int sj = 0; sj < t; sj += G)
-                for (int i = si; i < std::min(t, si + G); ++i)
-                    for (int j = sj; j < std::min(t, sj + G); ++j)
-                        if (!upper || i <= j)
-                            out.push_back(Tile{uint16_t(i), uint16_t(j), mat | (uint32_t(m) << 24)});
+    const size_t first = out.size(), count = size_t(residue_tile_count(n, shape, upper));
+    out.resize(first + count * nmod);
+    Tile* p = out.data() + first;
+    for (int si = 0; si < t; si += G)
+        for (int sj = upper ? si : 0; sj < t; sj += G)
+            for (int i = si; i < std::min(t, si + G); ++i)
+                for (int j = upper ? std::max(i, sj) : sj; j < std::min(t, sj + G); ++j)
+                    *p++ = Tile{uint16_t(i), uint16_t(j), mat};
+    // the other moduli: the same tiles
+    for (int m = 1; m < nmod; ++m)
+        for (size_t i = 0; i < count; ++i, ++p) {
+            *p = out[first + i];
+            p->mat |= uint32_t(m) << 24;
+        }
 }
 
 int residue_tile_count(int n, int shape, bool upper) {
@@ -390,35 +399,36 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
 static void spread_residue_tiles(std::vector<Tile>& tiles, const int* n, const GroupPlan& g) {
     constexpr int kXcds = 8;
     struct Run {
-        size_t first, count;
+        uint32_t first, count;
         double work;
     };
     std::vector<Run> runs;
-    for (size_t i = 0; i < tiles.size(); ++i) {
-        if (i == 0 || tiles[i].mat != tiles[i - 1].mat) runs.push_back(Run{i, 0, 0.0});
-        runs.back().count++;
-        runs.back().work += n[g.idx[tiles[i].mat & 0xffffffu]] + 64.0;
+    runs.reserve(size_t(g.count) * g.nmod);
+    for (size_t i = 0; i < tiles.size();) {
+        size_t e = i + 1;
+        while (e < tiles.size() && tiles[e].mat == tiles[i].mat) ++e;
+        runs.push_back(Run{uint32_t(i), uint32_t(e - i),
+                           double(e - i) * (n[g.idx[tiles[i].mat & 0xffffffu]] + 64.0)});
+        i = e;
     }
     std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.work > b.work; });
-    std::vector<size_t> queue[kXcds];
+    std::vector<Tile> queue[kXcds];
+    size_t next[kXcds] = {};
     double load[kXcds] = {};
+    for (auto& q : queue) q.reserve(tiles.size() / kXcds + 64);
     for (const Run& r : runs) {
         const int q = int(std::min_element(load, load + kXcds) - load);
-        for (size_t i = 0; i < r.count; ++i) queue[q].push_back(r.first + i);
+        queue[q].insert(queue[q].end(), tiles.begin() + r.first, tiles.begin() + r.first + r.count);
         load[q] += r.work;
     }
-    std::vector<Tile> out;
-    out.reserve(tiles.size());
-    size_t next[kXcds] = {};
     for (size_t pos = 0; pos < tiles.size(); ++pos) {
         // the XCD's own queue, or the longest left once it is empty
         int q = int(pos % kXcds);
         if (next[q] == queue[q].size())
             for (int x = 0; x < kXcds; ++x)
                 if (queue[x].size() - next[x] > queue[q].size() - next[q]) q = x;
-        out.push_back(tiles[queue[q][next[q]++]]);
+        tiles[pos] = queue[q][next[q]++];
     }
-    tiles.swap(out);
 }
 
 void build_group(GroupPlan& g, const double* const* H, double* const* P, const int* n,
