@@ -272,7 +272,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         q.expo_out = x.eb;
         q.maxin = x.maxi[par];
         q.clear = x.maxi[par ^ 1];
-        q.growth = kGrowthSquare;
+        q.limit = crt_limit(x.nmod) / kGrowthSquare;
         p.one = q;
         DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_out, s));
         q.pa = x.pb;
@@ -284,7 +284,7 @@ int forward_iteration(const OzCtx& x, const double* P_in, double* X2_out, double
         q.planes_out = x.pa;
         q.expo_out = x.expo[par ^ 1];
         q.clear = nullptr;
-        q.growth = kGrowthCanonical;
+        q.limit = crt_limit(x.nmod) / kGrowthCanonical;
         p.one = q;
         p.mode = EPI_UPDATE;
         DMP_CHECK(launch_residue_gemm(x.kind, x.nmod, x.mshape, p, x.nmt, x.nt_out, s,

@@ -124,7 +124,7 @@ struct MatDesc {
     int* expo_out;
     const uint64_t* maxin; // row maxima of P
     uint64_t* clear;       // nullable: row maxima to zero, for a later launch
-    double growth;
+    double limit;          // largest admissible row norm of the integers, over growth
 };
 
 // Device-side purification state of one matrix (host-readable copy).
@@ -226,7 +226,7 @@ struct CoefArgs {
 // in [0, 1]; TRS4's T = (4 - 2g) X + (g - 3) X2 + g I has t(x) in [0, 6] for
 // 0 <= g <= 6 and x in [0, 1].
 constexpr double kLamIterate = 1.0625, kLamTrs4 = 6.5;
-// MatDesc::growth, with the same room: x^2 / x <= 1; the canonical maps have
+// Growth (MatDesc), with the same room: x^2 / x <= 1; the canonical maps have
 // f(x) / x <= 5 / 4 (c < 1/2: ((1 - 2c) + (1 + c) x - x^2) / (1 - c) at x = (1
 // + c) / 2; c >= 1/2: (1 + c)^2 / (4 c) <= 9 / 8); of TRS4's, 2 - x <= 2 is the
 // largest (x t(x) <= 1.4).

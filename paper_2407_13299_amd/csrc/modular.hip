@@ -82,7 +82,24 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
     const int mod = int(tile.mat >> 24), mat = p.lone ? 0 : int(tile.mat & 0xffffffu);
     const MatDesc d = p.descs ? p.descs[mat] : p.one;
     const DevState* st = p.states ? p.states + mat : nullptr;
-    if (st != nullptr && (st->done || (p.skip_zero && st->gamma == 0.0))) return;
+    if (st != nullptr && st->done) return;
+    // the exponents of the output's planes, which the combination forms: each
+    // row's once, by the first modulus' diagonal tiles (in the combination every
+    // wavefront would work them out again, a tenth of its instructions: n =
+    // 2048 36 and 30 against 34 and 28 us), behind the first loads
+    auto exponents = [&]() __attribute__((always_inline)) {
+        constexpr int ROWS = 16 * WM * FM;
+        const int row = int(tile.I) * ROWS + int(threadIdx.x);
+        if (d.expo_out != nullptr && mod == 0 && tile.I == tile.J && int(threadIdx.x) < ROWS &&
+            row < int(round_up(d.M, kPad))) {
+            d.expo_out[row] = residue_exponent(d.maxin[row], d.KC * (FP16 ? 16 : 32), kLamIterate, d.limit);
+            if (d.clear != nullptr) d.clear[row] = 0;
+        }
+    };
+    if (st != nullptr && p.skip_zero && st->gamma == 0.0) {
+        exponents();
+        return;
+    }
     const bool clocked = p.clk != nullptr;
     const uint64_t clk_c = clocked ? __builtin_amdgcn_s_memtime() : 0;
     const uint64_t clk_r = clocked ? __builtin_amdgcn_s_memrealtime() : 0;
@@ -163,6 +180,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void k_residue_gemm(GemmParams p
 #pragma unroll
     for (int s = 0; s < NBUF - 1; ++s)
         if (s < RC) issue(s, s);
+    exponents();
     if (RC >= NBUF - 1) ops_wait<(NBUF - 3) * PER>(); else ops_wait<0>();
     bare_barrier();
     Frags fr[2];
@@ -348,8 +366,9 @@ constexpr bool pur_mode(int mode) {
 // transposed, those of its four 16-column blocks.  So an iterate or a square
 // is split without being read again, and without the launch that did
 // (k_residues: 23 us at n = 2048, 290 us at n = 8192).  The exponents come from
-// the row maxima of the iterate before the product (MatDesc::growth), as the
-// output's own are known only when every tile is done.
+// the row maxima of the iterate before the product (MatDesc::limit), as the
+// output's own are known only when every tile is done; the residue GEMM works
+// them out.
 //
 // Bound: memory for many tiles (N to 2 N bytes of residues and 12 to 28 bytes
 // of FP64 per element; n = 2048: 30 and 36 us); for few tiles the chain of
@@ -405,14 +424,9 @@ __global__ __launch_bounds__(64 * WAVES, MODE == EPI_UPDATE && WAVES == 4 ? 3 : 
     const int k0 = WAVES == 8 ? (rows ? (wave & 1) * 32 : 0) + (lane >> 4) * 8
                               : (rows ? lane >> 4 : (lane >> 4) & 1) * 16;
     const int row = rows ? 32 * int(tile.I) + lr : 64 * int(tile.J) + lr;
-    const uint64_t rmax = PUR ? d.maxin[row] : 0;
+    const int tx = PUR ? d.expo_out[row] : 0;
     ModSplit split{};
     if constexpr (PUR) split = lane_split();
-    int tx = 0;
-    auto exponent = [&]() __attribute__((always_inline)) {
-        if constexpr (PUR)
-            tx = residue_exponent(rmax, d.KC * (FP16 ? 16 : 32), kLamIterate, Crt<N>::table.limit / d.growth);
-    };
 
     auto quadrant = [&](auto full) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full)::value;
@@ -463,7 +477,6 @@ __global__ __launch_bounds__(64 * WAVES, MODE == EPI_UPDATE && WAVES == 4 ? 3 : 
             fetch(d.X2, beta != 0.0, xv);
             fetch(d.H, true, hv);
         }
-        exponent();   // between the loads and their first use
         uint32_t hi[4 * G], cmax = 0;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -567,8 +580,6 @@ __global__ __launch_bounds__(64 * WAVES, MODE == EPI_UPDATE && WAVES == 4 ? 3 : 
             quadrant(std::true_type{});
         else
             quadrant(std::false_type{});
-    } else {
-        exponent();
     }
     if constexpr (PUR) {
 #pragma unroll
@@ -594,10 +605,6 @@ __global__ __launch_bounds__(64 * WAVES, MODE == EPI_UPDATE && WAVES == 4 ? 3 : 
         // rows.  On the diagonal the upper tile (I even) writes its rows
         // whole and the mirror of its right half, the lower one (I odd, whose
         // left half lies below the diagonal) the right half of its rows.
-        if (diag && rows && (WAVES == 4 || (wave & 1)) && lane < 16) {
-            d.expo_out[row] = tx;
-            if (d.clear != nullptr) d.clear[row] = 0;
-        }
         if (diag && !rows && (half == 1 || wave < WAVES * 3 / 4)) return;
         const bool wanted = !diag || !rows || half == 0 || k0 >= 32;
         if (WAVES == 8 && !wanted) return;

@@ -116,4 +116,12 @@ struct Crt {
     static constexpr CrtTable table = make_crt(N);
 };
 
+// The limit for N moduli (kModMin .. kMaxMods).
+inline double crt_limit(int N) {
+    static constexpr double limits[kMaxMods - kModMin + 1] = {
+        Crt<11>::table.limit, Crt<12>::table.limit, Crt<13>::table.limit,
+        Crt<14>::table.limit, Crt<15>::table.limit, Crt<16>::table.limit};
+    return limits[N - kModMin];
+}
+
 }  // namespace dmp

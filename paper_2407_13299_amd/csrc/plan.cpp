@@ -599,13 +599,13 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
                 q.expo_out = L.expX;
                 q.maxin = maxi[par];
                 q.clear = maxi[par ^ 1];
-                q.growth = kGrowthSquare;
+                q.limit = crt_limit(g.nmod) / kGrowthSquare;
                 u.eb = expo[par];
                 u.rowmax = maxi[par ^ 1];
                 u.planes_out = L.planesP;
                 u.expo_out = expo[par ^ 1];
                 u.maxin = maxi[par];
-                u.growth = g.method == DMP_TRS4 ? kGrowthTrs4 : kGrowthCanonical;
+                u.limit = crt_limit(g.nmod) / (g.method == DMP_TRS4 ? kGrowthTrs4 : kGrowthCanonical);
                 // T replaces the iterate as the right operand, in its planes
                 // and exponents
                 (par == 0 ? out.st0[b] : out.st1[b]).expo = expo[par];
