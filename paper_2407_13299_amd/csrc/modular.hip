@@ -371,7 +371,7 @@ constexpr bool pur_mode(int mode) {
 // them out.
 //
 // Bound: memory for many tiles (N to 2 N bytes of residues and 12 to 28 bytes
-// of FP64 per element; n = 2048: 30 and 36 us); for few tiles the chain of
+// of FP64 per element; n = 2048: 28 and 34 us) and instructions; for few tiles the chain of
 // latencies, with one wavefront per SIMD (n = 256: 7.9 and 9.0 us, 4.5 of them
 // the two rounds of loads and the launch).  Hence 8 wavefronts rather than 4
 // (9.6 and 11 us) where the tiles do not fill the chip; loops and constants
