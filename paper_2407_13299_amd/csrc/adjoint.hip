@@ -93,12 +93,13 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     const TileChoice tc = tile_choice_env(kind, S, n);
     x.rb = tc.rb;
     x.rb_stride = int64_t(x.KC) * S * kFragBytes;
+    const int mods = std::max(mod_capacity(S, n), mod_backward(S));
     const size_t planes = std::max(plane_bytes(n, n, S, kind),
-                                   residue_plane_bytes(n, n, kind) * mod_capacity(S));
+                                   residue_plane_bytes(n, n, kind) * mods);
     x.pa = c.take<uint8_t>(planes);
     x.pb = c.take<uint8_t>(planes);
     if (residues) {
-        x.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+        x.res = c.take<uint8_t>(residue_out_bytes(n, n) * mods);
         for (int i = 0; i < 2; ++i) {
             x.expo[i] = c.take<int>(round_up(n, kPad));
             x.maxi[i] = c.take<uint64_t>(round_up(n, kPad));
@@ -138,11 +139,7 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
         x.nt_out = upper_tile_count(x.n, 32);
     }
     if (x.nmod > 0 && x.n >= kResidueBackward) {
-        // The backward operands Y and M = Y P have no bound on their row norms
-        // but sqrt(n) times the row maximum, so their products take the
-        // capacity (15 moduli for S = 7): the rounding to X then stays below
-        // the truncation of the digit slices for any row.
-        x.bmod = mod_capacity(x.S);
+        x.bmod = mod_backward(x.S);
         auto list = [&](bool upper, const Tile** out, int* count, int* shape) -> int {
             *shape = residue_shape(1, &x.n, x.bmod, upper);
             return cached_residue_tiles(x.n, x.bmod, *shape, upper, out, count);

@@ -21,34 +21,61 @@ constexpr int kMaxMods = 16;
 constexpr int kMods[kMaxMods] = {256, 255, 253, 251, 247, 241, 239, 233,
                                  229, 227, 223, 217, 211, 199, 197, 193};
 
-// Slice counts whose purification products run through residues, and their
-// number.  S counts digit slices: its products keep 8S - 2 bits of every
-// operand row but drop the slice pairs i + j > S + 1, which leaves an error
-// of about 2^(e_i + f_j) 2^(-8S + 8) sqrt(k / 2048) 2^-0.8 (measured 5.7e-15
-// for S = 7 at k = 2048).  N is the smallest count whose rounding to X, Y
-// stays below that for operands with rows maxima >= 0.15 (density matrices
-// of at least 15 % filling): 11, 13 and 15 products against 21, 28 and 36.
-// Lower filling shrinks 2^(e_i) faster than the row norm, so one or two more
-// moduli are taken (mod_count).  S <= 5 and S >= 9 keep the digit slices:
-// below 6 the slices are few enough (15 products) and their truncation is
-// what is studied; beyond 8 the integers no longer fit FP64.
+// Slice counts whose purification products run through residues, and the
+// moduli of each at large n: 11, 13 and 15 products against 21, 28 and 36.
+// S <= 5 and S >= 9 keep the digit slices: below 6 the slices are few enough (15
+// products) and their truncation is what is studied; beyond 8 the integers no
+// longer fit FP64.
 constexpr int kModSlicesLo = 6, kModSlicesHi = 8;
 constexpr int kModCount[3] = {11, 13, 15};
 constexpr int kModMin = 11;
 
-// Capacity (moduli) a purification with S slices may use: 0 for digit slices.
-constexpr int mod_capacity(int S) {
+// Moduli of a purification with S slices, nocc of n levels occupied: the
+// smallest count whose error is no larger than that of S digit slices.  Those
+// keep 8S - 2 bits of a row below its largest entry m_i, but drop the slice
+// pairs i + j > S + 1, which leaves about 2^(8 - 8S) m_i m_j sqrt(n); the
+// rounding to X, Y leaves |row i| |row j| / sqrt(M).  In a density matrix of
+// filling f the maxima are about f and the row norms sqrt(f), so the quotient of
+// the two errors goes as 1 / (f sqrt(n)) = sqrt(n) / nocc.  Measured as whole
+// purifications against 11 slices (Frobenius norm of the difference, medians
+// over seeds; Haar-distributed and nearly diagonal projectors, n = 8 .. 2048, f =
+// 0.03 .. 0.9), residues over slices: canonical, 13 moduli, S = 7, at most 4.5
+// sqrt(n) / nocc (f = 0.2, where the slices' powers of two lie closest to the
+// maxima), e.g. 2.3 at n = 64, f = 0.2; 1.2 at n = 300, f = 0.2; 0.24 at n =
+// 2048, f = 0.25; TRS4 5.6 sqrt(n) / nocc; each modulus more takes it down by 14
+// (n = 64, f = 0.2: 0.19).  From half filling on, the maxima pass 1/2 and the
+// slices' powers of two double: 0.60 at n = 64, f = 0.5.  S = 6 and 11 moduli:
+// the same quotients less a seventh.  The lines below stand a quarter of the
+// error above 1: nocc^2 >= 32 n (TRS4 50 n), or half filling and n >= 64 (TRS4
+// 100).  Fillings below 15 % and 0.4 % take one and two moduli more at any n.
+// S = 8: FP64 rounding is the larger error with 15 moduli as with 16.
+constexpr int mod_count(int S, int n, int nocc, bool trs4 = false) {
+    if (S < kModSlicesLo || S > kModSlicesHi) return 0;
+    const int64_t occ = nocc, levels = n;
+    int more = (occ * 100 < levels * 15 ? 1 : 0) + (occ * 1000 < levels * 4 ? 1 : 0);
+    const bool half = 2 * occ + 1 >= levels && n >= (trs4 ? 100 : 64);
+    if (S < 8 && !half) {
+        // one modulus: 14^2 in the square
+        int64_t lhs = (occ > 0 ? occ * occ : 1), rhs = (trs4 ? 50 : 32) * levels;
+        int steps = 0;
+        for (; steps < 3 && lhs < rhs; ++steps) lhs *= 200;
+        if (steps > more) more = steps;
+    }
+    const int c = kModCount[S - kModSlicesLo] + more;
+    return c < kMaxMods ? c : kMaxMods;
+}
+// Capacity (moduli) a purification of n levels with S slices may use, by either
+// method and at any occupation (one level needs the most), and at any n: 0 for
+// digit slices.
+constexpr int mod_capacity(int S, int n) { return mod_count(S, n, 1, true); }
+constexpr int mod_capacity(int S) { return mod_capacity(S, 1 << 24); }
+// Moduli of the adjoint's backward products, whose operands Y and Y P have no
+// bound on their row norms but sqrt(n) times the row maximum: the rounding to X
+// then stays below the truncation of the digit slices for any row.
+constexpr int mod_backward(int S) {
     if (S < kModSlicesLo || S > kModSlicesHi) return 0;
     const int c = kModCount[S - kModSlicesLo] + 2;
     return c < kMaxMods ? c : kMaxMods;
-}
-// Moduli of a purification with S slices, nocc of n levels occupied.
-constexpr int mod_count(int S, int n, int nocc) {
-    if (S < kModSlicesLo || S > kModSlicesHi) return 0;
-    const int64_t occ = nocc;
-    const int c = kModCount[S - kModSlicesLo] + (occ * 100 < int64_t(n) * 15 ? 1 : 0) +
-                  (occ * 1000 < int64_t(n) * 4 ? 1 : 0);
-    return c < mod_capacity(S) ? c : mod_capacity(S);
 }
 
 // Reconstruction constants of N moduli.  C' = X Y mod M satisfies C' / M =

@@ -290,7 +290,7 @@ void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int 
     for (int b = 0; b < count; ++b) {
         const int S = kind == DMP_FP64_NATIVE ? 0 : slices[b];
         const bool residues = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && mod_capacity(S) > 0;
-        const int nmod = residues ? mod_count(S, n[b], nocc ? nocc[b] : 0) : 0;
+        const int nmod = residues ? mod_count(S, n[b], nocc ? nocc[b] : 0, method == DMP_TRS4) : 0;
         // residues: the combination runs on 32 x 64 tiles
         const TileChoice tc = kind == DMP_FP64_NATIVE ? TileChoice{4, false}
                               : residues              ? TileChoice{1, false}
@@ -326,12 +326,12 @@ static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind, bool resid
     } else {
         // residues: room for the capacity, so that the workspace does not
         // depend on the occupation
-        const size_t planes = residues ? residue_plane_bytes(n, n, kind) * mod_capacity(S)
+        const size_t planes = residues ? residue_plane_bytes(n, n, kind) * mod_capacity(S, n)
                                        : plane_bytes(n, n, S, kind);
         m.planesP = c.take<uint8_t>(planes);
         m.planesX = c.take<uint8_t>(planes);
         if (residues) {
-            m.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S));
+            m.res = c.take<uint8_t>(residue_out_bytes(n, n) * mod_capacity(S, n));
             m.expP1 = c.take<int>(round_up(n, kPad));
             m.maxP1 = c.take<uint64_t>(round_up(n, kPad));
         }
@@ -359,7 +359,7 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
             parts = std::max<size_t>(parts, std::max(native_blocks(nb), native_pairs(nb)));
         } else {
             parts += size_t(oz_tiles(nb, g.rb));
-            if (residues) mtiles += size_t(residue_tile_count(nb, kShapeSmall, true)) * mod_capacity(g.S);
+            if (residues) mtiles += size_t(residue_tile_count(nb, kShapeSmall, true)) * mod_capacity(g.S, nb);
             const int kc = int(chunks_of(nb, g.kind));
             g.min_kc = b == 0 ? kc : std::min(g.min_kc, kc);
             g.max_kc = std::max(g.max_kc, kc);
