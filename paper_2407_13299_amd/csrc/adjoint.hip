@@ -676,6 +676,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
     double* Pw = c.take<double>(size_t(n) * n);
     int st = bind_ctx(x, t->H, nocc, P, s);
     if (st == DMP_OK) st = launch_purify_init(x.pd, x.st, 1, n, tol, max_iter, s);
+    if (st == DMP_OK) st = launch_purify_e0(x.pd, x.st, 1, x.st, 1, s);
     DevState h{};
     if (st == DMP_OK && (hipMemcpyAsync(&h, x.st, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
                          hipStreamSynchronize(s) != hipSuccess)) {

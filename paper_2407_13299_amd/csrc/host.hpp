@@ -97,6 +97,8 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
 // Small purification kernels (purify.hip), one block / matrix per entry of pd.
 int launch_purify_init(const PurDesc* pd, DevState* st, int count, int max_n, double tol,
                        int max_iter, hipStream_t s);
+// ``all``: the ``total`` states of the call (a non-finite matrix stops them all)
+int launch_purify_e0(const PurDesc* pd, DevState* st, int count, const DevState* all, int total, hipStream_t s);
 int launch_finalize_coef(const PurDesc* pd, DevState* st, int count, hipStream_t s);
 int launch_finalize_iter(const PurDesc* pd, DevState* st, int count, hipStream_t s);
 int e0_blocks();

@@ -346,7 +346,7 @@ static MatLayout carve_matrix(Carver& c, int n, int S, dmp_kind kind, bool resid
     return m;
 }
 
-size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
+size_t carve_group(Carver& c, GroupPlan& g, const int* n, bool states) {
     size_t parts = 0, mtiles = 0;
     const bool residues = g.nmod > 0;
     g.lay.resize(g.count);
@@ -387,7 +387,7 @@ size_t carve_group(Carver& c, GroupPlan& g, const int* n) {
     g.tiles = c.take<Tile>(std::max<size_t>(1, g.kind == DMP_FP64_NATIVE ? 1 : parts));
     g.mtiles = mtiles > 0 ? c.take<Tile>(mtiles) : nullptr;
     g.pairs = c.take<IPair>(g.max_pairs);
-    g.st = c.take<DevState>(g.count);
+    g.st = states ? c.take<DevState>(g.count) : nullptr;
     g.partials = c.take<double>(std::max<size_t>(1, parts) * kPartials);
     return c.used();
 }

@@ -210,8 +210,9 @@ int oz_tiles(int n, int rb);
 // grouping the occupations can lead to.
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
                  int forced_rb, std::vector<GroupPlan>& groups, const int* nocc = nullptr);
-// Carve the workspace regions of a group (base == nullptr: measure only).
-size_t carve_group(Carver& c, GroupPlan& g, const int* n);
+// Carve the workspace regions of a group (base == nullptr: measure only);
+// states false: all but its device states, which the caller places.
+size_t carve_group(Carver& c, GroupPlan& g, const int* n, bool states = true);
 
 // Host copies of a group's descriptors, ready to upload.
 struct GroupHost {

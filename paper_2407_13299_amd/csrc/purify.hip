@@ -263,17 +263,27 @@ __global__ __launch_bounds__(256) void k_mirror_iterate(const PurDesc* pd, const
     }
 }
 
-__global__ __launch_bounds__(256) void k_finalize_e0(const PurDesc* pd, DevState* states) {
+// Energy of P0 from its partials; one block per matrix.  A non-finite entry in
+// any matrix of the call (the ``total`` states ``all``) refuses the whole call:
+// every state is then marked done before the first iteration.
+__global__ __launch_bounds__(256) void k_finalize_e0(const PurDesc* pd, DevState* states, const DevState* all,
+                                                     int total) {
     __shared__ double sh[4];
     const PurDesc& d = pd[blockIdx.x];
     DevState& s = states[blockIdx.x];
-    double e = 0.0;
+    double e = 0.0, bad = 0.0;
     for (int i = threadIdx.x; i < kE0Blocks; i += 256) e += d.e0[i];
+    for (int i = threadIdx.x; i < total; i += 256) bad += all[i].nonfinite ? 1.0 : 0.0;
     e = block_sum(e, sh);
+    bad = block_sum(bad, sh);
     if (threadIdx.x == 0) {
         s.E = e;
         s.E_prev = e;
         s.trace_p = double(d.nocc);
+        if (bad != 0.0) {
+            s.done = 1;
+            s.stop_reason = DMP_STOP_NONFINITE;
+        }
     }
 }
 
@@ -479,7 +489,12 @@ int launch_purify_init(const PurDesc* pd, DevState* st, int count, int max_n, do
     k_gershgorin<<<dim3((max_n + 3) / 4, count), 256, 0, s>>>(pd);
     k_finalize_init<<<count, 256, 0, s>>>(pd, st, tol, max_iter);
     k_init_p0<<<dim3(kE0Blocks, count), 256, 0, s>>>(pd, st);
-    k_finalize_e0<<<count, 256, 0, s>>>(pd, st);
+    DMP_CHECK_HIP(hipGetLastError());
+    return DMP_OK;
+}
+
+int launch_purify_e0(const PurDesc* pd, DevState* st, int count, const DevState* all, int total, hipStream_t s) {
+    k_finalize_e0<<<count, 256, 0, s>>>(pd, st, all, total);
     DMP_CHECK_HIP(hipGetLastError());
     return DMP_OK;
 }
@@ -547,8 +562,7 @@ int upload_group(GroupPlan& g, const double* const* H, double* const* P, const i
     return DMP_OK;
 }
 
-int launch_init(GroupPlan& g, double tol, int max_iter, hipStream_t s) {
-    DMP_CHECK(launch_purify_init(g.pd, g.st, g.count, g.max_n, tol, max_iter, s));
+int launch_start(GroupPlan& g, hipStream_t s) {
     // row maxima of P0 (later iterates get theirs from the update's epilogue)
     if (g.kind != DMP_FP64_NATIVE)
         DMP_CHECK(launch_split_grouped_rowmax(g.splitP[0], g.count, g.units_rowmax, g.st, s));
@@ -556,6 +570,18 @@ int launch_init(GroupPlan& g, double tol, int max_iter, hipStream_t s) {
     if (g.nmod > 0)
         DMP_CHECK(launch_split_grouped_digits(g.splitP[0], g.count, g.units_digits, g.S, g.kind, g.st, s,
                                               CoefArgs{}, false, g.nmod));
+    return DMP_OK;
+}
+
+// The initial guesses of all groups, whose states lie in one array, and the row
+// maxima and planes they start from.
+int launch_init(std::vector<GroupPlan>& groups, const DevState* all, int total, double tol, int max_iter,
+                hipStream_t s) {
+    for (auto& g : groups) DMP_CHECK(launch_purify_init(g.pd, g.st, g.count, g.max_n, tol, max_iter, s));
+    for (auto& g : groups) {
+        DMP_CHECK(launch_purify_e0(g.pd, g.st, g.count, all, total, s));
+        DMP_CHECK(launch_start(g, s));
+    }
     return DMP_OK;
 }
 
@@ -897,7 +923,7 @@ int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
     if (cg) {
         int it = 0;
         for (auto& h : host_st) it = std::max(it, h.iters);
-        cg->last_iters = it;
+        if (it > 0) cg->last_iters = it;
     }
     return DMP_OK;
 }
@@ -1019,7 +1045,13 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
     std::vector<GroupPlan> groups;
     plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr);
     Carver c(ws);
-    for (auto& g : groups) carve_group(c, g, n);
+    DevState* const states = c.take<DevState>(size_t(count));
+    int first = 0;
+    for (auto& g : groups) {
+        carve_group(c, g, n, false);
+        g.st = ws ? states + first : nullptr;
+        first += g.count;
+    }
     if (need_out) *need_out = c.used();
     if (ws == nullptr) return DMP_OK;
     if (ws_bytes < c.used()) {
@@ -1031,13 +1063,12 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
     std::lock_guard<std::mutex> serial(purify_mutex());
     std::vector<std::unique_ptr<GroupHost>> keep;
     StreamDrain drain{s};   // declared after ``keep``: the stream drains first
-    for (auto& g : groups) {
+    for (auto& g : groups)
         DMP_CHECK(upload_group(g, H, P, n, nocc, kind == DMP_FP64_NATIVE || (flags & DMP_REFINE_MCWEENY), s, keep));
-        DMP_CHECK(launch_init(g, tol, max_iter, s));
-    }
+    DMP_CHECK(launch_init(groups, states, count, tol, max_iter, s));
     std::vector<DevState> host_st(count);
-    // a non-finite H sets its state's done flag: nothing iterates on it, and
-    // the state read that ends the run reports it
+    // a non-finite H marks every state done before the first iteration
+    // (k_finalize_e0); the first state read reports it
     auto reject_nonfinite = [&]() -> int {
         for (auto& h : host_st)
             if (h.nonfinite) {
