@@ -219,6 +219,11 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
  *   H returns DMP_ENONFINITE.  Blocks until done.
  * ------------------------------------------------------------------- */
 size_t dmp_purify_workspace_bytes(int n, int slices, dmp_kind kind);
+/* The fewest bytes dmp_purify and dmp_purify_ex accept.  Below
+ * dmp_purify_workspace_bytes (S = 6, 7, 8: 16 n^2 + 3 N n^2 bytes and a little,
+ * N = 14 to 16, FP16 5 N) the products run on digit slices, which take 2 S n^2
+ * (FP16 4 S) instead of the 3 N: slower, and with the slices' errors. */
+size_t dmp_purify_min_workspace_bytes(int n, int slices, dmp_kind kind);
 int dmp_purify(const double* H, int n, int nocc, double tol, int slices,
                dmp_kind kind, int max_iter, double* P, double* E,
                dmp_info* info, void* ws, size_t ws_bytes, void* stream);
@@ -264,6 +269,10 @@ int dmp_purify_ex(const double* H, int n, int nocc, double tol, int slices,
  * ------------------------------------------------------------------- */
 size_t dmp_purify_batched_workspace_bytes(int count, const int* n, int slices,
                                           dmp_kind kind);
+/* As dmp_purify_min_workspace_bytes: below the size above, the whole batch
+ * runs on digit slices. */
+size_t dmp_purify_batched_min_workspace_bytes(int count, const int* n, int slices,
+                                              dmp_kind kind);
 int dmp_purify_batched(int count, const double* const* H, const int* n,
                        const int* nocc, double tol, int slices, dmp_kind kind,
                        int max_iter, double* const* P, double* E,

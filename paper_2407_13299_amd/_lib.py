@@ -21,8 +21,8 @@ EXPORTS = [
     "dmp_last_error", "dmp_version", "dmp_max_slices",
     "dmp_gemm_workspace_bytes", "dmp_ozaki_gemm", "dmp_ozaki_gemm_noalloc",
     "dmp_gemm_batched_workspace_bytes", "dmp_ozaki_gemm_batched",
-    "dmp_purify_workspace_bytes", "dmp_purify", "dmp_purify_ex",
-    "dmp_purify_batched_workspace_bytes", "dmp_purify_batched", "dmp_purify_batched_ex",
+    "dmp_purify_workspace_bytes", "dmp_purify_min_workspace_bytes", "dmp_purify", "dmp_purify_ex",
+    "dmp_purify_batched_workspace_bytes", "dmp_purify_batched_min_workspace_bytes", "dmp_purify_batched", "dmp_purify_batched_ex",
     "dmp_autotune_slices",
     "dmp_purify_fwd_tape", "dmp_purify_bwd_workspace_bytes", "dmp_purify_bwd",
     "dmp_tape_info", "dmp_tape_coefficients", "dmp_tape_free",
@@ -73,6 +73,7 @@ _SIGS = {
     "dmp_gemm_batched_workspace_bytes": (_SZ, [_I, _IP, _IP, _IP, _I, _I]),
     "dmp_ozaki_gemm_batched": (_I, [_I, _IP, _IP, _IP, _PP, _PP, _PP, _I, _I, _P, _SZ, _P]),
     "dmp_purify_workspace_bytes": (_SZ, [_I, _I, _I]),
+    "dmp_purify_min_workspace_bytes": (_SZ, [_I, _I, _I]),
     "dmp_purify": (_I, [_P, _I, _I, _D, _I, _I, _I, _P, ctypes.POINTER(_D),
                         ctypes.POINTER(DmpInfo), _P, _SZ, _P]),
     "dmp_purify_ex": (_I, [_P, _I, _I, _D, _I, _I, _I, _I, _I, _P, ctypes.POINTER(_D),
@@ -80,6 +81,7 @@ _SIGS = {
     "dmp_purify_batched_ex": (_I, [_I, _PP, _IP, _IP, _D, _I, _I, _I, _I, _I, _PP,
                                    ctypes.POINTER(_D), ctypes.POINTER(DmpInfo), _P, _SZ, _P]),
     "dmp_purify_batched_workspace_bytes": (_SZ, [_I, _IP, _I, _I]),
+    "dmp_purify_batched_min_workspace_bytes": (_SZ, [_I, _IP, _I, _I]),
     "dmp_purify_batched": (_I, [_I, _PP, _IP, _IP, _D, _I, _I, _I, _PP, ctypes.POINTER(_D),
                                 ctypes.POINTER(DmpInfo), _P, _SZ, _P]),
     "dmp_autotune_slices": (_I, [_I, _D, _I]),

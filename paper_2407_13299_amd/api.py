@@ -39,8 +39,15 @@ def _check_matrix(t, name):
         raise ValueError(f"{name} must be a contiguous 2-D tensor")
 
 
-def _workspace(nbytes: int, device):
-    return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+def _workspace(nbytes: int, device, least=None):
+    """Workspace of nbytes, or where the device has not so much left, of the
+    ``least`` bytes the call accepts."""
+    try:
+        return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if least is None or least >= nbytes:
+            raise
+    return torch.empty(max(int(least), 256), dtype=torch.uint8, device=device)
 
 
 def _keep_for(ws: torch.Tensor, stream):
@@ -178,20 +185,23 @@ def purify(H, nocc, tol=1e-8, slices=7, kind="int8", max_iter=200, out=None, str
     """Density-matrix purification (canonical or TRS4), optionally followed
     by one FP64 McWeeny refinement step; returns (P, E, info dict).
     ``triangle`` (kind 'native'): rocBLAS dsyrk / dsyrkx upper-triangle
-    products instead of full DGEMMs."""
+    products instead of full DGEMMs.  ``workspace``: a uint8 tensor of
+    dmp_purify_workspace_bytes, or a smaller one of at least
+    dmp_purify_min_workspace_bytes (digit slices); replaced by an own one if
+    smaller still."""
     lib = _lib.load()
     n = _square(H)
     if out is not None:
         _check_out(out, (n, n), H)
     P = out if out is not None else torch.empty_like(H)
     kd = _kind(kind)
-    need = lib.dmp_purify_workspace_bytes(n, slices, kd)
+    least = lib.dmp_purify_min_workspace_bytes(n, slices, kd)
     ws = workspace
     if ws is not None and (not isinstance(ws, torch.Tensor) or ws.dtype != torch.uint8
                            or ws.device != H.device or not ws.is_contiguous()):
         raise TypeError("workspace must be a contiguous uint8 tensor on the device of H")
-    if ws is None or ws.numel() < need:
-        ws = _workspace(need, H.device)
+    if ws is None or ws.numel() < least:
+        ws = _workspace(lib.dmp_purify_workspace_bytes(n, slices, kd), H.device, least)
     e = ctypes.c_double(0.0)
     info = _lib.DmpInfo()
     flags = (_lib.REFINE_MCWEENY if refine else 0) | (_lib.NATIVE_TRIANGLE if triangle else 0)
@@ -223,7 +233,8 @@ def purify_batched(Hs, noccs, tol=1e-8, slices=0, kind="int8", max_iter=200, str
     n = IA(*[h.shape[0] for h in Hs])
     nocc = IA(*[int(x) for x in noccs])
     kd = _kind(kind)
-    ws = _workspace(lib.dmp_purify_batched_workspace_bytes(cnt, n, int(slices), kd), Hs[0].device)
+    ws = _workspace(lib.dmp_purify_batched_workspace_bytes(cnt, n, int(slices), kd), Hs[0].device,
+                    lib.dmp_purify_batched_min_workspace_bytes(cnt, n, int(slices), kd))
     E = (ctypes.c_double * cnt)()
     infos = (_lib.DmpInfo * cnt)()
     flags = _lib.REFINE_MCWEENY if refine else 0

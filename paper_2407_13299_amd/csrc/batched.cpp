@@ -18,19 +18,29 @@ int dmp_autotune_slices(int n, double target, dmp_kind kind) {
 
 extern "C" {
 
-size_t dmp_purify_batched_workspace_bytes(int count, const int* n, int slices, dmp_kind kind) {
-    if (count < 1 || !n) return 0;
+static void batched_bytes(int count, const int* n, int slices, dmp_kind kind, size_t* need, size_t* least) {
+    if (count < 1 || !n) return;
     for (int b = 0; b < count; ++b)
-        if (n[b] < 1) return 0;
+        if (n[b] < 1) return;
     std::vector<int> s;
     batch_slices(count, n, slices, kind, s);
     std::vector<const double*> h(count, nullptr);
     std::vector<double*> p(count, nullptr);
     std::vector<int> nocc(count, 0);
-    size_t need = 0;
     purify_many(count, h.data(), n, nocc.data(), 1.0, s.data(), kind, 1, DMP_CANONICAL, 0, p.data(), nullptr,
-                nullptr, nullptr, 0, nullptr, &need);
+                nullptr, nullptr, 0, nullptr, need, least);
+}
+
+size_t dmp_purify_batched_workspace_bytes(int count, const int* n, int slices, dmp_kind kind) {
+    size_t need = 0;
+    batched_bytes(count, n, slices, kind, &need, nullptr);
     return need;
+}
+
+size_t dmp_purify_batched_min_workspace_bytes(int count, const int* n, int slices, dmp_kind kind) {
+    size_t least = 0;
+    batched_bytes(count, n, slices, kind, nullptr, &least);
+    return least;
 }
 
 int dmp_purify_batched_ex(int count, const double* const* H, const int* n, const int* nocc,
@@ -61,7 +71,7 @@ int dmp_purify_batched_ex(int count, const double* const* H, const int* n, const
         return DMP_ENOMEM;
     }
     return purify_many(count, H, n, nocc, tol, s.data(), kind, max_iter, method, flags, P, E, info,
-                       ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr);
+                       ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr, nullptr);
 }
 
 int dmp_purify_batched(int count, const double* const* H, const int* n, const int* nocc,

@@ -92,7 +92,7 @@ int native_dsyrkx_upper(hipStream_t stream, int n, const double* A, const double
 int purify_many(int count, const double* const* H, const int* n, const int* nocc, double tol,
                 const int* slices, dmp_kind kind, int max_iter, int method, int flags,
                 double* const* P, double* E, dmp_info* info, void* ws, size_t ws_bytes,
-                hipStream_t s, size_t* need_out);
+                hipStream_t s, size_t* need_out, size_t* least_out);
 
 // Small purification kernels (purify.hip), one block / matrix per entry of pd.
 int launch_purify_init(const PurDesc* pd, DevState* st, int count, int max_n, double tol,

@@ -1,6 +1,7 @@
 // Slice-pair products of the Ozaki scheme (Sec. 2.4) on gfx950 matrix cores,
 // with the FP64 summation and the purification work fused into the epilogue.
-// (Purification products with S = 6, 7, 8 run through residues, modular.hip.)
+// (Purification products with S = 6, 7, 8 run through residues, modular.hip,
+// unless the workspace is too small for those.)
 //
 // A workgroup of 8 wavefronts owns one 128 x 64 output tile (4 x 2 quadrants
 // of 32 x 32, one per wavefront), or, in the 64-row variant, 4 wavefronts own
@@ -518,23 +519,17 @@ static bool purification_mode(int mode) {
     return mode == EPI_SQUARE || mode == EPI_UPDATE || mode == EPI_SQUARE_TRS4;
 }
 
-// The purification epilogues: not for the slice counts whose purification
-// products run through residues (launch_ozgemm refuses those).
-constexpr bool has_purification(int S) { return mod_capacity(S) == 0; }
-
 // The parts of a split tail run no epilogue, so one instantiation serves every
 // mode.
 template <int S, int RB, int PHASE>
 static void launch_rb(bool fp16, const GemmParams& p, int ntiles, hipStream_t stream) {
     constexpr int threads = 128 * RB;
-    if constexpr (PHASE == kPiece || has_purification(S)) {
-        if (PHASE == kPiece || purification_mode(p.mode)) {
-            if (fp16)
-                k_ozgemm<S, true, 0, true, RB, PHASE><<<ntiles, threads, 0, stream>>>(p);
-            else
-                k_ozgemm<S, false, 0, true, RB, PHASE><<<ntiles, threads, 0, stream>>>(p);
-            return;
-        }
+    if (PHASE == kPiece || purification_mode(p.mode)) {
+        if (fp16)
+            k_ozgemm<S, true, 0, true, RB, PHASE><<<ntiles, threads, 0, stream>>>(p);
+        else
+            k_ozgemm<S, false, 0, true, RB, PHASE><<<ntiles, threads, 0, stream>>>(p);
+        return;
     }
     if constexpr (PHASE != kPiece) {
         if (fp16)
@@ -555,21 +550,19 @@ static void launch_s(bool fp16, const GemmParams& p, int ntiles, int rb, hipStre
     launch_rb<S, 4, PHASE>(fp16, p, ntiles, stream);
 }
 
-// Workgroups of the slice GEMM resident per CU (the purification-mode one
-// where there is one; both are bound by the LDS).
+// Workgroups of the purification-mode slice GEMM resident per CU.
 template <int S>
 static int resident_s(bool fp16, int rb, int* per_cu) {
-    constexpr bool PUR = has_purification(S);
     hipError_t e;
     if constexpr (S <= kMaxSlices64) {
         if (rb == 2) {
-            e = fp16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, true, 0, PUR, 2>, 256, 0)
-                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, false, 0, PUR, 2>, 256, 0);
+            e = fp16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, true, 0, true, 2>, 256, 0)
+                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, false, 0, true, 2>, 256, 0);
             return e == hipSuccess ? DMP_OK : DMP_EHIP;
         }
     }
-    e = fp16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, true, 0, PUR>, kGemmThreads, 0)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, false, 0, PUR>, kGemmThreads, 0);
+    e = fp16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, true, 0, true>, kGemmThreads, 0)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_ozgemm<S, false, 0, true>, kGemmThreads, 0);
     return e == hipSuccess ? DMP_OK : DMP_EHIP;
 }
 
@@ -605,10 +598,6 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
     if (ntiles <= 0) return DMP_OK;
     if (rb != 4 && (rb != 2 || kind == DMP_MARKIDIS_FP16 || S > kMaxSlices64)) {
         set_error("64-row tiles exist for the Ozaki kinds with S <= %d only", kMaxSlices64);
-        return DMP_EINVAL;
-    }
-    if (kind != DMP_MARKIDIS_FP16 && purification_mode(p.mode) && !has_purification(S)) {
-        set_error("no slice GEMM for purification products with S = %d", S);
         return DMP_EINVAL;
     }
     if (p.fix != nullptr) {

@@ -285,11 +285,11 @@ int native_pairs(int n) {
 int oz_tiles(int n, int rb) { return upper_tile_count(n, 32 * rb); }
 
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
-                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc) {
+                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc, bool digits) {
     groups.clear();
     for (int b = 0; b < count; ++b) {
         const int S = kind == DMP_FP64_NATIVE ? 0 : slices[b];
-        const bool residues = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && mod_capacity(S) > 0;
+        const bool residues = !digits && (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && mod_capacity(S) > 0;
         const int nmod = residues ? mod_count(S, n[b], nocc ? nocc[b] : 0, method == DMP_TRS4) : 0;
         // residues: the combination runs on 32 x 64 tiles
         const TileChoice tc = kind == DMP_FP64_NATIVE ? TileChoice{4, false}

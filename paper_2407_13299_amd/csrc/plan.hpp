@@ -207,9 +207,10 @@ int oz_tiles(int n, int rb);
 // same tiles and scales, hence bit-identical results, alone or in a batch.
 // nocc null (workspace queries, which do not know it): every matrix that may
 // use residues is a group of its own, which needs no less workspace than any
-// grouping the occupations can lead to.
+// grouping the occupations can lead to.  digits: digit slices for every matrix.
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
-                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc = nullptr);
+                 int forced_rb, std::vector<GroupPlan>& groups, const int* nocc = nullptr,
+                 bool digits = false);
 // Carve the workspace regions of a group (base == nullptr: measure only);
 // states false: all but its device states, which the caller places.
 size_t carve_group(Carver& c, GroupPlan& g, const int* n, bool states = true);

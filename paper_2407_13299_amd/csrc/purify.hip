@@ -1033,29 +1033,41 @@ void fill_info(const DevState& h, int S, dmp_kind kind, dmp_info* info) {
 
 }  // namespace
 
-// Purify count matrices that share the kind; used by both entry points.
+// Purify count matrices that share the kind; used by both entry points.  ws
+// null: only the bytes needed (need_out) and the fewest accepted (least_out).
 int purify_many(int count, const double* const* H, const int* n, const int* nocc, double tol,
                 const int* slices, dmp_kind kind, int max_iter, int method, int flags,
                 double* const* P, double* E, dmp_info* info, void* ws, size_t ws_bytes,
-                hipStream_t s, size_t* need_out) {
+                hipStream_t s, size_t* need_out, size_t* least_out) {
     // groups of equal slice count and tile choice (the choice follows from
     // each matrix's own n and S, so a matrix gets the same tiles, hence the
     // same fixed-order trace sums and bit-identical results, alone or in a
     // batch)
     std::vector<GroupPlan> groups;
-    plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr);
-    Carver c(ws);
-    DevState* const states = c.take<DevState>(size_t(count));
-    int first = 0;
-    for (auto& g : groups) {
-        carve_group(c, g, n, false);
-        g.st = ws ? states + first : nullptr;
-        first += g.count;
+    DevState* states = nullptr;
+    auto plan = [&](bool digits) -> size_t {
+        plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr, digits);
+        Carver c(ws);
+        states = c.take<DevState>(size_t(count));
+        int first = 0;
+        for (auto& g : groups) {
+            carve_group(c, g, n, false);
+            g.st = ws ? states + first : nullptr;
+            first += g.count;
+        }
+        return c.used();
+    };
+    if (ws == nullptr) {
+        const size_t need = plan(false);
+        if (need_out) *need_out = need;
+        if (least_out) *least_out = std::min(need, plan(true));
+        return DMP_OK;
     }
-    if (need_out) *need_out = c.used();
-    if (ws == nullptr) return DMP_OK;
-    if (ws_bytes < c.used()) {
-        set_error("workspace of %zu bytes required", c.used());
+    // a workspace too small for residue products (3 (N + 1) bytes an element
+    // beside the FP64 matrices, where digit slices take 2 S): digit slices
+    const size_t need = plan(false);
+    if (ws_bytes < need && ws_bytes < plan(true)) {
+        set_error("workspace of %zu bytes required", need);
         return DMP_ENOMEM;
     }
     DMP_CHECK(check_workspace_alignment(ws));
@@ -1185,8 +1197,19 @@ size_t dmp_purify_workspace_bytes(int n, int slices, dmp_kind kind) {
     double* p = nullptr;
     int nocc = 0;
     purify_many(1, &h, &n, &nocc, 1.0, &slices, kind, 1, DMP_CANONICAL, 0, &p, nullptr, nullptr,
-                nullptr, 0, nullptr, &need);
+                nullptr, 0, nullptr, &need, nullptr);
     return need;
+}
+
+size_t dmp_purify_min_workspace_bytes(int n, int slices, dmp_kind kind) {
+    if (dmp_purify_workspace_bytes(n, slices, kind) == 0) return 0;
+    size_t least = 0;
+    const double* h = nullptr;
+    double* p = nullptr;
+    int nocc = 0;
+    purify_many(1, &h, &n, &nocc, 1.0, &slices, kind, 1, DMP_CANONICAL, 0, &p, nullptr, nullptr,
+                nullptr, 0, nullptr, nullptr, &least);
+    return least;
 }
 
 int dmp_purify_ex(const double* H, int n, int nocc, double tol, int slices, dmp_kind kind,
@@ -1205,7 +1228,7 @@ int dmp_purify_ex(const double* H, int n, int nocc, double tol, int slices, dmp_
         return DMP_ENOMEM;
     }
     return purify_many(1, &H, &n, &nocc, tol, &slices, kind, max_iter, method, flags, &P, E, info,
-                       ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr);
+                       ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr, nullptr);
 }
 
 int dmp_purify(const double* H, int n, int nocc, double tol, int slices, dmp_kind kind,
