@@ -215,7 +215,11 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
  *   Outputs: P (device, n x n, exactly symmetric), *E (host) = tr(P H),
  *   *info (host, may be NULL).
  *   H is read as symmetric (the initial guess and the energy use its upper
- *   triangle; the Gershgorin bounds use whole rows).  A non-finite entry in
+ *   triangle; the Gershgorin bounds use whole rows).  The products through
+ *   residues (S = 6, 7, 8) rely on an initial guess with spectrum in [0, 1],
+ *   which the bounds ensure for a symmetric H; an H with an element below the
+ *   diagonal smaller than its mirror (by more than rounding: 2^-16 (h_max -
+ *   h_min) / n^2) is run on digit slices, which do not.  A non-finite entry in
  *   H returns DMP_ENONFINITE.  Blocks until done.
  * ------------------------------------------------------------------- */
 size_t dmp_purify_workspace_bytes(int n, int slices, dmp_kind kind);

@@ -123,7 +123,8 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.fix = x.fix_pieces > 0 ? c.take<int>(size_t(x.fix_pieces) * piece_ints(S, x.rb)) : nullptr;
 }
 
-int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
+// digits: digit slices where residues would run (a lopsided H).
+int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, bool digits, hipStream_t s) {
     x.H = H;
     const int TM = 32 * x.rb;
     const int tm = tile_rows(x.n, TM), tn = tile_cols(x.n);
@@ -131,7 +132,8 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, hipStream_t s) {
     DMP_CHECK(cached_tiles(tm, tn, false, &x.tiles_full, TM));
     x.nt_up = upper_tile_count(x.n, TM);
     x.nt_full = tm * tn;
-    x.nmod = mod_count(x.S, x.n, nocc);
+    x.nmod = digits ? 0 : mod_count(x.S, x.n, nocc);
+    x.bmod = 0;
     if (x.nmod > 0) {
         x.mshape = residue_shape(1, &x.n, x.nmod, true);
         DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
@@ -674,7 +676,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
     carve_ctx(c, x, n, slices, kind);
     double* X2 = c.take<double>(size_t(n) * n);
     double* Pw = c.take<double>(size_t(n) * n);
-    int st = bind_ctx(x, t->H, nocc, P, s);
+    int st = bind_ctx(x, t->H, nocc, P, false, s);
     if (st == DMP_OK) st = launch_purify_init(x.pd, x.st, 1, n, tol, max_iter, s);
     if (st == DMP_OK) st = launch_purify_e0(x.pd, x.st, 1, x.st, 1, s);
     DevState h{};
@@ -692,6 +694,12 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
         return st;
     }
     t->init = h;
+    // residue products rely on the spectrum of P0 (k_init_p0)
+    if (h.lopsided && x.nmod > 0) st = bind_ctx(x, t->H, nocc, P, true, s);
+    if (st != DMP_OK) {
+        dmp_tape_free(t);
+        return st;
+    }
     // n x n device slots owned by the tape, allocated in blocks that double
     // in size (8, 16, ... slots): a few allocations for a whole run
     const size_t nn = size_t(n) * n;
@@ -892,7 +900,7 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
     std::vector<double*> segP(t->stride + 1), segX(t->stride);
     int2* pairs = nullptr;
     carve_bwd(c, t, &x, b, segP.data(), segX.data(), &pairs);
-    DMP_CHECK(bind_ctx(x, t->H, t->nocc, segP[0], s));
+    DMP_CHECK(bind_ctx(x, t->H, t->nocc, segP[0], t->init.lopsided != 0, s));
     double *Y = b[0], *Yn = b[1], *M = b[2], *MP = b[3], *PM = b[4];
     std::vector<int2> hp = tile_pairs32(n);
     StreamDrain drain{s};   // ``hp`` outlives its copy, also on an error return

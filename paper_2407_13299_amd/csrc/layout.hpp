@@ -143,7 +143,13 @@ struct DevState {
     int row_hmax;         // first row attaining h_max (Gershgorin)
     int row_hmin;         // first row attaining h_min
     int which;            // 0: lam = theta / (h_max - mu), 1: (1 - theta) / (mu - h_min)
+    int lopsided;         // 1: the lower half of H, which only the bounds read, is
+                          // smaller than the upper one, which P0 is made of: the
+                          // spectrum of P0 may leave [0, 1]
 };
+// Stop reason of a lopsided matrix planned for residue products, which rely on
+// that spectrum: it has run no iteration, and runs again on digit slices.
+constexpr int kStopLopsided = 100;
 
 // One operand to split (single launch: passed by value; grouped launch: an
 // array in device memory, blocks mapped to matrices by the first-unit
@@ -200,7 +206,7 @@ struct PurDesc {
     int n, nocc;
     int part_begin, part_end;   // partial range of this matrix
     int method;                 // DMP_CANONICAL or DMP_TRS4
-    int pad_;
+    int residues;               // 1: its products run through residues
 };
 
 // Step run by extra blocks of a launch (count > 0): block b < count works on

@@ -486,6 +486,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         d.X3 = L.X3;
         d.T = L.T;
         d.method = g.method;
+        d.residues = g.nmod > 0 ? 1 : 0;
         d.rows = L.rows;
         d.rowbad = L.rowbad;
         d.e0 = L.e0;

@@ -189,7 +189,17 @@ __device__ inline int2 tile_pair(int pi, int T) {
 // writes P0's tile (I, J) and, transposed through LDS, tile (J, I), also
 // with coalesced rows.  Its energy partial is the sum over the upper
 // elements of (1 or 2) P0_ij H_ij, in a fixed order.
-__global__ __launch_bounds__(256) void k_init_p0(const PurDesc* pd, const DevState* states) {
+//
+// The spectrum of P0 lies in [0, 1] if the Gershgorin discs, which were taken
+// from whole rows of H, hold the mirrored upper triangle: if no element below
+// the diagonal is smaller than its mirror by more than (h_max - h_min) d / n,
+// each disc is too small by less than d (h_max - h_min), and the spectrum
+// exceeds [0, 1] by less than d.  d = 2^-16 / n (padded to 64): TRS4's steps
+// without a second product double it, nine of them leave it below 1 / (128 n),
+// well within the room of kLamIterate (|row|^2 <= (1 + d) m + d + 2 d^2 for a
+// row maximum m >= 1 / n; below that the other bound of the norm is the smaller
+// one), and it is far above the rounding of an H formed as a product.
+__global__ __launch_bounds__(256) void k_init_p0(const PurDesc* pd, DevState* states) {
     __shared__ double sh[4];
     __shared__ double tileT[32][33];
     const PurDesc& d = pd[blockIdx.y];
@@ -200,16 +210,25 @@ __global__ __launch_bounds__(256) void k_init_p0(const PurDesc* pd, const DevSta
     const double* H = d.H;
     double* P = d.Pb[0];
     const double lam = s.lambda, mu = s.mu, theta = s.theta;
+    const double slack = fabs(lam) * (s.h_max - s.h_min) * 0x1p-16 / (double(n) * double(round_up(n, 64)));
     const int T = (n + 31) / 32;
     const int npairs = T * (T + 1) / 2;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     double e = 0.0;
+    bool lopsided = false;
     if (!s.nonfinite) {
         for (int pi = blockIdx.x; pi < npairs; pi += kE0Blocks) {
             const int2 ij = tile_pair(pi, T);
             const int I = ij.x, J = ij.y;
-            for (int r = ty; r < 32; r += 8) {
-                const int i = I * 32 + r, j = J * 32 + tx;
+            double low[4];   // the elements of H below the diagonal that this thread mirrors
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = J * 32 + ty + 8 * u, j = I * 32 + tx;
+                low[u] = i < n && j < n && (I != J || j < i) ? H[int64_t(i) * n + j] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = ty + 8 * u, i = I * 32 + r, j = J * 32 + tx;
                 double p = 0.0;
                 if (i < n && j < n && !(I == J && j < i)) {
                     const int64_t ij = int64_t(i) * n + j;
@@ -221,16 +240,22 @@ __global__ __launch_bounds__(256) void k_init_p0(const PurDesc* pd, const DevSta
                 tileT[r][tx] = p;
             }
             __syncthreads();
-            for (int r = ty; r < 32; r += 8) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
                 // element (J 32 + r, I 32 + tx) = tile (I, J)[tx][r]
-                const int i = J * 32 + r, j = I * 32 + tx;
-                if (i < n && j < n && (I != J || j < i)) P[int64_t(i) * n + j] = tileT[tx][r];
+                const int r = ty + 8 * u, i = J * 32 + r, j = I * 32 + tx;
+                if (i < n && j < n && (I != J || j < i)) {
+                    const double p = tileT[tx][r];
+                    P[int64_t(i) * n + j] = p;
+                    lopsided |= fabs(p) - fabs(lam * low[u]) > slack;
+                }
             }
             __syncthreads();
         }
     }
     e = block_sum(e, sh);
     if (threadIdx.x == 0) d.e0[blockIdx.x] = e;
+    if (lopsided) states[blockIdx.y].lopsided = 1;
 }
 
 // The final iterate of a canonical Ozaki purification, which the products
@@ -283,6 +308,9 @@ __global__ __launch_bounds__(256) void k_finalize_e0(const PurDesc* pd, DevState
         if (bad != 0.0) {
             s.done = 1;
             s.stop_reason = DMP_STOP_NONFINITE;
+        } else if (d.residues && s.lopsided && !s.done) {
+            s.done = 1;
+            s.stop_reason = kStopLopsided;
         }
     }
 }
@@ -1033,46 +1061,33 @@ void fill_info(const DevState& h, int S, dmp_kind kind, dmp_info* info) {
 
 }  // namespace
 
-// Purify count matrices that share the kind; used by both entry points.  ws
-// null: only the bytes needed (need_out) and the fewest accepted (least_out).
-int purify_many(int count, const double* const* H, const int* n, const int* nocc, double tol,
-                const int* slices, dmp_kind kind, int max_iter, int method, int flags,
-                double* const* P, double* E, dmp_info* info, void* ws, size_t ws_bytes,
-                hipStream_t s, size_t* need_out, size_t* least_out) {
-    // groups of equal slice count and tile choice (the choice follows from
-    // each matrix's own n and S, so a matrix gets the same tiles, hence the
-    // same fixed-order trace sums and bit-identical results, alone or in a
-    // batch)
-    std::vector<GroupPlan> groups;
-    DevState* states = nullptr;
-    auto plan = [&](bool digits) -> size_t {
-        plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr, digits);
-        Carver c(ws);
-        states = c.take<DevState>(size_t(count));
-        int first = 0;
-        for (auto& g : groups) {
-            carve_group(c, g, n, false);
-            g.st = ws ? states + first : nullptr;
-            first += g.count;
-        }
-        return c.used();
-    };
-    if (ws == nullptr) {
-        const size_t need = plan(false);
-        if (need_out) *need_out = need;
-        if (least_out) *least_out = std::min(need, plan(true));
-        return DMP_OK;
+namespace {
+
+// The plan of a call and the bytes it takes.  Groups of equal slice count and
+// tile choice (the choice follows from each matrix's own n and S, so a matrix
+// gets the same tiles, hence the same fixed-order trace sums and bit-identical
+// results, alone or in a batch).  digits: digit slices for every matrix;
+// split_tails false: no part buffers (the same bits).
+size_t plan_call(int count, const int* n, const int* nocc, const int* slices, dmp_kind kind, int method, void* ws,
+                 bool digits, bool split_tails, std::vector<GroupPlan>& groups, DevState** states) {
+    plan_groups(count, n, slices, kind, method, forced_tile_rb(), groups, ws ? nocc : nullptr, digits);
+    Carver c(ws);
+    *states = c.take<DevState>(size_t(count));
+    int first = 0;
+    for (auto& g : groups) {
+        g.split_tail = g.split_tail && split_tails;
+        carve_group(c, g, n, false);
+        g.st = ws ? *states + first : nullptr;
+        first += g.count;
     }
-    // a workspace too small for residue products (3 (N + 1) bytes an element
-    // beside the FP64 matrices, where digit slices take 2 S): digit slices
-    const size_t need = plan(false);
-    if (ws_bytes < need && ws_bytes < plan(true)) {
-        set_error("workspace of %zu bytes required", need);
-        return DMP_ENOMEM;
-    }
-    DMP_CHECK(check_workspace_alignment(ws));
-    // one purification at a time per process (see purify_mutex)
-    std::lock_guard<std::mutex> serial(purify_mutex());
+    return c.used();
+}
+
+// Run a planned call; ``lopsided`` receives the matrices it left undone
+// (kStopLopsided).
+int run_call(std::vector<GroupPlan>& groups, const DevState* states, int count, const double* const* H, const int* n,
+             const int* nocc, double tol, dmp_kind kind, int max_iter, int flags, double* const* P, double* E,
+             dmp_info* info, hipStream_t s, std::vector<int>& lopsided) {
     std::vector<std::unique_ptr<GroupHost>> keep;
     StreamDrain drain{s};   // declared after ``keep``: the stream drains first
     for (auto& g : groups)
@@ -1123,6 +1138,10 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
         for (int b = 0; b < g.count; ++b) {
             const DevState& h = host_st[off + b];
             const int m = g.idx[b];
+            if (h.stop_reason == kStopLopsided) {
+                lopsided.push_back(m);
+                continue;
+            }
             if ((h.iters + h.refined) & 1)
                 DMP_CHECK_HIP(hipMemcpyAsync(P[m], g.lay[b].Pw, size_t(n[m]) * n[m] * sizeof(double),
                                              hipMemcpyDeviceToDevice, s));
@@ -1135,6 +1154,74 @@ int purify_many(int count, const double* const* H, const int* n, const int* nocc
     DMP_CHECK_HIP(hipStreamSynchronize(s));
     return status;
 }
+
+}  // namespace
+
+// Purify count matrices that share the kind; used by both entry points.  ws
+// null: only the bytes needed (need_out) and the fewest accepted (least_out).
+int purify_many(int count, const double* const* H, const int* n, const int* nocc, double tol,
+                const int* slices, dmp_kind kind, int max_iter, int method, int flags,
+                double* const* P, double* E, dmp_info* info, void* ws, size_t ws_bytes,
+                hipStream_t s, size_t* need_out, size_t* least_out) {
+    std::vector<GroupPlan> groups;
+    DevState* states = nullptr;
+    auto plan = [&](bool digits) {
+        return plan_call(count, n, nocc, slices, kind, method, ws, digits, true, groups, &states);
+    };
+    if (ws == nullptr) {
+        const size_t need = plan(false);
+        if (need_out) *need_out = need;
+        if (least_out) *least_out = std::min(need, plan(true));
+        return DMP_OK;
+    }
+    // a workspace too small for residue products (3 (N + 1) bytes an element
+    // beside the FP64 matrices, where digit slices take 2 S): digit slices
+    const size_t need = plan(false);
+    if (ws_bytes < need && ws_bytes < plan(true)) {
+        set_error("workspace of %zu bytes required", need);
+        return DMP_ENOMEM;
+    }
+    DMP_CHECK(check_workspace_alignment(ws));
+    // one purification at a time per process (see purify_mutex)
+    std::lock_guard<std::mutex> serial(purify_mutex());
+    std::vector<int> again;
+    const int status = run_call(groups, states, count, H, n, nocc, tol, kind, max_iter, flags, P, E, info, s, again);
+    if (status < 0 || again.empty()) return status;
+    // the lopsided ones, on digit slices in the same workspace (always large
+    // enough without part buffers: the residues' capacity exceeds 2 S planes)
+    const int m = int(again.size());
+    std::vector<const double*> h2(m);
+    std::vector<double*> p2(m);
+    std::vector<int> n2(m), occ2(m), s2(m), none;
+    std::vector<double> e2(m);
+    std::vector<dmp_info> info2(m);
+    for (int i = 0; i < m; ++i) {
+        const int b = again[i];
+        h2[i] = H[b];
+        p2[i] = P[b];
+        n2[i] = n[b];
+        occ2[i] = nocc[b];
+        s2[i] = slices[b];
+    }
+    size_t used = 0;
+    for (bool tails : {true, false}) {
+        used = plan_call(m, n2.data(), occ2.data(), s2.data(), kind, method, ws, true, tails, groups, &states);
+        if (used <= ws_bytes) break;
+    }
+    if (used > ws_bytes) {
+        set_error("workspace of %zu bytes required", used);
+        return DMP_ENOMEM;
+    }
+    const int status2 = run_call(groups, states, m, h2.data(), n2.data(), occ2.data(), tol, kind, max_iter, flags,
+                                 p2.data(), e2.data(), info2.data(), s, none);
+    if (status2 < 0) return status2;
+    for (int i = 0; i < m; ++i) {
+        if (E) E[again[i]] = e2[i];
+        if (info) info[again[i]] = info2[i];
+    }
+    return std::max(status, status2);
+}
+
 }  // namespace dmp
 
 using namespace dmp;
