@@ -57,9 +57,11 @@
  *     overlap.
  *   - Purification runs with the same workspace, sizes, kind, slice count
  *     and method replay recorded launch sequences (hipGraphs, kept per
- *     device for the life of the process, at most 16): a repeated run is one
- *     graph launch of as many iterations as the previous such run needed,
- *     then one read of the device state.
+ *     device for the life of the process: at most 24, three for each of eight
+ *     sequences).  A repeated run launches as many iterations as the previous
+ *     such run needed, one graph for the whole multiples of 8 (n >= 1024: 4, n >=
+ *     4096: 2) and one for every two of the rest, then reads the device state
+ *     once.
  *   - Environment switches, for measurements only (results are the same,
  *     bit for bit, except for the tile height, which sets the order of the
  *     trace sums): DMP_TAIL_SPLIT=0 keeps every product tile whole,

@@ -652,6 +652,20 @@ std::vector<int64_t> launch_key(const std::vector<GroupPlan>& groups, int m, int
     return k;
 }
 
+int iterations_per_sync(int max_n) {
+    if (max_n >= 4096) return 2;
+    if (max_n >= 1024) return 4;
+    return 8;
+}
+
+std::vector<int> replay_plan(int m, int predicted) {
+    std::vector<int> plan;
+    const int whole = predicted / m * m;
+    if (whole > 0) plan.push_back(whole);
+    for (int done = whole; done < predicted; done += 2) plan.push_back(2);
+    return plan;
+}
+
 std::mutex& purify_mutex() {
     static std::mutex mu;
     return mu;

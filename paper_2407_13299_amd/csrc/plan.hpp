@@ -237,7 +237,19 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
 std::vector<int64_t> launch_key(const std::vector<GroupPlan>& groups, int m, int device,
                                 int extra);
 
+// Iterations per replay of a recorded graph: even, so a replay ends with the
+// iterate in the buffer it started from.
+int iterations_per_sync(int max_n);
+// The graphs (iterations of each) a run of ``predicted`` iterations launches: the
+// whole multiples of m in one, then pairs.
+std::vector<int> replay_plan(int m, int predicted);
+
 // ---- caches ---------------------------------------------------------------
+// Recorded graphs kept per process: those of eight launch sequences that are run
+// in turn, each with its replay of m iterations, its whole multiples of m and its
+// pair.
+constexpr size_t kGraphsPerSequence = 3, kGraphCacheCapacity = 8 * kGraphsPerSequence;
+
 // Thread-safe cache keyed by a vector of integers.  Holds at most
 // ``capacity`` values (0: no limit); beyond that the least recently used is
 // dropped.  Values are shared pointers: dropping one from the cache leaves

@@ -724,14 +724,6 @@ int launch_oz_iterations(std::vector<GroupPlan>& groups, int m, hipStream_t s,
     return DMP_OK;
 }
 
-// Iterations per replay of the cached graph: even, so a replay ends with the
-// iterate in the buffer it started from.
-int iterations_per_sync(int max_n) {
-    if (max_n >= 4096) return 2;
-    if (max_n >= 1024) return 4;
-    return 8;
-}
-
 bool graphs_enabled() {
     const char* e = std::getenv("DMP_NO_GRAPH");
     return !(e && e[0] == '1');
@@ -746,8 +738,6 @@ struct CachedGraph {
     hipGraphExec_t exec = nullptr;
     int last_iters = 0;    // iterations the previous run of this sequence took
 };
-
-constexpr size_t kGraphCacheCapacity = 16;
 
 // Never destroyed: its graphs would otherwise be released by a static
 // destructor after the HIP runtime may already have shut down.
@@ -852,7 +842,11 @@ int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
     for (auto& g : groups) max_n = std::max(max_n, g.max_n);
     const int m = iterations_per_sync(max_n);
     if (g_timing.on) return run_oz_timed(groups, max_iter, m, s, host_st, n);
+    // Graphs are held here until their last read, and none is dropped from the
+    // cache before its launches end: only the holder of the purification lock
+    // adds to the cache, and it drains its stream before it lets go.
     std::shared_ptr<CachedGraph> cg;
+    std::vector<std::shared_ptr<CachedGraph>> held;
     if (graphs_enabled()) {
         int dev = 0;
         DMP_CHECK_HIP(hipGetDevice(&dev));
@@ -912,14 +906,10 @@ int run_oz_groups(std::vector<GroupPlan>& groups, int max_iter, hipStream_t s,
             return graph_cache().get_or_create(launch_key(groups, count, dev, env | tag),
                                                [&]() { return capture_iterations(groups, count); });
         };
-        const int whole = predicted / m * m;
-        if (whole > 0) {
-            DMP_CHECK(iterations(whole, whole == m ? cg : graph_of(whole, 2)));
-            launched = whole;
-        }
-        if (launched < predicted) {
-            const auto two = m == 2 ? cg : graph_of(2, 4);
-            for (; launched < predicted; launched += 2) DMP_CHECK(iterations(2, two));
+        for (int count : replay_plan(m, predicted)) {
+            held.push_back(count == m ? cg : graph_of(count, count == 2 ? 4 : 2));
+            DMP_CHECK(iterations(count, held.back()));
+            launched += count;
         }
     }
     if (launched == 0) {
