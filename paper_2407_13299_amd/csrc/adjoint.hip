@@ -82,7 +82,12 @@ struct OzCtx {
     int bmod = 0, nt_bsym = 0, nt_bfull = 0, nt_outfull = 0;
     int shape_bsym = 0, shape_bfull = 0;
     const Tile *bsym = nullptr, *bfull = nullptr, *tiles_outfull = nullptr;
+    Tile* lists = nullptr;              // the tile lists above, of at most
+    size_t list_cap = 0;                // list_cap tiles together
 };
+
+// Which products of the context run: its tile lists are those.
+enum Pass { kForward, kBackward };
 
 void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.n = n;
@@ -105,6 +110,15 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
             x.maxi[i] = c.take<uint64_t>(round_up(n, kPad));
         }
     }
+    // the lists of the backward pass (which may recompute forward steps)
+    const int TM = 32 * x.rb;
+    x.list_cap = size_t(upper_tile_count(n, TM)) + size_t(tile_rows(n, TM)) * tile_cols(n);
+    if (residues)
+        x.list_cap += size_t(residue_tile_count(n, kShapeSmall, true)) * mods + size_t(upper_tile_count(n, 32));
+    if (residues && n >= kResidueBackward)
+        x.list_cap += size_t(residue_tile_count(n, kShapeSmall, true) + residue_tile_count(n, kShapeSmall, false)) *
+                          mod_backward(S) + size_t(tile_rows(n, 32)) * tile_cols(n);
+    x.lists = c.take<Tile>(x.list_cap);
     x.ea = c.take<int>(round_up(n, kPad));
     x.eb = c.take<int>(round_up(n, kPad));
     x.ma = c.take<uint64_t>(round_up(n, kPad));
@@ -124,32 +138,43 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
 }
 
 // digits: digit slices where residues would run (a lopsided H).
-int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, bool digits, hipStream_t s) {
+int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, Pass pass, bool digits, hipStream_t s) {
     x.H = H;
     const int TM = 32 * x.rb;
-    const int tm = tile_rows(x.n, TM), tn = tile_cols(x.n);
-    DMP_CHECK(cached_tiles(tm, tn, true, &x.tiles_up, TM));
-    DMP_CHECK(cached_tiles(tm, tn, false, &x.tiles_full, TM));
-    x.nt_up = upper_tile_count(x.n, TM);
-    x.nt_full = tm * tn;
     x.nmod = digits ? 0 : mod_count(x.S, x.n, nocc);
-    x.bmod = 0;
+    x.bmod = x.nmod > 0 && x.n >= kResidueBackward ? mod_backward(x.S) : 0;
+    std::vector<Tile> host;
+    host.reserve(x.list_cap);
+    auto begin = [&](const Tile** out) { *out = x.lists + host.size(); };
+    auto tiles = [&](int rows, bool upper, const Tile** out) {
+        begin(out);
+        append_tiles(host, tile_rows(x.n, rows), tile_cols(x.n), upper, 0, rows);
+    };
+    auto residues = [&](int mods, bool upper, const Tile** out, int* count, int* shape) {
+        begin(out);
+        *shape = residue_shape(1, &x.n, mods, upper);
+        *count = residue_tile_count(x.n, *shape, upper) * mods;
+        append_residue_tiles(host, x.n, mods, *shape, upper, 0);
+    };
+    x.nt_up = upper_tile_count(x.n, TM);
+    x.nt_full = tile_rows(x.n, TM) * tile_cols(x.n);
+    x.nt_out = upper_tile_count(x.n, 32);
+    x.nt_outfull = tile_rows(x.n, 32) * tile_cols(x.n);
+    const bool back = pass == kBackward;
+    if (x.nmod == 0 || (back && x.bmod == 0)) tiles(TM, true, &x.tiles_up);
+    if (back && x.bmod == 0) tiles(TM, false, &x.tiles_full);
     if (x.nmod > 0) {
-        x.mshape = residue_shape(1, &x.n, x.nmod, true);
-        DMP_CHECK(cached_residue_tiles(x.n, x.nmod, x.mshape, true, &x.mtiles, &x.nmt));
-        DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, true, &x.tiles_out, 32));
-        x.nt_out = upper_tile_count(x.n, 32);
+        residues(x.nmod, true, &x.mtiles, &x.nmt, &x.mshape);
+        tiles(32, true, &x.tiles_out);
     }
-    if (x.nmod > 0 && x.n >= kResidueBackward) {
-        x.bmod = mod_backward(x.S);
-        auto list = [&](bool upper, const Tile** out, int* count, int* shape) -> int {
-            *shape = residue_shape(1, &x.n, x.bmod, upper);
-            return cached_residue_tiles(x.n, x.bmod, *shape, upper, out, count);
-        };
-        DMP_CHECK(list(true, &x.bsym, &x.nt_bsym, &x.shape_bsym));
-        DMP_CHECK(list(false, &x.bfull, &x.nt_bfull, &x.shape_bfull));
-        DMP_CHECK(cached_tiles(tile_rows(x.n, 32), tn, false, &x.tiles_outfull, 32));
-        x.nt_outfull = tile_rows(x.n, 32) * tn;
+    if (back && x.bmod > 0) {
+        residues(x.bmod, true, &x.bsym, &x.nt_bsym, &x.shape_bsym);
+        residues(x.bmod, false, &x.bfull, &x.nt_bfull, &x.shape_bfull);
+        tiles(32, false, &x.tiles_outfull);
+    }
+    if (host.size() > x.list_cap) {
+        set_error("tile lists of %zu tiles where %zu were planned", host.size(), x.list_cap);
+        return DMP_EINVAL;
     }
     x.tail = TailSplit{x.nt_up, 1};
     if (x.fix != nullptr && tail_split_enabled()) {
@@ -169,8 +194,9 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, bool digits, hipSt
     d.nocc = nocc;
     d.part_begin = 0;
     d.part_end = x.nmod > 0 ? x.nt_out : x.nt_up;
+    StreamDrain drain{s};   // ``host`` and ``d`` outlive their copies
+    DMP_CHECK_HIP(hipMemcpyAsync(x.lists, host.data(), host.size() * sizeof(Tile), hipMemcpyHostToDevice, s));
     DMP_CHECK_HIP(hipMemcpyAsync(x.pd, &d, sizeof(d), hipMemcpyHostToDevice, s));
-    DMP_CHECK_HIP(hipStreamSynchronize(s));
     return DMP_OK;
 }
 
@@ -676,7 +702,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
     carve_ctx(c, x, n, slices, kind);
     double* X2 = c.take<double>(size_t(n) * n);
     double* Pw = c.take<double>(size_t(n) * n);
-    int st = bind_ctx(x, t->H, nocc, P, false, s);
+    int st = bind_ctx(x, t->H, nocc, P, kForward, false, s);
     if (st == DMP_OK) st = launch_purify_init(x.pd, x.st, 1, n, tol, max_iter, s);
     if (st == DMP_OK) st = launch_purify_e0(x.pd, x.st, 1, x.st, 1, s);
     DevState h{};
@@ -695,7 +721,7 @@ int dmp_purify_fwd_tape(const double* H, int n, int nocc, double tol, int slices
     }
     t->init = h;
     // residue products rely on the spectrum of P0 (k_init_p0)
-    if (h.lopsided && x.nmod > 0) st = bind_ctx(x, t->H, nocc, P, true, s);
+    if (h.lopsided && x.nmod > 0) st = bind_ctx(x, t->H, nocc, P, kForward, true, s);
     if (st != DMP_OK) {
         dmp_tape_free(t);
         return st;
@@ -900,7 +926,7 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
     std::vector<double*> segP(t->stride + 1), segX(t->stride);
     int2* pairs = nullptr;
     carve_bwd(c, t, &x, b, segP.data(), segX.data(), &pairs);
-    DMP_CHECK(bind_ctx(x, t->H, t->nocc, segP[0], t->init.lopsided != 0, s));
+    DMP_CHECK(bind_ctx(x, t->H, t->nocc, segP[0], kBackward, t->init.lopsided != 0, s));
     double *Y = b[0], *Yn = b[1], *M = b[2], *MP = b[3], *PM = b[4];
     std::vector<int2> hp = tile_pairs32(n);
     StreamDrain drain{s};   // ``hp`` outlives its copy, also on an error return

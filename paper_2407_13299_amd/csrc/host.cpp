@@ -1,5 +1,5 @@
-// Host-side helpers of libdmp that call HIP or rocBLAS: the device tile
-// lists, rocBLAS handles and products, the occupancy cache.
+// Host-side helpers of libdmp that call HIP or rocBLAS: rocBLAS handles and
+// products, the occupancy cache.
 #include "host.hpp"
 
 #include <algorithm>
@@ -12,32 +12,6 @@
 #include <memory>
 
 namespace dmp {
-
-int cached_tiles(int tm, int tn, bool upper, const Tile** out, int TM) {
-    // device copies live until the process ends (the cache has no limit)
-    static KeyedCache<Tile> cache;
-    int dev = 0;
-    DMP_CHECK_HIP(hipGetDevice(&dev));
-    int st = DMP_OK;
-    auto v = cache.get_or_create({dev, tm, tn, upper ? 1 : 0, TM}, [&]() -> std::shared_ptr<Tile> {
-        std::vector<Tile> host;
-        append_tiles(host, tm, tn, upper, 0, TM);
-        Tile* devp = nullptr;
-        hipError_t e = hipMalloc(&devp, std::max<size_t>(1, host.size()) * sizeof(Tile));
-        if (e == hipSuccess && !host.empty())
-            e = hipMemcpy(devp, host.data(), host.size() * sizeof(Tile), hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            set_error("tile list upload failed: %s", hipGetErrorString(e));
-            if (devp) (void)hipFree(devp);
-            st = DMP_EHIP;
-            return nullptr;
-        }
-        return std::shared_ptr<Tile>(devp, [](Tile*) {});   // kept for the process
-    });
-    if (!v) return st != DMP_OK ? st : DMP_EHIP;
-    *out = v.get();
-    return DMP_OK;
-}
 
 // One rocBLAS handle per device and host thread: a handle carries its stream,
 // so threads that share one would race between setting the stream and the
@@ -144,8 +118,6 @@ int forced_tile_rb() {
 TileChoice tile_choice_env(dmp_kind kind, int S, int n) {
     return tile_choice(kind, S, n, forced_tile_rb());
 }
-
-int tile_blocks_for(dmp_kind kind, int S, int n) { return tile_choice_env(kind, S, n).rb; }
 
 }  // namespace dmp
 

@@ -12,10 +12,6 @@
 
 namespace dmp {
 
-// Device copy of the tile order of a single tm x tn product, cached per
-// device for the life of the process.
-int cached_tiles(int tm, int tn, bool upper, const Tile** out, int TM = kTileM);
-
 // rocBLAS handle of the current device (created once), bound to ``stream``.
 int blas_handle(hipStream_t stream, rocblas_handle* out);
 
@@ -46,12 +42,6 @@ int launch_split_grouped_digits(const SplitDesc* descs_dev, int count, int units
                                 const CoefArgs& coef = CoefArgs{}, bool combined = false, int nmod = 0);
 
 struct GemmParams;
-// 32-row blocks per slice-GEMM tile (2: 64-row tiles, 4: 128-row tiles) of
-// the products of an n x n Ozaki purification (and of its adjoint); a
-// function of (kind, S, n) only.  The general GEMM entry points keep 128-row
-// tiles, which measured faster on dense random operands.
-int tile_blocks_for(dmp_kind kind, int S, int n);
-
 // rb: 32-row blocks per tile of the left operand (4, or 2 for the 64-row
 // variant: Ozaki kinds, S <= kMaxSlices64)
 int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStream_t stream,
@@ -62,8 +52,6 @@ int launch_ozgemm(int S, dmp_kind kind, const GemmParams& p, int ntiles, hipStre
 // ``step`` (count > 0) runs in extra blocks of the residue GEMM.
 int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p, int ntiles, int nout,
                         hipStream_t stream, const CoefArgs& step = CoefArgs{});
-// Device copy of the residue GEMM's tile list of one matrix, cached.
-int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count);
 // Workgroups of the purification-mode slice GEMM (kind, S, rb) resident on
 // the current device at once (CUs x workgroups per CU).
 int gemm_slots(int S, dmp_kind kind, int rb, int* slots);

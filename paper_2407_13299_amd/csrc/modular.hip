@@ -692,30 +692,4 @@ int launch_residue_gemm(dmp_kind kind, int nmod, int shape, const GemmParams& p,
     return combine[nmod - kModMin](kind == DMP_OZ_FP16, p, nout, stream);
 }
 
-int cached_residue_tiles(int n, int nmod, int shape, bool upper, const Tile** out, int* count) {
-    // device copies live until the process ends (as those of cached_tiles)
-    static KeyedCache<Tile> cache;
-    int dev = 0;
-    DMP_CHECK_HIP(hipGetDevice(&dev));
-    std::vector<Tile> host;
-    append_residue_tiles(host, n, nmod, shape, upper, 0);
-    *count = int(host.size());
-    int st = DMP_OK;
-    auto v = cache.get_or_create({dev, n, nmod, shape, upper ? 1 : 0}, [&]() -> std::shared_ptr<Tile> {
-        Tile* devp = nullptr;
-        hipError_t e = hipMalloc(&devp, host.size() * sizeof(Tile));
-        if (e == hipSuccess) e = hipMemcpy(devp, host.data(), host.size() * sizeof(Tile), hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            set_error("tile list upload failed: %s", hipGetErrorString(e));
-            if (devp) (void)hipFree(devp);
-            st = DMP_EHIP;
-            return nullptr;
-        }
-        return std::shared_ptr<Tile>(devp, [](Tile*) {});   // kept for the process
-    });
-    if (!v) return st != DMP_OK ? st : DMP_EHIP;
-    *out = v.get();
-    return DMP_OK;
-}
-
 }  // namespace dmp
