@@ -51,8 +51,9 @@ __device__ inline ModSplit lane_split() { return kModSplits.r[threadIdx.x & (kMa
 // of X = rint(v 2^-t) for NE elements (8 or 16; FP16: 8, as halves); plane m
 // starts at m ``plane`` bytes from ``base`` (a lane that is not ``wanted``
 // stores nothing).  Per element X = Xh 2^27 + Xl exactly; per modulus z = Xh
-// (2^27 mod p) + Xl, q = rint(z / p) (|z| < 2^40, so the product with 1 / p is
-// off by less than 2^-13, closer than any z / p comes to a tie for odd p), and
+// (2^27 mod p) + Xl, q = rint(z / p) (|X| < 2^62.2 with 16 moduli, so |z| < 2^43 and
+// the product with 1 / p is off by less than 2^-17, closer than any z / p, p odd,
+// comes to a tie: 2^-9), and
 // z - q p modulo 256 is the residue's byte (p = 256: +-128 are the same byte).
 // The integers z and q are read from the low words of z + 1.5 2^52 and q + 1.5
 // 2^52: four full-rate instructions per modulus.  The moduli are a loop: as
