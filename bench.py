@@ -58,13 +58,21 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_code_digest(path):
-    """SHA-256 of a kernel source with its // comments and all whitespace
+def kernel_code_digest(paths):
+    """SHA-256 of kernel sources with their // comments and all whitespace
     removed: it changes with the code, not with the comments."""
     import hashlib
     import re
-    text = re.sub(r"//[^\n]*", "", open(path).read())
+    text = "".join(re.sub(r"//[^\n]*", "", open(path).read()) for path in paths)
     return hashlib.sha256(re.sub(r"\s+", "", text).encode()).hexdigest()
+
+
+def product_sources(slices):
+    """What determines the bytes a purification product moves: its kernels, the
+    headers they share and the plan of their tiles."""
+    own = ["modular.hip", "modular.hpp", "residues.hpp"] if by_residues(slices) else ["ozgemm.hip"]
+    return [os.path.join(ROOT, "paper_2407_13299_amd", "csrc", f)
+            for f in own + ["ldsload.hpp", "layout.hpp", "plan.cpp"]]
 
 
 def by_residues(slices):
@@ -76,10 +84,9 @@ def by_residues(slices):
 def profiled_traffic(kind, slices, which="update"):
     """HBM bytes per product (summed over its launches) from
     the committed rocprofv3 counter summary, or None when that summary was
-    taken on another version of the kernel code (or for another configuration)."""
-    kernel, source = ("residue", "modular.hip") if by_residues(slices) else ("k_ozgemm", "ozgemm.hip")
+    taken on another version of the products' code (or for another configuration)."""
+    kernel = "residue" if by_residues(slices) else "k_ozgemm"
     path = os.path.join(ROOT, "profiles", f"{kernel}_{kind}_s{slices}_tb8192_traffic.md")
-    src = os.path.join(ROOT, "paper_2407_13299_amd", "csrc", source)
     if not os.path.exists(path):
         return None
     vals = {}
@@ -87,7 +94,7 @@ def profiled_traffic(kind, slices, which="update"):
         if " = " in line:
             k, v = line.split(" = ", 1)
             vals[k.strip()] = v.strip()
-    if vals.get("code_sha256") != kernel_code_digest(src):
+    if vals.get("code_sha256") != kernel_code_digest(product_sources(slices)):
         return None
     v = vals.get(f"{which}_traffic_bytes")
     return float(v) if v is not None else None
