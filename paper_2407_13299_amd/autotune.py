@@ -10,14 +10,19 @@ the reference).  The model
 
 is fitted by least squares to log2 of the errors above the FP64 noise floor,
 and C is raised so that the model bounds every measured point.  INT8 and FP16
-slices give bit-identical products, so one fit serves both kinds.
+slices give bit-identical products, so one fit serves both kinds.  S = 6, 7, 8
+run on digit slices here (the least workspace), whose errors the residue
+products, the ordinary ones of those counts, do not exceed.
 
     python -m paper_2407_13299_amd.autotune --out csrc/tuned_table.h
 
 With --tiles it measures instead the tile choice of the purification
-products per (kind, S, n): the tile height (64 or 128 rows) and whether the
-last, partly filled round of tiles is split along the reduction.  For every
-size a spectrum-controlled Hamiltonian runs a fixed number of iterations
+products on digit slices per (kind, S, n): the tile height (64 or 128 rows) and
+whether the last, partly filled round of tiles is split along the reduction.
+Those of S = 6, 7, 8 serve purifications in the least workspace and the
+adjoint's backward products of small matrices, and are measured in that
+workspace; sizes at which it is the ordinary one (n about 1100, where the part
+buffer takes more than the residues) are left out.  For every size a spectrum-controlled Hamiltonian runs a fixed number of iterations
 under every choice (interleaved rounds, median of the rounds); a choice other
 than the default (64-row tiles with a split tail, 128-row tiles beyond S = 7)
 is taken only when it is faster by more than a margin, and the winners are
@@ -38,19 +43,35 @@ SIZES = (128, 256, 512, 1024, 1536, 2048, 3072)
 SLICES = (4, 5, 6, 7, 8)
 REF_SLICES = 11
 NOISE = 1e-14          # below this the error is FP64 rounding, not the split
+KIND_IDS = {"int8": 1, "fp16": 2}
+RESIDUE_SLICES = (6, 7, 8)   # counts whose products ordinarily run through residues
+
+
+def digit_workspace(lib, n, s, kind):
+    """Bytes of a workspace in which an n x n purification with S slices runs on
+    digit slices, or None where every accepted one is large enough for residue
+    products."""
+    least = lib.dmp_purify_min_workspace_bytes(n, s, KIND_IDS[kind])
+    full = lib.dmp_purify_workspace_bytes(n, s, KIND_IDS[kind])
+    return None if s in RESIDUE_SLICES and least >= full else least
 
 
 def measure(sizes=SIZES, slices=SLICES, seed=7, log=print):
     import torch
-    from . import api
+    from . import _lib, api
     from .workloads import spectrum_hamiltonian
+    lib = _lib.load()
     rows = []
     for n in sizes:
         h, _, _ = spectrum_hamiltonian(n, n // 2, seed=seed + n)
         hd = torch.from_numpy(h).cuda()
         p_ref, _, _ = api.purify(hd, n // 2, tol=1e-12, slices=REF_SLICES)
         for s in slices:
-            p, _, info = api.purify(hd, n // 2, tol=1e-12, slices=s)
+            nbytes = digit_workspace(lib, n, s, "int8")
+            if nbytes is None:
+                continue
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+            p, _, info = api.purify(hd, n // 2, tol=1e-12, slices=s, workspace=ws)
             torch.cuda.synchronize()
             err = float(torch.max(torch.abs(p - p_ref)).item())
             rows.append((n, s, err, info["stop"]))
@@ -79,7 +100,7 @@ def write_header(path, c, a, rows, target=1e-10):
         "// and the default accuracy target of the batched entry point when it",
         "// picks S itself.  Written by paper_2407_13299_amd/autotune.py from",
         "// these measurements (spectrum-controlled H, half filled, gap 0.2 Ha,",
-        f"// max |P_S - P_{REF_SLICES}|):",
+        f"// max |P_S - P_{REF_SLICES}|, digit slices; residue products are no further off):",
     ]
     for n, s, e, stop in rows:
         lines.append(f"//   n = {n:5d}  S = {s:2d}  {e:.3e}  {stop}")
@@ -102,7 +123,6 @@ TILE_SIZES = (256, 384, 512, 640, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3072,
 TILE_CASES = (("int8", 6), ("int8", 7), ("int8", 8), ("fp16", 7))
 TILE_ITERS = 10        # iterations per timed run (stopped by max_iter)
 TILE_MARGIN = 0.015    # a non-default choice must be this much faster
-KIND_IDS = {"int8": 1, "fp16": 2}
 MAX_SLICES_64 = 8      # largest S with 64-row tiles (kMaxSlices64 in layout.hpp)
 # slice range each measured (kind, S) stands for in the table (S = 9..12 have
 # 128-row tiles only, the table's fallback)
@@ -146,10 +166,15 @@ def measure_tiles(sizes=TILE_SIZES, cases=TILE_CASES, rounds=3, seed=11, log=pri
                 wss = {}
                 for c in choices:
                     use(*c)
-                    wss[c] = torch.empty(lib.dmp_purify_workspace_bytes(n, s, KIND_IDS[kind]),
-                                         dtype=torch.uint8, device="cuda")
+                    nbytes = digit_workspace(lib, n, s, kind)
+                    if nbytes is None:
+                        break
+                    wss[c] = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
                     api.purify(hd, n // 2, tol=1e-300, slices=s, kind=kind, max_iter=TILE_ITERS,
                                out=P, workspace=wss[c])          # warm-up and graph capture
+                if len(wss) < len(choices):
+                    log(f"{kind} S={s} n={n}: no workspace for digit slices alone")
+                    continue
                 times = {c: [] for c in choices}
                 for _ in range(rounds):
                     for c in choices:
@@ -209,7 +234,9 @@ def write_tiles_header(path, rows, margin=TILE_MARGIN):
     picks = pick_tiles(rows, margin)
     table = tile_ranges(picks)
     lines = [
-        "// Tile choice of the Ozaki purification products, used by dmp::tile_choice:",
+        "// Tile choice of the Ozaki purification products on digit slices, used by",
+        "// dmp::tile_choice (S = 6, 7, 8: in the least workspace, and the backward",
+        "// products of small matrices; ordinarily those run through residues):",
         "// per kind and slice range, for n in [n_lo, n_hi], the tile height (rb = 2:",
         "// 64-row tiles, two workgroups per CU; rb = 4: 128-row tiles) and whether",
         "// the last, partly filled round of tiles is split along the reduction.",

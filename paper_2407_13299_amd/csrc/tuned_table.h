@@ -4,7 +4,7 @@
 // and the default accuracy target of the batched entry point when it
 // picks S itself.  Written by paper_2407_13299_amd/autotune.py from
 // these measurements (spectrum-controlled H, half filled, gap 0.2 Ha,
-// max |P_S - P_11|):
+// max |P_S - P_11|, digit slices; residue products are no further off):
 //   n =   128  S =  4  9.379e-07  stagnated
 //   n =   128  S =  5  1.692e-09  stagnated
 //   n =   128  S =  6  1.583e-11  converged

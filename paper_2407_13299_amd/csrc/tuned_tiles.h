@@ -1,4 +1,6 @@
-// Tile choice of the Ozaki purification products, used by dmp::tile_choice:
+// Tile choice of the Ozaki purification products on digit slices, used by
+// dmp::tile_choice (S = 6, 7, 8: in the least workspace, and the backward
+// products of small matrices; ordinarily those run through residues):
 // per kind and slice range, for n in [n_lo, n_hi], the tile height (rb = 2:
 // 64-row tiles, two workgroups per CU; rb = 4: 128-row tiles) and whether
 // the last, partly filled round of tiles is split along the reduction.
