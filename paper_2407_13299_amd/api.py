@@ -41,13 +41,14 @@ def _check_matrix(t, name):
 
 def _workspace(nbytes: int, device, least=None):
     """Workspace of nbytes, or where the device has not so much left, of the
-    ``least`` bytes the call accepts."""
+    fewest bytes the call accepts (``least()``)."""
     try:
         return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
-        if least is None or least >= nbytes:
+        few = nbytes if least is None else least()
+        if few >= nbytes:
             raise
-    return torch.empty(max(int(least), 256), dtype=torch.uint8, device=device)
+    return torch.empty(max(int(few), 256), dtype=torch.uint8, device=device)
 
 
 def _keep_for(ws: torch.Tensor, stream):
@@ -195,13 +196,14 @@ def purify(H, nocc, tol=1e-8, slices=7, kind="int8", max_iter=200, out=None, str
         _check_out(out, (n, n), H)
     P = out if out is not None else torch.empty_like(H)
     kd = _kind(kind)
-    least = lib.dmp_purify_min_workspace_bytes(n, slices, kd)
+    need = lib.dmp_purify_workspace_bytes(n, slices, kd)
+    least = lambda: lib.dmp_purify_min_workspace_bytes(n, slices, kd)
     ws = workspace
     if ws is not None and (not isinstance(ws, torch.Tensor) or ws.dtype != torch.uint8
                            or ws.device != H.device or not ws.is_contiguous()):
         raise TypeError("workspace must be a contiguous uint8 tensor on the device of H")
-    if ws is None or ws.numel() < least:
-        ws = _workspace(lib.dmp_purify_workspace_bytes(n, slices, kd), H.device, least)
+    if ws is None or (ws.numel() < need and ws.numel() < least()):
+        ws = _workspace(need, H.device, least)
     e = ctypes.c_double(0.0)
     info = _lib.DmpInfo()
     flags = (_lib.REFINE_MCWEENY if refine else 0) | (_lib.NATIVE_TRIANGLE if triangle else 0)
@@ -234,7 +236,7 @@ def purify_batched(Hs, noccs, tol=1e-8, slices=0, kind="int8", max_iter=200, str
     nocc = IA(*[int(x) for x in noccs])
     kd = _kind(kind)
     ws = _workspace(lib.dmp_purify_batched_workspace_bytes(cnt, n, int(slices), kd), Hs[0].device,
-                    lib.dmp_purify_batched_min_workspace_bytes(cnt, n, int(slices), kd))
+                    lambda: lib.dmp_purify_batched_min_workspace_bytes(cnt, n, int(slices), kd))
     E = (ctypes.c_double * cnt)()
     infos = (_lib.DmpInfo * cnt)()
     flags = _lib.REFINE_MCWEENY if refine else 0

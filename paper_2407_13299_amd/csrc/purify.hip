@@ -1279,7 +1279,9 @@ size_t dmp_purify_workspace_bytes(int n, int slices, dmp_kind kind) {
 }
 
 size_t dmp_purify_min_workspace_bytes(int n, int slices, dmp_kind kind) {
-    if (dmp_purify_workspace_bytes(n, slices, kind) == 0) return 0;
+    if (n < 1) return 0;
+    if (kind != DMP_FP64_NATIVE && (slices < 1 || slices > kMaxSlices)) return 0;
+    if (kind == DMP_MARKIDIS_FP16 && slices > kMaxTerms) return 0;
     size_t least = 0;
     const double* h = nullptr;
     double* p = nullptr;

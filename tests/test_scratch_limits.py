@@ -46,9 +46,9 @@ def test_allocation_falls_back(monkeypatch):
             raise torch.OutOfMemoryError("no room")
         return real(size, **kw)
     monkeypatch.setattr(api.torch, "empty", empty)
-    assert api._workspace(4000, "cpu", 1000).numel() == 4000
-    assert api._workspace(6000, "cpu", 1000).numel() == 1000
-    for least in (None, 6000, 5500):
+    assert api._workspace(4000, "cpu", lambda: 1000).numel() == 4000
+    assert api._workspace(6000, "cpu", lambda: 1000).numel() == 1000
+    for least in (None, lambda: 6000, lambda: 5500):
         with pytest.raises(torch.OutOfMemoryError):
             api._workspace(6000, "cpu", least)
 
