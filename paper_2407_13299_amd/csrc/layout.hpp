@@ -112,7 +112,7 @@ struct MatDesc {
     int M, N, KC;          // rows, columns, reduction chunks
     int ldc;
     int state_index;       // index of the matrix's DevState
-    int pad_;
+    int nmod;              // residue products: the matrix's moduli
     // residue products (pa, pb hold residue planes, each rows x a_rb_stride):
     uint8_t* res;          // the residues of the product, [moduli][residue_out_bytes(M, N)]
     // The purification modes also write the residue planes of the output, as
@@ -178,6 +178,8 @@ struct SplitDesc {
                         // read as A[k, r]
     double lam;         // residues: largest eigenvalue magnitude of the (positive
                         // semidefinite) source, with some room; 0: none known
+    double limit;       // residues: largest admissible row norm (crt_limit(nmod))
+    int nmod;           // residues: the operand's moduli, 0 for digits
 };
 
 // The operands of a split launch: an array in device memory, or one or two by
@@ -285,6 +287,9 @@ struct GemmParams {
     // matrix ``mat`` is states[mat].
     int lone;
     const Tile* mtiles;     // residue products: the residue GEMM's tile list
+    // residue products of a batch: 1 if its matrices differ in their moduli (the
+    // combination then reads each one's constants from its descriptor's count)
+    int mixed;
     // residue products: the update has no product while the state's gamma is 0
     // (TRS4; the state's gamma must be final before the launch)
     int skip_zero;

@@ -297,8 +297,7 @@ void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int 
                                                       : tile_choice(kind, S, n[b], forced_rb);
         GroupPlan* g = nullptr;
         for (auto& x : groups)
-            if (x.S == S && x.rb == tc.rb && x.split_tail == tc.split_tail && x.nmod == nmod &&
-                kind != DMP_FP64_NATIVE && !(residues && nocc == nullptr))
+            if (x.S == S && x.rb == tc.rb && x.split_tail == tc.split_tail && kind != DMP_FP64_NATIVE)
                 g = &x;
         if (!g) {
             groups.emplace_back();
@@ -308,8 +307,10 @@ void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int 
             g->method = method;
             g->rb = tc.rb;
             g->split_tail = tc.split_tail;
-            g->nmod = nmod;
         }
+        g->mixed = g->mixed || (g->count > 0 && nmod != g->nmod);
+        g->nmod = std::max(g->nmod, nmod);
+        g->mods.push_back(nmod);
         g->idx.push_back(b);
         g->count++;
     }
@@ -469,7 +470,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
             for (int b : order) sizes.push_back(n[g.idx[b]]);
             g.mshape = residue_shape(cnt, sizes.data(), g.nmod, true);
             for (int b : order)
-                append_residue_tiles(out.mtiles, n[g.idx[b]], g.nmod, g.mshape, true, uint32_t(b));
+                append_residue_tiles(out.mtiles, n[g.idx[b]], g.mods[b], g.mshape, true, uint32_t(b));
             if (cnt > 1) spread_residue_tiles(out.mtiles, n, g);
             g.nmt = int(out.mtiles.size());
         }
@@ -515,6 +516,8 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         sd.ub_rowmax = urow;
         sd.ub_digits = udig;
         sd.state_index = b;
+        sd.nmod = g.mods[b];
+        sd.limit = g.mods[b] > 0 ? crt_limit(g.mods[b]) : 0.0;
         urow += split_units_rowmax(nb);
         udig += split_units_digits(nb, KC);
         // Row maxima: those of P come from the update's epilogue (of P0 from
@@ -564,6 +567,7 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
         md.H = H[m];
         md.X2 = L.X2;
         md.res = L.res;
+        md.nmod = g.mods[b];
         // square: A = B = planes of P
         md.pa = L.planesP;
         md.pb = L.planesP;
@@ -600,13 +604,13 @@ void build_group(GroupPlan& g, const double* const* H, double* const* P, const i
                 q.expo_out = L.expX;
                 q.maxin = maxi[par];
                 q.clear = maxi[par ^ 1];
-                q.limit = crt_limit(g.nmod) / kGrowthSquare;
+                q.limit = crt_limit(g.mods[b]) / kGrowthSquare;
                 u.eb = expo[par];
                 u.rowmax = maxi[par ^ 1];
                 u.planes_out = L.planesP;
                 u.expo_out = expo[par ^ 1];
                 u.maxin = maxi[par];
-                u.limit = crt_limit(g.nmod) / (g.method == DMP_TRS4 ? kGrowthTrs4 : kGrowthCanonical);
+                u.limit = crt_limit(g.mods[b]) / (g.method == DMP_TRS4 ? kGrowthTrs4 : kGrowthCanonical);
                 // T replaces the iterate as the right operand, in its planes
                 // and exponents
                 (par == 0 ? out.st0[b] : out.st1[b]).expo = expo[par];
@@ -632,7 +636,8 @@ std::vector<int64_t> launch_key(const std::vector<GroupPlan>& groups, int m, int
         k.insert(k.end(), {int64_t(g.count), int64_t(g.S), int64_t(g.kind), int64_t(g.method),
                            int64_t(g.rb), int64_t(g.ntiles), int64_t(g.units_rowmax),
                            int64_t(g.units_digits), int64_t(g.tail.nfull), int64_t(g.tail.nsplit),
-                           int64_t(g.nmod), int64_t(g.nmt), int64_t(g.mshape)});
+                           int64_t(g.nmod), int64_t(g.nmt), int64_t(g.mshape),
+                           int64_t(g.mixed)});
         p(g.pd);
         p(g.st);
         p(g.splitP[0]);

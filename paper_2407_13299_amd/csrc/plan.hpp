@@ -193,7 +193,9 @@ struct GroupPlan {
     int fix_pieces = 0;               // its capacity in parts
     int min_kc = 0, max_kc = 0;       // fewest / most reduction chunks of a matrix
     TailSplit tail{0, 1};             // tail split of the slice GEMMs
-    int nmod = 0;                     // moduli of its residue products (0: digit slices)
+    int nmod = 0;                     // most moduli of its residue products (0: digit slices)
+    std::vector<int> mods;            // [count] moduli of each matrix
+    bool mixed = false;               // they differ
     Tile* mtiles = nullptr;           // residue GEMM tile list, nmt entries of shape mshape
     int nmt = 0, mshape = 0;
 };
@@ -202,12 +204,11 @@ int native_blocks(int n);
 int native_pairs(int n);
 int oz_tiles(int n, int rb);
 
-// Partition a batch into groups of equal (S, tile choice, moduli); the choice
-// follows from each matrix's own (kind, S, n, nocc), so a matrix gets the
-// same tiles and scales, hence bit-identical results, alone or in a batch.
-// nocc null (workspace queries, which do not know it): every matrix that may
-// use residues is a group of its own, which needs no less workspace than any
-// grouping the occupations can lead to.  digits: digit slices for every matrix.
+// Partition a batch into groups of equal (S, tile choice); the choice, and the
+// moduli of a residue product, follow from each matrix's own (kind, S, n, nocc),
+// so a matrix gets the same tiles and scales, hence bit-identical results, alone
+// or in a batch.  nocc null (workspace queries, which do not know it): the same
+// groups.  digits: digit slices for every matrix.
 void plan_groups(int count, const int* n, const int* slices, dmp_kind kind, int method,
                  int forced_rb, std::vector<GroupPlan>& groups, const int* nocc = nullptr,
                  bool digits = false);

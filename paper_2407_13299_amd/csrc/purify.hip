@@ -617,7 +617,7 @@ double gemm_ops(const GroupPlan& g, const int* n) {
     double t = 0.0;
     for (int b = 0; b < g.count; ++b) {
         const double m = n[g.idx[b]];
-        const double products = g.nmod > 0 ? g.nmod : 0.5 * g.S * (g.S + 1);
+        const double products = g.nmod > 0 ? g.mods[b] : 0.5 * g.S * (g.S + 1);
         t += products * m * m * (m + 1);
     }
     return t;
@@ -678,6 +678,7 @@ int launch_oz_iteration(GroupPlan& g, int par, bool follows, hipStream_t s,
     p.upper_only = trs4 ? 0 : 1;
     p.spread = g.count > 1 ? 1 : 0;
     p.lone = g.count == 1 ? 1 : 0;
+    p.mixed = g.mixed ? 1 : 0;
     auto split_t = [&]() -> int {
         DMP_CHECK(launch_split_grouped_rowmax(g.splitT[par], g.count, g.units_rowmax, g.st, s));
         return launch_split_grouped_digits(g.splitT[par], g.count, g.units_digits, g.S, g.kind, g.st, s,

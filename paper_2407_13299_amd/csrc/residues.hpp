@@ -47,7 +47,7 @@ constexpr ModSplits make_splits() {
 __constant__ const ModSplits kModSplits = make_splits();
 __device__ inline ModSplit lane_split() { return kModSplits.r[threadIdx.x & (kMaxMods - 1)]; }
 
-// One lane's bytes of a fragment in each of N planes: the balanced residues
+// One lane's bytes of a fragment in each of ``mods`` planes: the balanced residues
 // of X = rint(v 2^-t) for NE elements (8 or 16; FP16: 8, as halves); plane m
 // starts at m ``plane`` bytes from ``base`` (a lane that is not ``wanted``
 // stores nothing).  Per element X = Xh 2^27 + Xl exactly; per modulus z = Xh
@@ -58,9 +58,9 @@ __device__ inline ModSplit lane_split() { return kModSplits.r[threadIdx.x & (kMa
 // The integers z and q are read from the low words of z + 1.5 2^52 and q + 1.5
 // 2^52: four full-rate instructions per modulus.  The moduli are a loop: as
 // straight-line code, run once, they wait for instructions.
-template <int N, bool FP16, int NE>
+template <bool FP16, int NE>
 __device__ __forceinline__ void store_residues(const double (&v)[NE], int t, const ModSplit& split, uint8_t* base,
-                                               int64_t plane, bool wanted = true) {
+                                               int64_t plane, int mods, bool wanted = true) {
     constexpr int E = FP16 ? 2 : 4, NW = NE / E;   // elements per word, words
     typedef uint32_t Words __attribute__((ext_vector_type(NW)));
     constexpr double kMagic = 0x1.8p52;
@@ -76,7 +76,7 @@ __device__ __forceinline__ void store_residues(const double (&v)[NE], int t, con
     }
     const uint64_t invs = static_cast<uint64_t>(__double_as_longlong(split.inv));
 #pragma unroll 1
-    for (int m = 0; m < N; ++m) {
+    for (int m = 0; m < mods; ++m) {
         const double c = double(__builtin_amdgcn_readlane(split.c, m));
         const uint32_t neg = uint32_t(__builtin_amdgcn_readlane(int(split.neg), m));
         const double inv = __longlong_as_double(static_cast<long long>(

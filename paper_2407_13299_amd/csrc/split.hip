@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256) void k_digits(SplitSet set, const DevState* st
             make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
-// Residues of an operand: the units and the staging of k_digits, with N
+// Residues of an operand: the units and the staging of k_digits, with N = d.nmod
 // planes of one byte (FP16: one half) per element, plane m holding the
 // balanced residues modulo kMods[m] (residues.hpp).  A plane is laid out in
 // fragments of 16 rows x 64 (FP16: 32) reduction elements, 1 KiB each in the
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void k_digits(SplitSet set, const DevState* st
 // null).  Bound by memory: 8 + N bytes per element, 4.8 TB/s at n = 8192,
 // N = 13 (292 us); half of the moduli per wavefront, twice the wavefronts, took
 // 400 us.
-template <int N, bool FP16, bool COMB>
+template <bool FP16, bool COMB>
 __global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* st) {
     constexpr int CK = FP16 ? 16 : 32;
     constexpr int NE = CK / 2;
@@ -530,15 +530,15 @@ __global__ __launch_bounds__(256) void k_residues(SplitSet set, const DevState* 
     const ModSplit split = lane_split();
     double v[NE];
     const bool needed = load_operand<CK, COMB>(d, st, panel, rb, kq, r, k0, rc < RC, v);
-    const int e = d.maxbits != nullptr ? residue_exponent(bits, d.K, d.lam, Crt<N>::table.limit) : d.expo[r];
+    const int e = d.maxbits != nullptr ? residue_exponent(bits, d.K, d.lam, d.limit) : d.expo[r];
     if (rc == 0 && lane < 16) {
         if (d.maxbits != nullptr) d.expo[r] = e;
         if (d.clear != nullptr) d.clear[r] = 0;
     }
     if (!needed) return;
 
-    store_residues<N, FP16>(v, e, split, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
-                            int64_t(rb_count) * 2 * RC * kFragBytes);
+    store_residues<FP16>(v, e, split, d.planes + (int64_t(rows16) * RC + rc) * kFragBytes + lane * 16,
+                         int64_t(rb_count) * 2 * RC * kFragBytes, d.nmod);
 }
 
 // ---------------------------------------------------------------------------
@@ -568,18 +568,17 @@ static void launch_halves(bool comb, const SplitSet& set, const DevState* st, in
         k_digits<2, true, true><<<grid, 256, 0, stream>>>(set, st, coef);
 }
 
-// Residue planes of N moduli.
-template <int N>
-static void launch_residues_n(bool fp16, bool comb, const SplitSet& set, const DevState* st, int units,
-                              hipStream_t stream) {
+// Residue planes.
+static void launch_residues(bool fp16, bool comb, const SplitSet& set, const DevState* st, int units,
+                            hipStream_t stream) {
     if (fp16 && comb)
-        k_residues<N, true, true><<<units, 256, 0, stream>>>(set, st);
+        k_residues<true, true><<<units, 256, 0, stream>>>(set, st);
     else if (fp16)
-        k_residues<N, true, false><<<units, 256, 0, stream>>>(set, st);
+        k_residues<true, false><<<units, 256, 0, stream>>>(set, st);
     else if (comb)
-        k_residues<N, false, true><<<units, 256, 0, stream>>>(set, st);
+        k_residues<false, true><<<units, 256, 0, stream>>>(set, st);
     else
-        k_residues<N, false, false><<<units, 256, 0, stream>>>(set, st);
+        k_residues<false, false><<<units, 256, 0, stream>>>(set, st);
 }
 
 using DigitsFn = void (*)(bool, bool, const SplitSet&, const DevState*, int, const CoefArgs&, hipStream_t);
@@ -588,13 +587,9 @@ static const DigitsFn kDigits[kMaxSlices + 1] = {
     launch_digits_s<4>, launch_digits_s<5>,  launch_digits_s<6>,  launch_digits_s<7>,
     launch_digits_s<8>, launch_digits_s<9>,  launch_digits_s<10>, launch_digits_s<11>,
     launch_digits_s<12>};
-using ResiduesFn = void (*)(bool, bool, const SplitSet&, const DevState*, int, hipStream_t);
-static const ResiduesFn kResidues[kMaxMods - kModMin + 1] = {
-    launch_residues_n<11>, launch_residues_n<12>, launch_residues_n<13>,
-    launch_residues_n<14>, launch_residues_n<15>, launch_residues_n<16>};
 
-// The planes of ``units`` units: residues of nmod moduli, or (nmod 0) the
-// kind's digit or half planes.
+// The planes of ``units`` units: residues (of at most nmod moduli; each operand's
+// own count is in its descriptor), or (nmod 0) the kind's digit or half planes.
 static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitSet& set, const DevState* st,
                          int units, const CoefArgs& coef, hipStream_t stream) {
     if (nmod != 0 && (nmod < kModMin || nmod > kMaxMods || coef.count != 0)) {
@@ -602,7 +597,7 @@ static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitS
         return DMP_EINVAL;
     }
     if (nmod != 0)
-        kResidues[nmod - kModMin](kind == DMP_OZ_FP16, comb, set, st, units, stream);
+        launch_residues(kind == DMP_OZ_FP16, comb, set, st, units, stream);
     else if (kind == DMP_MARKIDIS_FP16)
         launch_halves(comb, set, st, units, coef, stream);
     else
@@ -611,9 +606,11 @@ static int launch_planes(int S, dmp_kind kind, int nmod, bool comb, const SplitS
     return DMP_OK;
 }
 
-static SplitSet single(const SplitDesc& d) {
+static SplitSet single(const SplitDesc& d, int nmod = 0) {
     SplitSet s{};
     s.two[0] = d;
+    s.two[0].nmod = nmod;
+    s.two[0].limit = nmod >= kModMin && nmod <= kMaxMods ? crt_limit(nmod) : 0.0;
     s.two[0].ub_rowmax = s.two[0].ub_colmax = s.two[0].ub_digits = 0;
     s.count = 1;
     return s;
@@ -634,7 +631,7 @@ static int launch_maxima(const SplitSet& set, int rowmax_units, int colmax_units
 int launch_split_digits(const SplitDesc& d, int S, dmp_kind kind, const DevState* st,
                         hipStream_t stream, int nmod) {
     if (round_up(d.R, kPad) == 0) return DMP_OK;
-    return launch_planes(S, kind, nmod, d.A2 != nullptr, single(d), st, split_units_digits(d.R, d.KC),
+    return launch_planes(S, kind, nmod, d.A2 != nullptr, single(d, nmod), st, split_units_digits(d.R, d.KC),
                          CoefArgs{}, stream);
 }
 
