@@ -168,9 +168,15 @@ void count_split_units(SplitDesc* d, int count, SplitUnits& u) {
 }
 
 bool split_takes_maxima(const SplitDesc* d, int count) {
-    for (int i = 0; i < count; ++i)
+    int64_t again = 0;
+    bool columns = false;
+    for (int i = 0; i < count; ++i) {
         if (d[i].K > kSelfMaxK) return false;
-    return true;
+        const int groups = (d[i].KC + 3) / 4;   // workgroups of a row block
+        if (groups > 2) again += int64_t(d[i].R) * d[i].K * 8 * (groups - 1);
+        columns = columns || d[i].trans != 0;
+    }
+    return again <= (columns ? kSelfMaxBytes : kSelfMaxBytesRows);
 }
 
 // ---- split tail -------------------------------------------------------------------

@@ -89,8 +89,17 @@ void count_split_units(SplitDesc* d, int count, SplitUnits& u);
 // workgroup then reads its 32 rows over the whole reduction, instead of one or
 // two launches before it.  That read is a chain of K / 64 loads: at K = 64 ..
 // 512 the split takes 9 .. 11 us beside 5 us and two launches of 4 us, at K =
-// 1301 60 us beside 12 + 11 us.
+// 1301 60 us beside 12 + 11 us.  And where a row block has more than two
+// workgroups (K above 256 in INT8, above 128 in FP16) it reads the operands
+// again, from the caches, for each of them but one; beyond kSelfMaxBytes in all
+// that costs more than the two launches, beyond kSelfMaxBytesRows more than the
+// one of operands that are rows.  A whole product, launches and self: m x 64 x
+// 512, m = 4096 (51 MB) 39 and 38 us, 8192 (101 MB) 45 and 50, 65536 242 and 279;
+// rows alone, 2048 (25 MB) 32 and 32, 4096 36 and 39; batches, 24 of 64 .. 512 (61
+// MB) 119 and 116, 16 of 256 .. 512 (99 MB) 105 and 111, FP16 24 of 64 .. 512 (156
+// MB) 166 and 177; m x 64 x 256, 65536 131 and 124.
 constexpr int kSelfMaxK = 512;
+constexpr int64_t kSelfMaxBytes = 64000000, kSelfMaxBytesRows = 26000000;
 bool split_takes_maxima(const SplitDesc* d, int count);
 
 // ---- split tail -----------------------------------------------------------
