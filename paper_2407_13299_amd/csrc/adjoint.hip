@@ -23,6 +23,7 @@
 // the quantity the finite-difference and perturbation-theory checks compare.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -32,7 +33,13 @@
 namespace dmp {
 namespace {
 
+// Blocks of the dot products of an n x n step, four elements a thread: 1024 from
+// n = 1024 on, as few as the matrix has work for below (1024 empty ones and the
+// sum of their partials take 1.7 us more a step at n = 64).
 constexpr int kDotBlocks = 1024;
+inline int dot_blocks(int n) {
+    return int(std::min<int64_t>(kDotBlocks, (int64_t(n) * n + 1023) / 1024));
+}
 // Smallest n whose backward products run through residues: below, an operand's
 // split and the combination are launches more than the digit slices need.  A
 // whole gradient with digit slices and with residues: n = 240 2.28 and 2.43
@@ -118,7 +125,6 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     if (residues && n >= kResidueBackward)
         x.list_cap += size_t(residue_tile_count(n, kShapeSmall, true) + residue_tile_count(n, kShapeSmall, false)) *
                           mod_backward(S) + size_t(tile_rows(n, 32)) * tile_cols(n);
-    x.lists = c.take<Tile>(x.list_cap);
     x.ea = c.take<int>(round_up(n, kPad));
     x.eb = c.take<int>(round_up(n, kPad));
     x.ma = c.take<uint64_t>(round_up(n, kPad));
@@ -131,6 +137,7 @@ void carve_ctx(Carver& c, OzCtx& x, int n, int S, dmp_kind kind) {
     x.dots = c.take<double>(kDotBlocks * 4);
     x.scal = c.take<double>(8);
     x.pd = c.take<PurDesc>(1);
+    x.lists = c.take<Tile>(x.list_cap);   // beside the descriptor: one copy for both
     x.st = c.take<DevState>(1);
     x.fix_pieces = (kind == DMP_OZ_INT8 || kind == DMP_OZ_FP16) && tc.split_tail && !residues
                        ? tail_split_capacity(upper_tile_count(n, 32 * x.rb), x.KC, x.rb) : 0;
@@ -194,9 +201,12 @@ int bind_ctx(OzCtx& x, const double* H, int nocc, double* P0, Pass pass, bool di
     d.nocc = nocc;
     d.part_begin = 0;
     d.part_end = x.nmod > 0 ? x.nt_out : x.nt_up;
-    StreamDrain drain{s};   // ``host`` and ``d`` outlive their copies
-    DMP_CHECK_HIP(hipMemcpyAsync(x.lists, host.data(), host.size() * sizeof(Tile), hipMemcpyHostToDevice, s));
-    DMP_CHECK_HIP(hipMemcpyAsync(x.pd, &d, sizeof(d), hipMemcpyHostToDevice, s));
+    const size_t gap = size_t(reinterpret_cast<uint8_t*>(x.lists) - reinterpret_cast<uint8_t*>(x.pd));
+    std::vector<uint8_t> staged(gap + host.size() * sizeof(Tile));
+    std::memcpy(staged.data(), &d, sizeof(d));
+    std::memcpy(staged.data() + gap, host.data(), host.size() * sizeof(Tile));
+    StreamDrain drain{s};   // ``staged`` outlives its copy
+    DMP_CHECK_HIP(hipMemcpyAsync(x.pd, staged.data(), staged.size(), hipMemcpyHostToDevice, s));
     return DMP_OK;
 }
 
@@ -397,7 +407,7 @@ __global__ __launch_bounds__(256) void k_adj_dots(const double* Y, const double*
                                                   const double* X2, const double* MP, int n,
                                                   double* out) {
     __shared__ double sh[4];
-    const int64_t tot = int64_t(n) * n, step = int64_t(kDotBlocks) * 256;
+    const int64_t tot = int64_t(n) * n, step = int64_t(gridDim.x) * 256;
     double a = 0.0, b = 0.0, c = 0.0;
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < tot; i += 4 * step) {
         double y[4], p[4], x[4], m[4];
@@ -430,11 +440,11 @@ __global__ __launch_bounds__(256) void k_adj_dots(const double* Y, const double*
 }
 
 // cbar of one step from the dot partials and the recorded c, branch.
-__global__ __launch_bounds__(256) void k_adj_cbar(const double* dots, double c, int branch,
-                                                  int clamped, double* scal) {
+__global__ __launch_bounds__(256) void k_adj_cbar(const double* dots, int blocks, double c,
+                                                  int branch, int clamped, double* scal) {
     __shared__ double sh[4];
     double a = 0.0, b = 0.0, g = 0.0;
-    for (int i = threadIdx.x; i < kDotBlocks; i += 256) {
+    for (int i = threadIdx.x; i < blocks; i += 256) {
         a += dots[i * 4 + 0];
         b += dots[i * 4 + 1];
         g += dots[i * 4 + 2];
@@ -505,7 +515,7 @@ __global__ __launch_bounds__(256) void k_adj_dots0(const double* Y, const double
     __shared__ double sh[4];
     const int64_t tot = int64_t(n) * n;
     double tr = 0.0, yh = 0.0;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < tot; i += int64_t(kDotBlocks) * 256) {
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < tot; i += int64_t(gridDim.x) * 256) {
         yh += Y[i] * H[i];
         if (i / n == i % n) tr += Y[i];
     }
@@ -517,10 +527,10 @@ __global__ __launch_bounds__(256) void k_adj_dots0(const double* Y, const double
     }
 }
 
-__global__ __launch_bounds__(256) void k_adj_scal0(const double* dots, double* scal) {
+__global__ __launch_bounds__(256) void k_adj_scal0(const double* dots, int blocks, double* scal) {
     __shared__ double sh[4];
     double tr = 0.0, yh = 0.0;
-    for (int i = threadIdx.x; i < kDotBlocks; i += 256) {
+    for (int i = threadIdx.x; i < blocks; i += 256) {
         tr += dots[i * 4 + 0];
         yh += dots[i * 4 + 1];
     }
@@ -986,8 +996,8 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
                 bb = (1.0 + cc) / (1.0 - cc);
                 g = -1.0 / (1.0 - cc);
             }
-            k_adj_dots<<<kDotBlocks, 256, 0, s>>>(Y, P, X2, MP, n, x.dots);
-            k_adj_cbar<<<1, 256, 0, s>>>(x.dots, cc, br, t->clamped[j], x.scal);
+            k_adj_dots<<<dot_blocks(n), 256, 0, s>>>(Y, P, X2, MP, n, x.dots);
+            k_adj_cbar<<<1, 256, 0, s>>>(x.dots, dot_blocks(n), cc, br, t->clamped[j], x.scal);
             k_adj_combine<<<unsigned(hp.size()), 256, 0, s>>>(Y, M, MP, PM, P, X2, Yn, n, a, bb, g,
                                                                t->t1[j], t->t2[j], x.scal, pairs);
             DMP_CHECK_HIP(hipGetLastError());
@@ -995,8 +1005,8 @@ int dmp_purify_bwd(const dmp_tape* t, const double* Pbar, double* Hbar, void* ws
         }
     }
     const DevState& i0 = t->init;
-    k_adj_dots0<<<kDotBlocks, 256, 0, s>>>(Y, t->H, n, x.dots);
-    k_adj_scal0<<<1, 256, 0, s>>>(x.dots, x.scal);
+    k_adj_dots0<<<dot_blocks(n), 256, 0, s>>>(Y, t->H, n, x.dots);
+    k_adj_scal0<<<1, 256, 0, s>>>(x.dots, dot_blocks(n), x.scal);
     k_adj_initial<<<1024, 256, 0, s>>>(Y, t->H, Hbar, n, i0.lambda, i0.mu, i0.theta, i0.h_min, i0.h_max,
                                        i0.which, i0.row_hmax, i0.row_hmin, x.scal);
     DMP_CHECK_HIP(hipGetLastError());
