@@ -18,8 +18,13 @@
  *     from n = 1400 on) take the multi-modulus form of the scheme instead: the
  *     scaled rows become integers, 11, 13 or 15 (up to 16) exact products of
  *     their residues modulo p <= 256 run on the same matrix cores, and the
- *     Chinese remainder theorem gives the integer product back, with a smaller
- *     error than the S slices'.
+ *     Chinese remainder theorem gives the integer product back.  A row is held
+ *     to 43, 51 or 58 bits (more with more moduli) below a bound of its norm
+ *     instead of 8S - 2 below its largest entry, but no pairs are dropped; the
+ *     number of moduli follows from S, n and the filling so that the error of a
+ *     purification is no larger than with S slices (S = 8: FP64 rounding, the
+ *     larger one in both).  Smaller workspaces and an H with a smaller lower
+ *     half run on digit slices (see dmp_purify).
  *   - Density-matrix purification (Sec. 2.3; canonical, trace-conserving
  *     form of Palser and Manolopoulos cited in Sec. 1): from
  *     P0 = lam (mu I - H) + (nocc/n) I the iteration
@@ -31,7 +36,11 @@
  *     else is FP64 (Sec. 4).
  *   - Stopping (Sec. 3): |E_k - E_{k-1}| < tol with E = tr(P H); stagnation
  *     when E rose in each of the last two iterations by less than 1e-2 Ha;
- *     or max_iter.
+ *     or max_iter.  TRS4 (dmp_purify_ex) ends with gamma a quotient of two
+ *     rounding errors, with any kind of product, and P's error scatters with it:
+ *     1e-14 to 1e-8 at a tolerance of 1e-8 in the energy with slices or residues
+ *     (n = 200, half filled, twelve matrices: FP64 products 7e-15 to 4e-13,
+ *     S = 7 2e-14 to 6e-13); DMP_REFINE_MCWEENY takes that away (2e-14).
  *
  * Conventions for every entry point
  *   - Matrices are row-major FP64 in DEVICE memory owned by the caller.
@@ -64,8 +73,9 @@
  *     once.
  *   - Environment switches, for measurements only (results are the same,
  *     bit for bit, except for the tile height, which sets the order of the
- *     trace sums): DMP_TAIL_SPLIT=0 keeps every product tile whole,
- *     DMP_TILE_ROWS=64 or 128 forces the purification tile height,
+ *     trace sums): DMP_TAIL_SPLIT=0 keeps every tile of the slice products
+ *     whole, DMP_TILE_ROWS=64 or 128 forces the tile height of a purification's
+ *     slice products (products through residues have neither),
  *     DMP_NO_GRAPH=1 launches the iterations eagerly.
  */
 #ifndef DMP_H
@@ -161,8 +171,9 @@ int dmp_max_slices(dmp_kind kind);
  *   exact product, where 2^(e_i - 1) <= max|row i of op(A)| < 2^e_i and f_j
  *   likewise for column j of op(B).  Asynchronous on ``stream``.
  *   The workspace size depends on the current device as well: when the
- *   output tiles do not fill whole rounds of its CUs, it includes a buffer
- *   for the last round's partial sums.  Query on the device that runs the
+ *   output tiles do not fill whole rounds of its CUs, or hold less than half of
+ *   them (tall, narrow products with a long reduction), it includes a buffer for
+ *   the partial sums of the last round, or of all tiles.  Query on the device that runs the
  *   product (DMP_TAIL_SPLIT=0 in the environment, at query and at run time,
  *   keeps every tile whole and the buffer out).
  * ------------------------------------------------------------------- */
@@ -177,7 +188,7 @@ int dmp_ozaki_gemm(char transA, char transB, int m, int n, int k,
  * loops, harnesses that forbid allocation).  Same arguments, result and
  * asynchrony as dmp_ozaki_gemm with kind DMP_OZ_INT8, DMP_OZ_FP16 or
  * DMP_MARKIDIS_FP16 (DMP_FP64_NATIVE returns DMP_EINVAL), but no workspace:
- * the digit planes, exponents, maxima and tile list live in a 64 MiB array
+ * the digit planes, exponents and maxima live in a 64 MiB array
  * that the library holds on every GPU it runs on until the process ends.
  * A product whose scratch exceeds it returns DMP_EINVAL with the size it
  * needs (it holds m = n = k = 2048 at S <= 7, about plane bytes
@@ -194,9 +205,9 @@ int dmp_ozaki_gemm_noalloc(char transA, char transB, int m, int n, int k,
 
 /* Grouped GEMM: count independent products C_b = A_b B_b (no transposes,
  * row-major, leading dimensions equal to the row lengths), all with the
- * same slices and kind.  The row splits of all A_b and the slice GEMM of all
- * products are one grouped launch each; the column split of every B_b is a
- * launch of its own.  m, n, k and the pointer arrays are HOST arrays of
+ * same slices and kind.  The splits of all operands and the slice GEMM of all
+ * products are one grouped launch each (the splits two more for the operands'
+ * maxima where those are long or many).  m, n, k and the pointer arrays are HOST arrays of
  * length count; the matrices are on the device.  Returns 0 from the
  * workspace query for a null array or a size below 1.  Synchronises the
  * stream once, after copying the per-product descriptors into the workspace
@@ -227,7 +238,7 @@ int dmp_ozaki_gemm_batched(int count, const int* m, const int* n, const int* k,
 size_t dmp_purify_workspace_bytes(int n, int slices, dmp_kind kind);
 /* The fewest bytes dmp_purify and dmp_purify_ex accept.  Below
  * dmp_purify_workspace_bytes (S = 6, 7, 8: 16 n^2 + 3 N n^2 bytes and a little,
- * N = 14 to 16, FP16 5 N) the products run on digit slices, which take 2 S n^2
+ * N = 13 to 16, FP16 5 N) the products run on digit slices, which take 2 S n^2
  * (FP16 4 S) instead of the 3 N: slower, and with the slices' errors. */
 size_t dmp_purify_min_workspace_bytes(int n, int slices, dmp_kind kind);
 int dmp_purify(const double* H, int n, int nocc, double tol, int slices,

@@ -140,7 +140,7 @@ def ozaki_gemm_noalloc(A, B, slices=7, kind="int8", trans_a=False, trans_b=False
 
 
 def ozaki_gemm_batched(As, Bs, slices=7, kind="int8", stream=None):
-    """C_b = A_b B_b for lists of matrices (grouped row split and slice GEMM)."""
+    """C_b = A_b B_b for lists of matrices (grouped splits of all operands and one grouped slice GEMM)."""
     lib = _lib.load()
     cnt = len(As)
     if len(Bs) != cnt:

@@ -502,9 +502,9 @@ __global__ __launch_bounds__(256) void k_digits(SplitSet set, const DevState* st
 // bytes from reduction element (l / 16) NE on); a 16-row block's fragments are
 // contiguous.  Each wavefront forms one of its unit's 2 x 2 fragments.  The
 // iterates of a purification and their squares get their planes from the
-// combination that forms them; this kernel serves the first iterate, TRS4's T
-// and the restart from a checkpoint, whose exponents are given (maxbits
-// null).  Bound by memory: 8 + N bytes per element, 4.8 TB/s at n = 8192,
+// combination that forms them; this kernel serves the first iterate, TRS4's T,
+// the operands of the adjoint's products, and the restart from a checkpoint, whose
+// exponents are given (maxbits null).  Bound by memory: 8 + N bytes per element, 4.8 TB/s at n = 8192,
 // N = 13 (292 us); half of the moduli per wavefront, twice the wavefronts, took
 // 400 us.
 template <bool FP16, bool COMB>
